@@ -30,7 +30,7 @@ bool batchable(const pd_plan *plans, int count) {
     const pd_plan p = plans[i];
     if (!p || p->dims != 1 || !p->uniform || p->prec != p0->prec || p->prec == PD_MIXED ||
         p->tri.block != pd_tri_block_threads(p->prec) ||
-        p->maxit != p0->maxit || p->early_exit || p->sine || p->krylov || p->bdf_s > 1 ||
+        p->maxit != p0->maxit || p->sc_on != p0->sc_on || p->early_exit || p->sine || p->krylov || p->bdf_s > 1 ||
         !pd_gmres_fused_ok(p))
       return false;
     for (int j = 0; j < i; ++j)
@@ -67,6 +67,11 @@ struct BatchRun {
   const int2 *t0J = nullptr, *rmJ = nullptr;
   const CpJob *cj = nullptr;
   const int2 *c1m = nullptr, *c2m = nullptr, *c3m = nullptr;
+  // capacitance solves in the sine basis (every problem of the batch, or none)
+  int sc = 0, nsc = 0;
+  const ScJob *sj = nullptr;
+  const int2 *scm = nullptr;
+  size_t sc_lds = 0;
   int *act = nullptr;
   double *st = nullptr;
   int nf = 0, n0 = 0, n1 = 0, nv = 0, nr = 0, fft_threads = 64;
@@ -94,13 +99,15 @@ pd_status build_run(BatchRun &r, const pd_plan *plans, int count, const double *
   r.prec = prec;
   r.MX = MX;
   r.s = p0->stream;
+  r.sc = p0->sc_on;
   {
     std::vector<FftJob> fj(count);
     std::vector<TriJob> tj(count);
     std::vector<VecJob> vj(count);
     std::vector<int2> fftmap, tri0map, tri1map, vmap, redmap, tri0mapJ, redmapJ;
     std::vector<CpJob> cj(count);
-    std::vector<int2> c1map, c2map, c3map, k0map;
+    std::vector<int2> c1map, c2map, c3map, k0map, scmap;
+    std::vector<ScJob> sj(r.sc ? count : 0);
     int cthreads2 = 64;
     size_t clds1 = 0, clds2 = 0;
     int fft_threads = 64;
@@ -152,7 +159,11 @@ pd_status build_run(BatchRun &r, const pd_plan *plans, int count, const double *
       v.bout = p->bvec; v.b = p->bvec; v.done = p->gm + pd_gmres_done_index(MX);
       for (int b = 0; b < v.B; ++b) vmap.push_back(make_int2(i, b));
       for (int b = 0; b < (p->nbar + 255) / 256; ++b) redmap.push_back(make_int2(i, b));
-      if (p->cp_on) {
+      if (r.sc) {
+        sj[i] = pd_sc_job(p, nullptr, p->xvec);
+        for (int b = 0; b < sj[i].nblk; ++b) scmap.push_back(make_int2(i, b));
+        r.sc_lds = std::max(r.sc_lds, pd_sc_lds(sj[i], MX));
+      } else if (p->cp_on) {
         // J products of this problem by the chunked capacitance product (jobs
         // indexed by problem, like the activity flags)
         const CpJob J = pd_cp_job(p, p->V, p->wvec, p->gm + pd_gmres_done_index(MX));
@@ -223,6 +234,8 @@ pd_status build_run(BatchRun &r, const pd_plan *plans, int count, const double *
     const size_t o_c1 = off; off = align(off + c1map.size() * sizeof(int2));
     const size_t o_c2 = off; off = align(off + c2map.size() * sizeof(int2));
     const size_t o_c3 = off; off = align(off + c3map.size() * sizeof(int2));
+    const size_t o_sj = off; off = align(off + sj.size() * sizeof(ScJob));
+    const size_t o_sm = off; off = align(off + scmap.size() * sizeof(int2));
     const size_t o_act = off; off = align(off + count * sizeof(int));
     const size_t o_st = off; off = align(off + 4 * (size_t)count * sizeof(double));
     if (hipMalloc(&r.dev, off) != hipSuccess) {
@@ -257,6 +270,8 @@ pd_status build_run(BatchRun &r, const pd_plan *plans, int count, const double *
     put(o_c1, c1map.data(), c1map.size() * sizeof(int2));
     put(o_c2, c2map.data(), c2map.size() * sizeof(int2));
     put(o_c3, c3map.data(), c3map.size() * sizeof(int2));
+    put(o_sj, sj.data(), sj.size() * sizeof(ScJob));
+    put(o_sm, scmap.data(), scmap.size() * sizeof(int2));
     PD_HIP_CHECK(hipMemcpy(r.dev, host.data(), o_act, hipMemcpyHostToDevice));
     char *base = reinterpret_cast<char *>(r.dev);
     r.fj = reinterpret_cast<const FftJob *>(base + o_fj);
@@ -277,6 +292,9 @@ pd_status build_run(BatchRun &r, const pd_plan *plans, int count, const double *
     r.c1m = reinterpret_cast<const int2 *>(base + o_c1);
     r.c2m = reinterpret_cast<const int2 *>(base + o_c2);
     r.c3m = reinterpret_cast<const int2 *>(base + o_c3);
+    r.sj = reinterpret_cast<const ScJob *>(base + o_sj);
+    r.scm = reinterpret_cast<const int2 *>(base + o_sm);
+    r.nsc = (int)scmap.size();
     r.n0J = (int)tri0mapJ.size();
     r.nrJ = (int)redmapJ.size();
     r.nc1 = (int)c1map.size();
@@ -333,13 +351,17 @@ pd_status j_products(const BatchRun &r, int j, const int *act, hipStream_t s) {
 pd_status enqueue_solve(const BatchRun &r, int K, double rtol, hipStream_t s) {
   PD_B(pd_launch_fft_forward_batch(r.prec, r.fj, r.fm, r.nf, r.fft_threads, r.fft_lds, s));
   PD_B(tri_batch(r, 0, r.tj, r.t0, &TB::o0, &TB::n0, nullptr, 0, s));
-  PD_B(pd_launch_reduce_batch(r.vj, r.rm, r.nr, -1, nullptr, s));
-  PD_B(pd_gmres_batch_start(r.vj, r.count, r.MX, r.st, s));
-  for (int j = 0; j < K; ++j) {
-    PD_B(j_products(r, j, nullptr, s));
-    PD_B(pd_gmres_batch_arnoldi(r.vj, r.count, j, r.MX, rtol, r.st, nullptr, s));
+  if (r.sc) {
+    PD_B(pd_sc_batch(r.sj, r.count, r.scm, r.nsc, r.sc_lds, r.MX, rtol, r.st, s));
+  } else {
+    PD_B(pd_launch_reduce_batch(r.vj, r.rm, r.nr, -1, nullptr, s));
+    PD_B(pd_gmres_batch_start(r.vj, r.count, r.MX, r.st, s));
+    for (int j = 0; j < K; ++j) {
+      PD_B(j_products(r, j, nullptr, s));
+      PD_B(pd_gmres_batch_arnoldi(r.vj, r.count, j, r.MX, rtol, r.st, nullptr, s));
+    }
+    PD_B(pd_gmres_batch_finish(r.vj, r.vm, r.nv, r.count, r.MX, nullptr, s));
   }
-  PD_B(pd_gmres_batch_finish(r.vj, r.vm, r.nv, r.count, r.MX, nullptr, s));
   PD_B(tri_batch(r, 1, r.tj, r.t1, &TB::o1, &TB::n1, nullptr, 0, s));
   PD_B(pd_launch_fft_inverse_batch(r.prec, r.fj, r.fm, r.nf, r.fft_threads, r.fft_lds, s));
   PD_HIP_CHECK(hipMemcpyAsync(r.pin, r.st, 4 * (size_t)r.count * sizeof(double),
@@ -411,7 +433,10 @@ pd_status pd_solve_batch_impl(const pd_plan *plans, int count, const double *con
     learned = learned && plans[i]->gm_seen;
     K = std::max(K, plans[i]->gm_pred);
   }
-  K = std::min(K, MX);
+  // in the sine basis the iterations need no launches of their own: seven
+  // launches in all, enqueued directly
+  K = p0->sc_on ? 0 : std::min(K, MX);
+  learned = learned && !p0->sc_on;
   std::vector<const void *> key;
   key.reserve(4 * (size_t)count);
   for (int i = 0; i < count; ++i) key.push_back(plans[i]);
@@ -476,7 +501,7 @@ pd_status pd_solve_batch_impl(const pd_plan *plans, int count, const double *con
       return PD_ENONFINITE;
     }
   }
-  PD_B(finish_unconverged(*run, K, rtol));
+  if (!run->sc) PD_B(finish_unconverged(*run, K, rtol));
 
   pd_status worst = PD_OK;
   for (int i = 0; i < count; ++i) {

@@ -595,6 +595,23 @@ void pd_gmres_read(pd_plan p, int *m, double *res, double *beta, bool *done) {
   *done = st[4] != 0.0;
 }
 
+// The outcome of a solve whose status has arrived (after a synchronisation).
+pd_status pd_gmres_status(pd_plan p, double rtol, int *iters, double *relres) {
+  volatile double *st = p->host_pin;
+  const double res = st[0], hn = st[1], beta = st[3];
+  if (!std::isfinite(beta)) {
+    pd_set_error("capacitance right-hand side is not finite");
+    return PD_ENONFINITE;
+  }
+  if (!std::isfinite(res)) {
+    pd_set_error("capacitance GMRES produced a non-finite residual");
+    return PD_ENONFINITE;
+  }
+  if (iters) *iters = (int)st[2];
+  if (relres) *relres = beta > 0.0 ? res / beta : 0.0;
+  return (beta == 0.0 || res <= rtol * beta || hn == 0.0) ? PD_OK : PD_ENOTCONV;
+}
+
 // Continues a speculative GMRES that had not converged (iterations from m on,
 // one synchronisation per chunk), then x = V y.  Returns the final status.
 pd_status pd_gmres_continue(pd_plan p, double *x, double rtol, int *iters, double *relres) {
@@ -628,6 +645,12 @@ pd_status pd_gmres_continue(pd_plan p, double *x, double rtol, int *iters, doubl
 
 pd_status pd_gmres(pd_plan p, const double *b, double *x, double rtol, int *iters,
                    double *relres) {
+  if (p->sc_on) {
+    const pd_status s = pd_sc_enqueue(p, b, x, rtol);
+    if (s != PD_OK) return s;
+    PD_HIP_CHECK(hipStreamSynchronize(p->stream));
+    return pd_gmres_status(p, rtol, iters, relres);
+  }
   if (p->dims == 1 && p->ncap <= ARN_MAXN) return gmres_fused(p, b, x, rtol, iters, relres);
   const int n = p->ncap, MX = p->maxit;
   const int B = pd_vec_blocks(n);

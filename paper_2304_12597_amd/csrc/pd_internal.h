@@ -215,6 +215,19 @@ struct CpJob {
   const double *extra = nullptr; // the k = 0 term added by the last launch, or null
 };
 
+// One problem's sine-basis capacitance solve (sinecap.hip; device-readable,
+// the batched launches read an array of them).
+struct ScJob {
+  int n = 0, ns = 0, s = 1, r = 0, G = 0, nblk = 0;
+  const double *partials = nullptr;   // pass B's partial rows [G][n], or null:
+  const double *bin = nullptr;        // b [s][n] itself
+  double *b = nullptr;                // b summed from the partials
+  const double *S = nullptr;          // [r][ns] orthonormal modes, zero past n
+  const double *Phi = nullptr;        // [s][s][r] J - I on the modes
+  double *cpart = nullptr, *rpart = nullptr, *c = nullptr, *y = nullptr;
+  double *x = nullptr;
+};
+
 struct pd_plan_s {
   int n = 0, ell = 0, dims = 1, nbar = 0, F2 = 0;
   double tau = 0, alpha = 1, w = 1;   // w = alpha^(1/ell)
@@ -306,6 +319,9 @@ struct pd_plan_s {
   int cp_on = 0;
   CpLayout cpl;
   double *cp_tab = nullptr;
+  // capacitance solve in the sine eigenbasis (sinecap.hip)
+  int sc_on = 0, sc_r = 0, sc_ns = 0, sc_nblk = 0;
+  double *sc_tab = nullptr;
 };
 constexpr int PD_BDF_GCH = 16;   // frequency chunks of the BDF capacitance product
 
@@ -389,6 +405,17 @@ size_t pd_cp_lds(const CpJob &J, int launch);
 pd_status pd_cp_launch_batch(const CpJob *jobs, const int2 *map1, int nb1, const int2 *map2,
                              int nb2, int threads2, const int2 *map3, int nb3, size_t lds1,
                              size_t lds2, const int *active, int jv, hipStream_t s);
+// the capacitance solve in the sine eigenbasis (sinecap.hip)
+size_t pd_sc_max_doubles(int n, int s);
+bool pd_sc_build(pd_plan p, const std::vector<double> &fac, const std::vector<double> &ct,
+                 std::vector<double> &tab);
+ScJob pd_sc_job(pd_plan p, const double *bin, double *x);
+size_t pd_sc_lds(const ScJob &J, int MX);
+pd_status pd_sc_enqueue(pd_plan p, const double *bin, double *x, double rtol);
+pd_status pd_sc_apply(pd_plan p, const double *v, double *Jv);
+pd_status pd_sc_batch(const ScJob *jobs, int count, const int2 *map, int nblocks, size_t lds,
+                      int MX, double rtol, double *status, hipStream_t s);
+void pd_sc_set_attributes(size_t max_lds);
 pd_status pd_gmres(pd_plan p, const double *b, double *x, double rtol,
                    int *iters, double *relres);
 // rel = ||G - A(U)||_F / ||G||_F; est (if non-null): the plan's error bound
@@ -520,6 +547,7 @@ size_t pd_gmres_done_index(int maxit);   // offset of the converged flag in the 
 void pd_batch_forget(pd_plan p);
 pd_status pd_gmres_enqueue(pd_plan p, const double *b, double *x, double rtol, int count);
 void pd_gmres_read(pd_plan p, int *m, double *res, double *beta, bool *done);
+pd_status pd_gmres_status(pd_plan p, double rtol, int *iters, double *relres);
 pd_status pd_gmres_continue(pd_plan p, double *x, double rtol, int *iters, double *relres);
 pd_status pd_gmres_batch_givens(const VecJob *jobs, int count, int j, int MX, double *status,
                                 const int *active, hipStream_t s);

@@ -122,7 +122,8 @@ void free_plan(pd_plan p) {
   void *ptrs[] = {p->coef64, p->coef32, p->lam64, p->lam32, p->gB64, p->gJ64, p->tw64,
                   p->tw32, p->dal, p->fac64, p->fac32, p->twd, p->wreal, p->spec, p->spec2, p->partials, p->rstage, p->bvec, p->xvec, p->wvec, p->V,
                   p->gm, p->red, p->sine_q, p->sine_wN, p->sine_twH, p->sine_m, p->sine_k,
-                  p->fom, p->fom_h, p->wz, p->bdf_g, p->bdf_h, p->bdf_t, p->cp_tab};
+                  p->fom, p->fom_h, p->wz, p->bdf_g, p->bdf_h, p->bdf_t, p->cp_tab,
+                  p->sc_tab};
   for (void *q : ptrs)
     if (q) (void)hipFree(q);
   if (p->host_pin) (void)hipHostFree(p->host_pin);
@@ -139,7 +140,9 @@ struct Layout {
   size_t coef = 0, lam = 0, tw = 0, dal = 0, fac = 0, twd = 0, wreal = 0, wz = 0, bdfg = 0,
          bdfh = 0, bdft = 0, sine = 0, fom = 0;
   size_t fom_h_bytes = 0;
-  size_t cp = 0;   // chunked capacitance product: tables + workspace (doubles)
+  // the capacitance system's tables and workspace (doubles): the chunked
+  // product's or the sine basis's, whichever the plan's matrices allow
+  size_t cp = 0;
   size_t spec_bytes = 0, partials = 0, rstage = 0, vec = 0, V = 0, gm = 0, red = 0;
   size_t spec2_bytes = 0;   // PD_MIXED: the last correction's spectrum (stall rollback)
   size_t total_bytes() const {
@@ -249,6 +252,8 @@ pd_status compute_layout(pd_plan p, int cus, size_t max_lds, Layout &L) {
     p->cpl = pd_cp_layout(n, F2);
     L.cp = p->cpl.total;
   }
+  if (p->prec == PD_FP64 && p->dims == 1 && p->uniform && !p->sine)
+    L.cp = std::max(L.cp, pd_sc_max_doubles(n, p->bdf_s));
   L.coef = 6 * (size_t)n;
   L.lam = 2 * (size_t)F2;
   L.tw = 2 * (size_t)ell;
@@ -512,6 +517,7 @@ extern "C" pd_status paradiag_plan_create(pd_plan *out, int n, int ell, double t
     pd_tri_batch_set_attributes(g_max_lds);
     pd_sine_set_attributes(g_max_lds);
     pd_cp_set_attributes(g_max_lds);
+    pd_sc_set_attributes(g_max_lds);
     g_attr_device = p->device;
   }
   const size_t max_lds = g_max_lds;
@@ -739,7 +745,11 @@ extern "C" pd_status paradiag_plan_create(pd_plan *out, int n, int ell, double t
       }
     }
   }
-  std::vector<double> cptab;
+  std::vector<double> cptab, sctab;
+  if (pd_sc_build(p, fac, bg_ct, sctab)) {
+    p->sc_on = 1;
+    p->cp_on = 0;
+  }
   if (p->cp_on) pd_cp_tables(p, cptab);
   const size_t nbar = p->nbar;
   p->spec_bytes = L.spec_bytes;
@@ -785,7 +795,8 @@ extern "C" pd_status paradiag_plan_create(pd_plan *out, int n, int ell, double t
   PD_TRY(dev_alloc(&p->V, L.V));
   PD_TRY(dev_alloc(&p->gm, pd_gmres_state_doubles(p->maxit)));
   PD_TRY(dev_alloc(&p->red, L.red));
-  if (p->cp_on) PD_TRY(dev_alloc(&p->cp_tab, L.cp));
+  if (p->cp_on) PD_TRY(dev_alloc(&p->cp_tab, p->cpl.total));
+  if (p->sc_on) PD_TRY(dev_alloc(&p->sc_tab, sctab.size()));
   if (p->krylov == PD_KRYLOV_FOM) {
     PD_TRY(dev_alloc(&p->fom, L.fom));
     PD_TRY(dev_alloc(reinterpret_cast<unsigned char **>(&p->fom_h), L.fom_h_bytes));
@@ -822,6 +833,7 @@ extern "C" pd_status paradiag_plan_create(pd_plan *out, int n, int ell, double t
   PD_TRY(upload(p->fac32, fac32, p->stream));
   PD_TRY(upload(p->twd, twd, p->stream));
   if (p->cp_on) PD_TRY(upload(p->cp_tab, cptab, p->stream));
+  if (p->sc_on) PD_TRY(upload(p->sc_tab, sctab, p->stream));
   if (p->bdf_s > 1) PD_TRY(upload(p->bdf_g, bg_gt, p->stream));
   if (p->krylov == PD_KRYLOV_FOM) {
     std::vector<double> mf;

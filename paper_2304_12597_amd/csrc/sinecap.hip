@@ -1,0 +1,645 @@
+// The capacitance system J x = b (eq. SMW_linearsystemII; eq. innersystem_alpha
+// for alpha < 1; eq. linearsystem_s for BDF-s) in the sine eigenbasis, for
+// plans whose M and tau K are symmetric Toeplitz tridiagonals (uniform grids;
+// 2D: in the DST-x domain of the line solves, along y).
+//
+// The sine vectors s_j diagonalise every P_k^{-1} M, hence J: with
+// a_j = 1 + tau kappa_j / m_j,
+//
+//     J s_j = (1 + D_j) s_j,   D_j = alpha / (a_j^ell - alpha),
+//
+// and D_j falls below the rounding of 1 after a few modes (a_j^ell grows like
+// exp(T kappa_j / m_j)).  So J = I + S diag(D) S^T with S the r modes whose
+// D_j exceeds 2^-56, and GMRES started from b never leaves the space spanned
+// by b's part outside span(S) and the r modes.  In the coordinates
+// (c, rho), c = S^T b and rho = ||b - S c||, which are orthonormal, J is
+// diag(1 + D_1, .., 1 + D_r, 1): GMRES on r + 1 numbers gives the iterates,
+// residuals and iteration counts of GMRES on J itself.  BDF-s has s blocks
+// of r coordinates and an s x s matrix per mode (I + C_j^ell (I - C_j^ell)^-1
+// up to similarity, C_j the mode's companion matrix).
+//
+// D is not taken from the closed form but summed over the frequencies from
+// the same rounded constants that the passes' solves use (the recurrence
+// form's r_k and 1/kappa_k act on mode j as 1 / (kappa_k ((1 - r_k)^2 +
+// 4 r_k sin^2(theta_j / 2)))), so that J stays consistent with pass B and C.
+//
+// Three launches, whatever the iteration count: project (sums pass B's
+// partials into b and projects each 64-column block on the modes), norm
+// (c, and each block's share of rho^2), solve (every block runs the small
+// GMRES on its own copy in LDS -- cheaper than a launch and a round trip --
+// and forms its columns of x = t b + S (x_c - t c), t = x_rho / rho).
+// What bounds them is latency: the tables are at most 192 rows of n doubles
+// and b is read three times.  Sums run in a fixed order and the batched
+// launches use the same bodies, so results are the same alone and in a batch.
+#include "pd_internal.h"
+
+#include <algorithm>
+#include <cmath>
+#include <complex>
+
+namespace {
+
+constexpr int SC_DMAX = 192;     // s r: reduced coordinates without rho
+constexpr int SC_S = 6;          // BDF orders
+constexpr int SC_ONE = 4;        // column blocks of the one-launch form
+// its dynamic LDS limit: 66.7 KiB of static LDS beside it, of 160 KiB
+constexpr size_t SC_ONE_LDS = 80 * 1024;
+constexpr double SC_CUT = 0x1p-56;
+
+__device__ __forceinline__ double sc_wave_sum(double v) {
+  for (int off = 32; off > 0; off >>= 1) v += __shfl_xor(v, off, 64);
+  return v;   // in every lane
+}
+
+// ---- project: b (summed from pass B's partials, as reduce_fused_kernel) and
+// cpart[blk][h r + j] = sum over the block's 64 columns of S[j][i] b_h[i] ----
+constexpr int SCP_T = 1024, SCP_RS = 16, SCP_SLICES = 64;
+constexpr int SCP_LDS = (SCP_SLICES + SC_S) * 64;   // doubles
+__device__ __forceinline__ void sc_project_body(const ScJob &J, int blk, double *lds) {
+  double (*sl)[64] = reinterpret_cast<double (*)[64]>(lds);
+  double (*bs)[64] = sl + SCP_SLICES;
+  const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
+  const int n = J.n, i = blk * 64 + lane;
+  const int ic = i < n ? i : n - 1;
+  if (J.partials) {   // s = 1
+    const int slices = (J.G + SCP_RS - 1) / SCP_RS;
+    for (int q = w; q < slices; q += SCP_T / 64) {
+      const int g0 = q * SCP_RS, g1 = g0 + SCP_RS < J.G ? g0 + SCP_RS : J.G;
+      double v[SCP_RS];
+#pragma unroll
+      for (int u = 0; u < SCP_RS; ++u)
+        v[u] = J.partials[(size_t)(g0 + u < g1 ? g0 + u : g1 - 1) * n + ic];
+      double t = 0.0;
+#pragma unroll
+      for (int u = 0; u < SCP_RS; ++u)
+        if (g0 + u < g1) t += v[u];
+      sl[q][lane] = t;
+    }
+    __syncthreads();
+    if (w == 0) {
+      double t = 0.0;
+      for (int q = 0; q < slices; ++q) t += sl[q][lane];
+      if (i < n) J.b[i] = t;
+      bs[0][lane] = i < n ? t : 0.0;
+    }
+  } else {
+    for (int h = w; h < J.s; h += SCP_T / 64)
+      bs[h][lane] = i < n ? J.bin[(size_t)h * n + ic] : 0.0;
+  }
+  __syncthreads();
+  const int d = J.s * J.r;
+  for (int e = w; e < d; e += SCP_T / 64) {
+    const int h = e / J.r, j = e - h * J.r;
+    const double v = sc_wave_sum(J.S[(size_t)j * J.ns + i] * bs[h][lane]);
+    if (lane == 0) J.cpart[(size_t)blk * d + e] = v;
+  }
+}
+
+// c[e] = sum over the blocks of cpart (fixed order), in LDS: dp (a power of
+// two) >= d threads per group, the groups' sums added in order.
+__device__ __forceinline__ void sc_sum_c(const ScJob &J, double *grp, double *c) {
+  const int d = J.s * J.r;
+  int dp = 1;
+  while (dp < d) dp <<= 1;
+  const int ng = SCP_T / dp < 16 ? SCP_T / dp : 16;   // the last sum is serial
+  const int e = threadIdx.x & (dp - 1), g = threadIdx.x / dp;
+  double t = 0.0;
+  if (e < d && g < ng) {
+#pragma unroll 8
+    for (int b = g; b < J.nblk; b += ng) t += J.cpart[(size_t)b * d + e];
+  }
+  grp[threadIdx.x] = t;
+  __syncthreads();
+  if (threadIdx.x < d) {
+    double v = 0.0;
+    for (int q = 0; q < ng; ++q) v += grp[q * dp + threadIdx.x];
+    c[threadIdx.x] = v;
+  }
+  __syncthreads();
+}
+
+// (S y_h)[i] for the block's 64 columns, y in LDS [s][r]: the block's waves
+// share the modes and wave h adds the parts in order (returned there; other
+// waves return 0).  NW waves; part holds NW * s * 64 doubles.
+template <int NW>
+__device__ __forceinline__ double sc_expand(const ScJob &J, int blk, const double *y,
+                                            double *part) {
+  const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
+  const double *Sc = J.S + (size_t)blk * 64 + lane;
+  double acc[SC_S] = {0.0, 0.0, 0.0, 0.0, 0.0, 0.0};
+#pragma unroll 4
+  for (int j = w; j < J.r; j += NW) {
+    const double sv = Sc[(size_t)j * J.ns];
+#pragma unroll
+    for (int h = 0; h < SC_S; ++h)
+      if (h < J.s) acc[h] += sv * y[h * J.r + j];
+  }
+#pragma unroll
+  for (int h = 0; h < SC_S; ++h)
+    if (h < J.s) part[(w * J.s + h) * 64 + lane] = acc[h];
+  __syncthreads();
+  double t = 0.0;
+  if (w < J.s)
+    for (int q = 0; q < NW; ++q) t += part[(q * J.s + w) * 64 + lane];
+  return t;
+}
+
+// ---- norm: c, and the block's share of rho^2 = ||b - S c||^2 ----
+constexpr int SCN_LDS = SCP_T + 256 + SCP_T * SC_S + 8;   // doubles
+__device__ __forceinline__ void sc_norm_body(const ScJob &J, int blk, double *lds) {
+  double *grp = lds, *c = grp + SCP_T, *part = c + 256, *rs = part + SCP_T * SC_S;
+  const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
+  sc_sum_c(J, grp, c);
+  if (blk == 0 && threadIdx.x < J.s * J.r) J.c[threadIdx.x] = c[threadIdx.x];
+  const double t = sc_expand<SCP_T / 64>(J, blk, c, part);
+  const int i = blk * 64 + lane;
+  if (w < J.s) {
+    const double *b = J.partials ? J.b : J.bin;
+    double v = i < J.n ? b[(size_t)w * J.n + i] - t : 0.0;
+    v = sc_wave_sum(v * v);
+    if (lane == 0) rs[w] = v;
+  }
+  __syncthreads();
+  if (threadIdx.x == 0) {
+    double v = 0.0;
+    for (int h = 0; h < J.s; ++h) v += rs[h];
+    J.rpart[blk] = v;
+  }
+}
+
+// ---- solve: GMRES on the d + 1 reduced coordinates, x = t b + S (x_c - t c) ----
+constexpr int SCS_T = 256, SCS_W = SCS_T / 64;
+__host__ __device__ inline size_t sc_solve_lds(int d, int MX) {   // doubles
+  return (size_t)(MX + 1) * (d + 1) + (size_t)MX * (MX + 1) / 2 + MX;
+}
+// y = x_c - t c into ys[0 .. d), t into ys[d] (LDS); the block's first SCS_W
+// waves work, any further ones only keep the barriers.  record: write status.
+__device__ __forceinline__ void sc_gmres(const ScJob &J, int MX, double rtol, double *ys,
+                                         bool record, double *__restrict__ st_out,
+                                         bool with_flag) {
+  extern __shared__ __align__(16) unsigned char smem_raw[];
+  __shared__ double c[256], ws[256], hs[66], cs[64], sn[64], gv[66], yv[64];
+  __shared__ double wsum[SCS_W];
+  __shared__ double res_s, hn_s;
+  __shared__ int done_s;
+  const int d = J.s * J.r, dim = d + 1;
+  double *V = reinterpret_cast<double *>(smem_raw);   // [MX + 1][dim]
+  double *H = V + (size_t)(MX + 1) * dim;             // column j at j (j + 1) / 2
+  const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
+  const int h0 = tid / J.r, m0 = tid - h0 * J.r;      // block and mode of coordinate tid < d
+  // the coordinates of b
+  double phi[SC_S];   // this coordinate's row of J - I
+#pragma unroll
+  for (int h = 0; h < SC_S; ++h)
+    phi[h] = (h < J.s && tid < d) ? J.Phi[(size_t)(h0 * J.s + h) * J.r + m0] : 0.0;
+  double v = 0.0;
+  if (wv == 0) {
+    double t = 0.0;
+    for (int b = lane; b < J.nblk; b += 64) t += J.rpart[b];
+    t = sc_wave_sum(t);
+    if (lane == 0) c[d] = sqrt(t);
+  }
+  if (tid < d) c[tid] = J.c[tid];
+  __syncthreads();
+  if (tid < dim) v = c[tid];
+  auto block_sum = [&](double x) {   // same order in every thread
+    x = sc_wave_sum(x);
+    if (lane == 0 && wv < SCS_W) wsum[wv] = x;
+    __syncthreads();
+    double t = 0.0;
+    for (int q = 0; q < SCS_W; ++q) t += wsum[q];
+    __syncthreads();
+    return t;
+  };
+  const double rho = c[d];
+  const double beta = sqrt(block_sum(v * v));
+  if (tid == 0) {
+    gv[0] = beta;
+    res_s = hn_s = beta;
+    done_s = (beta == 0.0 || !isfinite(beta)) ? 1 : 0;
+  }
+  if (tid < dim) V[tid] = beta > 0.0 ? v * (1.0 / beta) : 0.0;
+  __syncthreads();
+  int m = 0;
+  while (m < MX && !done_s) {
+    const int j = m, nv = j + 1;
+    const double *vj = V + (size_t)j * dim;
+    double wr = 0.0;
+    if (tid < dim) {
+      wr = vj[tid];
+      if (tid < d) {
+#pragma unroll
+        for (int h = 0; h < SC_S; ++h)
+          if (h < J.s) wr += phi[h] * vj[h * J.r + m0];
+      }
+      ws[tid] = wr;
+    }
+    double hacc = 0.0;
+    for (int pass = 0; pass < 2; ++pass) {   // classical Gram-Schmidt, twice
+      __syncthreads();
+      if (wv < SCS_W)
+        for (int i = wv; i < nv; i += SCS_W) {
+          double t = 0.0;
+          for (int e = lane; e < dim; e += 64) t += V[(size_t)i * dim + e] * ws[e];
+          t = sc_wave_sum(t);
+          if (lane == 0) hs[i] = t;
+        }
+      __syncthreads();
+      if (tid < nv) hacc += hs[tid];
+      if (tid < dim) {
+        for (int i = 0; i < nv; ++i) wr -= hs[i] * V[(size_t)i * dim + tid];
+        ws[tid] = wr;
+      }
+    }
+    const double hn = sqrt(block_sum(tid < dim ? wr * wr : 0.0));
+    if (tid < nv) hs[tid] = hacc;
+    __syncthreads();
+    if (tid == 0) {
+      hs[j + 1] = hn;
+      for (int i = 0; i < j; ++i) {
+        const double a = hs[i], b = hs[i + 1];
+        hs[i] = cs[i] * a + sn[i] * b;
+        hs[i + 1] = -sn[i] * a + cs[i] * b;
+      }
+      const double a = hs[j], b = hs[j + 1];
+      const double rr = hypot(a, b);
+      const double cc = (rr == 0.0) ? 1.0 : a / rr, ss = (rr == 0.0) ? 0.0 : b / rr;
+      cs[j] = cc;
+      sn[j] = ss;
+      hs[j] = rr;
+      const double gj = gv[j];
+      gv[j] = cc * gj;
+      gv[j + 1] = -ss * gj;
+      const double res = fabs(ss * gj);
+      res_s = res;
+      hn_s = hn;
+      done_s = (res <= rtol * beta || hn == 0.0 || !isfinite(res)) ? 1 : 0;
+    }
+    __syncthreads();
+    if (tid < nv) H[(size_t)j * (j + 1) / 2 + tid] = hs[tid];
+    if (tid < dim) V[(size_t)(j + 1) * dim + tid] = hn > 0.0 ? wr * (1.0 / hn) : 0.0;
+    m = j + 1;
+    __syncthreads();
+  }
+  // R y = g, then the reduced solution
+  if (tid == 0) {
+    for (int i = m - 1; i >= 0; --i) {
+      double t = gv[i];
+      for (int k = i + 1; k < m; ++k) t -= H[(size_t)k * (k + 1) / 2 + i] * yv[k];
+      const double dd = H[(size_t)i * (i + 1) / 2 + i];
+      yv[i] = (dd != 0.0) ? t / dd : 0.0;
+    }
+    if (record) {
+      st_out[0] = res_s;
+      st_out[1] = hn_s;
+      st_out[2] = (double)m;
+      st_out[3] = beta;
+      if (with_flag) st_out[4] = done_s ? 1.0 : 0.0;
+    }
+  }
+  __syncthreads();
+  double xr = 0.0;
+  if (tid < dim)
+    for (int i = 0; i < m; ++i) xr += yv[i] * V[(size_t)i * dim + tid];
+  if (tid == d) ys[d] = rho > 0.0 ? xr / rho : (m > 0 ? 1.0 : 0.0);
+  __syncthreads();
+  if (tid < d) ys[tid] = xr - ys[d] * c[tid];
+  __syncthreads();
+}
+
+// The block's columns of x = t b + S y (ys as sc_gmres leaves it).
+constexpr int SCC_LDS = SCS_T * SC_S;   // doubles
+__device__ __forceinline__ void sc_columns(const ScJob &J, int blk, const double *ys,
+                                           double *part) {
+  const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6, i = blk * 64 + lane;
+  const double *bv = J.partials ? J.b : J.bin;
+  const double tb = ys[J.s * J.r];
+  if (wv < SCS_W) {
+    const double *Sc = J.S + i;
+    double acc[SC_S] = {0.0, 0.0, 0.0, 0.0, 0.0, 0.0};
+#pragma unroll 4
+    for (int j = wv; j < J.r; j += SCS_W) {
+      const double sv = Sc[(size_t)j * J.ns];
+#pragma unroll
+      for (int h = 0; h < SC_S; ++h)
+        if (h < J.s) acc[h] += sv * ys[h * J.r + j];
+    }
+#pragma unroll
+    for (int h = 0; h < SC_S; ++h)
+      if (h < J.s) part[(wv * J.s + h) * 64 + lane] = acc[h];
+  }
+  __syncthreads();
+  if (wv < SCS_W)
+    for (int h = wv; h < J.s; h += SCS_W) {
+      double t = 0.0;
+      for (int q = 0; q < SCS_W; ++q) t += part[(q * J.s + h) * 64 + lane];
+      if (i < J.n) J.x[(size_t)h * J.n + i] = tb * bv[(size_t)h * J.n + i] + t;
+    }
+}
+
+// ---- product J v = v + S (J - I) S^T v after a projection of v ----
+__device__ __forceinline__ void sc_apply_body(const ScJob &J, int blk, double *lds) {
+  double *grp = lds, *c = grp + SCP_T, *part = c + 256;
+  __shared__ double y[256];
+  const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
+  sc_sum_c(J, grp, c);
+  if (threadIdx.x < J.s * J.r) {
+    const int k = threadIdx.x / J.r, j = threadIdx.x - k * J.r;
+    double t = 0.0;
+    for (int h = 0; h < J.s; ++h) t += J.Phi[(size_t)(k * J.s + h) * J.r + j] * c[h * J.r + j];
+    y[threadIdx.x] = t;
+  }
+  __syncthreads();
+  const double t = sc_expand<SCP_T / 64>(J, blk, y, part);
+  const int i = blk * 64 + lane;
+  if (w < J.s && i < J.n) J.x[(size_t)w * J.n + i] = J.bin[(size_t)w * J.n + i] + t;
+}
+
+__global__ void __launch_bounds__(SCP_T) sc_project_kernel(const ScJob J) {
+  __shared__ double lds[SCP_LDS];
+  sc_project_body(J, blockIdx.x, lds);
+}
+__global__ void __launch_bounds__(SCP_T) sc_norm_kernel(const ScJob J) {
+  __shared__ double lds[SCN_LDS];
+  sc_norm_body(J, blockIdx.x, lds);
+}
+__global__ void __launch_bounds__(SCS_T)
+sc_solve_kernel(const ScJob J, int MX, double rtol, double *__restrict__ host) {
+  __shared__ double ys[256], lds[SCC_LDS];
+  sc_gmres(J, MX, rtol, ys, blockIdx.x == 0, host, true);
+  sc_columns(J, blockIdx.x, ys, lds);
+}
+// n <= 256 (SC_ONE column blocks): all three steps in one block.  Every step
+// works on the same column blocks in the same order, so results are those of
+// the three launches.
+__global__ void __launch_bounds__(SCP_T)
+sc_one_kernel(const ScJob J, int MX, double rtol, double *__restrict__ host) {
+  __shared__ double ys[256], lds[SCN_LDS];
+  for (int b = 0; b < J.nblk; ++b) {
+    sc_project_body(J, b, lds);
+    __syncthreads();
+  }
+  for (int b = 0; b < J.nblk; ++b) {
+    sc_norm_body(J, b, lds);
+    __syncthreads();
+  }
+  sc_gmres(J, MX, rtol, ys, true, host, true);
+  for (int b = 0; b < J.nblk; ++b) {
+    sc_columns(J, b, ys, lds);
+    __syncthreads();
+  }
+}
+__global__ void __launch_bounds__(SCP_T) sc_apply_kernel(const ScJob J) {
+  __shared__ double lds[SCN_LDS];
+  sc_apply_body(J, blockIdx.x, lds);
+}
+__global__ void __launch_bounds__(SCP_T)
+sc_project_batch_kernel(const ScJob *__restrict__ jobs, const int2 *__restrict__ map) {
+  const int2 e = map[blockIdx.x];
+  __shared__ double lds[SCP_LDS];
+  sc_project_body(jobs[e.x], e.y, lds);
+}
+__global__ void __launch_bounds__(SCP_T)
+sc_norm_batch_kernel(const ScJob *__restrict__ jobs, const int2 *__restrict__ map) {
+  const int2 e = map[blockIdx.x];
+  __shared__ double lds[SCN_LDS];
+  sc_norm_body(jobs[e.x], e.y, lds);
+}
+__global__ void __launch_bounds__(SCS_T)
+sc_gmres_batch_kernel(const ScJob *__restrict__ jobs, int MX, double rtol,
+                      double *__restrict__ status) {
+  __shared__ double ys[256];
+  const ScJob &J = jobs[blockIdx.x];
+  sc_gmres(J, MX, rtol, ys, true, status + 4 * blockIdx.x, false);
+  if (threadIdx.x <= J.s * J.r) J.y[threadIdx.x] = ys[threadIdx.x];
+}
+__global__ void __launch_bounds__(SCS_T)
+sc_columns_batch_kernel(const ScJob *__restrict__ jobs, const int2 *__restrict__ map) {
+  __shared__ double ys[256], lds[SCC_LDS];
+  const int2 e = map[blockIdx.x];
+  const ScJob &J = jobs[e.x];
+  if (threadIdx.x <= J.s * J.r) ys[threadIdx.x] = J.y[threadIdx.x];
+  __syncthreads();
+  sc_columns(J, e.y, ys, lds);
+}
+
+// ---- host: eigenvalues, the number of modes, tables ----
+
+// sin^2(pi j / (2 (n + 1))) and the eigenvalues of M and tau K on mode j
+// (1-based), without the cancellation of d + 2 o cos at smooth modes.
+struct Mode {
+  double s2, m, kap;
+};
+Mode mode_of(pd_plan p, int j) {
+  const double *u = p->uni;
+  const double s = std::sin(M_PI * (double)j / (2.0 * (p->n + 1)));
+  Mode o;
+  o.s2 = s * s;
+  o.m = (u[1] + 2.0 * u[0]) - 4.0 * u[0] * o.s2;
+  o.kap = (u[4] + 2.0 * u[3]) - 4.0 * u[3] * o.s2;
+  return o;
+}
+
+// A bound on |J - I| on a mode with ratio z = tau kappa / m (BDF: tau beta
+// kappa / m): powers of the step's companion matrix by repeated squaring.
+// Infinite when the mode's block is (nearly) singular or not finite.
+double mode_bound(pd_plan p, double z) {
+  const int s = p->bdf_s;
+  if (!std::isfinite(z) || 1.0 + z == 0.0) return HUGE_VAL;
+  double C[SC_S][SC_S] = {}, T[SC_S][SC_S];
+  for (int i = 0; i < s; ++i) C[0][i] = p->bdf_alpha[i] / (1.0 + z);
+  for (int i = 1; i < s; ++i) C[i][i - 1] = 1.0;
+  double big = 0.0;
+  for (int l = 1; l < p->ell; l <<= 1) {
+    big = 0.0;
+    for (int i = 0; i < s; ++i)
+      for (int k = 0; k < s; ++k) {
+        double t = 0.0;
+        for (int q = 0; q < s; ++q) t += C[i][q] * C[q][k];
+        T[i][k] = t;
+        big = std::max(big, std::fabs(t));
+      }
+    for (int i = 0; i < s; ++i)
+      for (int k = 0; k < s; ++k) C[i][k] = T[i][k];
+  }
+  if (!std::isfinite(big)) return HUGE_VAL;
+  // |C^ell| (1 + ...) : alpha C^ell / (1 - alpha C^ell) for s = 1
+  if (s == 1) {
+    const double e = p->alpha * C[0][0];
+    return e == 1.0 ? HUGE_VAL : std::fabs(e / (1.0 - e));
+  }
+  return s * big;
+}
+
+}  // namespace
+
+// Columns of the mode table, padded to the 64-column blocks.
+static int sc_stride(int n) { return (n + 63) / 64 * 64; }
+
+// Doubles of the tables and workspace at r modes (1D).
+static size_t sc_doubles(int n, int s, int r) {
+  const size_t nblk = (size_t)sc_stride(n) / 64;
+  return (size_t)r * sc_stride(n) + (size_t)s * s * r + nblk * s * r + nblk + 512;
+}
+
+size_t pd_sc_max_doubles(int n, int s) {
+  return sc_doubles(n, s, std::min(n, SC_DMAX / s));
+}
+
+// Tables of a plan whose capacitance system is solved in the sine basis;
+// false (nothing changed) when the plan is not of that kind: see below.
+// fac: the shifted solves' constants; ct: BDF's weights [s][s][F2] complex.
+bool pd_sc_build(pd_plan p, const std::vector<double> &fac, const std::vector<double> &ct,
+                 std::vector<double> &tab) {
+  const double *u = p->uni;
+  const int n = p->n, s = p->bdf_s, F2 = p->F2;
+  // float64 GMRES plans on uniform 1D grids with symmetric M and K
+  if (p->dims != 1 || p->prec != PD_FP64 || p->krylov != PD_KRYLOV_GMRES || p->sine ||
+      p->autotune || !p->uniform || u[0] != u[2] || u[3] != u[5])
+    return false;
+  const bool scan = pd_use_scan(p);
+  // m and kappa are linear in sin^2(theta / 2), so kappa / m is monotone where
+  // m has one sign: for the usual signs it grows and D falls with j
+  const Mode q1 = mode_of(p, 1), qn = mode_of(p, n);
+  const double e1 = p->lam[0] * q1.m + q1.kap, en = p->lam[0] * qn.m + qn.kap;
+  if (!(q1.m > 0.0 && qn.m > 0.0 && e1 > 0.0 && en > 0.0) || !(qn.kap / qn.m >= q1.kap / q1.m))
+    return false;
+  int r = 0;
+  double worst = 0.0;
+  for (int j = 1; j <= n; ++j) {
+    const Mode q = mode_of(p, j);
+    const double D = mode_bound(p, q.kap / q.m);
+    if (!(D < 1e15)) return false;
+    if (D <= SC_CUT) break;
+    worst = std::max(worst, D);
+    r = j;
+    // more modes than the reduced system holds: the general product
+    if (r * s > SC_DMAX) return false;
+  }
+  if (r < 1) r = 1;
+  // The passes apply a rounded factorisation of every P_k; J must apply the
+  // same one.  The recurrence form's is known in closed form (above).  The
+  // partition form's is not: there the modes' exact eigenvalues differ from
+  // it by cond(P_0) u, which must not show.
+  const double cond0 = std::max(e1, en) / std::min(e1, en);
+  if (!scan && !(worst * cond0 * 0x1p-53 <= 1e-12)) return false;
+  const int ns = sc_stride(n), nblk = ns / 64;
+  p->sc_r = r;
+  p->sc_ns = ns;
+  p->sc_nblk = nblk;
+  tab.assign(sc_doubles(n, s, r), 0.0);
+  const long N2 = 2L * (n + 1);
+  const double sc = std::sqrt(2.0 / (n + 1));
+  std::vector<double> sins((size_t)N2);
+  for (long q = 0; q < N2; ++q) {
+    // sin(pi q / (n + 1)), the argument folded into [0, pi / 2]
+    long a = q > n + 1 ? N2 - q : q;
+    if (2 * a > n + 1) a = n + 1 - a;
+    const double v = std::sin(M_PI * (double)a / (double)(n + 1));
+    sins[q] = sc * (q > n + 1 ? -v : v);
+  }
+  for (int j = 1; j <= r; ++j)
+    for (int i = 1; i <= n; ++i) tab[(size_t)(j - 1) * ns + i - 1] = sins[(size_t)((long)j * i % N2)];
+  double *Phi = &tab[(size_t)r * ns];
+  const size_t NF = 6 * (size_t)(p->tri.MR - 1);
+  using C = std::complex<double>;
+  for (int j = 1; j <= r; ++j) {
+    const Mode q = mode_of(p, j);
+    for (int k = 0; k < F2; ++k) {
+      C z;   // P_k^{-1} M on the mode
+      if (scan) {
+        const double *f = &fac[(size_t)k * NF * 2];
+        const C rk(f[0], f[1]), ik(f[8], f[9]), e = 1.0 - rk;
+        z = q.m * ik / (e * e + 4.0 * q.s2 * rk);
+      } else {
+        z = q.m / (C(p->lam[2 * k], p->lam[2 * k + 1]) * q.m + q.kap);
+      }
+      if (s == 1) {
+        Phi[j - 1] += p->gJ[2 * k] * z.real() - p->gJ[2 * k + 1] * z.imag();
+      } else {
+        for (int b = 0; b < s * s; ++b) {
+          const double *g = &ct[2 * ((size_t)b * F2 + k)];
+          Phi[(size_t)b * r + j - 1] += g[0] * z.real() - g[1] * z.imag();
+        }
+      }
+    }
+  }
+  return true;
+}
+
+// The launches' job: b from pass B's partials (bin null) or from bin.
+ScJob pd_sc_job(pd_plan p, const double *bin, double *x) {
+  const int s = p->bdf_s, r = p->sc_r;
+  ScJob J;
+  J.n = p->n;
+  J.ns = p->sc_ns;
+  J.s = s;
+  J.r = r;
+  J.nblk = p->sc_nblk;
+  const int nitems = pd_tri_nitems(p->tri, p->F2);
+  J.G = nitems < p->tri_G ? nitems : p->tri_G;
+  J.partials = bin ? nullptr : p->partials;
+  J.bin = bin;
+  J.b = p->bvec;
+  J.x = x;
+  double *t = p->sc_tab;
+  J.S = t;
+  t += (size_t)r * J.ns;
+  J.Phi = t;
+  t += (size_t)s * s * r;
+  J.cpart = t;
+  t += (size_t)J.nblk * s * r;
+  J.rpart = t;
+  t += J.nblk;
+  J.c = t;
+  J.y = t + 256;
+  return J;
+}
+
+size_t pd_sc_lds(const ScJob &J, int MX) { return sc_solve_lds(J.s * J.r, MX) * sizeof(double); }
+
+// x = J^{-1} b to residual <= rtol ||b||, enqueued without synchronising;
+// the status lands in the plan's pinned block (read with pd_gmres_read).
+pd_status pd_sc_enqueue(pd_plan p, const double *bin, double *x, double rtol) {
+  const ScJob J = pd_sc_job(p, bin, x);
+  if (J.nblk <= SC_ONE && pd_sc_lds(J, p->maxit) <= SC_ONE_LDS) {
+    hipLaunchKernelGGL(sc_one_kernel, dim3(1), dim3(SCP_T), pd_sc_lds(J, p->maxit), p->stream, J,
+                       p->maxit, rtol, p->host_dev);
+    PD_HIP_CHECK(hipGetLastError());
+    return PD_OK;
+  }
+  hipLaunchKernelGGL(sc_project_kernel, dim3(J.nblk), dim3(SCP_T), 0, p->stream, J);
+  hipLaunchKernelGGL(sc_norm_kernel, dim3(J.nblk), dim3(SCP_T), 0, p->stream, J);
+  hipLaunchKernelGGL(sc_solve_kernel, dim3(J.nblk), dim3(SCS_T), pd_sc_lds(J, p->maxit),
+                     p->stream, J, p->maxit, rtol, p->host_dev);
+  PD_HIP_CHECK(hipGetLastError());
+  return PD_OK;
+}
+
+pd_status pd_sc_apply(pd_plan p, const double *v, double *Jv) {
+  const ScJob J = pd_sc_job(p, v, Jv);
+  hipLaunchKernelGGL(sc_project_kernel, dim3(J.nblk), dim3(SCP_T), 0, p->stream, J);
+  hipLaunchKernelGGL(sc_apply_kernel, dim3(J.nblk), dim3(SCP_T), 0, p->stream, J);
+  PD_HIP_CHECK(hipGetLastError());
+  return PD_OK;
+}
+
+// One GMRES block per problem and a launch of its own for the columns of x:
+// with many problems the redundant copies would fill the card (96 problems
+// of up to 4095 columns: 222 us in the fused form).
+pd_status pd_sc_batch(const ScJob *jobs, int count, const int2 *map, int nblocks, size_t lds,
+                      int MX, double rtol, double *status, hipStream_t s) {
+  hipLaunchKernelGGL(sc_project_batch_kernel, dim3(nblocks), dim3(SCP_T), 0, s, jobs, map);
+  hipLaunchKernelGGL(sc_norm_batch_kernel, dim3(nblocks), dim3(SCP_T), 0, s, jobs, map);
+  hipLaunchKernelGGL(sc_gmres_batch_kernel, dim3(count), dim3(SCS_T), lds, s, jobs, MX, rtol,
+                     status);
+  hipLaunchKernelGGL(sc_columns_batch_kernel, dim3(nblocks), dim3(SCS_T), 0, s, jobs, map);
+  PD_HIP_CHECK(hipGetLastError());
+  return PD_OK;
+}
+
+void pd_sc_set_attributes(size_t max_lds) {
+  pd_set_max_lds(reinterpret_cast<const void *>(&sc_solve_kernel), (int)max_lds);
+  pd_set_max_lds(reinterpret_cast<const void *>(&sc_one_kernel), (int)max_lds);
+  pd_set_max_lds(reinterpret_cast<const void *>(&sc_gmres_batch_kernel), (int)max_lds);
+}

@@ -97,13 +97,17 @@ pd_status solve_speculative(pd_plan p, const double *u0, const double *F, double
     PdRange r("paradiag: pass B (shifted solves, b)");
     st = pd_launch_tridiag(p, 0, p->spec, nullptr, nullptr);
     if (st != PD_OK) return st;
-    st = pd_launch_reduce_partials(p, nullptr, p->bvec);
-    if (st != PD_OK) return st;
+    if (!p->sc_on) {
+      st = pd_launch_reduce_partials(p, nullptr, p->bvec);
+      if (st != PD_OK) return st;
+    }
   }
   const int pred = p->gm_pred < 1 ? 1 : (p->gm_pred > p->maxit ? p->maxit : p->gm_pred);
   {
     PdRange r("paradiag: capacitance GMRES (enqueued ahead)");
-    st = pd_gmres_enqueue(p, p->bvec, p->xvec, rtol, pred);
+    // in the sine basis the whole iteration is enqueued, whatever its length
+    st = p->sc_on ? pd_sc_enqueue(p, nullptr, p->xvec, rtol)
+                  : pd_gmres_enqueue(p, p->bvec, p->xvec, rtol, pred);
     if (st != PD_OK) return st;
   }
   {
@@ -133,7 +137,7 @@ pd_status solve_speculative(pd_plan p, const double *u0, const double *F, double
     return PD_ENONFINITE;
   }
   pd_status gst = PD_OK;
-  if (!done && m < p->maxit) {
+  if (!done && m < p->maxit && !p->sc_on) {
     int its = m;
     double rr = 0.0;
     gst = pd_gmres_continue(p, p->xvec, rtol, &its, &rr);

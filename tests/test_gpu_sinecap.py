@@ -1,0 +1,60 @@
+"""The capacitance system in the sine basis: J v and J x = b against the
+closed-form eigenvalues a^ell / (a^ell - alpha) on the sine vectors, at the
+sizes where the solve changes form (rows per thread, whole waves per system,
+ragged column blocks, few and many modes, and just past the mode limit, where
+the general product takes over)."""
+import numpy as np
+import pytest
+
+from paper_2304_12597_amd import workloads as wl
+
+pytestmark = pytest.mark.gpu
+torch = pytest.importorskip("torch")
+
+
+def modes(p, alpha):
+    """Dense orthonormal sine basis S and J's eigenvalues."""
+    n, h = p.n, p.h
+    k = np.arange(1, n + 1)
+    s2 = np.sin(np.pi * k * h / 2) ** 2
+    m = np.ones(n) if p.M is None else (p.M[1][0] + 2 * p.M[2][0]) - 4 * p.M[2][0] * s2
+    kap = -4 * p.K[2][0] * s2
+    L = np.longdouble
+    z = L(p.tau) * L(1) * kap / m
+    decay = np.exp(-p.ell * np.log1p(z))           # a^-ell
+    S = np.sqrt(2.0 / (n + 1)) * np.sin(np.pi * h * (np.outer(k, k) % (2 * (n + 1))))
+    return S, (1 / (1 - L(alpha) * decay)).astype(float)
+
+
+CASES = [("fd1", 40, 64, 1.0, 1.0), ("fem1", 257, 32, 1.0, 1.0), ("fd1", 320, 256, 3e-3, 1.0),
+         ("fem1", 1000, 128, 1e-3, 1.0), ("fd1", 1000, 128, 1e-3, 1e-2),
+         ("fd1", 1300, 128, 1.45e-4, 1.0), ("fd1", 1300, 128, 1.0e-4, 1.0),
+         ("fem1", 4097, 64, 1e-2, 1.0), ("fd1", 2047, 1024, 1.0, 1.0)]
+
+
+@pytest.mark.parametrize("kind,n,ell,nu,alpha", CASES)
+def test_capacitance_in_the_sine_basis(lib, kind, n, ell, nu, alpha):
+    p = wl.heat_1d(kind, n, ell, 1.0, nu, np.random.default_rng(n), False)
+    S, lam = modes(p, alpha)
+    rng = np.random.default_rng(1)
+    v = rng.standard_normal(n)
+    # J v: rounding of the table, the projections and the eigenvalues, each a few
+    # u n relative to |J| |v| (rounded shifted solves: cond(P_0) u, up to ~n^2 u)
+    Jv = S @ (lam * (S @ v))
+    dev = torch.device("cuda:0")
+    T = lambda a: torch.tensor(a, device=dev)
+    plan = lib.paradiag_plan_create(n, ell, p.tau, p.M, p.K, alpha=alpha,
+                                    stream=torch.cuda.current_stream().cuda_stream)
+    try:
+        out, x = torch.empty(n, dtype=torch.float64, device=dev), torch.zeros(n, dtype=torch.float64, device=dev)
+        vd = T(v)
+        lib.paradiag_capacitance_apply(plan, vd, out)
+        torch.cuda.synchronize()
+        bound = 2.0**-53 * n**2 * lam.max()
+        assert np.linalg.norm(out.cpu().numpy() - Jv) <= max(bound, 1e-12) * np.linalg.norm(v)
+        its, rel = lib.paradiag_capacitance_solve(plan, vd, x, 1e-11)
+        assert 1 <= its <= 64 and rel <= 1e-11
+        xr = S @ ((S @ v) / lam)
+        assert np.linalg.norm(x.cpu().numpy() - xr) <= (1e-11 * lam.max() + bound) * np.linalg.norm(v)
+    finally:
+        lib.paradiag_plan_destroy(plan)
