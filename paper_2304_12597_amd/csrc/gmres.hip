@@ -566,7 +566,96 @@ pd_status gmres_fused(pd_plan p, const double *b, double *x, double rtol, int *i
   return (res <= rtol * beta || st[1] == 0.0) ? PD_OK : PD_ENOTCONV;
 }
 
+// GMRES on J = diag(1 + Phi[0 .. nc), 1) from b = (c + c2, rho), all iterations in
+// one single-block launch (the vectors of a 2D capacitance system in its sine
+// coordinates, at most ARN_MAXN; sinecap.hip): rho^2 is summed from rpart
+// into c[nc], the product is formed by the thread that owns the entry, and
+// y = x_c - t c2, y[nc] = t = x_rho / rho are left for the columns of x.
+template <int RPT>
+__global__ void __launch_bounds__(ARN_T)
+gm_diag_kernel(int nc, double *__restrict__ c, const double *__restrict__ c2,
+               const double *__restrict__ Phi,
+               const double *__restrict__ rpart, int nparts, double *__restrict__ V,
+               double *__restrict__ w, double *__restrict__ gm, int MX, double rtol,
+               double *__restrict__ y, double *__restrict__ host) {
+  constexpr int NW = ARN_T / 64;
+  __shared__ double part[NW];
+  __shared__ double yv[64];
+  __shared__ double tsh;
+  const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6, n = nc + 1;
+  GmLayout L{MX};
+  double s = 0.0;
+  for (int i = tid; i < nparts; i += ARN_T) s += rpart[i];
+  s = wave_sum(s);
+  if (lane == 0) part[wv] = s;
+  __syncthreads();
+  double rho = 0.0;
+  for (int q = 0; q < NW; ++q) rho += part[q];
+  rho = sqrt(rho);
+  if (tid == 0) c[nc] = rho;
+  for (int r = tid; r < nc; r += ARN_T) c[r] += c2[r];
+  __syncthreads();
+  gm_init_body<RPT>(n, c, V, gm, MX, host, true);
+  __syncthreads();
+  for (int j = 0; j < MX; ++j) {
+    if (gm[L.st(GM_DONE)] != 0.0) break;
+#pragma unroll
+    for (int k = 0; k < RPT; ++k) {
+      const int r = tid + k * ARN_T;
+      if (r < n) {
+        const double v = V[(size_t)j * n + r];
+        w[r] = r < nc ? v + Phi[r] * v : v;
+      }
+    }
+    arnoldi_step_body<RPT>(n, V, w, gm, MX, j, rtol, host, true);
+    __syncthreads();
+  }
+  const int m = (int)gm[L.st(2)];
+  if (tid == 0) {
+    for (int i = m - 1; i >= 0; --i) {
+      double t = gm[L.g(i)];
+      for (int k = i + 1; k < m; ++k) t -= gm[L.H(i, k)] * yv[k];
+      const double d = gm[L.H(i, i)];
+      yv[i] = (d != 0.0) ? t / d : 0.0;
+    }
+    double t = 0.0;
+    for (int i = 0; i < m; ++i) t += yv[i] * V[(size_t)i * n + nc];
+    tsh = rho > 0.0 ? t / rho : (m > 0 ? 1.0 : 0.0);
+    y[nc] = tsh;
+  }
+  __syncthreads();
+  const double tb = tsh;
+#pragma unroll
+  for (int k = 0; k < RPT; ++k) {
+    const int r = tid + k * ARN_T;
+    if (r < nc) {
+      double t = 0.0;
+      for (int i = 0; i < m; ++i) t += yv[i] * V[(size_t)i * n + r];
+      y[r] = t - tb * c2[r];
+    }
+  }
+}
+
 }  // namespace
+
+pd_status pd_gmres_diag(pd_plan p, int nc, double *c, const double *c2, const double *Phi,
+                        const double *rpart, int nparts, double *y, double rtol) {
+  const int n = nc + 1;
+  if (n > ARN_MAXN) {
+    pd_set_error("capacitance GMRES: too many coordinates");
+    return PD_ENOTSUP;
+  }
+#define PD_GD(RPT)                                                                             \
+  hipLaunchKernelGGL((gm_diag_kernel<RPT>), dim3(1), dim3(ARN_T), 0, p->stream, nc, c, c2, Phi, rpart, \
+                     nparts, p->V, p->wvec, p->gm, p->maxit, rtol, y, p->host_dev)
+  if (n <= ARN_T) PD_GD(1);
+  else if (n <= 4 * ARN_T) PD_GD(4);
+  else if (n <= 8 * ARN_T) PD_GD(8);
+  else PD_GD(16);
+#undef PD_GD
+  PD_HIP_CHECK(hipGetLastError());
+  return PD_OK;
+}
 
 bool pd_gmres_fused_ok(pd_plan p) { return p->dims == 1 && p->ncap <= ARN_MAXN; }
 size_t pd_gmres_done_index(int maxit) { return (size_t)GmLayout{maxit}.st(GM_DONE); }

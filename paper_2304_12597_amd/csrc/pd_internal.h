@@ -224,7 +224,7 @@ struct ScJob {
   double *b = nullptr;                // b summed from the partials
   const double *S = nullptr;          // [r][ns] orthonormal modes, zero past n
   const double *Phi = nullptr;        // [s][s][r] J - I on the modes
-  double *cpart = nullptr, *rpart = nullptr, *c = nullptr, *y = nullptr;
+  double *cpart = nullptr, *cpart2 = nullptr, *rpart = nullptr, *c = nullptr, *y = nullptr;
   double *x = nullptr;
 };
 
@@ -416,6 +416,13 @@ pd_status pd_sc_apply(pd_plan p, const double *v, double *Jv);
 pd_status pd_sc_batch(const ScJob *jobs, int count, const int2 *map, int nblocks, size_t lds,
                       int MX, double rtol, double *status, hipStream_t s);
 void pd_sc_set_attributes(size_t max_lds);
+size_t pd_sc2_max_doubles(int n);
+bool pd_sc2_build(pd_plan p, std::vector<double> &tab);
+size_t pd_sc2_size(pd_plan p);
+pd_status pd_sc2_finish(pd_plan p);
+// GMRES on diag(1 + Phi, 1) from (c + c2, rho), rho^2 = the sum of rpart (gmres.hip)
+pd_status pd_gmres_diag(pd_plan p, int nc, double *c, const double *c2, const double *Phi,
+                        const double *rpart, int nparts, double *y, double rtol);
 pd_status pd_gmres(pd_plan p, const double *b, double *x, double rtol,
                    int *iters, double *relres);
 // rel = ||G - A(U)||_F / ||G||_F; est (if non-null): the plan's error bound

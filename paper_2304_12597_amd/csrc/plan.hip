@@ -254,14 +254,16 @@ pd_status compute_layout(pd_plan p, int cus, size_t max_lds, Layout &L) {
   }
   if (p->prec == PD_FP64 && p->dims == 1 && p->uniform && !p->sine)
     L.cp = std::max(L.cp, pd_sc_max_doubles(n, p->bdf_s));
+  if (p->prec == PD_FP64 && p->dims == 2 && p->bdf_s == 1) L.cp = pd_sc2_max_doubles(n);
   L.coef = 6 * (size_t)n;
   L.lam = 2 * (size_t)F2;
   L.tw = 2 * (size_t)ell;
   L.dal = 2 * (size_t)ell;
   L.spec_bytes = (size_t)F2 * p->nbar * cb;
   if (p->prec == PD_MIXED) L.spec2_bytes = L.spec_bytes;
-  L.vec = p->ncap;
-  L.V = (size_t)(p->maxit + 1) * p->ncap;
+  // 2D: the sine-basis capacitance solve has up to nbar + 1 coordinates
+  L.vec = p->ncap + (p->dims == 2 ? 2 : 0);
+  L.V = (size_t)(p->maxit + 1) * L.vec;
   L.gm = pd_gmres_state_doubles(p->maxit);
   const int B = pd_vec_blocks(p->ncap);
   size_t red_n = 2 * (size_t)B * (p->maxit + 2);
@@ -750,6 +752,7 @@ extern "C" pd_status paradiag_plan_create(pd_plan *out, int n, int ell, double t
     p->sc_on = 1;
     p->cp_on = 0;
   }
+  if (pd_sc2_build(p, sctab)) p->sc_on = 1;
   if (p->cp_on) pd_cp_tables(p, cptab);
   const size_t nbar = p->nbar;
   p->spec_bytes = L.spec_bytes;
@@ -796,7 +799,8 @@ extern "C" pd_status paradiag_plan_create(pd_plan *out, int n, int ell, double t
   PD_TRY(dev_alloc(&p->gm, pd_gmres_state_doubles(p->maxit)));
   PD_TRY(dev_alloc(&p->red, L.red));
   if (p->cp_on) PD_TRY(dev_alloc(&p->cp_tab, p->cpl.total));
-  if (p->sc_on) PD_TRY(dev_alloc(&p->sc_tab, sctab.size()));
+  if (p->sc_on)
+    PD_TRY(dev_alloc(&p->sc_tab, p->dims == 2 ? pd_sc2_size(p) : sctab.size()));
   if (p->krylov == PD_KRYLOV_FOM) {
     PD_TRY(dev_alloc(&p->fom, L.fom));
     PD_TRY(dev_alloc(reinterpret_cast<unsigned char **>(&p->fom_h), L.fom_h_bytes));
@@ -834,6 +838,7 @@ extern "C" pd_status paradiag_plan_create(pd_plan *out, int n, int ell, double t
   PD_TRY(upload(p->twd, twd, p->stream));
   if (p->cp_on) PD_TRY(upload(p->cp_tab, cptab, p->stream));
   if (p->sc_on) PD_TRY(upload(p->sc_tab, sctab, p->stream));
+  if (p->sc_on && p->dims == 2) PD_TRY(pd_sc2_finish(p));
   if (p->bdf_s > 1) PD_TRY(upload(p->bdf_g, bg_gt, p->stream));
   if (p->krylov == PD_KRYLOV_FOM) {
     std::vector<double> mf;

@@ -27,7 +27,7 @@
 // partials into b and projects each 64-column block on the modes), norm
 // (c, and each block's share of rho^2), solve (every block runs the small
 // GMRES on its own copy in LDS -- cheaper than a launch and a round trip --
-// and forms its columns of x = t b + S (x_c - t c), t = x_rho / rho).
+// and forms its columns of x = t b' + S x_c, b' = b - S c, t = x_rho / rho).
 // What bounds them is latency: the tables are at most 192 rows of n doubles
 // and b is read three times.  Sums run in a fixed order and the batched
 // launches use the same bodies, so results are the same alone and in a batch.
@@ -95,20 +95,23 @@ __device__ __forceinline__ void sc_project_body(const ScJob &J, int blk, double 
   }
 }
 
-// c[e] = sum over the blocks of cpart (fixed order), in LDS: dp (a power of
-// two) >= d threads per group, the groups' sums added in order.
-__device__ __forceinline__ void sc_sum_c(const ScJob &J, double *grp, double *c) {
+// c[e] = sum over the blocks of cpart (fixed order), in LDS, by the block's
+// first NT threads: dp (a power of two) >= d threads per group, the groups'
+// sums added in order.
+template <int NT>
+__device__ __forceinline__ void sc_sum_c(const ScJob &J, const double *cpart, double *grp,
+                                         double *c) {
   const int d = J.s * J.r;
   int dp = 1;
   while (dp < d) dp <<= 1;
-  const int ng = SCP_T / dp < 16 ? SCP_T / dp : 16;   // the last sum is serial
+  const int ng = NT / dp < 16 ? NT / dp : 16;   // the last sum is serial
   const int e = threadIdx.x & (dp - 1), g = threadIdx.x / dp;
   double t = 0.0;
   if (e < d && g < ng) {
 #pragma unroll 8
-    for (int b = g; b < J.nblk; b += ng) t += J.cpart[(size_t)b * d + e];
+    for (int b = g; b < J.nblk; b += ng) t += cpart[(size_t)b * d + e];
   }
-  grp[threadIdx.x] = t;
+  if (threadIdx.x < NT) grp[threadIdx.x] = t;
   __syncthreads();
   if (threadIdx.x < d) {
     double v = 0.0;
@@ -144,22 +147,33 @@ __device__ __forceinline__ double sc_expand(const ScJob &J, int blk, const doubl
   return t;
 }
 
-// ---- norm: c, and the block's share of rho^2 = ||b - S c||^2 ----
+// ---- norm: c, b' = b - S c (left in x), the block's share of rho^2 =
+// ||b'||^2, and b' projected again.  b is up to max D times larger than x, so
+// b' keeps a part in span(S) of rounding size relative to b; the second
+// projection takes it out ("twice is enough") before x is formed from b' ----
 constexpr int SCN_LDS = SCP_T + 256 + SCP_T * SC_S + 8;   // doubles
 __device__ __forceinline__ void sc_norm_body(const ScJob &J, int blk, double *lds) {
   double *grp = lds, *c = grp + SCP_T, *part = c + 256, *rs = part + SCP_T * SC_S;
   const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
-  sc_sum_c(J, grp, c);
+  sc_sum_c<SCP_T>(J, J.cpart, grp, c);
   if (blk == 0 && threadIdx.x < J.s * J.r) J.c[threadIdx.x] = c[threadIdx.x];
   const double t = sc_expand<SCP_T / 64>(J, blk, c, part);
   const int i = blk * 64 + lane;
   if (w < J.s) {
     const double *b = J.partials ? J.b : J.bin;
     double v = i < J.n ? b[(size_t)w * J.n + i] - t : 0.0;
+    if (i < J.n) J.x[(size_t)w * J.n + i] = v;
+    grp[w * 64 + lane] = v;
     v = sc_wave_sum(v * v);
     if (lane == 0) rs[w] = v;
   }
   __syncthreads();
+  const int d = J.s * J.r;
+  for (int e = w; e < d; e += SCP_T / 64) {
+    const int h = e / J.r, j = e - h * J.r;
+    const double v = sc_wave_sum(J.S[(size_t)j * J.ns + i] * grp[h * 64 + lane]);
+    if (lane == 0) J.cpart2[(size_t)blk * d + e] = v;
+  }
   if (threadIdx.x == 0) {
     double v = 0.0;
     for (int h = 0; h < J.s; ++h) v += rs[h];
@@ -172,8 +186,8 @@ constexpr int SCS_T = 256, SCS_W = SCS_T / 64;
 __host__ __device__ inline size_t sc_solve_lds(int d, int MX) {   // doubles
   return (size_t)(MX + 1) * (d + 1) + (size_t)MX * (MX + 1) / 2 + MX;
 }
-// y = x_c - t c into ys[0 .. d), t into ys[d] (LDS); the block's first SCS_W
-// waves work, any further ones only keep the barriers.  record: write status.
+// y = x_c - t c' (c' = S^T b') into ys[0 .. d), t into ys[d] (LDS), so that
+// x = t b' + S y; the block's first SCS_W waves work, any further ones only keep the barriers.  record: write status.
 __device__ __forceinline__ void sc_gmres(const ScJob &J, int MX, double rtol, double *ys,
                                          bool record, double *__restrict__ st_out,
                                          bool with_flag) {
@@ -199,7 +213,9 @@ __device__ __forceinline__ void sc_gmres(const ScJob &J, int MX, double rtol, do
     t = sc_wave_sum(t);
     if (lane == 0) c[d] = sqrt(t);
   }
-  if (tid < d) c[tid] = J.c[tid];
+  sc_sum_c<SCS_T>(J, J.cpart2, ws, ys);
+  const double c2 = tid < d ? ys[tid] : 0.0;
+  if (tid < d) c[tid] = J.c[tid] + c2;
   __syncthreads();
   if (tid < dim) v = c[tid];
   auto block_sum = [&](double x) {   // same order in every thread
@@ -303,16 +319,15 @@ __device__ __forceinline__ void sc_gmres(const ScJob &J, int MX, double rtol, do
     for (int i = 0; i < m; ++i) xr += yv[i] * V[(size_t)i * dim + tid];
   if (tid == d) ys[d] = rho > 0.0 ? xr / rho : (m > 0 ? 1.0 : 0.0);
   __syncthreads();
-  if (tid < d) ys[tid] = xr - ys[d] * c[tid];
+  if (tid < d) ys[tid] = xr - ys[d] * c2;
   __syncthreads();
 }
 
-// The block's columns of x = t b + S y (ys as sc_gmres leaves it).
+// The block's columns of x = t b' + S y (ys as sc_gmres leaves it, b' in x).
 constexpr int SCC_LDS = SCS_T * SC_S;   // doubles
 __device__ __forceinline__ void sc_columns(const ScJob &J, int blk, const double *ys,
                                            double *part) {
   const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6, i = blk * 64 + lane;
-  const double *bv = J.partials ? J.b : J.bin;
   const double tb = ys[J.s * J.r];
   if (wv < SCS_W) {
     const double *Sc = J.S + i;
@@ -333,7 +348,7 @@ __device__ __forceinline__ void sc_columns(const ScJob &J, int blk, const double
     for (int h = wv; h < J.s; h += SCS_W) {
       double t = 0.0;
       for (int q = 0; q < SCS_W; ++q) t += part[(q * J.s + h) * 64 + lane];
-      if (i < J.n) J.x[(size_t)h * J.n + i] = tb * bv[(size_t)h * J.n + i] + t;
+      if (i < J.n) J.x[(size_t)h * J.n + i] = tb * J.x[(size_t)h * J.n + i] + t;
     }
 }
 
@@ -342,7 +357,7 @@ __device__ __forceinline__ void sc_apply_body(const ScJob &J, int blk, double *l
   double *grp = lds, *c = grp + SCP_T, *part = c + 256;
   __shared__ double y[256];
   const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
-  sc_sum_c(J, grp, c);
+  sc_sum_c<SCP_T>(J, J.cpart, grp, c);
   if (threadIdx.x < J.s * J.r) {
     const int k = threadIdx.x / J.r, j = threadIdx.x - k * J.r;
     double t = 0.0;
@@ -423,6 +438,147 @@ sc_columns_batch_kernel(const ScJob *__restrict__ jobs, const int2 *__restrict__
   sc_columns(J, e.y, ys, lds);
 }
 
+// ---- 2D: the lines along y of the DST-x domain, vectors [y][m] ----
+//
+// D(m, j) depends on kappa_m + kappa_j and is symmetric, so the modes are a
+// q x q square (m, j < q; entries below the cut hold D = 0).  The coordinates
+// c[j][m] = sum_y s_j(y) b[y][m], the norm of b - S c and x = t b + S y are
+// contractions on the matrix cores (v_mfma_f64_16x16x4f64: lane l supplies
+// A[l % 16][l / 16] and B[l / 16][l % 16]; D row l / 16 + 4 r, column l % 16
+// sits in result r); GMRES on the q^2 + 1 coordinates is one block
+// (pd_gmres_diag).  Before, every iteration was a parfor over all (k, m) lines
+// and five vector launches.
+typedef double v4d __attribute__((ext_vector_type(4)));
+__device__ __forceinline__ v4d sc_mfma(double a, double b, v4d c) {
+  return __builtin_amdgcn_mfma_f64_16x16x4f64(a, b, c, 0, 0, 0);
+}
+
+// One 16 x 16 tile of c per block, y split over the 4 waves.
+// Grid: (ceil(q / 16), ceil(q / 16)).
+__global__ void __launch_bounds__(256)
+sc2_project_kernel(int n, int ns, int q, const double *__restrict__ S,
+                   const double *__restrict__ b, double *__restrict__ c) {
+  __shared__ v4d red[4][64];
+  const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
+  const int m = blockIdx.x * 16 + (lane & 15), j0 = blockIdx.y * 16;
+  const int mc = m < n ? m : n - 1;
+  const double *Sr = S + (size_t)(j0 + (lane & 15)) * ns;   // rows past q are zero
+  v4d acc = {0.0, 0.0, 0.0, 0.0};
+  const int steps = ns / 4;
+  constexpr int U = 8;
+  for (int t0 = wv; t0 < steps; t0 += 4 * U) {
+    double av[U], bv[U];
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+      const int t = t0 + 4 * u, y = 4 * (t < steps ? t : wv) + (lane >> 4);
+      av[u] = t < steps ? Sr[y] : 0.0;                      // zero past n
+      bv[u] = b[(size_t)(y < n ? y : n - 1) * n + mc];
+    }
+#pragma unroll
+    for (int u = 0; u < U; ++u) acc = sc_mfma(av[u], bv[u], acc);
+  }
+  red[wv][lane] = acc;
+  __syncthreads();
+  if (wv == 0 && m < q) {
+#pragma unroll
+    for (int r = 0; r < 4; ++r) {
+      const int j = j0 + (lane >> 4) + 4 * r;
+      double t = red[0][lane][r];
+      for (int w = 1; w < 4; ++w) t += red[w][lane][r];
+      if (j < q) c[(size_t)j * q + m] = t;
+    }
+  }
+}
+
+// 16 rows y x 64 columns m per block, one 16 x 16 tile of S^T coef per wave.
+// MODE 0: b' = b - S c into x and rpart[block] = sum of b'^2; MODE 1:
+// x = t b' + S y (b = x = the b' of MODE 0, entry by entry), t = y[q^2].
+// Grid: (ceil(n / 64), ceil(n / 16)).
+template <int MODE>
+__global__ void __launch_bounds__(256)
+sc2_tile_kernel(int n, int ns, int q, const double *__restrict__ S,
+                const double *b, const double *__restrict__ coef, double *x,
+                double *__restrict__ rpart) {
+  __shared__ double red[4];
+  const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
+  const int y0 = blockIdx.y * 16, m = blockIdx.x * 64 + wv * 16 + (lane & 15);
+  double bv[4];
+#pragma unroll
+  for (int r = 0; r < 4; ++r) {
+    const int y = y0 + (lane >> 4) + 4 * r;
+    bv[r] = (y < n && m < n) ? b[(size_t)y * n + m] : 0.0;
+  }
+  v4d acc = {0.0, 0.0, 0.0, 0.0};
+  if (blockIdx.x * 64 + wv * 16 < q) {
+    const double *Sr = S + y0 + (lane & 15);
+    const int steps = (q + 3) / 4;
+    constexpr int U = 8;
+    for (int t0 = 0; t0 < steps; t0 += U) {
+      double av[U], cv[U];
+#pragma unroll
+      for (int u = 0; u < U; ++u) {
+        const int j = 4 * (t0 + u) + (lane >> 4);
+        const bool in = j < q && m < q;
+        av[u] = Sr[(size_t)(j < q ? j : 0) * ns];
+        cv[u] = in ? coef[(size_t)j * q + m] : 0.0;
+      }
+#pragma unroll
+      for (int u = 0; u < U; ++u) acc = sc_mfma(av[u], cv[u], acc);
+    }
+  }
+  if constexpr (MODE == 0) {
+    double t = 0.0;
+#pragma unroll
+    for (int r = 0; r < 4; ++r) {
+      const int y = y0 + (lane >> 4) + 4 * r;
+      const double v = (y < n && m < n) ? bv[r] - acc[r] : 0.0;
+      if (y < n && m < n) x[(size_t)y * n + m] = v;
+      t += v * v;
+    }
+    t = sc_wave_sum(t);
+    if (lane == 0) red[wv] = t;
+    __syncthreads();
+    if (threadIdx.x == 0)
+      rpart[(size_t)blockIdx.y * gridDim.x + blockIdx.x] = red[0] + red[1] + red[2] + red[3];
+  } else {
+    const double tb = coef[(size_t)q * q];
+#pragma unroll
+    for (int r = 0; r < 4; ++r) {
+      const int y = y0 + (lane >> 4) + 4 * r;
+      if (y < n && m < n) x[(size_t)y * n + m] = tb * bv[r] + acc[r];
+    }
+  }
+}
+
+// Phi[j][m] = D(m, j) summed over the frequencies (once per plan): with the
+// recurrence form's constants of line (k, m), or the exact eigenvalues.
+// th[i]: the line operator's eigenvalues, s2[i] = sin^2(theta_i / 2).
+__global__ void __launch_bounds__(64)
+sc2_phi_kernel(int n, int F2, int q, size_t NF, int scan, const cpx<double> *__restrict__ fac,
+               const double *__restrict__ lam, const double *__restrict__ gJ,
+               const double *__restrict__ th, const double *__restrict__ s2,
+               double *__restrict__ Phi) {
+  const int m = blockIdx.y, j = blockIdx.x * 64 + threadIdx.x;
+  if (j >= q) return;
+  const double sj = 4.0 * s2[j], kap = th[m] + th[j];
+  double t = 0.0;
+  for (int k = 0; k < F2; ++k) {
+    const double gr = gJ[2 * k], gi = gJ[2 * k + 1];
+    cpx<double> den, num = {1.0, 0.0};
+    if (scan) {
+      const cpx<double> *f = fac + ((size_t)k * n + m) * NF;
+      const cpx<double> r = f[0], e = {1.0 - r.re, -r.im};
+      num = f[4];
+      den = cpx<double>{e.re * e.re - e.im * e.im + sj * r.re, 2.0 * e.re * e.im + sj * r.im};
+    } else {
+      den = cpx<double>{lam[2 * k] + kap, lam[2 * k + 1]};
+    }
+    const cpx<double> z = cmul(num, crecip(den));
+    t += gr * z.re - gi * z.im;
+  }
+  Phi[(size_t)j * q + m] = t;
+}
+
 // ---- host: eigenvalues, the number of modes, tables ----
 
 // sin^2(pi j / (2 (n + 1))) and the eigenvalues of M and tau K on mode j
@@ -479,7 +635,7 @@ static int sc_stride(int n) { return (n + 63) / 64 * 64; }
 // Doubles of the tables and workspace at r modes (1D).
 static size_t sc_doubles(int n, int s, int r) {
   const size_t nblk = (size_t)sc_stride(n) / 64;
-  return (size_t)r * sc_stride(n) + (size_t)s * s * r + nblk * s * r + nblk + 512;
+  return (size_t)r * sc_stride(n) + (size_t)s * s * r + 2 * nblk * s * r + nblk + 512;
 }
 
 size_t pd_sc_max_doubles(int n, int s) {
@@ -567,6 +723,109 @@ bool pd_sc_build(pd_plan p, const std::vector<double> &fac, const std::vector<do
   return true;
 }
 
+// 2D: the sine modes along y of the lines m < q, q^2 + 1 coordinates for the
+// one-block GMRES; Phi is formed on the device by pd_sc2_finish.
+constexpr int SC2_QMAX = 127;    // q^2 + 1 <= 16384 entries
+static int sc2_rows(int q) { return (q + 15) / 16 * 16; }
+static int sc2_tiles(int n) { return ((n + 63) / 64) * ((n + 15) / 16); }
+static size_t sc2_doubles(int n, int q) {
+  const size_t q2 = (size_t)q * q;
+  return (size_t)sc2_rows(q) * sc_stride(n) + 4 * (q2 + 2) + 2 * (size_t)q + sc2_tiles(n);
+}
+size_t pd_sc2_max_doubles(int n) { return sc2_doubles(n, std::min(n, SC2_QMAX)); }
+
+bool pd_sc2_build(pd_plan p, std::vector<double> &tab) {
+  const double *u = p->uni;
+  const int n = p->n;
+  // float64 GMRES plans of backward Euler with symmetric T
+  if (p->dims != 2 || p->prec != PD_FP64 || p->krylov != PD_KRYLOV_GMRES || p->bdf_s > 1 ||
+      !p->uniform || u[3] != u[5])
+    return false;
+  const Mode q1 = mode_of(p, 1), qn = mode_of(p, n);
+  if (!(qn.kap >= q1.kap) || !(p->lam[0] + 2.0 * q1.kap > 0.0)) return false;
+  int q = 0;
+  double worst = 0.0;
+  for (int j = 1; j <= n; ++j) {
+    const double D = mode_bound(p, q1.kap + mode_of(p, j).kap);
+    if (!(D < 1e15)) return false;
+    if (D <= SC_CUT) break;
+    worst = std::max(worst, D);
+    q = j;
+    if (q > SC2_QMAX) return false;   // more modes: the general product
+  }
+  if (q < 1) q = 1;
+  // partition-form lines (more than a wave each): as in 1D
+  const double cond0 = (p->lam[0] + 2.0 * qn.kap) / (p->lam[0] + 2.0 * q1.kap);
+  if (!pd_line2d_scan(p) && !(worst * cond0 * 0x1p-53 <= 1e-12)) return false;
+  p->sc_r = q;
+  p->sc_ns = sc_stride(n);
+  tab.assign((size_t)sc2_rows(q) * p->sc_ns + 2 * (size_t)q, 0.0);
+  const long N2 = 2L * (n + 1);
+  const double sc = std::sqrt(2.0 / (n + 1));
+  for (int j = 1; j <= q; ++j) {
+    for (int i = 1; i <= n; ++i) {
+      long a = (long)j * i % N2;
+      const bool neg = a > n + 1;
+      if (neg) a = N2 - a;
+      if (2 * a > n + 1) a = n + 1 - a;
+      const double v = sc * std::sin(M_PI * (double)a / (double)(n + 1));
+      tab[(size_t)(j - 1) * p->sc_ns + i - 1] = neg ? -v : v;
+    }
+    const Mode md = mode_of(p, j);
+    tab[(size_t)sc2_rows(q) * p->sc_ns + j - 1] = md.kap;
+    tab[(size_t)sc2_rows(q) * p->sc_ns + q + j - 1] = md.s2;
+  }
+  return true;
+}
+size_t pd_sc2_size(pd_plan p) { return sc2_doubles(p->n, p->sc_r); }
+
+namespace {
+struct Sc2 {
+  double *S, *th, *s2, *Phi, *c, *c2, *y, *rpart;
+  explicit Sc2(pd_plan p) {
+    const size_t q = p->sc_r, q2 = q * q + 2;
+    S = p->sc_tab;
+    th = S + (size_t)sc2_rows(p->sc_r) * p->sc_ns;
+    s2 = th + q;
+    Phi = s2 + q;
+    c = Phi + q2;
+    c2 = c + q2;
+    y = c2 + q2;
+    rpart = y + q2;
+  }
+};
+}  // namespace
+
+pd_status pd_sc2_finish(pd_plan p) {
+  const Sc2 t(p);
+  const int q = p->sc_r;
+  hipLaunchKernelGGL(sc2_phi_kernel, dim3((q + 63) / 64, q), dim3(64), 0, p->stream, p->n, p->F2,
+                     q, (size_t)6 * (p->l2d.MR - 1), pd_line2d_scan(p) ? 1 : 0,
+                     reinterpret_cast<const cpx<double> *>(p->fac64), p->lam64, p->gJ64, t.th,
+                     t.s2, t.Phi);
+  PD_HIP_CHECK(hipGetLastError());
+  return PD_OK;
+}
+
+static pd_status sc2_enqueue(pd_plan p, const double *b, double *x, double rtol) {
+  const Sc2 t(p);
+  const int n = p->n, ns = p->sc_ns, q = p->sc_r, qt = (q + 15) / 16;
+  const dim3 tiles((n + 63) / 64, (n + 15) / 16);
+  hipLaunchKernelGGL(sc2_project_kernel, dim3(qt, qt), dim3(256), 0, p->stream, n, ns, q, t.S, b,
+                     t.c);
+  hipLaunchKernelGGL((sc2_tile_kernel<0>), tiles, dim3(256), 0, p->stream, n, ns, q, t.S, b, t.c,
+                     x, t.rpart);
+  hipLaunchKernelGGL(sc2_project_kernel, dim3(qt, qt), dim3(256), 0, p->stream, n, ns, q, t.S, x,
+                     t.c2);
+  PD_HIP_CHECK(hipGetLastError());
+  const pd_status st = pd_gmres_diag(p, q * q, t.c, t.c2, t.Phi, t.rpart, sc2_tiles(n), t.y, rtol);
+  if (st != PD_OK) return st;
+  hipLaunchKernelGGL((sc2_tile_kernel<1>), tiles, dim3(256), 0, p->stream, n, ns, q, t.S, x, t.y,
+                     x, t.rpart);
+  PD_HIP_CHECK(hipGetLastError());
+  return PD_OK;
+}
+
 // The launches' job: b from pass B's partials (bin null) or from bin.
 ScJob pd_sc_job(pd_plan p, const double *bin, double *x) {
   const int s = p->bdf_s, r = p->sc_r;
@@ -589,6 +848,8 @@ ScJob pd_sc_job(pd_plan p, const double *bin, double *x) {
   t += (size_t)s * s * r;
   J.cpart = t;
   t += (size_t)J.nblk * s * r;
+  J.cpart2 = t;
+  t += (size_t)J.nblk * s * r;
   J.rpart = t;
   t += J.nblk;
   J.c = t;
@@ -601,6 +862,13 @@ size_t pd_sc_lds(const ScJob &J, int MX) { return sc_solve_lds(J.s * J.r, MX) * 
 // x = J^{-1} b to residual <= rtol ||b||, enqueued without synchronising;
 // the status lands in the plan's pinned block (read with pd_gmres_read).
 pd_status pd_sc_enqueue(pd_plan p, const double *bin, double *x, double rtol) {
+  if (p->dims == 2) {
+    if (!bin) {
+      const pd_status st = pd_launch_reduce_partials(p, nullptr, p->bvec);
+      if (st != PD_OK) return st;
+    }
+    return sc2_enqueue(p, bin ? bin : p->bvec, x, rtol);
+  }
   const ScJob J = pd_sc_job(p, bin, x);
   if (J.nblk <= SC_ONE && pd_sc_lds(J, p->maxit) <= SC_ONE_LDS) {
     hipLaunchKernelGGL(sc_one_kernel, dim3(1), dim3(SCP_T), pd_sc_lds(J, p->maxit), p->stream, J,

@@ -309,7 +309,7 @@ extern "C" pd_status paradiag_solve(pd_plan p, const double *u0, const double *F
     if (st != PD_OK) return st;
   }
   if (p->krylov == PD_KRYLOV_FOM) return solve_fom(p, u0, F, U, tol, info);
-  if (p->prec != PD_MIXED && pd_gmres_fused_ok(p)) return solve_speculative(p, u0, F, U, tol, info);
+  if (p->prec != PD_MIXED && (p->sc_on || pd_gmres_fused_ok(p))) return solve_speculative(p, u0, F, U, tol, info);
   st = sweep_tail(p, U, tol, 0, 0, info, &gst);
   if (st != PD_OK) return st;
   pd_status final_status = gst;

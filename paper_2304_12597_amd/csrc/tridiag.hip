@@ -976,6 +976,25 @@ __global__ void reduce_partials_kernel(int n, int G, const double *__restrict__ 
   out[i] = (base ? base[i] : 0.0) + s;
 }
 
+// At most RS partial rows (2D: the frequency chunks): one slice, a thread per
+// column with every row's load in flight, summed in the same order.  The
+// kernel above has one busy wave of 16 there (511^2, 8 rows: 15.4 us).
+__global__ void __launch_bounds__(256)
+reduce_few_kernel(int n, int G, const double *__restrict__ partials,
+                  const double *__restrict__ base, double *__restrict__ out,
+                  const double *__restrict__ skip) {
+  const int i = blockIdx.x * 256 + threadIdx.x;
+  if (i >= n || (skip && *skip != 0.0)) return;
+  double v[RS];
+#pragma unroll
+  for (int g = 0; g < RS; ++g) v[g] = partials[(size_t)(g < G ? g : G - 1) * n + i];
+  double t = 0.0;
+#pragma unroll
+  for (int g = 0; g < RS; ++g)
+    if (g < G) t += v[g];
+  out[i] = (base ? base[i] : 0.0) + t;
+}
+
 template <typename R, int MR, int M>
 void launch_pipe(pd_plan p, int G, int nitems, const Coef<R> &cf, const R *lam,
                  const cpx<R> *fac, const double *gw, const cpx<R> *cin, const double *vin,
@@ -1196,7 +1215,10 @@ pd_status pd_launch_reduce_partials(pd_plan p, const double *base, double *out) 
   const int nitems = pd_tri_nitems(p->tri, p->F2);
   int G = nitems < p->tri_G ? nitems : p->tri_G;
   if (p->dims == 2) G = p->l2d.nkc;
-  if (G > 0 && (G + RS - 1) / RS <= RF_MAX_SLICES) {
+  if (G > 0 && G <= RS) {
+    hipLaunchKernelGGL(reduce_few_kernel, dim3((n + 255) / 256), dim3(256), 0, p->stream, n, G,
+                       p->partials, base, out, p->gm_skip);
+  } else if (G > 0 && (G + RS - 1) / RS <= RF_MAX_SLICES) {
     hipLaunchKernelGGL(reduce_fused_kernel, dim3((n + RF_COLS - 1) / RF_COLS), dim3(1024), 0,
                        p->stream, n, G, p->partials, base, out, p->gm_skip);
   } else if (G > RS) {
@@ -1214,7 +1236,7 @@ pd_status pd_launch_reduce_partials(pd_plan p, const double *base, double *out) 
 }
 
 pd_status pd_capacitance_apply_impl(pd_plan p, const double *v, double *Jv) {
-  if (p->sc_on) return pd_sc_apply(p, v, Jv);
+  if (p->sc_on && p->dims == 1) return pd_sc_apply(p, v, Jv);
   if (p->bdf_s > 1) return pd_bdf_apply(p, v, Jv);
   if (p->cp_on) return pd_cp_apply(p, v, Jv);
   pd_status st = pd_launch_tridiag(p, 2, v, nullptr, nullptr);

@@ -6,6 +6,7 @@ the general product takes over)."""
 import numpy as np
 import pytest
 
+from oracle import modal
 from paper_2304_12597_amd import workloads as wl
 
 pytestmark = pytest.mark.gpu
@@ -58,3 +59,24 @@ def test_capacitance_in_the_sine_basis(lib, kind, n, ell, nu, alpha):
         assert np.linalg.norm(x.cpu().numpy() - xr) <= (1e-11 * lam.max() + bound) * np.linalg.norm(v)
     finally:
         lib.paradiag_plan_destroy(plan)
+
+
+@pytest.mark.parametrize("n,ell,nu", [(16, 16, 1.0), (65, 64, 2e-2), (130, 64, 4e-3), (130, 16, 1e-3),
+                                      (127, 32, 5e-3)])
+def test_2d_solves_across_the_mode_limit(lib, n, ell, nu):
+    """One tile of modes, several, nearly the limit, past it (the general
+    product), and all lines of the grid: against the exact modal solution,
+    within the rounding of J's largest eigenvalue (about 1 / (nu T 2 pi^2))."""
+    p = wl.heat_2d(n, ell, 0.1, nu, np.random.default_rng(n))
+    dev = torch.device("cuda:0")
+    plan = lib.paradiag_plan_create(n, ell, p.tau, None, p.K, dims=2,
+                                    stream=torch.cuda.current_stream().cuda_stream)
+    try:
+        U = torch.empty((ell, n * n), dtype=torch.float64, device=dev)
+        info = lib.paradiag_solve(plan, torch.tensor(p.u0, device=dev), torch.tensor(p.F, device=dev), U, 1e-12)
+        torch.cuda.synchronize()
+    finally:
+        lib.paradiag_plan_destroy(plan)
+    ref = modal.modal_solution(p)
+    assert info.gmres_iters >= 1
+    assert np.linalg.norm(U.cpu().numpy() - ref) <= 1e-10 * np.linalg.norm(ref)
