@@ -26,7 +26,7 @@ __device__ __forceinline__ void fft_forward_body(int tile, int N, int n, int nba
                                                  const double *__restrict__ coef,
                                                  const double *__restrict__ dal,
                                                  const cpx<R> *__restrict__ tw,
-                                                 cpx<R> *__restrict__ out,
+                                                 cpx<R> *__restrict__ out, size_t ost,
                                                  double *__restrict__ red) {
   extern __shared__ __align__(16) unsigned char smem_raw[];
   cpx<R> *lds = reinterpret_cast<cpx<R> *>(smem_raw);
@@ -115,14 +115,14 @@ __device__ __forceinline__ void fft_forward_body(int tile, int N, int n, int nba
 #pragma unroll
     for (int u = 0; u < UNS; ++u) {
       const int k = kb + u * dt;
-      if (k < half && inb) out[(size_t)k * nbar + i] = X[u];
+      if (k < half && inb) out[(size_t)k * ost + i] = X[u];
     }
   }
   if (tid < S && inb) {
     const cpx<R> z = ccol[pd_fpad(half)];
     const R xr = (pnt & 1) ? z.im + z.im : z.re + z.re;
     const R xi = (pnt & 1) ? z.re - z.re : z.im - z.im;
-    out[(size_t)half * nbar + i] = cpx<R>{R(0.5) * xr, R(0.5) * xi};
+    out[(size_t)half * ost + i] = cpx<R>{R(0.5) * xr, R(0.5) * xi};
   }
   if (MODE == 1) {
     // block reduction of the two norms (float64)
@@ -160,9 +160,9 @@ fft_forward_kernel(int N, int n, int nbar, int dims, int C, int stride, double t
                    const double *__restrict__ u0, const double *__restrict__ F,
                    const double *__restrict__ U, const double *__restrict__ coef,
                    const double *__restrict__ dal, const cpx<R> *__restrict__ tw,
-                   cpx<R> *__restrict__ out, double *__restrict__ red) {
+                   cpx<R> *__restrict__ out, size_t ost, double *__restrict__ red) {
   fft_forward_body<R, MODE>(xcd_tile(blockIdx.x, gridDim.x), N, n, nbar, dims, C, stride, tau,
-                            u0, F, U, coef, dal, tw, out, red);
+                            u0, F, U, coef, dal, tw, out, ost, red);
 }
 
 template <typename R, int ACC>
@@ -437,14 +437,15 @@ int pd_choose_fft_C(int ell, int nbar, int prec, size_t max_lds) {
 static bool fft_C_valid(int C) { return C >= 1 && C <= 32 && (C & (C - 1)) == 0; }
 
 pd_status pd_launch_fft_forward(pd_plan p, const double *u0, const double *F,
-                                const double *U, void *out, int mode) {
+                                const double *U, void *out, int mode, size_t ost) {
   FftLaunch L = fft_config(p);
+  if (ost == 0) ost = p->nbar;
   if (!fft_C_valid(L.C)) return PD_EINVAL;
   const double *dal = p->alpha == 1.0 ? nullptr : p->dal;   // D_alpha = I for alpha = 1
 #define PD_FWD(R, M, TW, O)                                                                 \
   hipLaunchKernelGGL((fft_forward_kernel<R, M>), dim3(L.blocks), dim3(L.threads), L.lds,    \
                      p->stream, p->ell, p->n, p->nbar, p->dims, L.C, L.stride, p->tau, u0, \
-                     F, U, p->coef64, dal, TW, O, p->red)
+                     F, U, p->coef64, dal, TW, O, ost, p->red)
   if (p->prec == PD_FP64) {
     auto tw = reinterpret_cast<const cpx<double> *>(p->tw64);
     auto o = reinterpret_cast<cpx<double> *>(out);
@@ -807,7 +808,7 @@ fft_forward_batch_kernel(const FftJob *__restrict__ jobs, const int2 *__restrict
   const FftJob &j = jobs[m.x];
   fft_forward_body<R, MODE>(m.y, j.N, j.n, j.nbar, j.dims, j.C, j.stride, j.tau, j.u0, j.F, j.U,
                             j.coef, j.dal, reinterpret_cast<const cpx<R> *>(j.tw),
-                            reinterpret_cast<cpx<R> *>(j.spec), j.red);
+                            reinterpret_cast<cpx<R> *>(j.spec), j.nbar, j.red);
 }
 template <typename R>
 __global__ void __launch_bounds__(1024)

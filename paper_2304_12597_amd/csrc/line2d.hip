@@ -16,9 +16,13 @@
 #include "pd_partition.h"
 #include "pd_scan.h"
 
+#include <algorithm>
+#include <type_traits>
+
 namespace {
 
-template <typename R, int MR, int MODE, bool SCAN>
+// IN32: in is complex64 [F2][nbar] (mode 1 writes complex128 elsewhere).
+template <typename R, int MR, int MODE, bool SCAN, bool IN32 = false>
 __global__ void __launch_bounds__(512, 4)
 line2d_kernel(int n, int F2, int P, int S, int mgroups, int kchunk,
               const cpx<R> *__restrict__ fac, R toff, const double *__restrict__ gw,
@@ -26,7 +30,8 @@ line2d_kernel(int n, int F2, int P, int S, int mgroups, int kchunk,
               const double *__restrict__ xv, double wscale, cpx<R> *__restrict__ out,
               double *__restrict__ partials) {
   extern __shared__ __align__(16) unsigned char smem_raw[];
-  constexpr int NF = 6 * (MR - 1);
+  // constants per line, in global memory and in LDS
+  constexpr int NF = SCAN ? pd_scan_entries<MR>() : 6 * (MR - 1);
   const int tid = threadIdx.x;
   const int g = tid / P;
   const int lt = tid - g * P;
@@ -78,17 +83,16 @@ line2d_kernel(int n, int F2, int P, int S, int mgroups, int kchunk,
 
   for (int k = kbeg; k < kend; ++k) {
     __syncthreads();
-    // (the recurrence form's table: its pd_scan_entries entries of each row)
-    constexpr int NC = SCAN ? pd_scan_entries<MR>() : NF;
-    for (int idx = tid; idx < S * NC; idx += blockDim.x) {
-      const int gg = idx / NC, j = idx - gg * NC;
+    for (int idx = tid; idx < S * NF; idx += blockDim.x) {
+      const int gg = idx / NF, j = idx - gg * NF;
       const int mm = m0 + gg < n ? m0 + gg : n - 1;
       lfac_all[gg * NF + j] = fac[((size_t)k * n + mm) * NF + j];
     }
     if constexpr (MODE != 2) {
       // U loads in flight per thread (at clamped, valid addresses), then the
       // LDS stores; columns past n stage zeros
-      const cpx<R> *src = in + (size_t)k * nbar;
+      using In = typename std::conditional<IN32, cpx<float>, cpx<R>>::type;
+      const In *src = reinterpret_cast<const In *>(in) + (size_t)k * nbar;
       for (int b = tid; b < tile; b += U * (int)blockDim.x) {
         cpx<R> v[U];
 #pragma unroll
@@ -96,8 +100,8 @@ line2d_kernel(int n, int F2, int P, int S, int mgroups, int kchunk,
           const int idx = b + u * (int)blockDim.x;
           const int ic = idx < tile ? idx : tile - 1;
           const int y = ic >> lgS, mm = m0 + (ic & (S - 1));
-          const cpx<R> t = src[(size_t)y * n + (mm < n ? mm : n - 1)];
-          v[u] = pd_sel(mm < n, t, zero);
+          const In t = src[(size_t)y * n + (mm < n ? mm : n - 1)];
+          v[u] = pd_sel(mm < n, cpx<R>{(R)t.re, (R)t.im}, zero);
         }
 #pragma unroll
         for (int u = 0; u < U; ++u) {
@@ -171,7 +175,7 @@ line2d_kernel(int n, int F2, int P, int S, int mgroups, int kchunk,
   }
 }
 
-template <typename R, int MR, bool SCAN>
+template <typename R, int MR, bool SCAN, bool IN32 = false>
 pd_status launch2d_form(pd_plan p, int mode, const void *in, const double *xv, void *out) {
   const Line2DConfig &L = p->l2d;
   const cpx<R> *fac = (sizeof(R) == 8) ? reinterpret_cast<const cpx<R> *>(p->fac64)
@@ -179,12 +183,12 @@ pd_status launch2d_form(pd_plan p, int mode, const void *in, const double *xv, v
   const R toff = (R)p->uni[3];
   mode &= 0xff;
   if (mode == 1) {
-    hipLaunchKernelGGL((line2d_kernel<R, MR, 1, SCAN>), dim3(p->F2 * L.mgroups), dim3(L.block),
+    hipLaunchKernelGGL((line2d_kernel<R, MR, 1, SCAN, IN32>), dim3(p->F2 * L.mgroups), dim3(L.block),
                        L.lds, p->stream, p->n, p->F2, L.P, L.S, L.mgroups, L.kchunk, fac, toff,
                        p->gB64, reinterpret_cast<const cpx<R> *>(in), nullptr, xv, p->w,
                        reinterpret_cast<cpx<R> *>(out), nullptr);
   } else if (mode == 0) {
-    hipLaunchKernelGGL((line2d_kernel<R, MR, 0, SCAN>), dim3(L.nkc * L.mgroups), dim3(L.block),
+    hipLaunchKernelGGL((line2d_kernel<R, MR, 0, SCAN, IN32>), dim3(L.nkc * L.mgroups), dim3(L.block),
                        L.lds, p->stream, p->n, p->F2, L.P, L.S, L.mgroups, L.kchunk, fac, toff,
                        p->gB64, reinterpret_cast<const cpx<R> *>(in), nullptr, nullptr, p->w,
                        nullptr, p->partials);
@@ -201,6 +205,8 @@ pd_status launch2d_form(pd_plan p, int mode, const void *in, const double *xv, v
 template <typename R, int MR>
 pd_status launch2d(pd_plan p, int mode, const void *in, const double *xv, void *out) {
   if constexpr (sizeof(R) == 8) {
+    // complex64 spectra: always the recurrence form (pd_mixed64_ok)
+    if (p->in32) return launch2d_form<R, MR, true, true>(p, mode, in, xv, out);
     if (pd_line2d_scan(p)) return launch2d_form<R, MR, true>(p, mode, in, xv, out);
   }
   return launch2d_form<R, MR, false>(p, mode, in, xv, out);
@@ -237,26 +243,35 @@ Line2DConfig pd_choose_line2d(int n, int F2, int prec, int cus) {
 }
 
 // Factors for every (k, m): b = lambda_k + tau theta_m + tau T_d, a = c = tau T_off.
-void pd_line2d_factors(const pd_plan p, std::vector<double> &fac) {
+// float64 plans into fac, the others rounded to float into fac32.
+void pd_line2d_factors(const pd_plan p, std::vector<double> &fac, std::vector<float> &fac32) {
   const int n = p->n, F2 = p->F2, MR = p->l2d.MR;
-  const size_t NF = 6 * (size_t)(MR - 1);
-  fac.assign((size_t)F2 * n * NF * 2, 0.0);
+  const size_t NF = pd_line2d_entries(p);
+  const bool f32 = p->prec != PD_FP64;
+  if (f32)
+    fac32.assign((size_t)F2 * n * NF * 2, 0.0f);
+  else
+    fac.assign((size_t)F2 * n * NF * 2, 0.0);
   const double tl = p->uni[3], td = p->uni[4];
   const bool scan = pd_line2d_scan(p);
-  for (int k = 0; k < F2; ++k) {
+  std::vector<double> th(n);
+  for (int m = 0; m < n; ++m) th[m] = td + 2.0 * tl * std::cos((m + 1) * M_PI / (n + 1));
+  pd_parallel_rows(F2, 1 + 4096 / n, [&](int k) {
+    std::vector<double> row(f32 ? NF * 2 : 0);
     for (int m = 0; m < n; ++m) {
-      const double theta = td + 2.0 * tl * std::cos((m + 1) * M_PI / (n + 1));
+      const double theta = th[m];
       if (scan) {
-        // recurrence-form constants (pd_scan.h) at the same row stride
         pd_scan_table({tl, 0.0}, {p->lam[2 * k] + theta + td, p->lam[2 * k + 1]}, {tl, 0.0},
                       p->lam[2 * k + 1] == 0.0, n, MR,
                       reinterpret_cast<std::complex<double> *>(&fac[((size_t)k * n + m) * NF * 2]));
         continue;
       }
+      double *dst = f32 ? row.data() : &fac[((size_t)k * n + m) * NF * 2];
       pd_partition_factors(tl, 0.0, p->lam[2 * k] + theta + td, p->lam[2 * k + 1], tl, 0.0, MR,
-                           &fac[((size_t)k * n + m) * NF * 2]);
+                           dst);
+      if (f32) std::copy(row.begin(), row.end(), fac32.begin() + ((size_t)k * n + m) * NF * 2);
     }
-  }
+  });
 }
 
 pd_status pd_launch_line2d(pd_plan p, int mode, const void *in, const double *xv, void *out) {
@@ -275,6 +290,10 @@ pd_status pd_launch_line2d(pd_plan p, int mode, const void *in, const double *xv
 void pd_line2d_set_attributes(size_t max_lds) {
   const int v = (int)max_lds;
   const void *fns[] = {
+      reinterpret_cast<const void *>(&line2d_kernel<double, 4, 0, true, true>),
+      reinterpret_cast<const void *>(&line2d_kernel<double, 4, 1, true, true>),
+      reinterpret_cast<const void *>(&line2d_kernel<double, 8, 0, true, true>),
+      reinterpret_cast<const void *>(&line2d_kernel<double, 8, 1, true, true>),
       reinterpret_cast<const void *>(&line2d_kernel<double, 4, 0, false>),
       reinterpret_cast<const void *>(&line2d_kernel<double, 4, 0, true>),
       reinterpret_cast<const void *>(&line2d_kernel<double, 4, 1, false>),

@@ -6,6 +6,7 @@
 #include <cstddef>
 #include <cstdint>
 #include <string>
+#include <thread>
 #include <vector>
 
 #include "../../include/paradiag.h"
@@ -319,6 +320,11 @@ struct pd_plan_s {
   int cp_on = 0;
   CpLayout cpl;
   double *cp_tab = nullptr;
+  // PD_MIXED: the float64 plan of the shifted solves and the inverse
+  // transform.  It shares this plan's buffers (borrowed on its side) and owns
+  // its constant tables; in32: its spectra come as complex64.
+  pd_plan_s *inner = nullptr;
+  int borrowed = 0, in32 = 0;
   // capacitance solve in the sine eigenbasis (sinecap.hip)
   int sc_on = 0, sc_r = 0, sc_ns = 0, sc_nblk = 0;
   double *sc_tab = nullptr;
@@ -335,6 +341,33 @@ struct PdRange {
   PdRange &operator=(const PdRange &) = delete;
 };
 
+// fn(i) for i in [0, count), split over up to 8 host threads when there is
+// enough work (plan tables of many independent rows; 2D, 255^2, ell = 512:
+// 65 000 rows).  A thread that cannot start leaves its rows to the caller's.
+template <typename Fn>
+void pd_parallel_rows(int count, int min_rows, Fn fn) {
+  int nt = (int)std::thread::hardware_concurrency();
+  nt = nt > 8 ? 8 : nt;
+  if (nt > count / min_rows) nt = count / min_rows;
+  auto run = [&](int t) {
+    for (int i = t; i < count; i += nt) fn(i);
+  };
+  if (nt < 2) {
+    for (int i = 0; i < count; ++i) fn(i);
+    return;
+  }
+  std::vector<std::thread> th;
+  int t = 1;
+  try {
+    th.reserve(nt - 1);
+    for (; t < nt; ++t) th.emplace_back(run, t);
+  } catch (...) {
+  }
+  for (int u = t; u < nt; ++u) run(u);
+  run(0);
+  for (auto &x : th) x.join();
+}
+
 // error reporting
 void pd_set_error(const std::string &msg);
 #define PD_HIP_CHECK(call)                                                   \
@@ -350,9 +383,9 @@ void pd_set_error(const std::string &msg);
 // stage launchers (return PD_OK or an error code)
 // ---------------------------------------------------------------------------
 // forward time transform: mode 0 = h input, 1 = residual input (R = G - A(U),
-// norms accumulated into red)
+// norms accumulated into red); ost: entries between frequencies (0: nbar)
 pd_status pd_launch_fft_forward(pd_plan p, const double *u0, const double *F,
-                                const double *U, void *out, int mode);
+                                const double *U, void *out, int mode, size_t ost = 0);
 // inverse: accumulate = 0 store, 1 add into U
 pd_status pd_launch_fft_inverse(pd_plan p, const void *in, double *U,
                                 int accumulate);
@@ -369,7 +402,7 @@ int pd_dst_chirp_length(int n);
 pd_status pd_launch_dst_rows1d(pd_plan p, int mode, const double *u0, const double *F,
                                const double *in, double *out);
 Line2DConfig pd_choose_line2d(int n, int F2, int prec, int cus);
-void pd_line2d_factors(const pd_plan p, std::vector<double> &fac);
+void pd_line2d_factors(const pd_plan p, std::vector<double> &fac, std::vector<float> &fac32);
 pd_status pd_launch_line2d(pd_plan p, int mode, const void *in, const double *xv, void *out);
 void pd_line2d_set_attributes(size_t max_lds);
 // whole-pipeline helpers (1D or 2D)
@@ -508,6 +541,12 @@ inline bool pd_use_scan(const pd_plan p) {
 // the recurrence form as well (symmetric Toeplitz lines, pd_scan.h).
 inline bool pd_line2d_scan(const pd_plan p) {
   return p->dims == 2 && p->prec == PD_FP64 && p->l2d.P <= 64 && p->l2d.MR >= 4;
+}
+
+// Constants per 2D line (complex entries): the recurrence form's row of
+// pd_scan.h, or the elimination factors.
+inline size_t pd_line2d_entries(const pd_plan p) {
+  return pd_line2d_scan(p) ? 9 + (size_t)p->l2d.MR : 6 * (size_t)(p->l2d.MR - 1);
 }
 
 // Threads per shifted-solve block: 512 for complex128 (a 256-register budget

@@ -346,6 +346,10 @@ __device__ __forceinline__ void scan_solve_group(cpx<R> (&d)[MR], int len, int l
 inline void pd_scan_table(std::complex<double> a, std::complex<double> b, std::complex<double> c,
                           bool real, int n, int MR, std::complex<double> *dst) {
   using C = std::complex<long double>;
+  // the product without the library's checks for infinities (a call each)
+  auto mul = [](const C &x, const C &y) {
+    return C(x.real() * y.real() - x.imag() * y.imag(), x.real() * y.imag() + x.imag() * y.real());
+  };
   const C A(a.real(), a.imag()), B(b.real(), b.imag()), Cc(c.real(), c.imag());
   C kap;
   if (real) {
@@ -358,12 +362,12 @@ inline void pd_scan_table(std::complex<double> a, std::complex<double> b, std::c
     const C k1 = (B + s) / 2.0L, k2 = (B - s) / 2.0L;
     kap = std::abs(k1) >= std::abs(k2) ? k1 : k2;
   }
-  const C r1 = -A / kap, r2 = -Cc / kap, rho = r1 * r2;
+  const C r1 = -A / kap, r2 = (Cc == A) ? r1 : -Cc / kap, rho = mul(r1, r2);
   auto put = [&](int i, C v) { dst[i] = std::complex<double>((double)v.real(), (double)v.imag()); };
   C R1 = 1.0L, R2 = 1.0L;
   for (int q = 0; q < MR; ++q) {
-    R1 *= r1;
-    R2 *= r2;
+    R1 = mul(R1, r1);
+    R2 = mul(R2, r2);
   }
   put(0, r1);
   put(1, r2);
@@ -373,30 +377,30 @@ inline void pd_scan_table(std::complex<double> a, std::complex<double> b, std::c
   C S = 0.0L, pm = 1.0L, Sb = 1.0L, pb = rho;
   for (int m = n; m; m >>= 1) {
     if (m & 1) {
-      S += pm * Sb;
-      pm *= pb;
+      S += mul(pm, Sb);
+      pm = mul(pm, pb);
     }
-    Sb += pb * Sb;
-    pb *= pb;
+    Sb += mul(pb, Sb);
+    pb = mul(pb, pb);
   }
-  const C ik = 1.0L / kap, beta = rho / (1.0L + rho * S);
+  const C ik = 1.0L / kap, beta = rho / (1.0L + mul(rho, S));
   put(4, ik);
   put(5, beta);
   C K = 0.0L, p = r1;
   for (int q = 0; q < MR; ++q) {
     K += p;
-    p *= rho;
+    p = mul(p, rho);
   }
   put(6, K);
   C pq = 1.0L;
   for (int q = 0; q <= MR; ++q) {
     put(7 + q, pq);
-    pq *= r1;
+    pq = mul(pq, r1);
   }
   C Kr = 0.0L, pr = r1;
   for (int q = 0; q < n % MR; ++q) {
     Kr += pr;
-    pr *= rho;
+    pr = mul(pr, rho);
   }
   put(8 + MR, Kr);
 }

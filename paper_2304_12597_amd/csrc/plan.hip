@@ -119,6 +119,15 @@ pd_status upload(T *dst, const std::vector<T> &src, hipStream_t s) {
 
 void free_plan(pd_plan p) {
   if (!p) return;
+  if (p->borrowed) {   // a mixed plan's inner plan: only its tables are its own
+    void *own[] = {p->fac64, p->cp_tab, p->sc_tab};
+    for (void *q : own)
+      if (q) (void)hipFree(q);
+    delete p;
+    return;
+  }
+  free_plan(p->inner);
+  if (p->inner) p->spec2 = nullptr;   // the second half of spec
   void *ptrs[] = {p->coef64, p->coef32, p->lam64, p->lam32, p->gB64, p->gJ64, p->tw64,
                   p->tw32, p->dal, p->fac64, p->fac32, p->twd, p->wreal, p->spec, p->spec2, p->partials, p->rstage, p->bvec, p->xvec, p->wvec, p->V,
                   p->gm, p->red, p->sine_q, p->sine_wN, p->sine_twH, p->sine_m, p->sine_k,
@@ -145,12 +154,21 @@ struct Layout {
   size_t cp = 0;
   size_t spec_bytes = 0, partials = 0, rstage = 0, vec = 0, V = 0, gm = 0, red = 0;
   size_t spec2_bytes = 0;   // PD_MIXED: the last correction's spectrum (stall rollback)
+  size_t fac_bytes = 8;     // per entry of the shifted solves' constants
+  size_t inner = 0;         // PD_MIXED: the inner plan's own tables (bytes)
   size_t total_bytes() const {
-    return coef * 12 + lam * 12 + 2 * lam * 8 + tw * 12 + dal * 8 + fac * 12 + twd * 8 +
+    return coef * 12 + lam * 12 + 2 * lam * 8 + tw * 12 + dal * 8 + fac * fac_bytes + inner + twd * 8 +
            wreal * 8 + wz * 8 + bdfg * 8 + bdfh * 8 + bdft * 8 + spec_bytes + spec2_bytes + partials * 8 + rstage * 8 + 3 * vec * 8 + V * 8 + gm * 8 +
            red * 8 + sine * 8 + fom * 8 + fom_h_bytes + cp * 8;
   }
 };
+
+// A mixed plan whose shifted solves run in float64 on complex64 right-hand
+// sides: the float64 plan of the same problem uses the recurrence form.
+bool pd_mixed64_ok(const pd_plan p, const pd_plan q64) {
+  return p->prec == PD_MIXED && !p->early_exit && !p->autotune &&
+         (p->dims == 1 ? p->n <= 8192 && pd_use_scan(q64) : pd_line2d_scan(q64));
+}
 
 // Fills p->fft_C, fft_stride, tri, tri_G, l2d, dst_C; returns PD_OK or
 // PD_ENOTSUP when a tile does not fit in LDS.
@@ -186,7 +204,7 @@ pd_status compute_layout(pd_plan p, int cus, size_t max_lds, Layout &L) {
       pd_set_error("DST tile does not fit in LDS");
       return PD_ENOTSUP;
     }
-    L.fac = (size_t)F2 * n * 6 * (p->l2d.MR - 1) * 2;
+    L.fac = (size_t)F2 * n * pd_line2d_entries(p) * 2;
     // twiddles of the DST's FFT length; for the chirp-z form the chirp c_j
     // (j = 0..n) and the transformed wrapped chirp; then cos(pi (j+1)/(n+1))
     p->twd_chirp = 2 * (size_t)ND;
@@ -281,6 +299,20 @@ pd_status compute_layout(pd_plan p, int cus, size_t max_lds, Layout &L) {
     if (db > red_n) red_n = db;
   }
   L.red = red_n;
+  L.fac_bytes = p->prec == PD_FP64 ? 8 : 4;
+  if (p->prec == PD_MIXED && p->uniform) {
+    // the buffers that the inner float64 plan shares hold both plans' needs
+    pd_plan_s q = *p;
+    q.prec = PD_FP64;
+    Layout L64;
+    if (compute_layout(&q, cus, max_lds, L64) == PD_OK && pd_mixed64_ok(p, &q)) {
+      L.partials = std::max(L.partials, L64.partials);
+      L.rstage = std::max(L.rstage, L64.rstage);
+      L.red = std::max(L.red, L64.red);
+      if (p->dims == 2) L.wreal += 2 * (size_t)p->nbar;   // pass C's complex128 spectrum
+      L.inner = (L64.fac + L64.cp) * 8;
+    }
+  }
   return PD_OK;
 }
 
@@ -330,12 +362,12 @@ bool set_tri(pd_plan p, int MR, int cus, size_t max_lds) {
   if (p->uniform) {
     std::vector<double> fac;
     pd_uniform_factors(p, MR, fac);
+    if (p->prec == PD_FP64)
+      return hipMemcpy(p->fac64, fac.data(), fac.size() * sizeof(double),
+                       hipMemcpyHostToDevice) == hipSuccess;
     std::vector<float> fac32(fac.begin(), fac.end());
-    if (hipMemcpy(p->fac64, fac.data(), fac.size() * sizeof(double), hipMemcpyHostToDevice) !=
-            hipSuccess ||
-        hipMemcpy(p->fac32, fac32.data(), fac32.size() * sizeof(float), hipMemcpyHostToDevice) !=
-            hipSuccess)
-      return false;
+    return hipMemcpy(p->fac32, fac32.data(), fac32.size() * sizeof(float),
+                     hipMemcpyHostToDevice) == hipSuccess;
   }
   return true;
 }
@@ -448,28 +480,9 @@ extern "C" void paradiag_default_options(pd_options *opt) {
   opt->bdf_order = 1;
 }
 
-extern "C" pd_status paradiag_plan_create(pd_plan *out, int n, int ell, double tau,
-                                          const pd_tridiag *M, const pd_tridiag *K,
-                                          const pd_options *opt_in) {
-  PdRange whole("paradiag_plan_create");
-  g_last_error.clear();
-  if (!out) {
-    pd_set_error("out is NULL");
-    return PD_EINVAL;
-  }
-  *out = nullptr;
-  pd_options opt;
-  paradiag_default_options(&opt);
-  if (opt_in) opt = *opt_in;
-  {
-    std::string msg;
-    const pd_status vst = pdcheck::check_plan_args(n, ell, tau, M, K, opt, &msg);
-    if (vst != PD_OK) {
-      pd_set_error(msg);
-      return vst;
-    }
-  }
-
+// host: the mixed plan whose inner plan this is (its buffers are shared), or null
+static pd_status create_plan(pd_plan *out, int n, int ell, double tau, const pd_tridiag *M,
+                             const pd_tridiag *K, const pd_options &opt, pd_plan host) {
   pd_plan p = new (std::nothrow) pd_plan_s();
   if (!p) {
     pd_set_error("out of host memory");
@@ -495,6 +508,8 @@ extern "C" pd_status paradiag_plan_create(pd_plan *out, int n, int ell, double t
   p->stream = reinterpret_cast<hipStream_t>(opt.stream);
   p->mass_identity = (M == nullptr);
   p->bdf_s = opt.bdf_order;
+  p->borrowed = host ? 1 : 0;
+  p->in32 = host ? 1 : 0;
   bdf_coefficients(p->bdf_s, &p->bdf_beta, p->bdf_alpha);
   p->ncap = p->bdf_s * p->nbar;
   if (hipGetDevice(&p->device) != hipSuccess) {
@@ -638,9 +653,10 @@ extern "C" pd_status paradiag_plan_create(pd_plan *out, int n, int ell, double t
     return PD_ENOTSUP;
   }
   std::vector<double> fac;
+  std::vector<float> fac32;
   std::vector<double> twd;
   if (p->dims == 2) {
-    pd_line2d_factors(p, fac);
+    pd_line2d_factors(p, fac, fac32);
     const int N = p->dst_L ? p->dst_L : 2 * (n + 1);
     twd.assign(p->twd_cos + (size_t)n, 0.0);
     for (int m = 0; m < N; ++m) {
@@ -658,7 +674,7 @@ extern "C" pd_status paradiag_plan_create(pd_plan *out, int n, int ell, double t
   } else if (p->uniform) {
     pd_uniform_factors(p, p->tri.MR, fac);
   }
-  std::vector<float> fac32(fac.begin(), fac.end());
+  if (p->dims == 1 && p->prec != PD_FP64) fac32.assign(fac.begin(), fac.end());
   std::vector<double> sq, swN, stwH, sm, sk;
   if (p->sine && p->dst_L) {
     twd.assign(p->twd_cos, 0.0);
@@ -758,6 +774,27 @@ extern "C" pd_status paradiag_plan_create(pd_plan *out, int n, int ell, double t
   p->spec_bytes = L.spec_bytes;
   p->bytes = L.total_bytes();
   pd_status st = PD_OK;
+  if (host) {
+    p->coef64 = host->coef64;
+    p->lam64 = host->lam64;
+    p->gB64 = host->gB64;
+    p->gJ64 = host->gJ64;
+    p->tw64 = host->tw64;
+    p->dal = host->dal;
+    p->twd = host->twd;
+    p->wreal = host->wreal;
+    p->spec = host->spec;
+    p->partials = host->partials;
+    p->rstage = host->rstage;
+    p->bvec = host->bvec;
+    p->xvec = host->xvec;
+    p->wvec = host->wvec;
+    p->V = host->V;
+    p->gm = host->gm;
+    p->red = host->red;
+    p->host_pin = host->host_pin;
+    p->host_dev = host->host_dev;
+  }
 #define PD_TRY(x)      \
   do {                 \
     st = (x);          \
@@ -766,38 +803,45 @@ extern "C" pd_status paradiag_plan_create(pd_plan *out, int n, int ell, double t
       return st;       \
     }                  \
   } while (0)
-  PD_TRY(dev_alloc(&p->coef64, coef.size()));
-  PD_TRY(dev_alloc(&p->coef32, coef32.size()));
-  PD_TRY(dev_alloc(&p->lam64, p->lam.size()));
-  PD_TRY(dev_alloc(&p->lam32, lam32.size()));
-  PD_TRY(dev_alloc(&p->gB64, p->gB.size()));
-  PD_TRY(dev_alloc(&p->gJ64, p->gJ.size()));
-  PD_TRY(dev_alloc(&p->tw64, tw.size()));
-  PD_TRY(dev_alloc(&p->tw32, tw32.size()));
-  PD_TRY(dev_alloc(&p->dal, dal.size()));
-  PD_TRY(dev_alloc(&p->fac64, std::max(fac.size(), L.fac)));
-  PD_TRY(dev_alloc(&p->fac32, std::max(fac32.size(), L.fac)));
-  PD_TRY(dev_alloc(&p->twd, twd.size()));
-  if (p->dims == 2 || p->bdf_s > 1) PD_TRY(dev_alloc(&p->wreal, (size_t)ell * nbar));
-  if (p->bdf_s > 1) {
-    PD_TRY(dev_alloc(&p->wz, L.wz));
-    PD_TRY(dev_alloc(&p->bdf_g, L.bdfg));
-    if (p->dims == 2) {
-      PD_TRY(dev_alloc(&p->bdf_h, L.bdfh));
-      PD_TRY(dev_alloc(&p->bdf_t, L.bdft));
+  if (p->prec == PD_FP64)
+    PD_TRY(dev_alloc(&p->fac64, std::max(fac.size(), L.fac)));
+  else
+    PD_TRY(dev_alloc(&p->fac32, std::max(fac32.size(), L.fac)));
+  if (!host) {
+    PD_TRY(dev_alloc(&p->coef64, coef.size()));
+    PD_TRY(dev_alloc(&p->coef32, coef32.size()));
+    PD_TRY(dev_alloc(&p->lam64, p->lam.size()));
+    PD_TRY(dev_alloc(&p->lam32, lam32.size()));
+    PD_TRY(dev_alloc(&p->gB64, p->gB.size()));
+    PD_TRY(dev_alloc(&p->gJ64, p->gJ.size()));
+    PD_TRY(dev_alloc(&p->tw64, tw.size()));
+    PD_TRY(dev_alloc(&p->tw32, tw32.size()));
+    PD_TRY(dev_alloc(&p->dal, dal.size()));
+    PD_TRY(dev_alloc(&p->twd, twd.size()));
+    if (p->dims == 2 || p->bdf_s > 1) PD_TRY(dev_alloc(&p->wreal, L.wreal));
+    if (p->bdf_s > 1) {
+      PD_TRY(dev_alloc(&p->wz, L.wz));
+      PD_TRY(dev_alloc(&p->bdf_g, L.bdfg));
+      if (p->dims == 2) {
+        PD_TRY(dev_alloc(&p->bdf_h, L.bdfh));
+        PD_TRY(dev_alloc(&p->bdf_t, L.bdft));
+      }
     }
+    // a mixed plan with an inner plan: both spectra in one buffer, which is
+    // the inner plan's complex128 spectrum
+    PD_TRY(dev_alloc(reinterpret_cast<unsigned char **>(&p->spec),
+                     p->spec_bytes + (L.inner ? L.spec2_bytes : 0)));
+    if (L.spec2_bytes && !L.inner)
+      PD_TRY(dev_alloc(reinterpret_cast<unsigned char **>(&p->spec2), L.spec2_bytes));
+    PD_TRY(dev_alloc(&p->partials, L.partials));
+    PD_TRY(dev_alloc(&p->rstage, L.rstage));
+    PD_TRY(dev_alloc(&p->bvec, L.vec));
+    PD_TRY(dev_alloc(&p->xvec, L.vec));
+    PD_TRY(dev_alloc(&p->wvec, L.vec));
+    PD_TRY(dev_alloc(&p->V, L.V));
+    PD_TRY(dev_alloc(&p->gm, pd_gmres_state_doubles(p->maxit)));
+    PD_TRY(dev_alloc(&p->red, L.red));
   }
-  PD_TRY(dev_alloc(reinterpret_cast<unsigned char **>(&p->spec), p->spec_bytes));
-  if (L.spec2_bytes)
-    PD_TRY(dev_alloc(reinterpret_cast<unsigned char **>(&p->spec2), L.spec2_bytes));
-  PD_TRY(dev_alloc(&p->partials, L.partials));
-  PD_TRY(dev_alloc(&p->rstage, L.rstage));
-  PD_TRY(dev_alloc(&p->bvec, L.vec));
-  PD_TRY(dev_alloc(&p->xvec, L.vec));
-  PD_TRY(dev_alloc(&p->wvec, L.vec));
-  PD_TRY(dev_alloc(&p->V, L.V));
-  PD_TRY(dev_alloc(&p->gm, pd_gmres_state_doubles(p->maxit)));
-  PD_TRY(dev_alloc(&p->red, L.red));
   if (p->cp_on) PD_TRY(dev_alloc(&p->cp_tab, p->cpl.total));
   if (p->sc_on)
     PD_TRY(dev_alloc(&p->sc_tab, p->dims == 2 ? pd_sc2_size(p) : sctab.size()));
@@ -813,10 +857,11 @@ extern "C" pd_status paradiag_plan_create(pd_plan *out, int n, int ell, double t
     PD_TRY(dev_alloc(&p->sine_k, sk.size()));
   }
   // small status block written by kernels straight into pinned host memory
-  if (hipHostMalloc(reinterpret_cast<void **>(&p->host_pin), 8 * sizeof(double),
+  if (!host &&
+      (hipHostMalloc(reinterpret_cast<void **>(&p->host_pin), 8 * sizeof(double),
                     hipHostMallocMapped | hipHostMallocCoherent) != hipSuccess ||
-      hipHostGetDevicePointer(reinterpret_cast<void **>(&p->host_dev), p->host_pin, 0) !=
-          hipSuccess) {
+       hipHostGetDevicePointer(reinterpret_cast<void **>(&p->host_dev), p->host_pin, 0) !=
+           hipSuccess)) {
     (void)hipGetLastError();
     if (p->host_pin) (void)hipHostFree(p->host_pin);
     p->host_pin = nullptr;
@@ -824,18 +869,22 @@ extern "C" pd_status paradiag_plan_create(pd_plan *out, int n, int ell, double t
     free_plan(p);
     return PD_ENOMEM;
   }
-  PD_TRY(upload(p->coef64, coef, p->stream));
-  PD_TRY(upload(p->coef32, coef32, p->stream));
-  PD_TRY(upload(p->lam64, p->lam, p->stream));
-  PD_TRY(upload(p->lam32, lam32, p->stream));
-  PD_TRY(upload(p->gB64, p->gB, p->stream));
-  PD_TRY(upload(p->gJ64, p->gJ, p->stream));
-  PD_TRY(upload(p->tw64, tw, p->stream));
-  PD_TRY(upload(p->tw32, tw32, p->stream));
-  PD_TRY(upload(p->dal, dal, p->stream));
-  PD_TRY(upload(p->fac64, fac, p->stream));
-  PD_TRY(upload(p->fac32, fac32, p->stream));
-  PD_TRY(upload(p->twd, twd, p->stream));
+  if (!host) {
+    PD_TRY(upload(p->coef64, coef, p->stream));
+    PD_TRY(upload(p->coef32, coef32, p->stream));
+    PD_TRY(upload(p->lam64, p->lam, p->stream));
+    PD_TRY(upload(p->lam32, lam32, p->stream));
+    PD_TRY(upload(p->gB64, p->gB, p->stream));
+    PD_TRY(upload(p->gJ64, p->gJ, p->stream));
+    PD_TRY(upload(p->tw64, tw, p->stream));
+    PD_TRY(upload(p->tw32, tw32, p->stream));
+    PD_TRY(upload(p->dal, dal, p->stream));
+    PD_TRY(upload(p->twd, twd, p->stream));
+  }
+  if (p->prec == PD_FP64)
+    PD_TRY(upload(p->fac64, fac, p->stream));
+  else
+    PD_TRY(upload(p->fac32, fac32, p->stream));
   if (p->cp_on) PD_TRY(upload(p->cp_tab, cptab, p->stream));
   if (p->sc_on) PD_TRY(upload(p->sc_tab, sctab, p->stream));
   if (p->sc_on && p->dims == 2) PD_TRY(pd_sc2_finish(p));
@@ -878,8 +927,42 @@ extern "C" pd_status paradiag_plan_create(pd_plan *out, int n, int ell, double t
       return ts;
     }
   }
+  if (L.inner) {
+    pd_options o64 = opt;
+    o64.precision = PD_FP64;
+    o64.check_residual = 0;
+    p->spec2 = static_cast<unsigned char *>(p->spec) + p->spec_bytes;
+    const pd_status is = create_plan(&p->inner, n, ell, tau, M, K, o64, p);
+    if (is != PD_OK) {
+      p->spec2 = nullptr;
+      free_plan(p);
+      return is;
+    }
+  }
   *out = p;
   return PD_OK;
+}
+
+extern "C" pd_status paradiag_plan_create(pd_plan *out, int n, int ell, double tau,
+                                          const pd_tridiag *M, const pd_tridiag *K,
+                                          const pd_options *opt_in) {
+  PdRange whole("paradiag_plan_create");
+  g_last_error.clear();
+  if (!out) {
+    pd_set_error("out is NULL");
+    return PD_EINVAL;
+  }
+  *out = nullptr;
+  pd_options opt;
+  paradiag_default_options(&opt);
+  if (opt_in) opt = *opt_in;
+  std::string msg;
+  const pd_status st = pdcheck::check_plan_args(n, ell, tau, M, K, opt, &msg);
+  if (st != PD_OK) {
+    pd_set_error(msg);
+    return st;
+  }
+  return create_plan(out, n, ell, tau, M, K, opt, nullptr);
 }
 
 extern "C" pd_status paradiag_plan_check(int n, int ell, double tau, const pd_tridiag *M,
@@ -935,6 +1018,7 @@ extern "C" size_t paradiag_plan_bytes(int n, int ell, const pd_options *opt_in) 
   tmp.uniform = true;
   tmp.autotune = (opt.autotune != 0 && opt.dims == 1) ? 1 : 0;
   tmp.sine = opt.shifted_solver == PD_SHIFTED_SINE ? 1 : 0;
+  tmp.early_exit = opt.early_exit != 0 ? 1 : 0;
   tmp.krylov = opt.krylov;
   tmp.bdf_s = (opt.bdf_order >= 1 && opt.bdf_order <= 6) ? opt.bdf_order : 1;
   tmp.ncap = tmp.bdf_s * tmp.nbar;

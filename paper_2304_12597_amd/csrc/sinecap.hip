@@ -596,6 +596,26 @@ Mode mode_of(pd_plan p, int j) {
   return o;
 }
 
+// Rows j = 1..r of the orthonormal sine vectors, ns entries apart.  sin(pi q /
+// (n + 1)) comes from one table of arguments folded into [0, pi / 2].
+void sine_rows(int n, int r, int ns, double *S) {
+  const int N = n + 1;
+  const double sc = std::sqrt(2.0 / N);
+  std::vector<double> quarter((size_t)N / 2 + 1);
+  for (int a = 0; a <= N / 2; ++a) quarter[a] = sc * std::sin(M_PI * (double)a / (double)N);
+  pd_parallel_rows(r, 1 + 65536 / n, [&](int j) {
+    double *row = S + (size_t)j * ns;
+    int q = 0;   // (j + 1) i mod 2 N
+    for (int i = 0; i < n; ++i) {
+      q += j + 1;
+      if (q >= 2 * N) q -= 2 * N;
+      int a = q > N ? 2 * N - q : q;
+      if (2 * a > N) a = N - a;
+      row[i] = q > N ? -quarter[a] : quarter[a];
+    }
+  });
+}
+
 // A bound on |J - I| on a mode with ratio z = tau kappa / m (BDF: tau beta
 // kappa / m): powers of the step's companion matrix by repeated squaring.
 // Infinite when the mode's block is (nearly) singular or not finite.
@@ -684,18 +704,7 @@ bool pd_sc_build(pd_plan p, const std::vector<double> &fac, const std::vector<do
   p->sc_ns = ns;
   p->sc_nblk = nblk;
   tab.assign(sc_doubles(n, s, r), 0.0);
-  const long N2 = 2L * (n + 1);
-  const double sc = std::sqrt(2.0 / (n + 1));
-  std::vector<double> sins((size_t)N2);
-  for (long q = 0; q < N2; ++q) {
-    // sin(pi q / (n + 1)), the argument folded into [0, pi / 2]
-    long a = q > n + 1 ? N2 - q : q;
-    if (2 * a > n + 1) a = n + 1 - a;
-    const double v = std::sin(M_PI * (double)a / (double)(n + 1));
-    sins[q] = sc * (q > n + 1 ? -v : v);
-  }
-  for (int j = 1; j <= r; ++j)
-    for (int i = 1; i <= n; ++i) tab[(size_t)(j - 1) * ns + i - 1] = sins[(size_t)((long)j * i % N2)];
+  sine_rows(n, r, ns, tab.data());
   double *Phi = &tab[(size_t)r * ns];
   const size_t NF = 6 * (size_t)(p->tri.MR - 1);
   using C = std::complex<double>;
@@ -760,17 +769,8 @@ bool pd_sc2_build(pd_plan p, std::vector<double> &tab) {
   p->sc_r = q;
   p->sc_ns = sc_stride(n);
   tab.assign((size_t)sc2_rows(q) * p->sc_ns + 2 * (size_t)q, 0.0);
-  const long N2 = 2L * (n + 1);
-  const double sc = std::sqrt(2.0 / (n + 1));
+  sine_rows(n, q, p->sc_ns, tab.data());
   for (int j = 1; j <= q; ++j) {
-    for (int i = 1; i <= n; ++i) {
-      long a = (long)j * i % N2;
-      const bool neg = a > n + 1;
-      if (neg) a = N2 - a;
-      if (2 * a > n + 1) a = n + 1 - a;
-      const double v = sc * std::sin(M_PI * (double)a / (double)(n + 1));
-      tab[(size_t)(j - 1) * p->sc_ns + i - 1] = neg ? -v : v;
-    }
     const Mode md = mode_of(p, j);
     tab[(size_t)sc2_rows(q) * p->sc_ns + j - 1] = md.kap;
     tab[(size_t)sc2_rows(q) * p->sc_ns + q + j - 1] = md.s2;
@@ -800,7 +800,7 @@ pd_status pd_sc2_finish(pd_plan p) {
   const Sc2 t(p);
   const int q = p->sc_r;
   hipLaunchKernelGGL(sc2_phi_kernel, dim3((q + 63) / 64, q), dim3(64), 0, p->stream, p->n, p->F2,
-                     q, (size_t)6 * (p->l2d.MR - 1), pd_line2d_scan(p) ? 1 : 0,
+                     q, pd_line2d_entries(p), pd_line2d_scan(p) ? 1 : 0,
                      reinterpret_cast<const cpx<double> *>(p->fac64), p->lam64, p->gJ64, t.th,
                      t.s2, t.Phi);
   PD_HIP_CHECK(hipGetLastError());

@@ -573,7 +573,12 @@ __device__ __forceinline__ int pipe_entry(int lt, int q) {
   return lt * MR + ((q + (lt >> LG)) & (MR - 1));
 }
 
-template <int MR, int MODE, bool SCAN>
+// IN32: the right-hand side is complex64, its rows 2 n entries apart (each in
+// the first half of the complex128 row that mode 1 writes in its place).  A
+// 16-byte staging entry then holds two rows, a chunk MR / 2 entries, rotated
+// like a complex128 chunk of MR / 2 rows; slot 0's rows hold the two real
+// parts as float.
+template <int MR, int MODE, bool SCAN, bool IN32 = false>
 __device__ __forceinline__ void tridiag_pipe_body(
     int blk, int nblk, int n, int F2, int P, int spb, int nitems, const Coef<double> &cf,
     const double *__restrict__ coef64, const double *__restrict__ lam,
@@ -631,27 +636,47 @@ __device__ __forceinline__ void tridiag_pipe_body(
   // rows k = 0 (dwords 0, 1 of each entry) and k = ell/2 (dwords 2, 3).
   // part in [0, 4): only the windows of that quarter of the slot's rows
   // (the recurrence form spreads a prefetch over its phases); -1: all
+  constexpr int PR = IN32 ? 2 : 1;      // rows per 16-byte staging entry
+  constexpr int MS = MR / PR;           // staging entries per chunk
   auto issue = [&](int slot_in, int b, int part = -1) {
     const int sl = slot_in < nslots ? slot_in : nslots - 1;
-    const int w0 = part < 0 ? 0 : part * (MR / 4), w1 = part < 0 ? MR : (part + 1) * (MR / 4);
+    const int w0 = part < 0 ? 0 : part * MS / 4, w1 = part < 0 ? MS : (part + 1) * MS / 4;
     if constexpr (MODE != 2) {
       // staging entry e holds row tl*MR + q of the rotated layout, tl = e/MR
       // (rows >= n read row n-1 and are zeroed when read)
-      constexpr int LG = MR == 16 ? 0 : (MR == 8 ? 1 : 2);
+      constexpr int LG = MS == 16 ? 0 : (MS == 8 ? 1 : 2);
       const int lane = lt & 63;
       if (sl != 0) {
-        // the wave's MR windows of 64 entries, one 16-byte DMA each
+        // the wave's MS windows of 64 entries, one 16-byte DMA each (IN32: a
+        // row pair; a complex64 row has room for the pair of row n - 1)
         const Cx *src = in + (size_t)sl * n;
 #pragma unroll
-        for (int wdw = 0; wdw < MR; ++wdw) {
+        for (int wdw = 0; wdw < MS; ++wdw) {
           if (wdw < w0 || wdw >= w1) continue;
-          const int e0 = wib * 64 * MR + wdw * 64;
+          const int e0 = wib * 64 * MS + wdw * 64;
           const int e = e0 + lane;
-          const int tl = e / MR, j = e & (MR - 1);
-          const int q = (j - (tl >> LG)) & (MR - 1);
-          int r = tl * MR + q;
-          r = r < n ? r : n - 1;
+          const int tl = e / MS, j = e & (MS - 1);
+          const int q = (j - (tl >> LG)) & (MS - 1);
+          int r = tl * MS + q;
+          r = r * PR < n ? r : (n - 1) / PR;
           pd_lds_dma16(src + r, stage + e0);
+        }
+      } else if constexpr (IN32) {
+        // windows of 16 entries, one 4-byte DMA each: lane l fills dword l & 3
+        // of entry e0 + l/4, dwords 0 and 2 (the pair's rows) from the real
+        // part of row k = 0 and dwords 1 and 3 from that of row k = ell/2
+        const unsigned *srcA = reinterpret_cast<const unsigned *>(in);
+        const unsigned *srcB = reinterpret_cast<const unsigned *>(in + (size_t)(F2 - 1) * n);
+        const unsigned *lsrc = (lane & 1) ? srcB : srcA;
+#pragma unroll 8
+        for (int wdw = 0; wdw < 4 * MS; ++wdw) {
+          const int e0 = wib * 64 * MS + wdw * 16;
+          const int e = e0 + (lane >> 2);
+          const int tl = e / MS, j = e & (MS - 1);
+          const int q = (j - (tl >> LG)) & (MS - 1);
+          int r = (tl * MS + q) * 2 + ((lane >> 1) & 1);
+          r = r < n ? r : n - 1;
+          pd_lds_dma4(lsrc + (size_t)r * 2, stage + e0);
         }
       } else {
         // the wave's 4*MR windows of 16 entries, one 4-byte DMA each: lane
@@ -728,11 +753,19 @@ __device__ __forceinline__ void tridiag_pipe_body(
     } else {
       // staged right-hand side (slot 0: real parts of rows k = 0 and k = ell/2)
       Cx left, right;
+      auto row = [&](int t, int q) {
+        if constexpr (IN32) {
+          const float2 v = reinterpret_cast<const float2 *>(stage)[2 * pipe_entry<MS>(t, q >> 1) + (q & 1)];
+          return Cx{(double)v.x, (double)v.y};
+        } else {
+          return stage[pipe_entry<MR>(t, q)];
+        }
+      };
 #pragma unroll
-      for (int q = 0; q < MR; ++q) d[q] = pd_sel(q < len, stage[pipe_entry<MR>(lt, q)], zero);
-      left = pd_sel(lt > 0, stage[pipe_entry<MR>(lt > 0 ? lt - 1 : 0, MR - 1)], zero);
-      right = pd_sel(s0 + MR < n && lt + 1 < P, stage[pipe_entry<MR>(lt + 1 < P ? lt + 1 : lt, 0)],
-                     zero);
+      for (int q = 0; q < MR; ++q) d[q] = pd_sel(q < len, row(lt, q), zero);
+      // (IN32: a pair's second row may be row n, which nothing has written)
+      left = pd_sel(lt > 0 && s0 <= n, row(lt > 0 ? lt - 1 : 0, MR - 1), zero);
+      right = pd_sel(s0 + MR < n && lt + 1 < P, row(lt + 1 < P ? lt + 1 : lt, 0), zero);
       // right-hand side d = M r (- w M x), formed in place; ghost rows are zero
       Cx rl = left;
 #pragma unroll
@@ -883,7 +916,7 @@ __device__ __forceinline__ void tridiag_pipe_body(
 }
 
 // skip: if non-null and nonzero (a converged GMRES), the launch does nothing
-template <int MR, int MODE, bool SCAN>
+template <int MR, int MODE, bool SCAN, bool IN32 = false>
 __global__ void __launch_bounds__(512)
 tridiag_pipe_kernel(int n, int F2, int P, int spb, int nitems, Coef<double> cf,
                     const double *__restrict__ coef64, const double *__restrict__ lam,
@@ -893,7 +926,7 @@ tridiag_pipe_kernel(int n, int F2, int P, int spb, int nitems, Coef<double> cf,
                     cpx<double> *__restrict__ out, double *__restrict__ partials,
                     const double *__restrict__ skip) {
   if (skip && *skip != 0.0) return;
-  tridiag_pipe_body<MR, MODE, SCAN>(blockIdx.x, gridDim.x, n, F2, P, spb, nitems, cf, coef64, lam, fac,
+  tridiag_pipe_body<MR, MODE, SCAN, IN32>(blockIdx.x, gridDim.x, n, F2, P, spb, nitems, cf, coef64, lam, fac,
                               gw, in, vin, xv, wscale, rhs_has_mass, out, partials);
 }
 
@@ -1003,6 +1036,14 @@ void launch_pipe(pd_plan p, int G, int nitems, const Coef<R> &cf, const R *lam,
     const TriConfig &T = p->tri;
     if (MR == 16 && T.spb != 1) return;   // excluded by the caller's check
     if constexpr (MR >= 8) {
+      if constexpr (M != 2) {
+        if (p->in32) {   // always the recurrence form (pd_mixed64_ok)
+          hipLaunchKernelGGL((tridiag_pipe_kernel<MR, M, true, true>), dim3(G), dim3(T.block),
+                             T.lds, p->stream, p->n, p->F2, T.P, T.spb, nitems, cf, p->coef64, lam,
+                             fac, gw, cin, vin, x, p->w, has_mass, o, part, p->gm_skip);
+          return;
+        }
+      }
       if (pd_use_scan(p)) {
         hipLaunchKernelGGL((tridiag_pipe_kernel<MR, M, true>), dim3(G), dim3(T.block), T.lds,
                            p->stream, p->n, p->F2, T.P, T.spb, nitems, cf, p->coef64, lam, fac,
@@ -1183,12 +1224,12 @@ void pd_uniform_factors(const pd_plan p, int MR, std::vector<double> &fac) {
   const double *u = p->uni;
   if (pd_use_scan(p) && MR == p->tri.MR) {
     // recurrence-form constants (pd_scan.h) at the same row stride
-    for (int k = 0; k < F2; ++k) {
+    pd_parallel_rows(F2, 256, [&](int k) {
       const double lr = p->lam[2 * k], li = p->lam[2 * k + 1];
       pd_scan_table({lr * u[0] + u[3], li * u[0]}, {lr * u[1] + u[4], li * u[1]},
                     {lr * u[2] + u[5], li * u[2]}, li == 0.0, p->n, MR,
                     reinterpret_cast<std::complex<double> *>(&fac[(size_t)k * NF * 2]));
-    }
+    });
     double *dual = &fac[(size_t)F2 * NF * 2];
     const double *f0 = &fac[0], *fl = &fac[(size_t)(F2 - 1) * NF * 2];
     for (size_t j = 0; j < NF; ++j) {
@@ -1266,6 +1307,8 @@ void set_attr_mr(int v) {
       pd_set_max_lds(reinterpret_cast<const void *>(&tridiag_pipe_kernel<MR, 0, true>), v);
       pd_set_max_lds(reinterpret_cast<const void *>(&tridiag_pipe_kernel<MR, 1, true>), v);
       pd_set_max_lds(reinterpret_cast<const void *>(&tridiag_pipe_kernel<MR, 2, true>), v);
+      pd_set_max_lds(reinterpret_cast<const void *>(&tridiag_pipe_kernel<MR, 0, true, true>), v);
+      pd_set_max_lds(reinterpret_cast<const void *>(&tridiag_pipe_kernel<MR, 1, true, true>), v);
     }
   }
 }
