@@ -60,7 +60,13 @@ __device__ __forceinline__ void fft_forward_body(int tile, int N, int n, int nba
       for (int u = 0; u < UNR; ++u) {
         const int t = tb + u * dt;
         const int tc = t < N ? t : N - 1;
-        vals[u] = F[(size_t)tc * nbar + ic];
+        // MODE 3: the float residual, two rows in the second half of each
+        // complex128-sized row of the spectrum (scaled by dal already)
+        if constexpr (MODE == 3)
+          vals[u] = reinterpret_cast<const float *>(F)[(size_t)(tc >> 1) * 4 * nbar + 2 * nbar +
+                                                       (size_t)(tc & 1) * nbar + ic];
+        else
+          vals[u] = F[(size_t)tc * nbar + ic];
       }
 #pragma unroll
       for (int u = 0; u < UNR; ++u) {
@@ -68,7 +74,7 @@ __device__ __forceinline__ void fft_forward_body(int tile, int N, int n, int nba
         const int tc = t < N ? t : N - 1;
         double val = (MODE == 0) ? tau * vals[u] : vals[u];
         if (MODE == 0 && t == 0) val += h0;
-        if (dal) val *= dal[tc];
+        if (MODE != 3 && dal) val *= dal[tc];
         vals[u] = (t < N && inb) ? val : 0.0;
       }
     } else {
@@ -457,6 +463,7 @@ pd_status pd_launch_fft_forward(pd_plan p, const double *u0, const double *F,
     auto o = reinterpret_cast<cpx<float> *>(out);
     if (mode == 0) PD_FWD(float, 0, tw, o);
     else if (mode == 2) PD_FWD(float, 2, tw, o);
+    else if (mode == 3) PD_FWD(float, 3, tw, o);
     else PD_FWD(float, 1, tw, o);
   }
 #undef PD_FWD
@@ -784,6 +791,7 @@ void pd_fft_set_attributes(size_t max_lds) {
   pd_set_max_lds(reinterpret_cast<const void *>(&fft_forward_kernel<float, 1>), v);
   pd_set_max_lds(reinterpret_cast<const void *>(&fft_forward_kernel<double, 2>), v);
   pd_set_max_lds(reinterpret_cast<const void *>(&fft_forward_kernel<float, 2>), v);
+  pd_set_max_lds(reinterpret_cast<const void *>(&fft_forward_kernel<float, 3>), v);
   pd_set_max_lds(reinterpret_cast<const void *>(&dst_x_kernel<0, 0>), v);
   pd_set_max_lds(reinterpret_cast<const void *>(&dst_x_kernel<1, 0>), v);
   pd_set_max_lds(reinterpret_cast<const void *>(&dst_x_kernel<2, 0>), v);

@@ -257,7 +257,7 @@ void pd_line2d_factors(const pd_plan p, std::vector<double> &fac, std::vector<fl
   std::vector<double> th(n);
   for (int m = 0; m < n; ++m) th[m] = td + 2.0 * tl * std::cos((m + 1) * M_PI / (n + 1));
   pd_parallel_rows(F2, 1 + 4096 / n, [&](int k) {
-    std::vector<double> row(f32 ? NF * 2 : 0);
+    double row[2 * 6 * 7];   // rounded to float below (8 rows per thread at most)
     for (int m = 0; m < n; ++m) {
       const double theta = th[m];
       if (scan) {
@@ -266,10 +266,10 @@ void pd_line2d_factors(const pd_plan p, std::vector<double> &fac, std::vector<fl
                       reinterpret_cast<std::complex<double> *>(&fac[((size_t)k * n + m) * NF * 2]));
         continue;
       }
-      double *dst = f32 ? row.data() : &fac[((size_t)k * n + m) * NF * 2];
+      double *dst = f32 ? row : &fac[((size_t)k * n + m) * NF * 2];
       pd_partition_factors(tl, 0.0, p->lam[2 * k] + theta + td, p->lam[2 * k + 1], tl, 0.0, MR,
                            dst);
-      if (f32) std::copy(row.begin(), row.end(), fac32.begin() + ((size_t)k * n + m) * NF * 2);
+      if (f32) std::copy(row, row + NF * 2, fac32.begin() + ((size_t)k * n + m) * NF * 2);
     }
   });
 }

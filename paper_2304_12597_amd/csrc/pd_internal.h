@@ -324,6 +324,7 @@ struct pd_plan_s {
   // transform.  It shares this plan's buffers (borrowed on its side) and owns
   // its constant tables; in32: its spectra come as complex64.
   pd_plan_s *inner = nullptr;
+  hipEvent_t norms_ready = nullptr;
   int borrowed = 0, in32 = 0;
   // capacitance solve in the sine eigenbasis (sinecap.hip)
   int sc_on = 0, sc_r = 0, sc_ns = 0, sc_nblk = 0;
@@ -383,7 +384,8 @@ void pd_set_error(const std::string &msg);
 // stage launchers (return PD_OK or an error code)
 // ---------------------------------------------------------------------------
 // forward time transform: mode 0 = h input, 1 = residual input (R = G - A(U),
-// norms accumulated into red); ost: entries between frequencies (0: nbar)
+// norms accumulated into red), 2 = F itself, 3 = the float residual that
+// pd_residual_enqueue left beside out (mixed plans); ost: entries between frequencies (0: nbar)
 pd_status pd_launch_fft_forward(pd_plan p, const double *u0, const double *F,
                                 const double *U, void *out, int mode, size_t ost = 0);
 // inverse: accumulate = 0 store, 1 add into U
@@ -517,6 +519,12 @@ int pd_residual_blocks(pd_plan p);
 // ||G - A(U)||_F^2, ||G||_F^2 and ||M U||_F^2 in float64 (synchronises)
 pd_status pd_residual_norms(pd_plan p, const double *u0, const double *F, const double *U,
                             double *rn2, double *gn2, double *un2);
+// the same pass enqueued (norms' totals into the pinned status block); out: the
+// residual itself, 1D as float in the second halves of a complex128-sized
+// spectrum's rows, 2D as float64 [ell][nbar]; null: norms only
+pd_status pd_residual_enqueue(pd_plan p, const double *u0, const double *F, const double *U,
+                              void *out);
+pd_status pd_residual_read(pd_plan p, double *rn2, double *gn2, double *un2);
 int pd_fft_blocks(pd_plan p);
 int pd_vec_blocks(int n);
 size_t pd_gmres_state_doubles(int maxit);

@@ -136,6 +136,7 @@ void free_plan(pd_plan p) {
   for (void *q : ptrs)
     if (q) (void)hipFree(q);
   if (p->host_pin) (void)hipHostFree(p->host_pin);
+  if (p->norms_ready) (void)hipEventDestroy(p->norms_ready);
   delete p;
 }
 
@@ -932,6 +933,13 @@ static pd_status create_plan(pd_plan *out, int n, int ell, double tau, const pd_
     o64.precision = PD_FP64;
     o64.check_residual = 0;
     p->spec2 = static_cast<unsigned char *>(p->spec) + p->spec_bytes;
+    if (hipEventCreateWithFlags(&p->norms_ready, hipEventDisableTiming) != hipSuccess) {
+      p->spec2 = nullptr;
+      p->norms_ready = nullptr;
+      pd_set_error("event creation failed");
+      free_plan(p);
+      return PD_EHIP;
+    }
     const pd_status is = create_plan(&p->inner, n, ell, tau, M, K, o64, p);
     if (is != PD_OK) {
       p->spec2 = nullptr;
