@@ -45,12 +45,13 @@ struct BatchRun {
   std::vector<const void *> key;   // plans, u0, F, U
   double tol = 0.0;
   int K = 0, count = 0, prec = 0, MX = 0;
-  // shifted-solve launches, one per rows-per-thread bucket (MR 4, 8, 16):
+  // shifted-solve launches, one per bucket (rows per thread 4, 8, 16; the
+  // recurrence form with 8 and 16):
   // each bucket's entries are contiguous in the t0, t1, t0J and k0m maps
   struct TriBucket {
-    int MR = 0, o0 = 0, n0 = 0, o1 = 0, n1 = 0, o0J = 0, n0J = 0, ok0 = 0, nk0 = 0;
+    int MR = 0, scan = 0, o0 = 0, n0 = 0, o1 = 0, n1 = 0, o0J = 0, n0J = 0, ok0 = 0, nk0 = 0;
     size_t lds = 0;
-  } tb[3];
+  } tb[5];
   hipStream_t s = nullptr;
   void *dev = nullptr;
   double *pin = nullptr;           // statuses [4 * count]: residual, h, iterations, beta
@@ -113,11 +114,12 @@ pd_status build_run(BatchRun &r, const pd_plan *plans, int count, const double *
     int fft_threads = 64;
     size_t fft_lds = 0;
     // per rows-per-thread bucket: the shifted-solve block maps and LDS size
-    std::vector<int2> t0b[3], t1b[3], t0Jb[3], k0b[3];
-    size_t ldsb[3] = {0, 0, 0};
+    std::vector<int2> t0b[5], t1b[5], t0Jb[5], k0b[5];
+    size_t ldsb[5] = {0, 0, 0, 0, 0};
     for (int i = 0; i < count; ++i) {
       const pd_plan p = plans[i];
-      const int bi = p->tri.MR == 4 ? 0 : (p->tri.MR == 8 ? 1 : 2);
+      const int scan = prec == PD_FP64 && pd_use_scan(p) ? 1 : 0;
+      const int bi = (p->tri.MR == 4 ? 0 : (p->tri.MR == 8 ? 1 : 2)) + 2 * scan;
       if (p->tri.MR != 4 && p->tri.MR != 8 && p->tri.MR != 16) return PD_ENOTSUP;
       FftJob &f = fj[i];
       f.N = p->ell; f.n = p->n; f.nbar = p->nbar; f.dims = 1;
@@ -145,12 +147,11 @@ pd_status build_run(BatchRun &r, const pd_plan *plans, int count, const double *
       t.coef64 = p->coef64;
       t.lam = (prec == PD_FP64) ? (const void *)p->lam64 : (const void *)p->lam32;
       t.fac = (prec == PD_FP64) ? (const void *)p->fac64 : (const void *)p->fac32;
-      t.scan = (prec == PD_FP64 && pd_use_scan(p)) ? 1 : 0;
       t.gw = p->gB64; t.in = p->spec; t.vin = nullptr; t.xv = p->xvec; t.wscale = p->w;
       t.out = p->spec; t.partials = p->partials; t.skip = nullptr;
       for (int b = 0; b < t.nblk; ++b) t0b[bi].push_back(make_int2(i, b));
       for (int b = 0; b < t.nblk; ++b) t1b[bi].push_back(make_int2(i, b));
-      ldsb[bi] = std::max(ldsb[bi], p->tri.lds);   // batchable: the same packing as p->tri
+      ldsb[bi] = std::max(ldsb[bi], pd_tri_lds(p));   // batchable: the same packing as p->tri
 
       VecJob &v = vj[i];
       v.n = p->nbar; v.B = pd_vec_blocks(p->nbar); v.G = t.nblk;
@@ -180,9 +181,10 @@ pd_status build_run(BatchRun &r, const pd_plan *plans, int count, const double *
         for (int b = 0; b < (p->nbar + 255) / 256; ++b) redmapJ.push_back(make_int2(i, b));
       }
     }
-    for (int bi = 0; bi < 3; ++bi) {
+    for (int bi = 0; bi < 5; ++bi) {
       auto &B = r.tb[bi];
-      B.MR = 4 << bi;
+      B.scan = bi > 2 ? 1 : 0;
+      B.MR = 4 << (bi - 2 * B.scan);
       B.lds = ldsb[bi];
       B.o0 = (int)tri0map.size();
       B.n0 = (int)t0b[bi].size();
@@ -329,7 +331,7 @@ pd_status tri_batch(const BatchRun &r, int mode, const TriJob *jobs, const int2 
                     int j, hipStream_t s) {
   for (const auto &B : r.tb)
     if (B.*cnt > 0)
-      PD_B(pd_launch_tridiag_batch(r.prec, B.MR, mode, jobs, map + B.*off, B.*cnt, B.lds, act, j,
+      PD_B(pd_launch_tridiag_batch(r.prec, B.MR, B.scan, mode, jobs, map + B.*off, B.*cnt, B.lds, act, j,
                                    s));
   return PD_OK;
 }

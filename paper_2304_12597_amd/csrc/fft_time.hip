@@ -812,7 +812,8 @@ namespace {
 template <typename R, int MODE>
 __global__ void __launch_bounds__(1024)
 fft_forward_batch_kernel(const FftJob *__restrict__ jobs, const int2 *__restrict__ map) {
-  const int2 m = map[blockIdx.x];
+  // neighbouring tiles of a problem on one XCD, as alone (xcd_tile)
+  const int2 m = map[xcd_tile(blockIdx.x, gridDim.x)];
   const FftJob &j = jobs[m.x];
   fft_forward_body<R, MODE>(m.y, j.N, j.n, j.nbar, j.dims, j.C, j.stride, j.tau, j.u0, j.F, j.U,
                             j.coef, j.dal, reinterpret_cast<const cpx<R> *>(j.tw),
@@ -821,7 +822,7 @@ fft_forward_batch_kernel(const FftJob *__restrict__ jobs, const int2 *__restrict
 template <typename R>
 __global__ void __launch_bounds__(1024)
 fft_inverse_batch_kernel(const FftJob *__restrict__ jobs, const int2 *__restrict__ map) {
-  const int2 m = map[blockIdx.x];
+  const int2 m = map[xcd_tile(blockIdx.x, gridDim.x)];
   const FftJob &j = jobs[m.x];
   fft_inverse_body<R, 0>(m.y, j.N, j.nbar, j.C, j.stride,
                          reinterpret_cast<const cpx<R> *>(j.spec), j.dal ? j.dal + j.N : nullptr,

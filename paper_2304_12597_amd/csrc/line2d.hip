@@ -256,9 +256,11 @@ void pd_line2d_factors(const pd_plan p, std::vector<double> &fac, std::vector<fl
   const bool scan = pd_line2d_scan(p);
   std::vector<double> th(n);
   for (int m = 0; m < n; ++m) th[m] = td + 2.0 * tl * std::cos((m + 1) * M_PI / (n + 1));
-  pd_parallel_rows(F2, 1 + 4096 / n, [&](int k) {
+  const int mblk = (n + 63) / 64;   // units of 64 lines of a frequency
+  pd_parallel_rows(F2 * mblk, 4, [&](int unit) {
+    const int k = unit / mblk, ma = (unit - k * mblk) * 64, mb = ma + 64 < n ? ma + 64 : n;
     double row[2 * 6 * 7];   // rounded to float below (8 rows per thread at most)
-    for (int m = 0; m < n; ++m) {
+    for (int m = ma; m < mb; ++m) {
       const double theta = th[m];
       if (scan) {
         pd_scan_table({tl, 0.0}, {p->lam[2 * k] + theta + td, p->lam[2 * k + 1]}, {tl, 0.0},

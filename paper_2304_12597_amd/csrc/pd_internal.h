@@ -116,7 +116,6 @@ struct TriJob {
   void *out;
   double *partials;
   const double *skip;   // nonzero: the problem's GMRES has converged (J jobs)
-  int scan;             // the recurrence-form solve (pd_scan.h), P >= 64 float64 only
 };
 
 struct VecJob {     // one problem's vectors for the batched GMRES kernels
@@ -545,6 +544,16 @@ inline bool pd_use_scan(const pd_plan p) {
          p->tri.P % 64 == 0 && u[0] == u[2] && u[3] == u[5];
 }
 
+// LDS bytes of a pipelined recurrence-form block: staging for an item of each
+// of its systems, the waves' exchange and two buffers of constants.
+constexpr int PD_SCAN_SLOTS = 32;   // >= 9 + MR constants of a system
+inline size_t pd_pipe_scan_lds(const TriConfig &T) {
+  return (size_t)T.spb * ((size_t)T.P * T.MR + 3 * (size_t)(T.P / 64) + 2 * PD_SCAN_SLOTS) * 16;
+}
+inline size_t pd_tri_lds(const pd_plan p) {
+  return pd_use_scan(p) ? pd_pipe_scan_lds(p->tri) : p->tri.lds;
+}
+
 // The 2D line solves of float64 plans with groups of at most one wave use
 // the recurrence form as well (symmetric Toeplitz lines, pd_scan.h).
 inline bool pd_line2d_scan(const pd_plan p) {
@@ -573,9 +582,9 @@ pd_status pd_launch_fft_forward_batch(int prec, const FftJob *jobs, const int2 *
                                       int threads, size_t lds, hipStream_t s);
 pd_status pd_launch_fft_inverse_batch(int prec, const FftJob *jobs, const int2 *map, int nblocks,
                                       int threads, size_t lds, hipStream_t s);
-pd_status pd_launch_tridiag_batch(int prec, int MR, int mode, const TriJob *jobs, const int2 *map,
-                                  int nblocks, size_t lds, const int *active, int jv,
-                                  hipStream_t s);
+pd_status pd_launch_tridiag_batch(int prec, int MR, int scan, int mode, const TriJob *jobs,
+                                  const int2 *map, int nblocks, size_t lds, const int *active,
+                                  int jv, hipStream_t s);
 pd_status pd_launch_reduce_batch(const VecJob *jobs, const int2 *map, int nblocks, int base_j,
                                  const int *active, hipStream_t s);
 void pd_fft_batch_set_attributes(size_t max_lds);

@@ -562,7 +562,9 @@ __device__ __forceinline__ void tridiag_uniform_body(
 // factor row F2), so F2 - 1 items cover the half spectrum; slot s >= 1 is
 // k = s.  Slot 0 stages the two real parts with 4-byte DMA instructions.
 //
-// LDS: [spb*P*MR cpx stage][spb*P Row3 exchange][2*spb*NFP cpx factors]
+// LDS: [spb*P*MR cpx stage][spb*P Row3 exchange][2*spb*NFP cpx factors]; the
+// recurrence form needs 3 P/64 entries of exchange and 32 of constants a
+// system (pd_pipe_lds), so that two blocks fit on a CU at 8 rows per thread
 template <int MR>
 constexpr int pipe_nfp() { return (6 * (MR - 1) + 63) / 64 * 64; }
 
@@ -590,7 +592,7 @@ __device__ __forceinline__ void tridiag_pipe_body(
   using Cx = cpx<double>;
   extern __shared__ __align__(16) unsigned char smem_raw[];
   constexpr int NF = 6 * (MR - 1);
-  constexpr int NFP = pipe_nfp<MR>();
+  constexpr int NFP = SCAN ? PD_SCAN_SLOTS : pipe_nfp<MR>();
   // 16 rows per thread (one system per block): the paired item runs in block
   // 0's prologue, so the item loop holds a single copy of the partition solve
   constexpr bool PAIR_FIRST = (MR == 16);
@@ -602,8 +604,10 @@ __device__ __forceinline__ void tridiag_pipe_body(
   Cx *stage_all = reinterpret_cast<Cx *>(smem_raw);
   Cx *stage = stage_all + (size_t)g * rows;
   Row3<R> *xch_all = reinterpret_cast<Row3<R> *>(stage_all + (size_t)spb * rows);
-  Row3<R> *xch = xch_all + (size_t)g * P;
-  Cx *facb = reinterpret_cast<Cx *>(xch_all + (size_t)spb * P);
+  Row3<R> *xch = SCAN ? reinterpret_cast<Row3<R> *>(stage_all + (size_t)spb * rows + 3 * g * (P >> 6))
+                      : xch_all + (size_t)g * P;
+  Cx *facb = SCAN ? stage_all + (size_t)spb * (rows + 3 * (P >> 6))
+                  : reinterpret_cast<Cx *>(xch_all + (size_t)spb * P);
   const int s0 = lt * MR;
   int len = n - s0;
   len = len < 0 ? 0 : (len > MR ? MR : len);
@@ -645,7 +649,10 @@ __device__ __forceinline__ void tridiag_pipe_body(
       // staging entry e holds row tl*MR + q of the rotated layout, tl = e/MR
       // (rows >= n read row n-1 and are zeroed when read)
       constexpr int LG = MS == 16 ? 0 : (MS == 8 ? 1 : 2);
-      const int lane = lt & 63;
+      int lane = lt & 63;
+      // (formed here, not hoisted out of the loop over items: the windows'
+      // addresses would hold registers through the whole solve)
+      asm volatile("" : "+v"(lane));
       if (sl != 0) {
         // the wave's MS windows of 64 entries, one 16-byte DMA each (IN32: a
         // row pair; a complex64 row has room for the pair of row n - 1)
@@ -705,9 +712,9 @@ __device__ __forceinline__ void tridiag_pipe_body(
         pd_lds_dma16(fsrc + (idx < NF ? idx : NF - 1), fdst + c0);
       }
     } else if (part <= 0 && wib == 0) {
-      // the recurrence form's constants: one 64-entry window
+      // the recurrence form's constants: half a wave's window
       const int idx = lt & 63;
-      pd_lds_dma16(fsrc + (idx < NF ? idx : NF - 1), fdst);
+      if (idx < NFP) pd_lds_dma16(fsrc + (idx < NF ? idx : NF - 1), fdst);
     }
   };
 
@@ -753,6 +760,8 @@ __device__ __forceinline__ void tridiag_pipe_body(
     } else {
       // staged right-hand side (slot 0: real parts of rows k = 0 and k = ell/2)
       Cx left, right;
+      int l2 = lt;   // (as in issue: the entries' addresses are formed here)
+      asm volatile("" : "+v"(l2));
       auto row = [&](int t, int q) {
         if constexpr (IN32) {
           const float2 v = reinterpret_cast<const float2 *>(stage)[2 * pipe_entry<MS>(t, q >> 1) + (q & 1)];
@@ -762,10 +771,10 @@ __device__ __forceinline__ void tridiag_pipe_body(
         }
       };
 #pragma unroll
-      for (int q = 0; q < MR; ++q) d[q] = pd_sel(q < len, row(lt, q), zero);
+      for (int q = 0; q < MR; ++q) d[q] = pd_sel(q < len, row(l2, q), zero);
       // (IN32: a pair's second row may be row n, which nothing has written)
-      left = pd_sel(lt > 0 && s0 <= n, row(lt > 0 ? lt - 1 : 0, MR - 1), zero);
-      right = pd_sel(s0 + MR < n && lt + 1 < P, row(lt + 1 < P ? lt + 1 : lt, 0), zero);
+      left = pd_sel(lt > 0 && (!IN32 || s0 <= n), row(l2 > 0 ? l2 - 1 : 0, MR - 1), zero);
+      right = pd_sel(s0 + MR < n && lt + 1 < P, row(l2 + 1 < P ? l2 + 1 : l2, 0), zero);
       // right-hand side d = M r (- w M x), formed in place; ghost rows are zero
       Cx rl = left;
 #pragma unroll
@@ -821,7 +830,8 @@ __device__ __forceinline__ void tridiag_pipe_body(
               }
             }
           }
-          const int qb = lt & ~3;
+          int qb = lt & ~3;
+          asm volatile("" : "+v"(qb));
           if constexpr (DUAL) {
             // slot 0: the real parts go to rows k = 0 and k = ell/2
             Cx *da = out, *db = out + (size_t)(F2 - 1) * n;
@@ -916,8 +926,13 @@ __device__ __forceinline__ void tridiag_pipe_body(
 }
 
 // skip: if non-null and nonzero (a converged GMRES), the launch does nothing
+// Recurrence form, 8 rows per thread, mode 1: held to 128 registers so that
+// two blocks share a CU, one loading or storing while the other solves (n =
+// 4095, ell = 1024: 24.9 -> 22.3 us with 512 blocks).  Mode 0 keeps one block
+// per CU: more blocks are more partial rows (18.5 against 19.1 us, and 2 us in
+// their reduction).
 template <int MR, int MODE, bool SCAN, bool IN32 = false>
-__global__ void __launch_bounds__(512)
+__global__ void __launch_bounds__(512, SCAN && MR == 8 && MODE == 1 ? 4 : 2)
 tridiag_pipe_kernel(int n, int F2, int P, int spb, int nitems, Coef<double> cf,
                     const double *__restrict__ coef64, const double *__restrict__ lam,
                     const cpx<double> *__restrict__ fac, const double *__restrict__ gw,
@@ -1039,13 +1054,13 @@ void launch_pipe(pd_plan p, int G, int nitems, const Coef<R> &cf, const R *lam,
       if constexpr (M != 2) {
         if (p->in32) {   // always the recurrence form (pd_mixed64_ok)
           hipLaunchKernelGGL((tridiag_pipe_kernel<MR, M, true, true>), dim3(G), dim3(T.block),
-                             T.lds, p->stream, p->n, p->F2, T.P, T.spb, nitems, cf, p->coef64, lam,
+                             pd_tri_lds(p), p->stream, p->n, p->F2, T.P, T.spb, nitems, cf, p->coef64, lam,
                              fac, gw, cin, vin, x, p->w, has_mass, o, part, p->gm_skip);
           return;
         }
       }
       if (pd_use_scan(p)) {
-        hipLaunchKernelGGL((tridiag_pipe_kernel<MR, M, true>), dim3(G), dim3(T.block), T.lds,
+        hipLaunchKernelGGL((tridiag_pipe_kernel<MR, M, true>), dim3(G), dim3(T.block), pd_tri_lds(p),
                            p->stream, p->n, p->F2, T.P, T.spb, nitems, cf, p->coef64, lam, fac,
                            gw, cin, vin, x, p->w, has_mass, o, part, p->gm_skip);
         return;
@@ -1096,7 +1111,9 @@ pd_status launch_mr(pd_plan p, int mode, const void *in, const double *xv, void 
   const double *x = (mode == 1) ? xv : nullptr;
   cpx<R> *o = (mode == 1) ? cout : nullptr;
   double *part = (mode == 1) ? nullptr : p->partials;
-  const int Gp = ov.G > 0 ? ov.G : (nitems < p->tri_G ? nitems : p->tri_G);   // pipelined body: every mode
+  // pipelined body: every mode (mode 1 with 8 rows per thread: two blocks a CU)
+  const int capP = (mode == 1 && MR == 8 && pd_use_scan(p)) ? 2 * p->tri_G : p->tri_G;
+  const int Gp = ov.G > 0 ? ov.G : (nitems < capP ? nitems : capP);
   if (UNI && T.pipe && MR == 16 && T.spb != 1) {
     // the 16-row body pairs the real shifts in block 0's prologue: one
     // system per block
@@ -1325,8 +1342,13 @@ void pd_tri_set_attributes(size_t max_lds) {
 }
 
 namespace {
-template <typename R, int MR, int MODE, int MAXT>
-__global__ void __launch_bounds__(MAXT)
+// FORM 1: every problem of the launch takes the recurrence form (its bucket);
+// 0: any other.  Most blocks of a batch have one item, so nothing of their own
+// overlaps its load and stores: with 8 rows per thread two blocks share a CU
+// (96 problems, n <= 4095: pass B 426 -> 326 us, pass C 562 -> 391 us; the few
+// spilled registers cost less).
+template <typename R, int MR, int MODE, int MAXT, int FORM = 0>
+__global__ void __launch_bounds__(MAXT, FORM == 1 && MR == 8 ? 4 : 1)
 tridiag_batch_kernel(const TriJob *__restrict__ jobs, const int2 *__restrict__ map,
                      const int *__restrict__ active, int jv) {
   const int2 m = map[blockIdx.x];
@@ -1347,7 +1369,7 @@ tridiag_batch_kernel(const TriJob *__restrict__ jobs, const int2 *__restrict__ m
             j.vin ? j.vin + (size_t)jv * j.n : nullptr, j.xv, j.wscale, j.has_mass,
             reinterpret_cast<cpx<double> *>(j.out), j.partials);
       };
-      if (j.scan)
+      if constexpr (FORM == 1)
         body(std::true_type{});
       else
         body(std::false_type{});
@@ -1390,10 +1412,25 @@ __global__ void reduce_batch_kernel(const VecJob *__restrict__ jobs, const int2 
 }
 }  // namespace
 
-pd_status pd_launch_tridiag_batch(int prec, int MR, int mode, const TriJob *jobs, const int2 *map,
-                                  int nblocks, size_t lds, const int *active, int jv,
-                                  hipStream_t s) {
+pd_status pd_launch_tridiag_batch(int prec, int MR, int scan, int mode, const TriJob *jobs,
+                                  const int2 *map, int nblocks, size_t lds, const int *active,
+                                  int jv, hipStream_t s) {
   if (nblocks == 0) return PD_OK;
+#define PD_TBS(MRV, M)                                                                      \
+  hipLaunchKernelGGL((tridiag_batch_kernel<double, MRV, M, 512, 1>), dim3(nblocks), dim3(512), lds, \
+                     s, jobs, map, active, jv)
+  if (scan) {
+    if (prec != PD_FP64 || (MR != 8 && MR != 16)) {
+      pd_set_error("batched solve: unsupported recurrence form");
+      return PD_ENOTSUP;
+    }
+    if (mode == 0) { if (MR == 8) PD_TBS(8, 0); else PD_TBS(16, 0); }
+    else if (mode == 1) { if (MR == 8) PD_TBS(8, 1); else PD_TBS(16, 1); }
+    else { if (MR == 8) PD_TBS(8, 2); else PD_TBS(16, 2); }
+    PD_HIP_CHECK(hipGetLastError());
+    return PD_OK;
+  }
+#undef PD_TBS
 #define PD_TB(R, MRV, M)                                                                  \
   hipLaunchKernelGGL((tridiag_batch_kernel<R, MRV, M, (sizeof(R) == 8 ? 512 : 1024)>),      \
                      dim3(nblocks), dim3(sizeof(R) == 8 ? 512 : 1024), lds, s, jobs, map,  \
@@ -1433,6 +1470,12 @@ pd_status pd_launch_reduce_batch(const VecJob *jobs, const int2 *map, int nblock
 void pd_tri_batch_set_attributes(size_t max_lds) {
   const int v = (int)max_lds;
   const void *fns[] = {
+      reinterpret_cast<const void *>(&tridiag_batch_kernel<double, 8, 0, 512, 1>),
+      reinterpret_cast<const void *>(&tridiag_batch_kernel<double, 8, 1, 512, 1>),
+      reinterpret_cast<const void *>(&tridiag_batch_kernel<double, 8, 2, 512, 1>),
+      reinterpret_cast<const void *>(&tridiag_batch_kernel<double, 16, 0, 512, 1>),
+      reinterpret_cast<const void *>(&tridiag_batch_kernel<double, 16, 1, 512, 1>),
+      reinterpret_cast<const void *>(&tridiag_batch_kernel<double, 16, 2, 512, 1>),
       reinterpret_cast<const void *>(&tridiag_batch_kernel<double, 4, 0, 512>),
       reinterpret_cast<const void *>(&tridiag_batch_kernel<double, 4, 1, 512>),
       reinterpret_cast<const void *>(&tridiag_batch_kernel<double, 4, 2, 512>),
