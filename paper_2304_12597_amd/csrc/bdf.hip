@@ -266,6 +266,39 @@ bdf_residual2d_kernel(int n, int ell, int s, double tb, BdfAlpha c,
   }
 }
 
+// add[t][i] = sum_{j=t+1}^{s} alpha_j u_{t+1-j}[i], t < s: what h has beside
+// tau beta f.  Grid: (ceil(n/BB), s).
+__global__ void __launch_bounds__(BB)
+bdf_start_kernel(int n, int s, BdfAlpha c, const double *__restrict__ u0s,
+                 double *__restrict__ add) {
+  const int i = blockIdx.x * BB + threadIdx.x;
+  const int t = blockIdx.y;
+  if (i >= n) return;
+  double v = 0.0;
+  for (int j = t + 1; j <= s; ++j) v += c.a[j - 1] * u0s[(size_t)(s + t - j) * n + i];
+  add[(size_t)t * n + i] = v;
+}
+
+// spec[f][i] -= sum_{2 <= h < s} v_h[i] exp(-2 pi i f h / ell).  Grid:
+// (ceil(n/BB), F2).
+__global__ void __launch_bounds__(BB)
+bdf_sub_kernel(int n, int ell, int s, const double *__restrict__ v,
+               const cpx<double> *__restrict__ tw, cpx<double> *__restrict__ spec) {
+  const int i = blockIdx.x * BB + threadIdx.x;
+  const int f = blockIdx.y;
+  if (i >= n) return;
+  cpx<double> a = spec[(size_t)f * n + i];
+#pragma unroll
+  for (int h = 2; h < 6; ++h)
+    if (h < s) {
+      const cpx<double> w = tw[(f * h) & (ell - 1)];
+      const double x = v[(size_t)h * n + i];
+      a.re -= w.re * x;
+      a.im -= w.im * x;
+    }
+  spec[(size_t)f * n + i] = a;
+}
+
 BdfAlpha alpha_of(pd_plan p) {
   BdfAlpha c;
   for (int j = 0; j < 6; ++j) c.a[j] = p->bdf_alpha[j];
@@ -399,14 +432,86 @@ pd_status pd_bdf_residual_norms(pd_plan p, const double *u0s, const double *F,
   return PD_OK;
 }
 
+// 1D plans on the recurrence form with the capacitance system in the sine
+// basis: b^(s) is summed over the frequencies inside the solves (the gamma^(k)
+// sums, two blocks a pass; U_1 is never formed), and U is one more pass over
+// the same spectrum with the theta^(h) x_h in its right-hand side.  Against U_1
+// and a correction transformed apart (the general path below) that saves an
+// inverse transform, an accumulating one's second reading of U and two
+// spectrum passes; h's source term goes straight into the forward transform.
+static pd_status bdf_solve_fused(pd_plan p, const double *u0s, const double *F, double *U,
+                                 double rtol) {
+  const int n = p->n, s = p->bdf_s;
+  double *add = p->wvec;   // s rows
+  hipLaunchKernelGGL(bdf_start_kernel, dim3((n + BB - 1) / BB, s), dim3(BB), 0, p->stream, n, s,
+                     alpha_of(p), u0s, add);
+  PD_HIP_CHECK(hipGetLastError());
+  pd_status st = pd_launch_fft_forward(p, add, F, nullptr, p->spec, 4);
+  if (st != PD_OK) return st;
+  const size_t F2x2 = 2 * (size_t)p->F2;
+  for (int h = 0; h < s; h += 2) {
+    const bool two = h + 1 < s;
+    // partial rows in the work array of the transforms, idle here: 2 tri_G <=
+    // ell rows
+    st = pd_launch_tridiag_bdf_sums(p, p->spec, p->bdf_g + h * F2x2,
+                                    two ? p->bdf_g + (h + 1) * F2x2 : nullptr,
+                                    p->bvec + (size_t)h * n,
+                                    two ? p->bvec + (size_t)(h + 1) * n : nullptr, p->wreal);
+    if (st != PD_OK) return st;
+  }
+  st = pd_sc_enqueue(p, p->bvec, p->xvec, rtol);
+  if (st != PD_OK) return st;
+  if (s > 2) {
+    hipLaunchKernelGGL(bdf_sub_kernel, dim3((n + BB - 1) / BB, p->F2), dim3(BB), 0, p->stream, n,
+                       p->ell, s, p->xvec, reinterpret_cast<const cpx<double> *>(p->tw64),
+                       reinterpret_cast<cpx<double> *>(p->spec));
+    PD_HIP_CHECK(hipGetLastError());
+  }
+  st = pd_launch_tridiag_bdf_solve(p, p->spec, p->xvec, p->xvec + n, 0);
+  if (st != PD_OK) return st;
+  return pd_launch_fft_inverse(p, p->spec, U, 0);
+}
+
+// The report, the optional residual and the final synchronisation of a solve.
+static pd_status bdf_finish_solve(pd_plan p, const double *u0s, const double *F, const double *U,
+                                  int its, int checks, double rr, pd_status gst, pd_info *info) {
+  if (info) {
+    info->gmres_iters = its;
+    info->pint_loops = (p->krylov == PD_KRYLOV_FOM ? checks : its) + 2;
+    info->sweeps = 1;
+    info->gmres_rel_residual = rr;
+  }
+  if (p->check_residual) {
+    double rn2, gn2;
+    const pd_status st = pd_bdf_residual_norms(p, u0s, F, U, &rn2, &gn2);
+    if (st != PD_OK) return st;
+    if (info) info->rel_residual = gn2 > 0.0 ? std::sqrt(rn2 / gn2) : std::sqrt(rn2);
+  }
+  PD_HIP_CHECK(hipStreamSynchronize(p->stream));
+  if (gst == PD_ENOTCONV) pd_set_error("tolerance not reached");
+  return gst;
+}
+
 // The whole BDF solve: h, U_1 = Y(h) into U, b^(s), J^(s) x = b^(s) by
 // GMRES or by the block Galerkin method (krylov = PD_KRYLOV_FOM),
 // U -= Y(X(x)) (the transform of X(x) as an s-term sum).
 pd_status pd_bdf_solve(pd_plan p, const double *u0s, const double *F, double *U, double tol,
                        pd_info *info) {
   if (!bdf_plan_ok(p)) return PD_ENOTSUP;
+  int its = 0, checks = 0;
+  double rr = 0.0;
+  pd_status st, gst;
+  const bool fused = p->dims == 1 && p->sc_on && pd_use_scan(p) && 2 * p->tri_G <= p->ell;
+  if (fused) {
+    st = bdf_solve_fused(p, u0s, F, U, tol * PD_GMRES_TOL_FACTOR);
+    if (st != PD_OK) return st;
+    PD_HIP_CHECK(hipStreamSynchronize(p->stream));
+    gst = pd_gmres_status(p, tol * PD_GMRES_TOL_FACTOR, &its, &rr);
+    if (gst != PD_OK && gst != PD_ENOTCONV) return gst;
+    return bdf_finish_solve(p, u0s, F, U, its, checks, rr, gst, info);
+  }
   // h into the transform input (2D: into bdf_h, then to the DST-x domain)
-  pd_status st = pd_bdf_rhs(p, u0s, F, p->dims == 2 ? p->bdf_h : p->wreal);
+  st = pd_bdf_rhs(p, u0s, F, p->dims == 2 ? p->bdf_h : p->wreal);
   if (st != PD_OK) return st;
   if (p->dims == 2) {
     st = pd_launch_dst_x_rows(p, p->bdf_h, p->wreal, p->ell, 0);
@@ -416,9 +521,6 @@ pd_status pd_bdf_solve(pd_plan p, const double *u0s, const double *F, double *U,
   if (st != PD_OK) return st;
   st = extract(p, nullptr, U, p->bvec);
   if (st != PD_OK) return st;
-  int its = 0, checks = 0;
-  double rr = 0.0;
-  pd_status gst;
   if (p->krylov == PD_KRYLOV_FOM && p->dims == 2) {
     // the block Galerkin method works in the DST-x domain of the line solves:
     // b^(s) there (its s rows), x back to space
@@ -442,19 +544,5 @@ pd_status pd_bdf_solve(pd_plan p, const double *u0s, const double *F, double *U,
   if (st != PD_OK) return st;
   st = pd_inverse(p, p->spec, U, 1);
   if (st != PD_OK) return st;
-  if (info) {
-    info->gmres_iters = its;
-    info->pint_loops = (p->krylov == PD_KRYLOV_FOM ? checks : its) + 2;
-    info->sweeps = 1;
-    info->gmres_rel_residual = rr;
-  }
-  if (p->check_residual) {
-    double rn2, gn2;
-    st = pd_bdf_residual_norms(p, u0s, F, U, &rn2, &gn2);
-    if (st != PD_OK) return st;
-    if (info) info->rel_residual = gn2 > 0.0 ? std::sqrt(rn2 / gn2) : std::sqrt(rn2);
-  }
-  PD_HIP_CHECK(hipStreamSynchronize(p->stream));
-  if (gst == PD_ENOTCONV) pd_set_error("tolerance not reached");
-  return gst;
+  return bdf_finish_solve(p, u0s, F, U, its, checks, rr, gst, info);
 }

@@ -72,8 +72,10 @@ __device__ __forceinline__ void fft_forward_body(int tile, int N, int n, int nba
       for (int u = 0; u < UNR; ++u) {
         const int t = tb + u * dt;
         const int tc = t < N ? t : N - 1;
-        double val = (MODE == 0) ? tau * vals[u] : vals[u];
+        double val = (MODE == 0 || MODE == 4) ? tau * vals[u] : vals[u];
         if (MODE == 0 && t == 0) val += h0;
+        // MODE 4 (BDF): the first rows' starting-value terms, dims of them
+        if (MODE == 4 && t < dims) val += u0[(size_t)t * nbar + ic];
         if (MODE != 3 && dal) val *= dal[tc];
         vals[u] = (t < N && inb) ? val : 0.0;
       }
@@ -457,6 +459,10 @@ pd_status pd_launch_fft_forward(pd_plan p, const double *u0, const double *F,
     auto o = reinterpret_cast<cpx<double> *>(out);
     if (mode == 0) PD_FWD(double, 0, tw, o);
     else if (mode == 2) PD_FWD(double, 2, tw, o);
+    else if (mode == 4)
+      hipLaunchKernelGGL((fft_forward_kernel<double, 4>), dim3(L.blocks), dim3(L.threads), L.lds,
+                         p->stream, p->ell, p->n, p->nbar, p->bdf_s, L.C, L.stride,
+                         p->tau * p->bdf_beta, u0, F, U, p->coef64, dal, tw, o, ost, p->red);
     else PD_FWD(double, 1, tw, o);
   } else {
     auto tw = reinterpret_cast<const cpx<float> *>(p->tw32);
@@ -790,6 +796,7 @@ void pd_fft_set_attributes(size_t max_lds) {
   pd_set_max_lds(reinterpret_cast<const void *>(&fft_forward_kernel<float, 0>), v);
   pd_set_max_lds(reinterpret_cast<const void *>(&fft_forward_kernel<float, 1>), v);
   pd_set_max_lds(reinterpret_cast<const void *>(&fft_forward_kernel<double, 2>), v);
+  pd_set_max_lds(reinterpret_cast<const void *>(&fft_forward_kernel<double, 4>), v);
   pd_set_max_lds(reinterpret_cast<const void *>(&fft_forward_kernel<float, 2>), v);
   pd_set_max_lds(reinterpret_cast<const void *>(&fft_forward_kernel<float, 3>), v);
   pd_set_max_lds(reinterpret_cast<const void *>(&dst_x_kernel<0, 0>), v);

@@ -384,7 +384,8 @@ void pd_set_error(const std::string &msg);
 // ---------------------------------------------------------------------------
 // forward time transform: mode 0 = h input, 1 = residual input (R = G - A(U),
 // norms accumulated into red), 2 = F itself, 3 = the float residual that
-// pd_residual_enqueue left beside out (mixed plans); ost: entries between frequencies (0: nbar)
+// pd_residual_enqueue left beside out (mixed plans), 4 = tau beta F with the
+// bdf_s rows of u0 added to the first rows (BDF); ost: entries between frequencies (0: nbar)
 pd_status pd_launch_fft_forward(pd_plan p, const double *u0, const double *F,
                                 const double *U, void *out, int mode, size_t ost = 0);
 // inverse: accumulate = 0 store, 1 add into U
@@ -415,6 +416,11 @@ pd_status pd_launch_dst_x_rows(pd_plan p, const double *in, double *out, int tro
                                int accumulate);
 int pd_forward_norm_blocks(pd_plan p);
 int pd_dst_blocks(pd_plan p);
+// BDF of order s on the recurrence form (tridiag.hip)
+pd_status pd_launch_tridiag_bdf_sums(pd_plan p, const void *in, const double *g0, const double *g1,
+                                     double *out0, double *out1, double *partials);
+pd_status pd_launch_tridiag_bdf_solve(pd_plan p, void *spec, const double *x0, const double *x1,
+                                      int h0);
 // sum partials: out = base + sum_g partials[g]   (base may be NULL)
 pd_status pd_launch_reduce_partials(pd_plan p, const double *base,
                                     double *out);

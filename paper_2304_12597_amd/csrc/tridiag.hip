@@ -580,6 +580,18 @@ __device__ __forceinline__ int pipe_entry(int lt, int q) {
 // 16-byte staging entry then holds two rows, a chunk MR / 2 entries, rotated
 // like a complex128 chunk of MR / 2 rows; slot 0's rows hold the two real
 // parts as float.
+//
+// BDF plans (recurrence form): mode 3 is mode 0 for two weight tables at once
+// (gw and bp.g1; the second's partial rows follow the first's nblk), mode 4 is
+// mode 1 with two vectors, the right-hand side M (r - theta_a x_a - theta_b
+// x_b) with theta_h = exp(-2 pi i k h / ell) (xv = x_a, h = bp.h0; bp.x1 = x_b,
+// h = bp.h0 + 1, or null).
+struct BdfPair {
+  const double *g1 = nullptr, *x1 = nullptr;
+  const cpx<double> *tw = nullptr;
+  int h0 = 0;
+};
+
 template <int MR, int MODE, bool SCAN, bool IN32 = false>
 __device__ __forceinline__ void tridiag_pipe_body(
     int blk, int nblk, int n, int F2, int P, int spb, int nitems, const Coef<double> &cf,
@@ -587,9 +599,10 @@ __device__ __forceinline__ void tridiag_pipe_body(
     const cpx<double> *__restrict__ fac, const double *__restrict__ gw,
     const cpx<double> *__restrict__ in, const double *__restrict__ vin,
     const double *__restrict__ xv, double wscale, int rhs_has_mass,
-    cpx<double> *__restrict__ out, double *__restrict__ partials) {
+    cpx<double> *__restrict__ out, double *__restrict__ partials, const BdfPair bp = BdfPair{}) {
   using R = double;
   using Cx = cpx<double>;
+  constexpr bool OUT = MODE == 1 || MODE == 4;   // the solutions are stored
   extern __shared__ __align__(16) unsigned char smem_raw[];
   constexpr int NF = 6 * (MR - 1);
   constexpr int NFP = SCAN ? PD_SCAN_SLOTS : pipe_nfp<MR>();
@@ -614,12 +627,16 @@ __device__ __forceinline__ void tridiag_pipe_body(
   const Cx zero = {0.0, 0.0};
   const int nslots = F2 - 1;
 
-  double acc[(MODE == 1) ? 1 : MR];
-  R mx[(MODE == 1) ? MR : 1];
+  double acc[OUT ? 1 : MR], acc1[MODE == 3 ? MR : 1];
+  R mx[OUT ? MR : 1], mx1[MODE == 4 ? MR : 1];
   R dv[(MODE == 2) ? MR : 1];
-  if constexpr (MODE != 1) {
+  if constexpr (!OUT) {
 #pragma unroll
     for (int q = 0; q < MR; ++q) acc[q] = 0.0;
+  }
+  if constexpr (MODE == 3) {
+#pragma unroll
+    for (int q = 0; q < MR; ++q) acc1[q] = 0.0;
   }
   if constexpr (MODE == 2) {
     // M v is the same for all frequencies: form it once, in registers
@@ -729,23 +746,36 @@ __device__ __forceinline__ void tridiag_pipe_body(
     const int k = active ? slot : nslots - 1;
     const int kB = DUAL ? F2 - 1 : k;
     const R lr = lam[2 * k], li = lam[2 * k + 1], lrB = lam[2 * kB];
-    double gr = 0.0, gi = 0.0, grB = 0.0;
-    if constexpr (MODE != 1) {
-      gr = gw[2 * k];
-      gi = gw[2 * k + 1];
-      grB = gw[2 * kB];
+    double gr = 0.0, gi = 0.0, grB = 0.0, gr1 = 0.0, gi1 = 0.0, grB1 = 0.0;
+    auto weight = [&](const double *w, double &wr, double &wi, double &wB) {
+      wr = w[2 * k];
+      wi = w[2 * k + 1];
+      wB = w[2 * kB];
       if constexpr (SCAN) {
         // the recurrence form returns kappa_k y_k: fold 1/kappa_k into the
         // weights
         const Cx ik = lfac[4];
         if (DUAL) {
-          gr *= ik.re;
-          grB *= ik.im;
+          wr *= ik.re;
+          wB *= ik.im;
         } else {
-          const double t = gr * ik.re - gi * ik.im;
-          gi = gr * ik.im + gi * ik.re;
-          gr = t;
+          const double t = wr * ik.re - wi * ik.im;
+          wi = wr * ik.im + wi * ik.re;
+          wr = t;
         }
+      }
+    };
+    if constexpr (!OUT) weight(gw, gr, gi, grB);
+    if constexpr (MODE == 3) weight(bp.g1, gr1, gi1, grB1);
+    Cx ta = {1.0, 0.0}, tb = {1.0, 0.0};   // theta_a, theta_b (slot 0: k = 0 and ell/2)
+    if constexpr (MODE == 4) {
+      const int ell = 2 * (F2 - 1);
+      if (DUAL) {
+        ta.im = (bp.h0 & 1) ? -1.0 : 1.0;
+        tb.im = -ta.im;
+      } else {
+        ta = bp.tw[(k * bp.h0) & (ell - 1)];
+        tb = bp.tw[(k * (bp.h0 + 1)) & (ell - 1)];
       }
     }
     // sub- and super-diagonals: complex, or (k = 0, k = ell/2) componentwise
@@ -789,6 +819,9 @@ __device__ __forceinline__ void tridiag_pipe_body(
         if constexpr (MODE == 1) {
           v.re += mx[q];
           if (DUAL) v.im += mx[q];
+        } else if constexpr (MODE == 4) {
+          v.re += ta.re * mx[q] + tb.re * mx1[q];
+          v.im += ta.im * mx[q] + tb.im * mx1[q];
         }
         rl = r0;
         d[q] = v;
@@ -800,14 +833,14 @@ __device__ __forceinline__ void tridiag_pipe_body(
     // LDS-only barriers: the next item's prefetch keeps streaming in through
     // the reduction (xch does not alias the staging area)
     if constexpr (SCAN)
-      scan_solve<R, MR, OPS, true, MODE == 1>(d, len, lt, P, lfac, reinterpret_cast<Cx *>(xch),
+      scan_solve<R, MR, OPS, true, OUT>(d, len, lt, P, lfac, reinterpret_cast<Cx *>(xch),
                                                pre);
     else if (!DUAL && MR <= 8 && __all(len == MR))
       partition_solve<R, MR, OPS, true>(d, MR, lt, P, lfac, xch, ca, cc);
     else
       partition_solve<R, MR, OPS, true>(d, len, lt, P, lfac, xch, ca, cc);
 
-    if constexpr (MODE == 1) {
+    if constexpr (OUT) {
       if (active) {
         {
           // 4x4 transpose inside each lane quad (for every group of 4 rows
@@ -859,6 +892,11 @@ __device__ __forceinline__ void tridiag_pipe_body(
 #pragma unroll
         for (int q = 0; q < MR; ++q)
           acc[q] += DUAL ? gr * d[q].re + grB * d[q].im : gr * d[q].re - gi * d[q].im;
+        if constexpr (MODE == 3) {
+#pragma unroll
+          for (int q = 0; q < MR; ++q)
+            acc1[q] += DUAL ? gr1 * d[q].re + grB1 * d[q].im : gr1 * d[q].re - gi1 * d[q].im;
+        }
       }
     }
   };
@@ -868,9 +906,10 @@ __device__ __forceinline__ void tridiag_pipe_body(
     issue(0, 1);
   else if (blk < nitems)
     issue(item * spb + g, 0);
-  if constexpr (MODE == 1) {
+  if constexpr (OUT) {
     // -w M x, the same for every frequency, while the first item streams in
     minus_w_mx_direct<R, MR>(mx, coef64, xv, wscale, n, s0);
+    if constexpr (MODE == 4) minus_w_mx_direct<R, MR>(mx1, coef64, bp.x1, wscale, n, s0);
   }
   if (PAIR_FIRST && blk == 0) {
     // slot 0 first (its right-hand side staged, its factors into buffer 1);
@@ -906,7 +945,7 @@ __device__ __forceinline__ void tridiag_pipe_body(
       work(CplxOps<R>{}, slot, lfac, sync, pre);
   }
 
-  if constexpr (MODE != 1) {
+  if constexpr (!OUT) {
     __syncthreads();
     // padded (pad16) so that the per-thread writes of 16 consecutive rows
     // spread over the banks; spb * gstride doubles fit in the complex128
@@ -921,6 +960,17 @@ __device__ __forceinline__ void tridiag_pipe_body(
       double s = 0.0;
       for (int gg = 0; gg < spb; ++gg) s += base[(size_t)gg * gstride + pad16(i)];
       partials[(size_t)blk * n + i] = s;
+    }
+    if constexpr (MODE == 3) {
+      __syncthreads();
+#pragma unroll
+      for (int q = 0; q < MR; ++q) sd[pad16(s0 + q)] = acc1[q];
+      __syncthreads();
+      for (int i = tid; i < n; i += blockDim.x) {
+        double s = 0.0;
+        for (int gg = 0; gg < spb; ++gg) s += base[(size_t)gg * gstride + pad16(i)];
+        partials[(size_t)(nblk + blk) * n + i] = s;
+      }
     }
   }
 }
@@ -943,6 +993,19 @@ tridiag_pipe_kernel(int n, int F2, int P, int spb, int nitems, Coef<double> cf,
   if (skip && *skip != 0.0) return;
   tridiag_pipe_body<MR, MODE, SCAN, IN32>(blockIdx.x, gridDim.x, n, F2, P, spb, nitems, cf, coef64, lam, fac,
                               gw, in, vin, xv, wscale, rhs_has_mass, out, partials);
+}
+
+// BDF plans: modes 3 and 4 of the recurrence form.
+template <int MR, int MODE>
+__global__ void __launch_bounds__(512)
+tridiag_bdf_kernel(int n, int F2, int P, int spb, int nitems, Coef<double> cf,
+                   const double *__restrict__ coef64, const double *__restrict__ lam,
+                   const cpx<double> *__restrict__ fac, const double *__restrict__ gw,
+                   const cpx<double> *__restrict__ in, const double *__restrict__ xv,
+                   cpx<double> *__restrict__ out, double *__restrict__ partials,
+                   const BdfPair bp) {
+  tridiag_pipe_body<MR, MODE, true>(blockIdx.x, gridDim.x, n, F2, P, spb, nitems, cf, coef64, lam,
+                                    fac, gw, in, nullptr, xv, 1.0, 0, out, partials, bp);
 }
 
 // Uniform-coefficient fast path (constant diagonals: uniform grids).  The
@@ -1268,6 +1331,68 @@ void pd_uniform_factors(const pd_plan p, int MR, std::vector<double> &fac) {
   }
 }
 
+// out0, out1 [n] = the sums over all frequencies of Re(g_h P^{-1} M in), h = 0,
+// 1, for weight tables g0 and g1 [F2] (null: out0 alone is wanted); partials:
+// 2 tri_G rows of n.
+pd_status pd_launch_tridiag_bdf_sums(pd_plan p, const void *in, const double *g0, const double *g1,
+                                     double *out0, double *out1, double *partials) {
+  const TriConfig &T = p->tri;
+  const int nitems = pd_tri_nitems(T, p->F2), G = nitems < p->tri_G ? nitems : p->tri_G;
+  if (!pd_use_scan(p) || (G + RS - 1) / RS > RF_MAX_SLICES) {
+    pd_set_error("BDF sums: unsupported configuration");
+    return PD_ENOTSUP;
+  }
+  Coef<double> cf{};
+  const double *u = p->uni;
+  cf.ml = u[0]; cf.md = u[1]; cf.mu = u[2]; cf.kl = u[3]; cf.kd = u[4]; cf.ku = u[5];
+  BdfPair bp;
+  bp.g1 = g1 ? g1 : g0;
+#define PD_TB3(MR)                                                                               \
+  hipLaunchKernelGGL((tridiag_bdf_kernel<MR, 3>), dim3(G), dim3(T.block), pd_tri_lds(p), p->stream, \
+                     p->n, p->F2, T.P, T.spb, nitems, cf, p->coef64, p->lam64,                  \
+                     reinterpret_cast<const cpx<double> *>(p->fac64), g0,                       \
+                     static_cast<const cpx<double> *>(in), nullptr, nullptr, partials, bp)
+  if (T.MR == 8) PD_TB3(8);
+  else PD_TB3(16);
+#undef PD_TB3
+  for (int h = 0; h < (g1 ? 2 : 1); ++h)
+    hipLaunchKernelGGL(reduce_fused_kernel, dim3((p->n + RF_COLS - 1) / RF_COLS), dim3(1024), 0,
+                       p->stream, p->n, G, partials + (size_t)h * G * p->n, nullptr,
+                       h ? out1 : out0, nullptr);
+  PD_HIP_CHECK(hipGetLastError());
+  return PD_OK;
+}
+
+// spec = P^{-1} M (spec - theta^(h0) x0 - theta^(h0 + 1) x1) in place (x1 may be
+// null), theta_k^(h) = exp(-2 pi i k h / ell).
+pd_status pd_launch_tridiag_bdf_solve(pd_plan p, void *spec, const double *x0, const double *x1,
+                                      int h0) {
+  const TriConfig &T = p->tri;
+  const int nitems = pd_tri_nitems(T, p->F2), G = nitems < p->tri_G ? nitems : p->tri_G;
+  if (!pd_use_scan(p)) {
+    pd_set_error("BDF solves: unsupported configuration");
+    return PD_ENOTSUP;
+  }
+  Coef<double> cf{};
+  const double *u = p->uni;
+  cf.ml = u[0]; cf.md = u[1]; cf.mu = u[2]; cf.kl = u[3]; cf.kd = u[4]; cf.ku = u[5];
+  BdfPair bp;
+  bp.x1 = x1;
+  bp.tw = reinterpret_cast<const cpx<double> *>(p->tw64);
+  bp.h0 = h0;
+#define PD_TB4(MR)                                                                               \
+  hipLaunchKernelGGL((tridiag_bdf_kernel<MR, 4>), dim3(G), dim3(T.block), pd_tri_lds(p), p->stream, \
+                     p->n, p->F2, T.P, T.spb, nitems, cf, p->coef64, p->lam64,                  \
+                     reinterpret_cast<const cpx<double> *>(p->fac64), nullptr,                  \
+                     static_cast<const cpx<double> *>(spec), x0, static_cast<cpx<double> *>(spec), \
+                     nullptr, bp)
+  if (T.MR == 8) PD_TB4(8);
+  else PD_TB4(16);
+#undef PD_TB4
+  PD_HIP_CHECK(hipGetLastError());
+  return PD_OK;
+}
+
 pd_status pd_launch_reduce_partials(pd_plan p, const double *base, double *out) {
   const int n = p->nbar;
   const int nitems = pd_tri_nitems(p->tri, p->F2);
@@ -1324,6 +1449,8 @@ void set_attr_mr(int v) {
       pd_set_max_lds(reinterpret_cast<const void *>(&tridiag_pipe_kernel<MR, 0, true>), v);
       pd_set_max_lds(reinterpret_cast<const void *>(&tridiag_pipe_kernel<MR, 1, true>), v);
       pd_set_max_lds(reinterpret_cast<const void *>(&tridiag_pipe_kernel<MR, 2, true>), v);
+      pd_set_max_lds(reinterpret_cast<const void *>(&tridiag_bdf_kernel<MR, 3>), v);
+      pd_set_max_lds(reinterpret_cast<const void *>(&tridiag_bdf_kernel<MR, 4>), v);
       pd_set_max_lds(reinterpret_cast<const void *>(&tridiag_pipe_kernel<MR, 0, true, true>), v);
       pd_set_max_lds(reinterpret_cast<const void *>(&tridiag_pipe_kernel<MR, 1, true, true>), v);
     }
