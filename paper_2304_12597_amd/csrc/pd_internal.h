@@ -328,6 +328,8 @@ struct pd_plan_s {
   // capacitance solve in the sine eigenbasis (sinecap.hip)
   int sc_on = 0, sc_r = 0, sc_ns = 0, sc_nblk = 0;
   double *sc_tab = nullptr;
+  double *lu_tab = nullptr;    // general matrices: rows in thread order, pivots (tridiag_lu.hip)
+  int lu_on = 0;
 };
 constexpr int PD_BDF_GCH = 16;   // frequency chunks of the BDF capacitance product
 
@@ -395,6 +397,11 @@ pd_status pd_launch_fft_inverse(pd_plan p, const void *in, double *U,
 // Y = P^{-1} M (Hhat - w x), 2: J-product partials of P^{-1} M v.
 pd_status pd_launch_tridiag(pd_plan p, int mode, const void *in,
                             const double *xv, void *out);
+// the same for general matrices by two recurrences (tridiag_lu.hip)
+size_t pd_lu_doubles(const pd_plan p);
+pd_status pd_lu_setup(pd_plan p, std::vector<double> &bad);
+pd_status pd_launch_lu(pd_plan p, int mode, const void *in, const double *xv, void *out);
+void pd_lu_set_attributes(size_t max_lds);
 // 2D: orthonormal DST-I along x of every row. mode 0: h from (u0, F);
 // 1: float64 residual of (u0, F, U) with norms in red; 2: in.
 pd_status pd_launch_dst_x(pd_plan p, int mode, const double *u0, const double *F,

@@ -132,7 +132,7 @@ void free_plan(pd_plan p) {
                   p->tw32, p->dal, p->fac64, p->fac32, p->twd, p->wreal, p->spec, p->spec2, p->partials, p->rstage, p->bvec, p->xvec, p->wvec, p->V,
                   p->gm, p->red, p->sine_q, p->sine_wN, p->sine_twH, p->sine_m, p->sine_k,
                   p->fom, p->fom_h, p->wz, p->bdf_g, p->bdf_h, p->bdf_t, p->cp_tab,
-                  p->sc_tab};
+                  p->sc_tab, p->lu_tab};
   for (void *q : ptrs)
     if (q) (void)hipFree(q);
   if (p->host_pin) (void)hipHostFree(p->host_pin);
@@ -153,6 +153,7 @@ struct Layout {
   // the capacitance system's tables and workspace (doubles): the chunked
   // product's or the sine basis's, whichever the plan's matrices allow
   size_t cp = 0;
+  size_t lu = 0;   // general matrices by recurrences (doubles)
   size_t spec_bytes = 0, partials = 0, rstage = 0, vec = 0, V = 0, gm = 0, red = 0;
   size_t spec2_bytes = 0;   // PD_MIXED: the last correction's spectrum (stall rollback)
   size_t fac_bytes = 8;     // per entry of the shifted solves' constants
@@ -160,7 +161,7 @@ struct Layout {
   size_t total_bytes() const {
     return coef * 12 + lam * 12 + 2 * lam * 8 + tw * 12 + dal * 8 + fac * fac_bytes + inner + twd * 8 +
            wreal * 8 + wz * 8 + bdfg * 8 + bdfh * 8 + bdft * 8 + spec_bytes + spec2_bytes + partials * 8 + rstage * 8 + 3 * vec * 8 + V * 8 + gm * 8 +
-           red * 8 + sine * 8 + fom * 8 + fom_h_bytes + cp * 8;
+           red * 8 + sine * 8 + fom * 8 + fom_h_bytes + cp * 8 + lu * 8;
   }
 };
 
@@ -536,6 +537,7 @@ static pd_status create_plan(pd_plan *out, int n, int ell, double tau, const pd_
     pd_sine_set_attributes(g_max_lds);
     pd_cp_set_attributes(g_max_lds);
     pd_sc_set_attributes(g_max_lds);
+    pd_lu_set_attributes(g_max_lds);
     g_attr_device = p->device;
   }
   const size_t max_lds = g_max_lds;
@@ -645,6 +647,18 @@ static pd_status create_plan(pd_plan *out, int n, int ell, double tau, const pd_
     if (lst != PD_OK) {
       free_plan(p);
       return lst;
+    }
+    // General matrices: paradiag_plan_bytes is asked before the matrices are
+    // known and counts a uniform plan's tables, so the recurrences' tables are
+    // made only where they take no more than those (for many frequencies they
+    // would; those plans keep the partition form).
+    L.lu = pd_lu_doubles(p);
+    if (L.lu) {
+      pd_plan_s u = *p;
+      u.uniform = true;
+      Layout Lu;
+      if (compute_layout(&u, cus, max_lds, Lu) != PD_OK || L.total_bytes() > Lu.total_bytes())
+        L.lu = 0;
     }
   }
   if (p->krylov == PD_KRYLOV_FOM && !p->sine && !pd_fom_supported(p)) {
@@ -764,7 +778,7 @@ static pd_status create_plan(pd_plan *out, int n, int ell, double tau, const pd_
       }
     }
   }
-  std::vector<double> cptab, sctab;
+  std::vector<double> cptab, sctab, lubad;
   if (pd_sc_build(p, fac, bg_ct, sctab)) {
     p->sc_on = 1;
     p->cp_on = 0;
@@ -844,6 +858,7 @@ static pd_status create_plan(pd_plan *out, int n, int ell, double tau, const pd_
     PD_TRY(dev_alloc(&p->red, L.red));
   }
   if (p->cp_on) PD_TRY(dev_alloc(&p->cp_tab, p->cpl.total));
+  if (L.lu) PD_TRY(dev_alloc(&p->lu_tab, L.lu));
   if (p->sc_on)
     PD_TRY(dev_alloc(&p->sc_tab, p->dims == 2 ? pd_sc2_size(p) : sctab.size()));
   if (p->krylov == PD_KRYLOV_FOM) {
@@ -887,6 +902,7 @@ static pd_status create_plan(pd_plan *out, int n, int ell, double tau, const pd_
   else
     PD_TRY(upload(p->fac32, fac32, p->stream));
   if (p->cp_on) PD_TRY(upload(p->cp_tab, cptab, p->stream));
+  if (L.lu) PD_TRY(pd_lu_setup(p, lubad));
   if (p->sc_on) PD_TRY(upload(p->sc_tab, sctab, p->stream));
   if (p->sc_on && p->dims == 2) PD_TRY(pd_sc2_finish(p));
   if (p->bdf_s > 1) PD_TRY(upload(p->bdf_g, bg_gt, p->stream));
@@ -921,6 +937,7 @@ static pd_status create_plan(pd_plan *out, int n, int ell, double tau, const pd_
     free_plan(p);
     return PD_EHIP;
   }
+  p->lu_on = L.lu && std::find(lubad.begin(), lubad.end(), 1.0) == lubad.end();
   if (p->autotune) {
     const pd_status ts = autotune(p, cus, max_lds);
     if (ts != PD_OK) {

@@ -1277,6 +1277,7 @@ pd_status dispatch(pd_plan p, int mode, const void *in, const double *xv, void *
 
 pd_status pd_launch_tridiag(pd_plan p, int mode, const void *in, const double *xv, void *out) {
   if (p->dims == 2) return pd_launch_line2d(p, mode, in, xv, out);
+  if (p->lu_on) return pd_launch_lu(p, mode, in, xv, out);
   return p->uniform ? dispatch<true>(p, mode, in, xv, out)
                     : dispatch<false>(p, mode, in, xv, out);
 }
