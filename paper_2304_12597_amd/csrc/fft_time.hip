@@ -672,6 +672,9 @@ static Stencil2 pd_stencil2(pd_plan p) {
 
 pd_status pd_launch_dst_x(pd_plan p, int mode, const double *u0, const double *F,
                           const double *U, const double *in, double *out, int accumulate) {
+  if (p->twd_dense && mode != 1)
+    return pd_launch_dst_dense(p->n, p->ell * p->n, mode, p->tau, u0, p->nbar, F, in,
+                               p->twd + p->twd_dense, out, accumulate, p->stream);
   DstLaunch L = dst_config(p, p->ell);
   auto tw = reinterpret_cast<const cpx<double> *>(p->twd);
   if (p->dst_L) {
@@ -706,6 +709,9 @@ pd_status pd_launch_dst_x(pd_plan p, int mode, const double *u0, const double *F
 // added to it): the mode-2 transform on a [trows][nbar] array.
 pd_status pd_launch_dst_x_rows(pd_plan p, const double *in, double *out, int trows,
                                int accumulate) {
+  if (p->twd_dense)
+    return pd_launch_dst_dense(p->n, trows * p->n, 2, p->tau, nullptr, 0, nullptr, in,
+                               p->twd + p->twd_dense, out, accumulate, p->stream);
   DstLaunch L = dst_config(p, trows);
   auto tw = reinterpret_cast<const cpx<double> *>(p->twd);
   if (p->dst_L) {
@@ -741,6 +747,9 @@ pd_status pd_launch_dst_x_rows(pd_plan p, const double *in, double *out, int tro
 pd_status pd_launch_dst_rows1d(pd_plan p, int mode, const double *u0, const double *F,
                                const double *in, double *out) {
   if (!p->dst_L) return PD_EINVAL;
+  if (p->twd_dense)
+    return pd_launch_dst_dense(p->n, p->ell, mode == 0 ? 0 : 2, p->tau, u0, p->n, F, in,
+                               p->twd + p->twd_dense, out, 0, p->stream);
   const int N = p->dst_L, C = p->dst_C;
   const int stride = pd_fft_col_stride(N);
   const size_t lds = ((size_t)C * stride + pd_tw_entries(N)) * 16;

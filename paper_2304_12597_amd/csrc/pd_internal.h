@@ -303,6 +303,7 @@ struct pd_plan_s {
   int dst_L = 0;               // 2D: 0 if n + 1 is a power of two, else the
                                // chirp-z DST's FFT length L >= 2n - 1
   size_t twd_chirp = 0, twd_bhat = 0, twd_cos = 0;   // offsets (doubles) in twd
+  size_t twd_dense = 0;        // the DST as a product (dst_dense.hip); 0: FFT forms
   double *wreal = nullptr;     // 2D: [ell][nbar] float64 work array (DST-x domain);
                                // BDF: the time-domain input of the transforms
   // BDF of order s (Section 5); s = 1 is backward Euler and uses none of these
@@ -407,6 +408,12 @@ void pd_lu_set_attributes(size_t max_lds);
 pd_status pd_launch_dst_x(pd_plan p, int mode, const double *u0, const double *F,
                           const double *U, const double *in, double *out, int accumulate);
 int pd_choose_dst_C(int n);
+size_t pd_dst_dense_doubles(int n);
+pd_status pd_dst_dense_build(int n, double *tab, hipStream_t stream);
+pd_status pd_launch_dst_dense(int n, int rows, int mode, double tau, const double *u0, long nu0,
+                              const double *F, const double *in, const double *tab, double *out,
+                              int accumulate, hipStream_t stream);
+void pd_dst_dense_set_attributes(size_t max_lds);
 int pd_dst_chirp_length(int n);
 pd_status pd_launch_dst_rows1d(pd_plan p, int mode, const double *u0, const double *F,
                                const double *in, double *out);

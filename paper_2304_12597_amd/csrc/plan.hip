@@ -177,6 +177,12 @@ bool pd_mixed64_ok(const pd_plan p, const pd_plan q64) {
 pd_status compute_layout(pd_plan p, int cus, size_t max_lds, Layout &L) {
   const int n = p->n, ell = p->ell, F2 = p->F2;
   const size_t cb = (p->prec == PD_FP64) ? 16 : 8;
+  // the DST along x as a product: its tables after the FFT forms'
+  auto dense = [&] {
+    const size_t d = pd_dst_dense_doubles(n);
+    p->twd_dense = d ? (L.twd + 1) / 2 * 2 : 0;   // 16-byte aligned
+    if (d) L.twd = p->twd_dense + d;
+  };
   p->fft_C = pd_choose_fft_C(ell, p->nbar, p->prec, max_lds);
   p->fft_stride = pd_fft_col_stride(ell);
   if (((size_t)p->fft_C * p->fft_stride + pd_tw_entries(ell)) * cb > max_lds) {
@@ -213,6 +219,7 @@ pd_status compute_layout(pd_plan p, int cus, size_t max_lds, Layout &L) {
     p->twd_bhat = p->twd_chirp + (p->dst_L ? 2 * (size_t)(n + 1) : 0);
     p->twd_cos = p->twd_bhat + (p->dst_L ? 2 * (size_t)p->dst_L : 0);
     L.twd = p->twd_cos + (size_t)n;
+    dense();
     L.wreal = (size_t)ell * p->nbar;
     if ((size_t)p->l2d.nkc * p->nbar > L.partials) L.partials = (size_t)p->l2d.nkc * p->nbar;
     L.rstage = std::max(L.rstage, (size_t)((p->l2d.nkc + 15) / 16) * p->nbar);
@@ -249,6 +256,7 @@ pd_status compute_layout(pd_plan p, int cus, size_t max_lds, Layout &L) {
       p->twd_bhat = p->twd_chirp + 2 * (size_t)(n + 1);
       p->twd_cos = p->twd_bhat + 2 * (size_t)p->dst_L;
       L.twd = p->twd_cos;
+      dense();
     }
   }
   if (p->krylov == PD_KRYLOV_FOM) {
@@ -537,6 +545,7 @@ static pd_status create_plan(pd_plan *out, int n, int ell, double tau, const pd_
     pd_sine_set_attributes(g_max_lds);
     pd_cp_set_attributes(g_max_lds);
     pd_sc_set_attributes(g_max_lds);
+    pd_dst_dense_set_attributes(g_max_lds);
     pd_lu_set_attributes(g_max_lds);
     g_attr_device = p->device;
   }
@@ -690,7 +699,7 @@ static pd_status create_plan(pd_plan *out, int n, int ell, double tau, const pd_
     pd_uniform_factors(p, p->tri.MR, fac);
   }
   if (p->dims == 1 && p->prec != PD_FP64) fac32.assign(fac.begin(), fac.end());
-  std::vector<double> sq, swN, stwH, sm, sk;
+  std::vector<double> sq, swN, stwH, sm, sk;   // sine-basis plans
   if (p->sine && p->dst_L) {
     twd.assign(p->twd_cos, 0.0);
     for (int m = 0; m < p->dst_L; ++m) {
@@ -700,6 +709,14 @@ static pd_status create_plan(pd_plan *out, int n, int ell, double tau, const pd_
       twd[2 * m + 1] = -s;
     }
     chirp_tables(n, p->dst_L, &twd[p->twd_chirp], &twd[p->twd_bhat]);
+  }
+  if (p->twd_dense) {
+    const int N2 = 2 * (n + 1);
+    twd.resize(p->twd_dense + N2);
+    for (int m = 0; m < N2; ++m) {
+      double c;
+      cis(m, N2, c, twd[p->twd_dense + m]);   // sin(pi m / (n+1))
+    }
   }
   if (p->sine) {
     const int N = n + 1, H = N / 2;
@@ -832,7 +849,7 @@ static pd_status create_plan(pd_plan *out, int n, int ell, double tau, const pd_
     PD_TRY(dev_alloc(&p->tw64, tw.size()));
     PD_TRY(dev_alloc(&p->tw32, tw32.size()));
     PD_TRY(dev_alloc(&p->dal, dal.size()));
-    PD_TRY(dev_alloc(&p->twd, twd.size()));
+    PD_TRY(dev_alloc(&p->twd, std::max(twd.size(), L.twd)));
     if (p->dims == 2 || p->bdf_s > 1) PD_TRY(dev_alloc(&p->wreal, L.wreal));
     if (p->bdf_s > 1) {
       PD_TRY(dev_alloc(&p->wz, L.wz));
@@ -896,6 +913,7 @@ static pd_status create_plan(pd_plan *out, int n, int ell, double tau, const pd_
     PD_TRY(upload(p->tw32, tw32, p->stream));
     PD_TRY(upload(p->dal, dal, p->stream));
     PD_TRY(upload(p->twd, twd, p->stream));
+    if (p->twd_dense) PD_TRY(pd_dst_dense_build(n, p->twd + p->twd_dense, p->stream));
   }
   if (p->prec == PD_FP64)
     PD_TRY(upload(p->fac64, fac, p->stream));
