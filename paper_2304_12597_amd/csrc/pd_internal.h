@@ -414,6 +414,12 @@ pd_status pd_launch_dst_dense(int n, int rows, int mode, double tau, const doubl
                               const double *F, const double *in, const double *tab, double *out,
                               int accumulate, hipStream_t stream);
 void pd_dst_dense_set_attributes(size_t max_lds);
+// ... of rows of 2^m - 1 by the odd extension's own FFT (dst_odd.hip)
+bool pd_dst_odd_ok(int n);
+pd_status pd_launch_dst_odd(int n, int rows, int mode, double tau, const double *u0, long nu0,
+                            const double *F, const double *in, const double *tw, double *out,
+                            int accumulate, hipStream_t stream);
+void pd_dst_odd_set_attributes(size_t max_lds);
 int pd_dst_chirp_length(int n);
 pd_status pd_launch_dst_rows1d(pd_plan p, int mode, const double *u0, const double *F,
                                const double *in, double *out);

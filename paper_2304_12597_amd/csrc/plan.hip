@@ -546,6 +546,7 @@ static pd_status create_plan(pd_plan *out, int n, int ell, double tau, const pd_
     pd_cp_set_attributes(g_max_lds);
     pd_sc_set_attributes(g_max_lds);
     pd_dst_dense_set_attributes(g_max_lds);
+    pd_dst_odd_set_attributes(g_max_lds);
     pd_lu_set_attributes(g_max_lds);
     g_attr_device = p->device;
   }
