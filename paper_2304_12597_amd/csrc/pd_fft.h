@@ -146,10 +146,11 @@ __device__ __forceinline__ void stockham_stage(cpx<R> *lds, int lgN, int lgNs, i
   __syncthreads();
 }
 
+// lgNs: stages done by the caller (their sub-transforms have length 2^lgNs).
 template <typename R, bool INV>
-__device__ __forceinline__ void fft_lds(cpx<R> *lds, int N, int C, int stride, const cpx<R> *twl) {
+__device__ __forceinline__ void fft_lds(cpx<R> *lds, int N, int C, int stride, const cpx<R> *twl,
+                                        int lgNs = 0) {
   const int lgN = __builtin_ctz(N);
-  int lgNs = 0;
   while (lgNs + 3 <= lgN) {
     stockham_stage<R, INV, 8>(lds, lgN, lgNs, C, stride, twl);
     lgNs += 3;
@@ -159,6 +160,16 @@ __device__ __forceinline__ void fft_lds(cpx<R> *lds, int N, int C, int stride, c
   } else if (lgNs + 1 == lgN) {
     stockham_stage<R, INV, 2>(lds, lgN, lgNs, C, stride, twl);
   }
+}
+
+// Blocks are dispatched round-robin over the 8 XCDs, each with its own L2.
+// Neighbouring tiles read the two halves of the same 128-byte lines, so map
+// consecutive blocks of one XCD to consecutive tiles.
+__device__ __forceinline__ int xcd_tile(int b, int nb) {
+  constexpr int X = 8;
+  const int per = nb / X;            // tiles in the evenly divisible part
+  if (b >= per * X) return b;        // remainder keeps its position
+  return (b % X) * per + b / X;
 }
 
 }  // namespace pdfft

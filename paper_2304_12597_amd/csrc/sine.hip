@@ -27,9 +27,17 @@ namespace {
 
 using namespace pdfft;
 
-// C rows per block, H/8 threads per row, each owning 8 consecutive m.
-// MODE 0: rows h_t = tau f_t (+ u0 at t = 0); MODE 1: rows of `in`.
-// out may alias in (every row is read completely before it is written).
+// C rows per block, H/8 threads per row.  MODE 0: rows h_t = tau f_t (+ u0 at
+// t = 0); MODE 1: rows of `in`.  out may alias in (every row is read completely
+// before it is written).  A thread's eight packed inputs c_m = y_{2m} + i y_{2m+1},
+// m = lt + u H/8, are those of a first radix-8 butterfly, so they go from the
+// row to that stage in registers; after the last stage it splits four pairs
+// (m, H - m), which share their two entries and the twiddle.  Results are
+// staged in row order, one double in 17 left out so that a thread's 16 in a
+// row spread over the banks.
+// n = 8191, 2048 rows (268 MB): 153 us (MODE 0) and 128 us (MODE 1) with the raw
+// inputs staged in LDS, strided loads of wN and results on one bank; 92 and
+// 73 us now.  Bound by the LDS passes of the stages (56 us for the bytes).
 // LDS: [C * stride cpx columns][twiddles of length H][T double scan sums]
 // (at most 128 VGPRs: two 512-thread blocks per CU)
 template <int MODE>
@@ -50,62 +58,75 @@ dst_rows_kernel(int n, int C, int stride, double tau, const double *__restrict__
   const int G = 1 << lgG;
   const int c = tid >> lgG, lt = tid & (G - 1);
   const int row = blockIdx.x * C + c;
-  const size_t base = (size_t)row * n;
-  auto xval = [&](int j) -> double {          // x_j, j = 0..N; zero at both ends
-    const int i = j - 1;
-    const int ic = i < 0 ? 0 : (i >= n ? n - 1 : i);
-    double v;
-    if constexpr (MODE == 0) {
-      v = tau * F[base + ic];
-      if (row == 0) v += u0[ic];
-    } else {
-      v = in[base + ic];
-    }
-    return (i >= 0 && i < n) ? v : 0.0;
-  };
   Cx *col = lds + c * stride;
-  // packed input c_m = y_{2m} + i y_{2m+1}, m = lt + u G: consecutive lanes
-  // read neighbouring elements; real parts, then imaginary parts (16 loads
-  // in flight per phase)
-  double *cold = reinterpret_cast<double *>(col);
-#pragma unroll
-  for (int ph = 0; ph < 2; ++ph) {
-    double xa[8], xb[8];
+  {
+    const double *p = (MODE == 0 ? F : in) + (size_t)row * n - 1;   // x_j at p[j]
+    Cx v[8];
 #pragma unroll
     for (int u = 0; u < 8; ++u) {
-      const int j = 2 * (lt + u * G) + ph;
-      xa[u] = xval(j);
-      xb[u] = xval(N - j);
+      const int j = 2 * (lt + u * G);
+      const int j0 = j ? j : 1;                // x_0 = x_N = 0
+      double a = p[j0], b = p[N - j0], a1 = p[j + 1], b1 = p[N - j - 1];
+      if constexpr (MODE == 0) {
+        a *= tau; b *= tau; a1 *= tau; b1 *= tau;
+        if (row == 0) {
+          a += u0[j0 - 1];
+          b += u0[N - j0 - 1];
+          a1 += u0[j];
+          b1 += u0[N - j - 2];
+        }
+      }
+      if (j == 0) a = b = 0.0;
+      v[u] = Cx{sinq[j] * (a + b) + 0.5 * (a - b), sinq[j + 1] * (a1 + b1) + 0.5 * (a1 - b1)};
     }
+    small_dft<double, false, 8>(v);
 #pragma unroll
-    for (int u = 0; u < 8; ++u) {
-      const int m = lt + u * G;
-      const int j = 2 * m + ph;
-      cold[2 * pd_fpad(m) + ph] = sinq[j] * (xa[u] + xb[u]) + 0.5 * (xa[u] - xb[u]);
-    }
+    for (int r = 0; r < 8; ++r) col[9 * lt + r] = v[r];   // pd_fpad(8 lt + r)
   }
   __syncthreads();
-  fft_lds<double, false>(lds, H, C, stride, twl);
-  // split the packed real transform: Y_m = E_m + exp(-2 pi i m/N) O_m
-  double Rv[8], Iv[8];
+  fft_lds<double, false>(lds, H, C, stride, twl, 3);
+  // split the packed real transform: Y_m = E_m + exp(-2 pi i m/N) O_m and
+  // Y_{H-m} = conj(E_m - exp(-2 pi i m/N) O_m); beside m = 0 the pair of H/2
+  double R[2][4], I[2][4];
 #pragma unroll
-  for (int u = 0; u < 8; ++u) {
-    const int m = 8 * lt + u;
+  for (int u = 0; u < 4; ++u) {
+    const int m = lt + u * G;
     const Cx a = col[pd_fpad(m)];
     const Cx b = col[pd_fpad((H - m) & (H - 1))];
     const Cx E = {0.5 * (a.re + b.re), 0.5 * (a.im - b.im)};
     const Cx O = {0.5 * (a.im + b.im), 0.5 * (b.re - a.re)};
-    const Cx w = wN[m];
-    Rv[u] = E.re + (w.re * O.re - w.im * O.im);
-    Iv[u] = -(E.im + (w.re * O.im + w.im * O.re));
+    const Cx t = cmul(wN[m], O);
+    R[0][u] = E.re + t.re;
+    I[0][u] = -(E.im + t.im);
+    R[1][u] = E.re - t.re;
+    I[1][u] = E.im - t.im;
   }
-  // odd outputs: inclusive prefix sum of R'_0 = R_0/2, R'_m = R_m
-  if (lt == 0) Rv[0] *= 0.5;
+  if (lt == 0) {
+    const Cx a = col[pd_fpad(H / 2)];
+    R[0][0] *= 0.5;                            // R'_0 = R_0 / 2
+    R[1][0] = a.re;
+    I[1][0] = a.im;
+  }
+  __syncthreads();
+  // S_{2m} (m >= 1) at output index 2m - 1; R'_m at 2m, to be summed
+  double *orow = reinterpret_cast<double *>(col);
+  auto at = [](int i) { return i + (i >> 4); };
+  const double scale = sqrt(2.0 / (double)N);
+#pragma unroll
+  for (int u = 0; u < 4; ++u) {
+    const int m = lt + u * G, mp = m ? H - m : H / 2;
+    if (m) orow[at(2 * m - 1)] = scale * I[0][u];
+    orow[at(2 * m)] = R[0][u];
+    orow[at(2 * mp - 1)] = scale * I[1][u];
+    orow[at(2 * mp)] = R[1][u];
+  }
+  __syncthreads();
+  // odd outputs: inclusive prefix sum of R'_m, m = 8 lt .. 8 lt + 7 here
   double loc[8];
   double s = 0.0;
 #pragma unroll
   for (int u = 0; u < 8; ++u) {
-    s += Rv[u];
+    s += orow[17 * lt + 2 * u];
     loc[u] = s;
   }
   // prefix over the row's threads: within the wave by shuffles (segments of
@@ -123,23 +144,23 @@ dst_rows_kernel(int n, int C, int stride, double tau, const double *__restrict__
     for (int q = w0; q < (tid >> 6); ++q) incl += scan[q];
   }
   const double excl = incl - s;
-  // results in row order through LDS (every thread has finished its split
-  // reads), then contiguous stores
-  double *orow = reinterpret_cast<double *>(col);
-  const double scale = sqrt(2.0 / (double)N);
 #pragma unroll
-  for (int u = 0; u < 8; ++u) {
-    const int m = 8 * lt + u;
-    // S_{2m} (m >= 1) at output index 2m - 1, S_{2m+1} at 2m
-    if (m >= 1) orow[2 * m - 1] = scale * Iv[u];
-    orow[2 * m] = scale * (excl + loc[u]);
-  }
+  for (int u = 0; u < 8; ++u) orow[17 * lt + 2 * u] = scale * (excl + loc[u]);
   __syncthreads();
-  const int T = blockDim.x;
-  for (int idx = tid; idx < C * n; idx += T) {
-    const int rc = idx / n, i = idx - rc * n;
-    const double *src = reinterpret_cast<const double *>(lds + rc * stride);
-    out[(size_t)(blockIdx.x * C + rc) * n + i] = src[i];
+  const int T = blockDim.x, lgN = __builtin_ctz(N), total = C << lgN;
+  constexpr int U = 8;
+  for (int base = tid; base < total; base += U * T) {
+    double w[U];
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+      const int idx = base + u * T < total ? base + u * T : 0;
+      w[u] = reinterpret_cast<const double *>(lds + (idx >> lgN) * stride)[at(idx & n)];
+    }
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+      const int idx = base + u * T, i = idx & n;
+      if (idx < total && i < n) out[(size_t)(blockIdx.x * C + (idx >> lgN)) * n + i] = w[u];
+    }
   }
 }
 
@@ -148,6 +169,8 @@ dst_rows_kernel(int n, int C, int stride, double tau, const double *__restrict__
 // per-mode solve with its exact capacitance correction, inverse time DFT.
 // A, B: [ell][n] float64 (the DST coefficients of h and of U).
 // LDS: [C * stride cpx][twiddles][2 * nwaves * S double sums]
+// A tile is 2C doubles of a row (32 bytes at ell = 2048): neighbouring tiles on
+// one XCD share the lines in its L2 (n = 8191, ell = 2048: 201 -> 149 us).
 __global__ void __launch_bounds__(512)
 sine_modal_kernel(int N, int n, int C, int stride, const double *__restrict__ A,
                   const double *__restrict__ dal, const cpx<double> *__restrict__ tw,
@@ -163,7 +186,7 @@ sine_modal_kernel(int N, int n, int C, int stride, const double *__restrict__ A,
   double *sb = reinterpret_cast<double *>(twl + pd_tw_entries(N));
   double *sf = sb + nw * S;
   tw_to_lds(twl, tw, N);
-  const int tile = blockIdx.x;
+  const int tile = xcd_tile(blockIdx.x, gridDim.x);
   const int i0 = tile * S;
   const int pnt = tid & (S - 1);
   const int t0 = tid >> lgS, dt = T >> lgS;
