@@ -21,8 +21,7 @@
 
 namespace {
 
-// IN32: in is complex64 [F2][nbar] (mode 1 writes complex128 elsewhere).
-template <typename R, int MR, int MODE, bool SCAN, bool IN32 = false>
+template <typename R, int MR, int MODE, bool SCAN>
 __global__ void __launch_bounds__(512, 4)
 line2d_kernel(int n, int F2, int P, int S, int mgroups, int kchunk,
               const cpx<R> *__restrict__ fac, R toff, const double *__restrict__ gw,
@@ -91,8 +90,7 @@ line2d_kernel(int n, int F2, int P, int S, int mgroups, int kchunk,
     if constexpr (MODE != 2) {
       // U loads in flight per thread (at clamped, valid addresses), then the
       // LDS stores; columns past n stage zeros
-      using In = typename std::conditional<IN32, cpx<float>, cpx<R>>::type;
-      const In *src = reinterpret_cast<const In *>(in) + (size_t)k * nbar;
+      const cpx<R> *src = in + (size_t)k * nbar;
       for (int b = tid; b < tile; b += U * (int)blockDim.x) {
         cpx<R> v[U];
 #pragma unroll
@@ -100,8 +98,8 @@ line2d_kernel(int n, int F2, int P, int S, int mgroups, int kchunk,
           const int idx = b + u * (int)blockDim.x;
           const int ic = idx < tile ? idx : tile - 1;
           const int y = ic >> lgS, mm = m0 + (ic & (S - 1));
-          const In t = src[(size_t)y * n + (mm < n ? mm : n - 1)];
-          v[u] = pd_sel(mm < n, cpx<R>{(R)t.re, (R)t.im}, zero);
+          const cpx<R> t = src[(size_t)y * n + (mm < n ? mm : n - 1)];
+          v[u] = pd_sel(mm < n, t, zero);
         }
 #pragma unroll
         for (int u = 0; u < U; ++u) {
@@ -175,28 +173,201 @@ line2d_kernel(int n, int F2, int P, int S, int mgroups, int kchunk,
   }
 }
 
-template <typename R, int MR, bool SCAN, bool IN32 = false>
+// LDS of the kernel below: entry i of a line at i + i/8 (a thread's 8 rows 9
+// apart), lines apart so that the 16 lanes of a staging access, 16 / S rows of S
+// lines, fall on different banks.
+__host__ __device__ inline int line_entry(int i) { return i + (i >> 3); }
+__host__ __device__ inline int line_stride(int n, int S) {
+  const int e = line_entry(n - 1);
+  return S < 16 ? (e + 16) / 16 * 16 + 16 / S : (e + 1) | 1;
+}
+template <int MR>
+size_t line_lds(int n, int S) {
+  return (size_t)S * (line_stride(n, S) + pd_scan_entries<MR>()) * 16;
+}
+
+// Modes 0 and 1 in the recurrence form (float64, a line within a wave).  A
+// block keeps its S columns and walks over a chunk of the frequencies; the
+// blocks that walk over the same frequencies side by side are on one XCD, where
+// they share the lines at the columns' edges.  (The next rows in registers while
+// this item's lines are solved spilled: two blocks share a CU at 128 VGPRs.)
+// Before, staged rows fell on two banks, a scan took 136 lane moves through LDS
+// per wave, and an item five barriers.  n = 511, 129 frequencies: mode 1 407 -> 235 us
+// (1.07 GB, 4.6 TB/s), mode 0 285 -> 160 us (0.54 GB); n = 256: 89 -> 53, 70 -> 41 us;
+// n = 255, complex64, 257 frequencies: 163 -> 95, 127 -> 67 us.  Bound: mode 1 by
+// the bytes, mode 0 by the solves' arithmetic and the barriers.
+template <int MR, int MODE, bool IN32>
+__global__ void __launch_bounds__(512, 4)
+line2d_scan_kernel(int n, int F2, int P, int S, int mgroups, int kchunk,
+                   const cpx<double> *__restrict__ fac, const double *__restrict__ gw,
+                   const void *in, const double *__restrict__ xv, double wscale,
+                   cpx<double> *out, double *__restrict__ partials) {
+  extern __shared__ __align__(16) unsigned char smem_raw[];
+  using Cx = cpx<double>;
+  using In = typename std::conditional<IN32, cpx<float>, Cx>::type;
+  constexpr int NF = pd_scan_entries<MR>();
+  constexpr int FU = MR == 8 ? 2 : NF;   // constants per thread: NF / P, P >= 16 with 8 rows
+  const int tid = threadIdx.x, g = tid / P, lt = tid - g * P;
+  const int stride = line_stride(n, S);
+  const size_t nbar = (size_t)n * n;
+  Cx *tile = reinterpret_cast<Cx *>(smem_raw);
+  Cx *tabs = tile + (size_t)S * stride;
+  Cx *line = tile + (size_t)g * stride;
+  const Cx *tb = tabs + g * NF;
+  const int b = xcd_tile(blockIdx.x, gridDim.x);
+  const int kc = b / mgroups, m0 = (b - kc * mgroups) * S, m = m0 + g;
+  const int kbeg = kc * kchunk, kend = kbeg + kchunk < F2 ? kbeg + kchunk : F2;
+  const int s0 = lt * MR;
+  int len = n - s0;
+  len = len < 0 ? 0 : (len > MR ? MR : len);
+  const Cx zero = {0.0, 0.0};
+  double acc[MODE == 1 ? 1 : MR];
+  double xr[MODE == 1 ? MR : 1];   // -w x on this thread's rows
+#pragma unroll
+  for (int q = 0; q < MR; ++q) {
+    if constexpr (MODE == 0) acc[q] = 0.0;
+    if constexpr (MODE == 1)
+      xr[q] = (xv && m < n && q < len) ? -wscale * xv[(size_t)(s0 + q) * n + m] : 0.0;
+  }
+  // this thread's share of a tile: rows y0 + u P of column mm, and of its
+  // constants.  Offsets are formed where they are used (32 bits, from a
+  // register the compiler cannot keep them for): two blocks share a CU
+  const int lgS = __builtin_ctz(S), cl = tid & (S - 1);
+  const bool mact = m0 + cl < n;
+  const int mm = mact ? m0 + cl : n - 1;
+  int y0 = tid >> lgS;
+  auto at = [&](int u) {   // entry of row y0 + u P
+    if constexpr (MR == 8)
+      return cl * stride + line_entry(y0) + u * (P + (P >> 3));   // P a multiple of 8
+    else
+      return cl * stride + line_entry(y0 + u * P);
+  };
+  In v[MR];
+  Cx fv[FU];
+  auto load = [&](int k) {
+    const In *src = static_cast<const In *>(in) + (size_t)k * nbar;
+#pragma unroll
+    for (int u = 0; u < MR; ++u) {
+      const int y = y0 + u * P;
+      v[u] = src[(unsigned)((y < n ? y : n - 1) * n + mm)];
+    }
+    const Cx *fs = fac + ((size_t)k * n + m0) * NF;
+    const int last = (n - m0 < S ? n - m0 : S) * NF - 1;
+#pragma unroll
+    for (int u = 0; u < FU; ++u) {
+      const int e = tid + u * (int)blockDim.x;
+      const Cx t = fs[(unsigned)(e < last ? e : last)];
+      fv[u] = Cx{t.re, t.im};
+    }
+  };
+  for (int k = kbeg; k < kend; ++k) {
+    asm volatile("" : "+v"(y0));
+    load(k);
+    if (k != kbeg) __syncthreads();   // the item before has been stored
+#pragma unroll
+    for (int u = 0; u < MR; ++u) {
+      const int y = y0 + u * P;
+      if (y < n) tile[at(u)] = pd_sel(mact, Cx{(double)v[u].re, (double)v[u].im}, zero);
+    }
+#pragma unroll
+    for (int u = 0; u < FU; ++u) {
+      const int e = tid + u * (int)blockDim.x;
+      if (e < S * NF) tabs[e] = Cx{fv[u].re, fv[u].im};
+    }
+    __syncthreads();
+    Cx d[MR];
+#pragma unroll
+    for (int q = 0; q < MR; ++q) {
+      Cx t = zero;
+      if (q < len) {
+        t = line[line_entry(s0 + q)];
+        if constexpr (MODE == 1) t.re += xr[q];
+      }
+      d[q] = t;
+    }
+    if (MR == 8 || P >= 16)   // 8 rows: n > 64, P >= 16
+      scan_solve_lanes<double, MR, CplxOps<double>, MODE == 1>(d, len, lt, P, tb);
+    else
+      scan_solve_group<double, MR, CplxOps<double>, MODE == 1>(d, len, lt, P, tb);
+    if constexpr (MODE == 1) {
+      // every thread reads and writes its own rows of the tile only
+#pragma unroll
+      for (int q = 0; q < MR; ++q)
+        if (q < len) line[line_entry(s0 + q)] = d[q];
+      __syncthreads();
+      Cx *dst = out + (size_t)k * nbar;
+#pragma unroll
+      for (int u = 0; u < MR; ++u) {
+        const int y = y0 + u * P;
+        if (y < n && mact) dst[(unsigned)(y * n + mm)] = tile[at(u)];
+      }
+    } else {
+      // the recurrence form returns kappa y: fold 1/kappa into the weight
+      const Cx ik = tb[4];
+      const double gr = gw[2 * k] * ik.re - gw[2 * k + 1] * ik.im;
+      const double gi = gw[2 * k] * ik.im + gw[2 * k + 1] * ik.re;
+#pragma unroll
+      for (int q = 0; q < MR; ++q)
+        if (q < len) acc[q] += gr * d[q].re - gi * d[q].im;
+    }
+  }
+  if constexpr (MODE == 0) {
+    __syncthreads();
+    double *sd = reinterpret_cast<double *>(smem_raw);
+#pragma unroll
+    for (int q = 0; q < MR; ++q)
+      if (q < len) sd[2 * ((size_t)g * stride + line_entry(s0 + q))] = acc[q];
+    __syncthreads();
+    double *dst = partials + (size_t)kc * nbar;
+#pragma unroll
+    for (int u = 0; u < MR; ++u) {
+      const int y = y0 + u * P;
+      if (y < n && mact) dst[(unsigned)(y * n + mm)] = sd[2 * at(u)];
+    }
+  }
+}
+
+template <int MR, int MODE, bool IN32>
+void launch2d_scan(pd_plan p, const void *in, const double *xv, void *out) {
+  const Line2DConfig &L = p->l2d;
+  hipLaunchKernelGGL((line2d_scan_kernel<MR, MODE, IN32>), dim3(L.nkc * L.mgroups), dim3(L.block),
+                     line_lds<MR>(p->n, L.S), p->stream, p->n, p->F2, L.P, L.S, L.mgroups,
+                     L.kchunk, reinterpret_cast<const cpx<double> *>(p->fac64), p->gB64, in, xv,
+                     p->w, static_cast<cpx<double> *>(out), p->partials);
+}
+
+template <typename R, int MR, bool SCAN>
 pd_status launch2d_form(pd_plan p, int mode, const void *in, const double *xv, void *out) {
   const Line2DConfig &L = p->l2d;
   const cpx<R> *fac = (sizeof(R) == 8) ? reinterpret_cast<const cpx<R> *>(p->fac64)
                                        : reinterpret_cast<const cpx<R> *>(p->fac32);
   const R toff = (R)p->uni[3];
   mode &= 0xff;
-  if (mode == 1) {
-    hipLaunchKernelGGL((line2d_kernel<R, MR, 1, SCAN, IN32>), dim3(p->F2 * L.mgroups), dim3(L.block),
-                       L.lds, p->stream, p->n, p->F2, L.P, L.S, L.mgroups, L.kchunk, fac, toff,
-                       p->gB64, reinterpret_cast<const cpx<R> *>(in), nullptr, xv, p->w,
-                       reinterpret_cast<cpx<R> *>(out), nullptr);
-  } else if (mode == 0) {
-    hipLaunchKernelGGL((line2d_kernel<R, MR, 0, SCAN, IN32>), dim3(L.nkc * L.mgroups), dim3(L.block),
-                       L.lds, p->stream, p->n, p->F2, L.P, L.S, L.mgroups, L.kchunk, fac, toff,
-                       p->gB64, reinterpret_cast<const cpx<R> *>(in), nullptr, nullptr, p->w,
-                       nullptr, p->partials);
-  } else {
-    hipLaunchKernelGGL((line2d_kernel<R, MR, 2, SCAN>), dim3(L.nkc * L.mgroups), dim3(L.block),
-                       L.lds, p->stream, p->n, p->F2, L.P, L.S, L.mgroups, L.kchunk, fac, toff,
-                       p->gJ64, nullptr, reinterpret_cast<const double *>(in), nullptr, p->w,
-                       nullptr, p->partials);
+  if constexpr (SCAN) {
+    if (mode != 2) {
+      // in32: complex64 right-hand sides, mode 1 writes complex128 elsewhere
+      if (mode == 1 && p->in32) launch2d_scan<MR, 1, true>(p, in, xv, out);
+      else if (mode == 1) launch2d_scan<MR, 1, false>(p, in, xv, out);
+      else if (p->in32) launch2d_scan<MR, 0, true>(p, in, xv, out);
+      else launch2d_scan<MR, 0, false>(p, in, xv, out);
+      PD_HIP_CHECK(hipGetLastError());
+      return PD_OK;
+    }
+  }
+  auto launch = [&](auto m, int blocks, const double *gw, const cpx<R> *src, const double *v) {
+    hipLaunchKernelGGL((line2d_kernel<R, MR, decltype(m)::value, SCAN>), dim3(blocks), dim3(L.block),
+                       L.lds, p->stream, p->n, p->F2, L.P, L.S, L.mgroups, L.kchunk, fac, toff, gw,
+                       src, v, xv, p->w, reinterpret_cast<cpx<R> *>(out), p->partials);
+  };
+  if (mode == 2) {
+    launch(std::integral_constant<int, 2>{}, L.nkc * L.mgroups, p->gJ64, nullptr,
+           static_cast<const double *>(in));
+  } else if constexpr (!SCAN) {
+    const cpx<R> *src = reinterpret_cast<const cpx<R> *>(in);
+    if (mode == 1)
+      launch(std::integral_constant<int, 1>{}, p->F2 * L.mgroups, p->gB64, src, nullptr);
+    else
+      launch(std::integral_constant<int, 0>{}, L.nkc * L.mgroups, p->gB64, src, nullptr);
   }
   PD_HIP_CHECK(hipGetLastError());
   return PD_OK;
@@ -205,8 +376,7 @@ pd_status launch2d_form(pd_plan p, int mode, const void *in, const double *xv, v
 template <typename R, int MR>
 pd_status launch2d(pd_plan p, int mode, const void *in, const double *xv, void *out) {
   if constexpr (sizeof(R) == 8) {
-    // complex64 spectra: always the recurrence form (pd_mixed64_ok)
-    if (p->in32) return launch2d_form<R, MR, true, true>(p, mode, in, xv, out);
+    // always so with complex64 spectra (pd_mixed64_ok)
     if (pd_line2d_scan(p)) return launch2d_form<R, MR, true>(p, mode, in, xv, out);
   }
   return launch2d_form<R, MR, false>(p, mode, in, xv, out);
@@ -292,20 +462,20 @@ pd_status pd_launch_line2d(pd_plan p, int mode, const void *in, const double *xv
 void pd_line2d_set_attributes(size_t max_lds) {
   const int v = (int)max_lds;
   const void *fns[] = {
-      reinterpret_cast<const void *>(&line2d_kernel<double, 4, 0, true, true>),
-      reinterpret_cast<const void *>(&line2d_kernel<double, 4, 1, true, true>),
-      reinterpret_cast<const void *>(&line2d_kernel<double, 8, 0, true, true>),
-      reinterpret_cast<const void *>(&line2d_kernel<double, 8, 1, true, true>),
+      reinterpret_cast<const void *>(&line2d_scan_kernel<4, 0, true>),
+      reinterpret_cast<const void *>(&line2d_scan_kernel<4, 1, true>),
+      reinterpret_cast<const void *>(&line2d_scan_kernel<4, 0, false>),
+      reinterpret_cast<const void *>(&line2d_scan_kernel<4, 1, false>),
+      reinterpret_cast<const void *>(&line2d_scan_kernel<8, 0, true>),
+      reinterpret_cast<const void *>(&line2d_scan_kernel<8, 1, true>),
+      reinterpret_cast<const void *>(&line2d_scan_kernel<8, 0, false>),
+      reinterpret_cast<const void *>(&line2d_scan_kernel<8, 1, false>),
       reinterpret_cast<const void *>(&line2d_kernel<double, 4, 0, false>),
-      reinterpret_cast<const void *>(&line2d_kernel<double, 4, 0, true>),
       reinterpret_cast<const void *>(&line2d_kernel<double, 4, 1, false>),
-      reinterpret_cast<const void *>(&line2d_kernel<double, 4, 1, true>),
       reinterpret_cast<const void *>(&line2d_kernel<double, 4, 2, false>),
       reinterpret_cast<const void *>(&line2d_kernel<double, 4, 2, true>),
       reinterpret_cast<const void *>(&line2d_kernel<double, 8, 0, false>),
-      reinterpret_cast<const void *>(&line2d_kernel<double, 8, 0, true>),
       reinterpret_cast<const void *>(&line2d_kernel<double, 8, 1, false>),
-      reinterpret_cast<const void *>(&line2d_kernel<double, 8, 1, true>),
       reinterpret_cast<const void *>(&line2d_kernel<double, 8, 2, false>),
       reinterpret_cast<const void *>(&line2d_kernel<double, 8, 2, true>),
       reinterpret_cast<const void *>(&line2d_kernel<float, 4, 0, false>),

@@ -162,14 +162,4 @@ __device__ __forceinline__ void fft_lds(cpx<R> *lds, int N, int C, int stride, c
   }
 }
 
-// Blocks are dispatched round-robin over the 8 XCDs, each with its own L2.
-// Neighbouring tiles read the two halves of the same 128-byte lines, so map
-// consecutive blocks of one XCD to consecutive tiles.
-__device__ __forceinline__ int xcd_tile(int b, int nb) {
-  constexpr int X = 8;
-  const int per = nb / X;            // tiles in the evenly divisible part
-  if (b >= per * X) return b;        // remainder keeps its position
-  return (b % X) * per + b / X;
-}
-
 }  // namespace pdfft

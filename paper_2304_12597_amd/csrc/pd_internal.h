@@ -126,6 +126,16 @@ struct VecJob {     // one problem's vectors for the batched GMRES kernels
   const double *done;   // the problem's GMRES converged flag
 };
 
+// Blocks are dispatched round-robin over the 8 XCDs, each with its own L2.
+// Neighbouring tiles read the two halves of the same 128-byte lines, so map
+// consecutive blocks of one XCD to consecutive tiles.
+__device__ __forceinline__ int xcd_tile(int b, int nb) {
+  constexpr int X = 8;
+  const int per = nb / X;            // tiles in the evenly divisible part
+  if (b >= per * X) return b;        // remainder keeps its position
+  return (b % X) * per + b / X;
+}
+
 // Direct global -> LDS load of 16 bytes per lane (gfx950 global_load_lds):
 // lane j of the wave writes lds_base + 16 j; lds_base must be wave-uniform.
 // Completion is tracked by the vector-memory counter (wait with

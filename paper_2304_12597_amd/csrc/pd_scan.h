@@ -339,6 +339,121 @@ __device__ __forceinline__ void scan_solve_group(cpx<R> (&d)[MR], int len, int l
   }
 }
 
+// The same for symmetric systems (r1 = r2 = r) and groups of 16, 32 or 64 lanes,
+// without lane shuffles through LDS: the chunk multiplier R is one number for
+// the group, so a step of the scan needs its powers only, R^s inside a row of
+// 16 lanes (DPP), R^(lanes from the row's end) across rows.
+template <typename R, int MR, typename A, bool SCALE>
+__device__ __forceinline__ void scan_solve_lanes(cpx<R> (&d)[MR], int len, int lt, int P,
+                                                 const cpx<R> *tb) {
+  using Cx = cpx<R>;
+  auto fma = [](Cx s, Cx b, Cx c) { return A::fma(s, b, c); };
+  const Cx zero = {R(0), R(0)}, one = A::one();
+  const Cx r = tb[0];
+  const bool ragged = __any(len < MR);
+  const int lane = threadIdx.x & 63;
+  auto times = [](bool on, Cx x, Cx p) { return pd_sel(on, A::mul(x, p), x); };
+
+  Cx acc = zero;
+#pragma unroll
+  for (int q = 0; q < MR; ++q) {
+    acc = fma(d[q], r, acc);
+    d[q] = acc;
+  }
+  Cx c = acc, p = tb[2];   // p = R^s
+  c = fma(c, p, pd_dpp<0x111, 0xF>(c, zero));   // row_shr:1, 2, 4, 8
+  Cx a0 = pd_sel((lt & 1) != 0, p, one);        // R^(lt mod 2 s)
+  p = A::mul(p, p);
+  c = fma(c, p, pd_dpp<0x112, 0xF>(c, zero));
+  a0 = times(lt & 2, a0, p);
+  p = A::mul(p, p);
+  c = fma(c, p, pd_dpp<0x114, 0xF>(c, zero));
+  a0 = times(lt & 4, a0, p);
+  p = A::mul(p, p);
+  c = fma(c, p, pd_dpp<0x118, 0xF>(c, zero));
+  a0 = times(lt & 8, a0, p);
+  if (P > 16) {
+    c = fma(c, A::mul(a0, tb[2]), pd_dpp<0x142, 0xA>(c, zero));   // row_bcast:15, rows 1 and 3
+    p = A::mul(p, p);
+    a0 = times(lt & 16, a0, p);
+  }
+  if (P > 32) {
+    c = fma(c, A::mul(a0, tb[2]), pd_dpp<0x143, 0xC>(c, zero));   // row_bcast:31, rows 2 and 3
+    p = A::mul(p, p);
+    a0 = times(lt & 32, a0, p);
+  }
+  const Cx ex = pd_sel(lt > 0, pd_dpp<0x138, 0xF>(c, zero), zero);   // wave_shr:1
+  Cx h = zero, K = tb[6];
+  if (!ragged) {
+#pragma unroll
+    for (int q = MR - 1; q >= 0; --q) h = fma(d[q], r, h);
+  } else {
+    // full chunks, the one ragged chunk (len = n mod MR), empty chunks
+    K = pd_sel(len == MR, tb[6], pd_sel(len > 0, tb[8 + MR], zero));
+#pragma unroll
+    for (int q = MR - 1; q >= 0; --q) h = pd_sel(q < len, fma(d[q], r, h), h);
+  }
+  Cx z0 = A::mul(a0, fma(h, ex, K));
+  z0 = cadd(z0, pd_dpp<0x111, 0xF>(z0, zero));
+  z0 = cadd(z0, pd_dpp<0x112, 0xF>(z0, zero));
+  z0 = cadd(z0, pd_dpp<0x114, 0xF>(z0, zero));
+  z0 = cadd(z0, pd_dpp<0x118, 0xF>(z0, zero));
+  if (P > 16) z0 = cadd(z0, pd_dpp<0x142, 0xA>(z0, zero));
+  if (P > 32) z0 = cadd(z0, pd_dpp<0x143, 0xC>(z0, zero));
+  if (P == 64)
+    z0 = pd_readlane(z0, 63);
+  else
+    z0 = Cx{__shfl(z0.re, P - 1, P), __shfl(z0.im, P - 1, P)};
+  {
+    const Cx E = csub(A::mul(r, ex), A::mul(A::mul(tb[5], z0), a0));
+    if (!ragged) {
+#pragma unroll
+      for (int q = 0; q < MR; ++q) d[q] = fma(d[q], tb[7 + q], E);
+    } else {
+#pragma unroll
+      for (int q = 0; q < MR; ++q) d[q] = pd_sel(q < len, fma(d[q], tb[7 + q], E), zero);
+    }
+  }
+  acc = zero;
+#pragma unroll
+  for (int q = MR - 1; q >= 0; --q) {
+    acc = fma(d[q], r, acc);
+    d[q] = acc;
+  }
+  Cx cz = acc;
+  p = tb[2];
+  asm volatile("" : "+v"(p.re), "+v"(p.im));   // the powers anew, not kept from above
+  Cx e = times(!(lt & 1), p, p);                // R^(s - lt mod s), s = 2, 4, ...
+  cz = fma(cz, p, pd_dpp<0x101, 0xF>(cz, zero));   // row_shl:1, 2, 4, 8
+  p = A::mul(p, p);
+  cz = fma(cz, p, pd_dpp<0x102, 0xF>(cz, zero));
+  e = times(!(lt & 2), e, p);
+  p = A::mul(p, p);
+  cz = fma(cz, p, pd_dpp<0x104, 0xF>(cz, zero));
+  e = times(!(lt & 4), e, p);
+  p = A::mul(p, p);
+  cz = fma(cz, p, pd_dpp<0x108, 0xF>(cz, zero));
+  e = times(!(lt & 8), e, p);
+  if (P > 16) {
+    const int src = ((lane | 15) + 1) & 63;   // the next row's first lane
+    const Cx o = {__shfl(cz.re, src, 64), __shfl(cz.im, src, 64)};
+    cz = pd_sel((lt & 16) == 0, fma(cz, e, o), cz);
+    if (P > 32) {
+      e = times(!(lt & 16), e, A::mul(p, p));
+      cz = pd_sel(lt < 32, fma(cz, e, pd_readlane(cz, 32)), cz);
+    }
+  }
+  const Cx exz = pd_sel(lt + 1 < P, pd_dpp<0x130, 0xF>(cz, zero), zero);   // wave_shl:1
+  if constexpr (SCALE) {
+    const Cx ik = tb[4];
+#pragma unroll
+    for (int q = MR - 1; q >= 0; --q) d[q] = A::mul(ik, fma(d[q], tb[7 + MR - q], exz));
+  } else {
+#pragma unroll
+    for (int q = MR - 1; q >= 0; --q) d[q] = fma(d[q], tb[7 + MR - q], exz);
+  }
+}
+
 // The table above for one frequency (host).  a, b, c: the constant sub-,
 // main and super-diagonal; real: the system is real (lambda real), so the
 // discriminant is clamped at zero and every entry is real.  Computed in long
