@@ -116,6 +116,11 @@ pd_status build_run(BatchRun &r, const pd_plan *plans, int count, const double *
     // per rows-per-thread bucket: the shifted-solve block maps and LDS size
     std::vector<int2> t0b[5], t1b[5], t0Jb[5], k0b[5];
     size_t ldsb[5] = {0, 0, 0, 0, 0};
+    // tiles of 8192 points each, about, at the wider tile width
+    size_t tiles = 0;
+    int max_lds = 65536;
+    (void)hipDeviceGetAttribute(&max_lds, hipDeviceAttributeMaxSharedMemoryPerBlock, p0->device);
+    for (int i = 0; i < count; ++i) tiles += (size_t)plans[i]->nbar * plans[i]->ell / 8192;
     for (int i = 0; i < count; ++i) {
       const pd_plan p = plans[i];
       const int scan = prec == PD_FP64 && pd_use_scan(p) ? 1 : 0;
@@ -123,7 +128,9 @@ pd_status build_run(BatchRun &r, const pd_plan *plans, int count, const double *
       if (p->tri.MR != 4 && p->tri.MR != 8 && p->tri.MR != 16) return PD_ENOTSUP;
       FftJob &f = fj[i];
       f.N = p->ell; f.n = p->n; f.nbar = p->nbar; f.dims = 1;
-      f.C = p->fft_C; f.stride = p->fft_stride; f.tau = p->tau;
+      f.C = p->autotune ? p->fft_C
+                        : pd_choose_fft_C(p->ell, p->nbar, prec, max_lds, std::max<size_t>(tiles, 1));
+      f.stride = p->fft_stride; f.tau = p->tau;
       f.u0 = u0[i]; f.F = F[i]; f.U = nullptr; f.coef = p->coef64; f.dal = p->alpha == 1.0 ? nullptr : p->dal;
       f.tw = (prec == PD_FP64) ? (const void *)p->tw64 : (const void *)p->tw32;
       f.spec = p->spec; f.out = U[i]; f.red = p->red;

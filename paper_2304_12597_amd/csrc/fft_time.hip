@@ -418,12 +418,22 @@ FftLaunch fft_config(pd_plan p) {
 // Choose C (point pairs per block): keep LDS at <= 64 KiB where possible
 // (two blocks per CU), else up to two point pairs per block; at most 512
 // threads (C*N/8), and the tile no wider than the problem.
-int pd_choose_fft_C(int ell, int nbar, int prec, size_t max_lds) {
+// Column pairs per tile: 64 KB of LDS (three or more blocks a CU), or 80 KB (two)
+// where that doubles the tile's row segments and there are tiles enough for seven
+// rounds of two blocks a CU (tiles: of all problems of a launch; 0: of this one).
+// Times at 64 / 80 KB: 255^2 points, 512 steps, 4064 tiles, inverse 179 / 150 us;
+// 511^2, 256 steps, 8160 tiles, 255 / 230 us forward, 261 / 253 us inverse; 96
+// problems, 11000 tiles, 410 / 378 and 415 / 352 us; but 5001 points, 512 steps,
+// 313 tiles, 15.0 / 16.6 us and 256^2, 256 steps, 2048 tiles, 53 / 57 us.  A column's
+// arithmetic does not depend on the tile.
+int pd_choose_fft_C(int ell, int nbar, int prec, size_t max_lds, size_t tiles) {
   const size_t cb = (prec == PD_FP64) ? 16 : 8;
   const size_t col = (size_t)pd_fft_col_stride(ell) * cb, twb = pd_tw_entries(ell) * cb;
   int C = 1;
   while (C < 32 && 2 * C * col + twb <= 65536 && 2 * C * ell / 8 <= 512) C *= 2;
   while (C < 2 && 2 * C * col + twb <= max_lds && 2 * C * ell / 8 <= 512) C *= 2;
+  if (tiles == 0) tiles = (size_t)(nbar + 4 * C - 1) / (4 * C);
+  if (C < 32 && 2 * C * col + twb <= 81920 && 2 * C * ell / 8 <= 512 && tiles >= 7 * 512) C *= 2;
   int maxC = 1;
   while (2 * maxC < nbar && maxC < 32) maxC *= 2;
   if (C > maxC) C = maxC;

@@ -563,7 +563,7 @@ pd_status pd_residual_read(pd_plan p, double *rn2, double *gn2, double *un2);
 int pd_fft_blocks(pd_plan p);
 int pd_vec_blocks(int n);
 size_t pd_gmres_state_doubles(int maxit);
-int pd_choose_fft_C(int ell, int nbar, int prec, size_t max_lds);
+int pd_choose_fft_C(int ell, int nbar, int prec, size_t max_lds, size_t tiles = 0);
 // Work items of a shifted-solve launch: the pipelined body pairs the two real
 // shifts k = 0 and k = ell/2 into one item (slot 0), so F2 - 1 slots.
 inline int pd_tri_nitems(const TriConfig &T, int F2) {
