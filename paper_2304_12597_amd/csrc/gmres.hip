@@ -12,6 +12,7 @@
 // kernel per iteration updates the Givens QR and the residual estimate; the
 // host reads back 16 bytes per iteration to decide whether to stop.
 #include "pd_internal.h"
+#include "pd_small.h"
 
 #include <cmath>
 
@@ -221,11 +222,6 @@ __global__ void solve_combine_kernel(int n, int m, const double *__restrict__ V,
 constexpr int ARN_T = 1024;
 constexpr int ARN_MAXN = 16 * ARN_T;
 
-__device__ __forceinline__ double wave_sum(double v) {
-  for (int off = 32; off > 0; off >>= 1) v += __shfl_down(v, off, 64);
-  return v;   // valid in lane 0
-}
-
 template <int RPT>
 __device__ __forceinline__ void arnoldi_step_body(int n, double *__restrict__ V,
                                                   const double *__restrict__ w,
@@ -250,7 +246,7 @@ __device__ __forceinline__ void arnoldi_step_body(int n, double *__restrict__ V,
   }
   if (tid < j + 2) hcol[tid] = 0.0;
   double gj = 0.0, beta = 0.0;
-  if (tid == 0) {
+  if (wv == 0) {
     gj = gm[L.g(j)];
     beta = gm[L.st(3)];
   }
@@ -289,7 +285,7 @@ __device__ __forceinline__ void arnoldi_step_body(int n, double *__restrict__ V,
             const int r = tid + k * ARN_T;
             if (r < n) s += vr[i][k] * wr[k];
           }
-          s = wave_sum(s);
+          s = pd_wave_sum(s);
           if (lane == 0) part[wv][i] = s;
         }
     } else {
@@ -301,7 +297,7 @@ __device__ __forceinline__ void arnoldi_step_body(int n, double *__restrict__ V,
           const int r = tid + k * ARN_T;
           if (r < n) s += vi[r] * wr[k];
         }
-        s = wave_sum(s);
+        s = pd_wave_sum(s);
         if (lane == 0) part[wv][i] = s;
       }
     }
@@ -333,44 +329,38 @@ __device__ __forceinline__ void arnoldi_step_body(int n, double *__restrict__ V,
   double s = 0.0;
 #pragma unroll
   for (int k = 0; k < RPT; ++k) s += wr[k] * wr[k];
-  s = wave_sum(s);
+  s = pd_wave_sum(s);
   if (lane == 0) part[wv][0] = s;
   __syncthreads();
-  if (tid == 0) {
-    double nn = 0.0;
-    for (int q = 0; q < NW; ++q) nn += part[q][0];
-    const double hn = sqrt(nn);
-    hcol[j + 1] = hn;
-    for (int i = 0; i < j; ++i) {
-      const double c = csl[i], sn = snl[i];
-      const double a = hcol[i], b = hcol[i + 1];
-      hcol[i] = c * a + sn * b;
-      hcol[i + 1] = -sn * a + c * b;
+  if (wv == 0) {
+    const double hn = sqrt(pd_wave_sum(lane < NW ? part[lane][0] : 0.0));
+    double h = lane < nv ? hcol[lane] : 0.0, g = gj, gr;
+    double c = lane < j ? csl[lane] : 0.0, sn = lane < j ? snl[lane] : 0.0;
+    pd_givens_column(h, hn, j, lane, c, sn, gr, g);
+    if (lane <= j) gm[L.H(lane, j)] = h;
+    if (lane == j) {
+      gm[L.cs(j)] = c;
+      gm[L.sn(j)] = sn;
     }
-    const double a = hcol[j], b = hcol[j + 1];
-    const double rr = hypot(a, b);
-    const double c = (rr == 0.0) ? 1.0 : a / rr, sn = (rr == 0.0) ? 0.0 : b / rr;
-    gm[L.cs(j)] = c;
-    gm[L.sn(j)] = sn;
-    hcol[j] = rr;
-    hcol[j + 1] = 0.0;
-    gm[L.g(j)] = c * gj;
-    gm[L.g(j + 1)] = -sn * gj;
-    const double res = fabs(-sn * gj);
-    const double done = (res <= rtol * beta || hn == 0.0 || !isfinite(res)) ? 1.0 : 0.0;
-    gm[L.st(0)] = res;
-    gm[L.st(1)] = hn;
-    gm[L.st(2)] = (double)(j + 1);
-    gm[L.st(GM_DONE)] = done;
-    st_out[0] = res;
-    st_out[1] = hn;
-    st_out[2] = (double)(j + 1);
-    st_out[3] = beta;
-    if (with_flag) st_out[4] = done;
-    hsh = hn;
+    if (lane == 0) {
+      gm[L.H(j + 1, j)] = 0.0;
+      gm[L.g(j)] = gr;
+      gm[L.g(j + 1)] = g;
+      const double res = fabs(g);
+      const double done = (res <= rtol * beta || hn == 0.0 || !isfinite(res)) ? 1.0 : 0.0;
+      gm[L.st(0)] = res;
+      gm[L.st(1)] = hn;
+      gm[L.st(2)] = (double)(j + 1);
+      gm[L.st(GM_DONE)] = done;
+      st_out[0] = res;
+      st_out[1] = hn;
+      st_out[2] = (double)(j + 1);
+      st_out[3] = beta;
+      if (with_flag) st_out[4] = done;
+      hsh = hn;
+    }
   }
   __syncthreads();
-  if (tid < j + 2) gm[L.H(tid, j)] = hcol[tid];
   const double inv = (hsh > 0.0) ? 1.0 / hsh : 0.0;
   double *vn = V + (size_t)(j + 1) * n;
 #pragma unroll
@@ -420,7 +410,7 @@ __device__ __forceinline__ void gm_init_body(int n, const double *__restrict__ b
     br[k] = r < n ? b[r] : 0.0;
     s += br[k] * br[k];
   }
-  s = wave_sum(s);
+  s = pd_wave_sum(s);
   if (lane == 0) part[wv] = s;
   __syncthreads();   // also orders the reset of gm before thread 0 writes it
   if (tid == 0) {
@@ -586,7 +576,7 @@ gm_diag_kernel(int nc, double *__restrict__ c, const double *__restrict__ c2,
   GmLayout L{MX};
   double s = 0.0;
   for (int i = tid; i < nparts; i += ARN_T) s += rpart[i];
-  s = wave_sum(s);
+  s = pd_wave_sum(s);
   if (lane == 0) part[wv] = s;
   __syncthreads();
   double rho = 0.0;
@@ -611,17 +601,16 @@ gm_diag_kernel(int nc, double *__restrict__ c, const double *__restrict__ c2,
     __syncthreads();
   }
   const int m = (int)gm[L.st(2)];
-  if (tid == 0) {
-    for (int i = m - 1; i >= 0; --i) {
-      double t = gm[L.g(i)];
-      for (int k = i + 1; k < m; ++k) t -= gm[L.H(i, k)] * yv[k];
-      const double d = gm[L.H(i, i)];
-      yv[i] = (d != 0.0) ? t / d : 0.0;
+  if (wv == 0) {
+    const double yl = pd_back_substitute(lane < m ? gm[L.g(lane)] : 0.0, m, lane, [&](int k) {
+      return lane <= k ? gm[L.H(lane, k)] : 0.0;
+    });
+    if (lane < m) yv[lane] = yl;
+    const double t = pd_wave_sum(lane < m ? yl * V[(size_t)lane * n + nc] : 0.0);
+    if (lane == 0) {
+      tsh = rho > 0.0 ? t / rho : (m > 0 ? 1.0 : 0.0);
+      y[nc] = tsh;
     }
-    double t = 0.0;
-    for (int i = 0; i < m; ++i) t += yv[i] * V[(size_t)i * n + nc];
-    tsh = rho > 0.0 ? t / rho : (m > 0 ? 1.0 : 0.0);
-    y[nc] = tsh;
   }
   __syncthreads();
   const double tb = tsh;

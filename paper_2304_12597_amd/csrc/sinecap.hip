@@ -32,6 +32,7 @@
 // and b is read three times.  Sums run in a fixed order and the batched
 // launches use the same bodies, so results are the same alone and in a batch.
 #include "pd_internal.h"
+#include "pd_small.h"
 
 #include <algorithm>
 #include <cmath>
@@ -45,11 +46,6 @@ constexpr int SC_ONE = 4;        // column blocks of the one-launch form
 // its dynamic LDS limit: 66.7 KiB of static LDS beside it, of 160 KiB
 constexpr size_t SC_ONE_LDS = 80 * 1024;
 constexpr double SC_CUT = 0x1p-56;
-
-__device__ __forceinline__ double sc_wave_sum(double v) {
-  for (int off = 32; off > 0; off >>= 1) v += __shfl_xor(v, off, 64);
-  return v;   // in every lane
-}
 
 // ---- project: b (summed from pass B's partials, as reduce_fused_kernel) and
 // cpart[blk][h r + j] = sum over the block's 64 columns of S[j][i] b_h[i] ----
@@ -90,7 +86,7 @@ __device__ __forceinline__ void sc_project_body(const ScJob &J, int blk, double 
   const int d = J.s * J.r;
   for (int e = w; e < d; e += SCP_T / 64) {
     const int h = e / J.r, j = e - h * J.r;
-    const double v = sc_wave_sum(J.S[(size_t)j * J.ns + i] * bs[h][lane]);
+    const double v = pd_wave_sum(J.S[(size_t)j * J.ns + i] * bs[h][lane]);
     if (lane == 0) J.cpart[(size_t)blk * d + e] = v;
   }
 }
@@ -164,14 +160,14 @@ __device__ __forceinline__ void sc_norm_body(const ScJob &J, int blk, double *ld
     double v = i < J.n ? b[(size_t)w * J.n + i] - t : 0.0;
     if (i < J.n) J.x[(size_t)w * J.n + i] = v;
     grp[w * 64 + lane] = v;
-    v = sc_wave_sum(v * v);
+    v = pd_wave_sum(v * v);
     if (lane == 0) rs[w] = v;
   }
   __syncthreads();
   const int d = J.s * J.r;
   for (int e = w; e < d; e += SCP_T / 64) {
     const int h = e / J.r, j = e - h * J.r;
-    const double v = sc_wave_sum(J.S[(size_t)j * J.ns + i] * grp[h * 64 + lane]);
+    const double v = pd_wave_sum(J.S[(size_t)j * J.ns + i] * grp[h * 64 + lane]);
     if (lane == 0) J.cpart2[(size_t)blk * d + e] = v;
   }
   if (threadIdx.x == 0) {
@@ -192,7 +188,7 @@ __device__ __forceinline__ void sc_gmres(const ScJob &J, int MX, double rtol, do
                                          bool record, double *__restrict__ st_out,
                                          bool with_flag) {
   extern __shared__ __align__(16) unsigned char smem_raw[];
-  __shared__ double c[256], ws[256], hs[66], cs[64], sn[64], gv[66], yv[64];
+  __shared__ double c[256], ws[256], hs[64], yv[64];
   __shared__ double wsum[SCS_W];
   __shared__ double res_s, hn_s;
   __shared__ int done_s;
@@ -210,7 +206,7 @@ __device__ __forceinline__ void sc_gmres(const ScJob &J, int MX, double rtol, do
   if (wv == 0) {
     double t = 0.0;
     for (int b = lane; b < J.nblk; b += 64) t += J.rpart[b];
-    t = sc_wave_sum(t);
+    t = pd_wave_sum(t);
     if (lane == 0) c[d] = sqrt(t);
   }
   sc_sum_c<SCS_T>(J, J.cpart2, ws, ys);
@@ -219,7 +215,7 @@ __device__ __forceinline__ void sc_gmres(const ScJob &J, int MX, double rtol, do
   __syncthreads();
   if (tid < dim) v = c[tid];
   auto block_sum = [&](double x) {   // same order in every thread
-    x = sc_wave_sum(x);
+    x = pd_wave_sum(x);
     if (lane == 0 && wv < SCS_W) wsum[wv] = x;
     __syncthreads();
     double t = 0.0;
@@ -229,8 +225,9 @@ __device__ __forceinline__ void sc_gmres(const ScJob &J, int MX, double rtol, do
   };
   const double rho = c[d];
   const double beta = sqrt(block_sum(v * v));
+  // wave 0's lanes: the rotations, the rotated right-hand side; g: its last entry
+  double cs = 0.0, sn = 0.0, gl = 0.0, g = beta;
   if (tid == 0) {
-    gv[0] = beta;
     res_s = hn_s = beta;
     done_s = (beta == 0.0 || !isfinite(beta)) ? 1 : 0;
   }
@@ -257,7 +254,7 @@ __device__ __forceinline__ void sc_gmres(const ScJob &J, int MX, double rtol, do
         for (int i = wv; i < nv; i += SCS_W) {
           double t = 0.0;
           for (int e = lane; e < dim; e += 64) t += V[(size_t)i * dim + e] * ws[e];
-          t = sc_wave_sum(t);
+          t = pd_wave_sum(t);
           if (lane == 0) hs[i] = t;
         }
       __syncthreads();
@@ -268,43 +265,30 @@ __device__ __forceinline__ void sc_gmres(const ScJob &J, int MX, double rtol, do
       }
     }
     const double hn = sqrt(block_sum(tid < dim ? wr * wr : 0.0));
-    if (tid < nv) hs[tid] = hacc;
-    __syncthreads();
-    if (tid == 0) {
-      hs[j + 1] = hn;
-      for (int i = 0; i < j; ++i) {
-        const double a = hs[i], b = hs[i + 1];
-        hs[i] = cs[i] * a + sn[i] * b;
-        hs[i + 1] = -sn[i] * a + cs[i] * b;
+    if (wv == 0) {
+      double gr;
+      pd_givens_column(hacc, hn, j, lane, cs, sn, gr, g);
+      gl = lane == j ? gr : gl;
+      if (lane < nv) H[(size_t)j * (j + 1) / 2 + lane] = hacc;
+      if (lane == 0) {
+        const double res = fabs(g);
+        res_s = res;
+        hn_s = hn;
+        done_s = (res <= rtol * beta || hn == 0.0 || !isfinite(res)) ? 1 : 0;
       }
-      const double a = hs[j], b = hs[j + 1];
-      const double rr = hypot(a, b);
-      const double cc = (rr == 0.0) ? 1.0 : a / rr, ss = (rr == 0.0) ? 0.0 : b / rr;
-      cs[j] = cc;
-      sn[j] = ss;
-      hs[j] = rr;
-      const double gj = gv[j];
-      gv[j] = cc * gj;
-      gv[j + 1] = -ss * gj;
-      const double res = fabs(ss * gj);
-      res_s = res;
-      hn_s = hn;
-      done_s = (res <= rtol * beta || hn == 0.0 || !isfinite(res)) ? 1 : 0;
     }
-    __syncthreads();
-    if (tid < nv) H[(size_t)j * (j + 1) / 2 + tid] = hs[tid];
     if (tid < dim) V[(size_t)(j + 1) * dim + tid] = hn > 0.0 ? wr * (1.0 / hn) : 0.0;
     m = j + 1;
     __syncthreads();
   }
   // R y = g, then the reduced solution
+  if (wv == 0) {
+    const double yl = pd_back_substitute(gl, m, lane, [&](int k) {
+      return lane <= k ? H[(size_t)k * (k + 1) / 2 + lane] : 0.0;
+    });
+    if (lane < m) yv[lane] = yl;
+  }
   if (tid == 0) {
-    for (int i = m - 1; i >= 0; --i) {
-      double t = gv[i];
-      for (int k = i + 1; k < m; ++k) t -= H[(size_t)k * (k + 1) / 2 + i] * yv[k];
-      const double dd = H[(size_t)i * (i + 1) / 2 + i];
-      yv[i] = (dd != 0.0) ? t / dd : 0.0;
-    }
     if (record) {
       st_out[0] = res_s;
       st_out[1] = hn_s;
@@ -535,7 +519,7 @@ sc2_tile_kernel(int n, int ns, int q, const double *__restrict__ S,
       if (y < n && m < n) x[(size_t)y * n + m] = v;
       t += v * v;
     }
-    t = sc_wave_sum(t);
+    t = pd_wave_sum(t);
     if (lane == 0) red[wv] = t;
     __syncthreads();
     if (threadIdx.x == 0)
