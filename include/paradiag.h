@@ -70,19 +70,23 @@ typedef enum {
 } pd_krylov;
 
 typedef enum {
-  PD_SHIFTED_PARTITION = 0,  /* tridiagonal partition solves + parallel cyclic   */
-                             /* reduction, capacitance system by GMRES (any M, K) */
+  PD_SHIFTED_PARTITION = 0,  /* tridiagonal solves (recurrences or a partition    */
+                             /* method), capacitance system by GMRES (any M, K)   */
   PD_SHIFTED_SINE = 1        /* 1D, float64, symmetric Toeplitz M and K (uniform */
                              /* grid, zero Dirichlet ends), n + 1 a power of two */
-                             /* >= 16 or n <= 4095 (chirp-z DST): every shifted  */
-                             /* matrix and J_ell diagonal in the DST-I basis;    */
+                             /* >= 16 or n <= 4095 (DST as a product or in       */
+                             /* chirp-z form): every shifted matrix and J_ell     */
+                             /* diagonal in the DST-I basis;                     */
                              /* capacitance solved exactly                       */
 } pd_shifted_solver;
 
 typedef enum {
   PD_FP64 = 0,        /* everything in float64 / complex128                  */
-  PD_MIXED = 1,       /* complex64 transforms and shifted solves, float64    */
-                      /* capacitance Arnoldi, residual and refinement        */
+  PD_MIXED = 1,       /* complex64 forward transform and spectra, float64    */
+                      /* capacitance system, residual and refinement; shifted */
+                      /* solves and inverse transform in float64 where the    */
+                      /* recurrence form runs (uniform grids, n > 256 in 1D,  */
+                      /* n <= 512 a side in 2D), else complex64               */
   PD_FP32 = 2         /* one complex64 sweep, no refinement                  */
 } pd_precision;
 
@@ -180,8 +184,8 @@ pd_status paradiag_plan_create(pd_plan *out, int n, int ell, double tau,
  * initial value u0 [nbar] and nodal source F [ell][nbar] (device float64),
  * written to U [ell][nbar] (device float64, must not alias u0 or F).
  * tol: the capacitance GMRES stops at residual <= tol/100 * ||b|| (with
- * float32 shifted solves, PD_MIXED and PD_FP32, at no less than 1e-7 * ||b||,
- * the resolution of float32 capacitance products); PD_MIXED refines until
+ * float32 shifted solves at no less than 1e-7 * ||b||, the resolution of
+ * float32 capacitance products); PD_MIXED refines until
  * the float64 relative all-at-once residual is <= tol, or until a sweep
  * fails to lower it: then that sweep's correction is taken back and the best
  * iterate is returned with PD_ENOTCONV (info->rel_residual is its residual).
@@ -197,9 +201,9 @@ pd_status paradiag_solve(pd_plan plan, const double *u0, const double *F,
  * batch together -- 1D, uniform grid, float64 or float32 (not PD_MIXED),
  * backward Euler with the GMRES capacitance solver, the same precision and
  * maxit, no repeats -- form groups, and every stage of a group is one launch
- * for all of its problems (lockstep GMRES, each problem stopping on its own
- * convergence flag; a group's results equal the problems' results solved
- * alone, bit for bit).  Every other problem (2D, PD_MIXED, non-uniform
+ * for all of its problems (the capacitance GMRES one block per problem, or in
+ * lockstep, each problem stopping on its own convergence flag; a group's
+ * results equal the problems' results solved alone, bit for bit).  Every other problem (2D, PD_MIXED, non-uniform
  * grids, BDF, the sine basis, Algorithm 2) and any group of one is solved
  * with paradiag_solve, one after another.  Arrays as in paradiag_solve, one
  * per problem.  infos may be NULL.  Synchronises each group's first plan's

@@ -1,17 +1,21 @@
 // Batched solves: many independent problems, every stage launched once for
 // all of them.  Each launch maps its blocks to (problem, local block) pairs,
-// so problems of different sizes share the GPU in the same kernel; the
-// capacitance GMRES runs in lockstep, each problem stopping on its own
-// device-side convergence flag.  The per-problem arithmetic is the
-// single-problem kernels' own (the same device bodies, the same reduction
-// order), so a problem's result does not depend on the rest of the batch.
+// so problems of different sizes share the GPU in the same kernel.  The
+// per-problem arithmetic is the single-problem kernels' own (the same device
+// bodies, the same reduction order), so a problem's result does not depend on
+// the rest of the batch.
 //
-// The whole solve -- transforms, parfors, K GMRES iterations, x = V y --
-// is one launch sequence with no host round trip; once every plan of a
-// batch has been solved before (K = the largest iteration count they
-// needed), the sequence is captured as a HIP graph, cached per (plans,
-// arrays, tol, K) and replayed.  If some problem has not converged after K
-// iterations, an uncaptured loop continues it and the tail is redone.
+// Problems whose capacitance system is solved in the sine basis (sinecap.hip)
+// run in eight launches: the two transforms, the two parfors, and projection,
+// norm, GMRES (one block per problem, to its own convergence) and columns of x.
+//
+// Of the others the capacitance GMRES runs in lockstep, each problem stopping
+// on its own device-side convergence flag.  Their whole solve is one launch
+// sequence with no host round trip; once every plan of a batch has been solved
+// before (K = the largest iteration count they needed), the sequence is
+// captured as a HIP graph, cached per (plans, arrays, tol, K) and replayed.
+// If some problem has not converged after K iterations, an uncaptured loop
+// continues it and the tail is redone.
 #include "pd_internal.h"
 
 #include <algorithm>

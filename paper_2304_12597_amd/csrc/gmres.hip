@@ -10,7 +10,9 @@
 // classical Gram-Schmidt applied twice (CGS2), each pass one multi-block
 // kernel with deterministic float64 partial sums.  One small single-block
 // kernel per iteration updates the Givens QR and the residual estimate; the
-// host reads back 16 bytes per iteration to decide whether to stop.
+// host reads back 16 bytes per iteration to decide whether to stop.  Systems of
+// at most ARN_MAXN unknowns take one single-block kernel per iteration, those in
+// sine coordinates (sinecap.hip) one kernel for all iterations.
 #include "pd_internal.h"
 #include "pd_small.h"
 

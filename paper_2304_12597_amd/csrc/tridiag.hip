@@ -20,6 +20,7 @@
 // Complex128 systems with symmetric constant diagonals (uniform grids) and
 // whole waves per system use the recurrence form of pd_scan.h instead of
 // steps 1-3 (pd_use_scan); everything else about the kernels is shared.
+// General complex128 systems of 256 < n <= 4096 rows run in tridiag_lu.hip.
 //
 // The right-hand side is staged through LDS so that global loads and stores
 // are coalesced.  Modes: 0 accumulates b = sum_k gamma_k y_k (full spectrum,
