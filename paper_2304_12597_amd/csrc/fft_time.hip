@@ -264,6 +264,7 @@ fft_inverse_kernel(int N, int nbar, int C, int stride, const cpx<R> *__restrict_
 // Z[k] = 2 S_b[k] - 2i S_a[k].
 // MODE 0: v = h (tau f + u0 at t = 0); 1: v = float64 residual R (norms to
 // red); 2: v = in.  ACC: out += S instead of out = S.
+// Modes 0 and 2 run here for n < 31 only (dst_odd.hip, dst_dense.hip).
 template <int MODE, int ACC>
 __global__ void __launch_bounds__(1024)
 dst_x_kernel(int n, int ell, int C, int stride, double tau, const double *__restrict__ u0,

@@ -7,8 +7,8 @@
 //
 // so the parfor over k becomes a parfor over (k, m) of n-row line solves.
 // Spectra here are [ell/2+1][n*n] in the DST-x domain, index y*n + m.  A block
-// owns S consecutive m for one frequency (mode 1) or for a range of
-// frequencies (modes 0 and 2, which sum over k); its tile [y][m0..m0+S) is
+// owns S consecutive m for a range of frequencies (partition form, mode 1: for
+// one frequency); its tile [y][m0..m0+S) is
 // staged through LDS with coalesced row segments, and each line is solved by
 // P threads from constants precomputed per (k, m): float64 lines of at most
 // one wave by the recurrence form of pd_scan.h (the lines are symmetric

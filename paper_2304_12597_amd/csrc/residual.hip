@@ -19,7 +19,8 @@ constexpr int RB = 256;
 // are registers: the column's neighbours come by lane moves (DPP), the row
 // above from the walk.  A point costs 2 (2D: 3) loads; with a thread per point
 // it was 15 (14), and load instructions bounded the pass: n = 8191, ell =
-// 2048 at 201 us, 255^2, ell = 512 at 270 us.
+// 2048 at 201 us, 255^2, ell = 512 at 270 us; now 51 to 64 us (303 MB, 4.7 TB/s at
+// best) and 141 us, 65 and 204 us where the residual is written as float too.
 constexpr int RCOLS = 62, RUN = 8;
 
 // lane l's value from lane l - 1 / l + 1 (zero at the ends)

@@ -22,7 +22,7 @@
 // two scans of 6 steps, three barriers, against two such sweeps, 9 reduction
 // steps of a reciprocal and two barriers each in the partition form
 // (tridiag_kernel).  n = 3001, ell = 256: pass B 68 -> 18 us, pass C 68 -> 22 us,
-// J product 55 -> 15 us, the solve 375 -> 160 us.  Coefficients are kept a second time in the threads'
+// J product 55 -> 15 us, the solve 375 -> 155 us.  Coefficients are kept a second time in the threads'
 // order (row q of every thread side by side), so that their loads coalesce.
 //
 // Without pivoting the factorisation must not grow: a plan uses this form only
