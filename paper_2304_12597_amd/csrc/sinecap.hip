@@ -31,7 +31,7 @@
 // What bounds them is latency: the tables are at most 192 rows of n doubles
 // and b is read three times.  n = 8191, ell = 2048 (with the sum of pass B's
 // partials, 5 us of it): 6.5 + 4.9 + 9.7 us, where J products, Arnoldi steps and
-// the combination took 87; n = 4095, alpha = 0.1: 7.0 + 6.6 + 15.6, before 150;
+// the combination took 87; n = 4095, alpha = 0.01: 7.0 + 6.6 + 15.6, before 150;
 // n <= 256 in one launch, n = 63 11.7 us.  Sums run in a fixed order and the batched
 // launches use the same bodies, so results are the same alone and in a batch.
 #include "pd_internal.h"
