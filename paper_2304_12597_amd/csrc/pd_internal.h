@@ -340,7 +340,7 @@ struct pd_plan_s {
   int sc_on = 0, sc_r = 0, sc_ns = 0, sc_nblk = 0;
   double *sc_tab = nullptr;
   double *lu_tab = nullptr;    // general matrices: rows in thread order, pivots (tridiag_lu.hip)
-  int lu_on = 0;
+  int lu_on = 0, lu_G = 0;     // lu_G: blocks (partial rows) of a launch that sums
 };
 constexpr int PD_BDF_GCH = 16;   // frequency chunks of the BDF capacitance product
 
@@ -410,6 +410,7 @@ pd_status pd_launch_tridiag(pd_plan p, int mode, const void *in,
                             const double *xv, void *out);
 // the same for general matrices by two recurrences (tridiag_lu.hip)
 size_t pd_lu_doubles(const pd_plan p);
+int pd_lu_blocks(const pd_plan p, int cus);
 pd_status pd_lu_setup(pd_plan p, std::vector<double> &bad);
 pd_status pd_launch_lu(pd_plan p, int mode, const void *in, const double *xv, void *out);
 void pd_lu_set_attributes(size_t max_lds);

@@ -667,8 +667,14 @@ static pd_status create_plan(pd_plan *out, int n, int ell, double tau, const pd_
       pd_plan_s u = *p;
       u.uniform = true;
       Layout Lu;
-      if (compute_layout(&u, cus, max_lds, Lu) != PD_OK || L.total_bytes() > Lu.total_bytes())
+      const Layout partition = L;
+      p->lu_G = pd_lu_blocks(p, cus);
+      L.partials = std::max(L.partials, (size_t)p->lu_G * n);
+      L.rstage = std::max(L.rstage, (size_t)((p->lu_G + 15) / 16) * n);
+      if (compute_layout(&u, cus, max_lds, Lu) != PD_OK || L.total_bytes() > Lu.total_bytes()) {
+        L = partition;
         L.lu = 0;
+      }
     }
   }
   if (p->krylov == PD_KRYLOV_FOM && !p->sine && !pd_fom_supported(p)) {

@@ -20,7 +20,7 @@
 // Complex128 systems with symmetric constant diagonals (uniform grids) and
 // whole waves per system use the recurrence form of pd_scan.h instead of
 // steps 1-3 (pd_use_scan); everything else about the kernels is shared.
-// General complex128 systems of 256 < n <= 4096 rows run in tridiag_lu.hip.
+// General complex128 systems of n <= 4096 rows run in tridiag_lu.hip.
 //
 // The right-hand side is staged through LDS so that global loads and stores
 // are coalesced.  Modes: 0 accumulates b = sum_k gamma_k y_k (full spectrum,
@@ -1400,6 +1400,7 @@ pd_status pd_launch_reduce_partials(pd_plan p, const double *base, double *out) 
   const int nitems = pd_tri_nitems(p->tri, p->F2);
   int G = nitems < p->tri_G ? nitems : p->tri_G;
   if (p->dims == 2) G = p->l2d.nkc;
+  if (p->lu_on) G = p->lu_G;
   if (G > 0 && G <= RS) {
     hipLaunchKernelGGL(reduce_few_kernel, dim3((n + 255) / 256), dim3(256), 0, p->stream, n, G,
                        p->partials, base, out, p->gm_skip);

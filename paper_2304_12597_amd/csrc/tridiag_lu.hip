@@ -1,5 +1,5 @@
 // Shifted solves of general (non-constant) tridiagonal M and K in float64:
-// the parfor of Algorithm 1 on graded meshes, 256 < n <= 4096.
+// the parfor of Algorithm 1 on graded meshes, n <= 4096.
 //
 // P_k = L U without pivoting, l_i = a_i / d_{i-1}, d_i = b_i - l_i c_{i-1}, so a
 // solve is two first-order recurrences,
@@ -27,10 +27,13 @@
 //
 // Without pivoting the factorisation must not grow: a plan uses this form only
 // if every pivot is at least 1/16 of its diagonal entry (checked when the
-// pivots are formed); otherwise, and for n <= 256 (groups smaller than a wave)
-// and float32 plans, the partition form runs.
+// pivots are formed); otherwise, and for float32 plans, the partition form runs.
+// n <= 512 takes a wave per system whatever n is (identity rows past it): n = 200,
+// ell = 256, pass B 57 -> 15 us, pass C 55 -> 18 us, J product 44 -> 13 us,
+// the solve 315 -> 130 us of kernels.
 #include "pd_scan.h"
 
+#include <algorithm>
 #include <vector>
 
 namespace {
@@ -328,6 +331,18 @@ lu_solve_kernel(int n, int F2, int P, int spb, int nitems, const double *__restr
   }
 }
 
+// Threads of a group (a power of two, whole waves), of a block, and work items.
+constexpr int LU_T = 512;
+int lu_threads(int n) {
+  int P = 64;
+  while (P * MR < n) P *= 2;
+  return P;
+}
+int lu_items(const pd_plan p) {
+  const int spb = LU_T / lu_threads(p->n);
+  return (p->F2 + spb - 1) / spb;
+}
+
 size_t lu_lds(int P, int spb) {
   const int last = P * MR + 1;
   return (size_t)spb * (last + (last >> 3) + 1) * 16;
@@ -338,17 +353,19 @@ size_t lu_lds(int P, int spb) {
 // Doubles of the coefficients in the threads' order, the pivots and their
 // flags; 0 when the plan is not of this form.
 size_t pd_lu_doubles(const pd_plan p) {
-  if (p->dims != 1 || p->prec != PD_FP64 || p->uniform || p->autotune || p->tri.MR != MR ||
-      p->tri.P % 64 || p->tri.block > 512)
-    return 0;
-  return 6 * (size_t)p->tri.P * MR + 2 * (size_t)p->F2 * p->tri.P + p->F2;
+  if (p->dims != 1 || p->prec != PD_FP64 || p->uniform || p->autotune || p->n > 4096) return 0;
+  const int P = lu_threads(p->n);
+  return 6 * (size_t)P * MR + 2 * (size_t)p->F2 * P + p->F2;
 }
+
+// Blocks of a launch that sums over the frequencies.
+int pd_lu_blocks(const pd_plan p, int cus) { return std::min(lu_items(p), cus); }
 
 // Fills p->lu_tab on the plan's stream; bad, the host's end of a copy, is
 // valid once it is synchronised.  The form may be used if no entry of bad (one
 // per frequency) is then set.
 pd_status pd_lu_setup(pd_plan p, std::vector<double> &bad) {
-  const int n = p->n, P = p->tri.P;
+  const int n = p->n, P = lu_threads(n);
   bad.assign(p->F2, 1.0);
   double *piv = p->lu_tab + 6 * (size_t)P * MR, *flags = piv + 2 * (size_t)p->F2 * P;
   hipLaunchKernelGGL(lu_rows_kernel, dim3(P * MR / 64, 6), dim3(64), 0, p->stream, n, P, p->coef64,
@@ -362,15 +379,14 @@ pd_status pd_lu_setup(pd_plan p, std::vector<double> &bad) {
 }
 
 pd_status pd_launch_lu(pd_plan p, int mode, const void *in, const double *xv, void *out) {
-  const TriConfig &T = p->tri;
   const int has_mass = (mode & 0x100) ? 1 : 0;
   mode &= 0xff;
-  const int nitems = pd_tri_nitems(T, p->F2);
-  const int G = mode == 1 ? nitems : (nitems < p->tri_G ? nitems : p->tri_G);
-  const Cx *piv = reinterpret_cast<const Cx *>(p->lu_tab + 6 * (size_t)T.P * MR);
+  const int P = lu_threads(p->n), spb = LU_T / P, nitems = lu_items(p);
+  const int G = mode == 1 ? nitems : p->lu_G;
+  const Cx *piv = reinterpret_cast<const Cx *>(p->lu_tab + 6 * (size_t)P * MR);
 #define PD_LU(M, GW, IN, VIN, XV, O, PART)                                                     \
-  hipLaunchKernelGGL((lu_solve_kernel<M>), dim3(G), dim3(T.block), lu_lds(T.P, T.spb), p->stream, \
-                     p->n, p->F2, T.P, T.spb, nitems, p->lu_tab, p->lam64, piv, GW, IN, VIN, XV,  \
+  hipLaunchKernelGGL((lu_solve_kernel<M>), dim3(G), dim3(LU_T), lu_lds(P, spb), p->stream,     \
+                     p->n, p->F2, P, spb, nitems, p->lu_tab, p->lam64, piv, GW, IN, VIN, XV,     \
                      p->w, has_mass, O, PART, p->gm_skip)
   if (mode == 1)
     PD_LU(1, nullptr, static_cast<const Cx *>(in), nullptr, xv, static_cast<Cx *>(out), nullptr);

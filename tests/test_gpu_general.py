@@ -44,7 +44,9 @@ def pairs(n, nu, rng):
     return None, (lo, d, up)
 
 
-@pytest.mark.parametrize("make,n,ell,alpha", [(graded, 257, 16, 1.0), (graded, 511, 32, 1.0), (upwind, 512, 64, 1.0),
+@pytest.mark.parametrize("make,n,ell,alpha", [(graded, 5, 8, 1.0), (upwind, 40, 64, 1.0), (graded, 64, 256, 1.0),
+                                              (graded, 100, 64, 1.0), (upwind, 256, 32, 0.1), (graded, 200, 4096, 1.0),
+                                              (graded, 257, 16, 1.0), (graded, 511, 32, 1.0), (upwind, 512, 64, 1.0),
                                               (graded, 513, 32, 0.1), (upwind, 1000, 16, 1.0),
                                               (graded, 2049, 32, 1.0), (graded, 4096, 16, 1.0),
                                               (pairs, 600, 16, 0.5), (graded, 700, 2048, 1.0)])
