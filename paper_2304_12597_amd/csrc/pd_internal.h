@@ -243,7 +243,7 @@ struct pd_plan_s {
   double tau = 0, alpha = 1, w = 1;   // w = alpha^(1/ell)
   int prec = PD_FP64;
   int maxit = 64, max_sweeps = 16, check_residual = 0;
-  hipStream_t stream = nullptr;
+  hipStream_t stream = nullptr;   // changed by pd_bind_stream only
   int device = 0;
   bool mass_identity = true;
   // sqrt(ell (ell + 1) / 2) sqrt(lmax(M) / lmin(M)) when M is SPD and K SPSD
@@ -342,6 +342,15 @@ struct pd_plan_s {
   double *lu_tab = nullptr;    // general matrices: rows in thread order, pivots (tridiag_lu.hip)
   int lu_on = 0, lu_G = 0;     // lu_G: blocks (partial rows) of a launch that sums
 };
+
+// The stream that a plan's work goes to from now on.  A mixed plan and its
+// inner plan share buffers and launch in turn with nothing but the stream to
+// order them, so both move.  What was enqueued before has ended.
+inline void pd_bind_stream(pd_plan p, hipStream_t s) {
+  p->stream = s;
+  if (p->inner) p->inner->stream = s;
+}
+
 constexpr int PD_BDF_GCH = 16;   // frequency chunks of the BDF capacitance product
 
 // A named host range for profilers (roctx; shown by rocprofv3 --marker-trace):

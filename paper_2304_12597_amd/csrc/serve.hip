@@ -127,7 +127,7 @@ struct pd_server_s {
                                   job->req.M ? &job->M : nullptr, &job->K, &opt);
       }
       if (st == PD_OK) {
-        plan->stream = stream;
+        pd_bind_stream(plan, stream);   // a cached plan may come from another worker
         st = paradiag_solve(plan, job->req.u0, job->req.F, job->req.U, job->req.tol, &job->info);
       }
       {
