@@ -323,8 +323,8 @@ struct Mixed64 {
   }
 };
 
-pd_status solve_mixed64(pd_plan p, const double *u0, const double *F, double *U, double tol,
-                        pd_info *info) {
+pd_status mixed64_sweeps(pd_plan p, const double *u0, const double *F, double *U, double tol,
+                         pd_info *info) {
   const Mixed64 w{p, p->inner, u0, F, U, pd_gmres_tol(PD_FP64, tol)};
   double rel = -1.0, est = -1.0;
   bool converged = false, stalled = false;
@@ -415,6 +415,15 @@ pd_status solve_mixed64(pd_plan p, const double *u0, const double *F, double *U,
                          : "tolerance not reached");
   PD_HIP_CHECK(hipStreamSynchronize(p->stream));
   return converged ? PD_OK : PD_ENOTCONV;
+}
+
+// An error is known (from an event) before the sweep enqueued behind it has run:
+// nothing of a solve is in flight once it returns, whatever it returns.
+pd_status solve_mixed64(pd_plan p, const double *u0, const double *F, double *U, double tol,
+                        pd_info *info) {
+  const pd_status st = mixed64_sweeps(p, u0, F, U, tol, info);
+  if (st != PD_OK && st != PD_ENOTCONV) (void)hipStreamSynchronize(p->stream);
+  return st;
 }
 
 bool check_ptrs(const void *a, const void *b, const void *c) {
