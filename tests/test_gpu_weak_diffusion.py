@@ -1,0 +1,81 @@
+"""Weakly diffusive problems, whose capacitance matrix is far from the identity:
+solves at a tolerance below rounding against the modes' recurrences in extended
+precision.  D, the largest entry of J - I, multiplies the rounding of x and of
+b; the matrices' own rounding changes the exponents tau mu ell by up to their
+largest value times the unit roundoff."""
+import numpy as np
+import pytest
+
+from paper_2304_12597_amd import workloads as wl
+
+pytestmark = pytest.mark.gpu
+torch = pytest.importorskip("torch")
+
+L = np.longdouble
+BDF = {1: ([L(1)], L(1)), 2: ([L(4) / 3, -L(1) / 3], L(2) / 3), 3: ([L(18) / 11, -L(9) / 11, L(2) / 11], L(6) / 11),
+       4: ([L(48) / 25, -L(36) / 25, L(16) / 25, -L(3) / 25], L(12) / 25)}
+
+
+def rate(p, k):
+    """nu-scaled eigenvalue of M^-1 K on mode k of one direction."""
+    s2 = np.sin(k * L(np.pi) / (2 * (p.n + 1))) ** 2
+    mu = 4 * L(p.nu) * s2 * (p.n + 1) ** 2
+    return mu / (1 - 2 * s2 / 3) if p.M is not None else mu
+
+
+def series(p, s, mu, c0, a, b):
+    alpha, beta = BDF[s]
+    tau, hist, out = L(p.T) / p.ell, [L(c0)] * s, []
+    for j in range(1, p.ell + 1):
+        v = tau * beta * L(a) * np.cos(L(b) * j * tau) + sum(w * u for w, u in zip(alpha, hist))
+        hist = [v / (1 + tau * beta * mu)] + hist[:-1]
+        out.append(hist[0])
+    return np.array(out, dtype=float)
+
+
+def reference(p, s):
+    x = np.arange(1, p.n + 1) / (p.n + 1.0)
+    sine = lambda k: np.sin(k * np.pi * x)
+    if p.dims == 2:
+        return sum(series(p, s, rate(p, k) + rate(p, m), c, 0, 0)[:, None] * np.outer(sine(m), sine(k)).reshape(1, -1)
+                   for (k, m), c in p.u0_modes.items())
+    U = 0.0
+    for k in range(1, max(max(p.u0_modes), p.src_a.size) + 1):
+        a, b = (p.src_a[k - 1], p.src_b[k - 1]) if k <= p.src_a.size else (0.0, 0.0)
+        U = U + np.outer(series(p, s, rate(p, k), p.u0_modes.get(k, 0.0), a, b), sine(k))
+    return U
+
+
+def largest_entry(p, s):
+    alpha, beta = BDF[s]
+    C = np.zeros((s, s))
+    z = float(p.dims * rate(p, 1) * beta) * p.T / p.ell
+    C[0] = np.array(alpha, dtype=float) / (1 + z)
+    C[1:, :-1] += np.eye(s - 1)
+    P = np.linalg.matrix_power(C, p.ell)
+    return np.abs(P @ np.linalg.inv(np.eye(s) - P)).max()
+
+
+@pytest.mark.parametrize("kind,n,ell,nu,s", [
+    ("fem1", 63, 32, 1e-2, 3), ("fd1", 60, 128, 1e-4, 2), ("fem1", 31, 64, 1e-3, 2), ("fd1", 16, 512, 1e-3, 2),
+    ("fem1", 40, 128, 1e-4, 3), ("fd1", 31, 512, 1e-4, 4), ("fd1", 96, 32, 1e-5, 2), ("fem1", 64, 256, 1e-5, 3),
+    ("fem1", 63, 64, 1e-3, 1), ("fd1", 192, 32, 1e-4, 1), ("fd1", 257, 64, 3e-3, 3), ("fd1", 300, 64, 1e-2, 1),
+    ("fd2", 15, 16, 1e-3, 1), ("fd2", 63, 32, 1e-2, 1), ("fd2", 100, 32, 1e-2, 1)])
+def test_weakly_diffusive(lib, kind, n, ell, nu, s):
+    rng = np.random.default_rng(n + s)
+    p = wl.heat_2d(n, ell, 0.1, nu, rng) if kind == "fd2" else wl.heat_1d(kind, n, ell, 1.0, nu, rng, True)
+    dev = torch.device("cuda:0")
+    u0 = np.tile(p.u0, (s, 1)) if s > 1 else p.u0
+    F = torch.tensor(p.F, device=dev)
+    U = torch.empty_like(F)
+    kw = {"dims": 2} if kind == "fd2" else {"bdf_order": s}
+    plan = lib.paradiag_plan_create(n, ell, p.tau, p.M, p.K, stream=torch.cuda.current_stream().cuda_stream, **kw)
+    try:
+        lib.paradiag_solve(plan, torch.tensor(u0, device=dev), F, U, 1e-13, allow_notconv=True)
+        torch.cuda.synchronize()
+    finally:
+        lib.paradiag_plan_destroy(plan)
+    ref = reference(p, s)
+    err = np.linalg.norm(U.cpu().numpy() - ref) / np.linalg.norm(ref)
+    stiff = float(p.dims * rate(p, n)) * p.T
+    assert err <= 2.0**-53 * (32 * (1 + largest_entry(p, s)) + stiff), err
