@@ -412,6 +412,10 @@ Line2DConfig pd_choose_line2d(int n, int F2, int prec, int cus) {
   return L;
 }
 
+double pd_line2d_theta(const pd_plan p, int m) {
+  return p->uni[4] + 2.0 * p->uni[3] * std::cos((m + 1) * M_PI / (p->n + 1));
+}
+
 // Factors for every (k, m): b = lambda_k + tau theta_m + tau T_d, a = c = tau T_off.
 // float64 plans into fac, the others rounded to float into fac32.
 void pd_line2d_factors(const pd_plan p, std::vector<double> &fac, std::vector<float> &fac32) {
@@ -425,7 +429,7 @@ void pd_line2d_factors(const pd_plan p, std::vector<double> &fac, std::vector<fl
   const double tl = p->uni[3], td = p->uni[4];
   const bool scan = pd_line2d_scan(p);
   std::vector<double> th(n);
-  for (int m = 0; m < n; ++m) th[m] = td + 2.0 * tl * std::cos((m + 1) * M_PI / (n + 1));
+  for (int m = 0; m < n; ++m) th[m] = pd_line2d_theta(p, m);
   const int mblk = (n + 63) / 64;   // units of 64 lines of a frequency
   pd_parallel_rows(F2 * mblk, 4, [&](int unit) {
     const int k = unit / mblk, ma = (unit - k * mblk) * 64, mb = ma + 64 < n ? ma + 64 : n;

@@ -444,6 +444,7 @@ int pd_dst_chirp_length(int n);
 pd_status pd_launch_dst_rows1d(pd_plan p, int mode, const double *u0, const double *F,
                                const double *in, double *out);
 Line2DConfig pd_choose_line2d(int n, int F2, int prec, int cus);
+double pd_line2d_theta(const pd_plan p, int m);   // the eigenvalue of line m along x
 void pd_line2d_factors(const pd_plan p, std::vector<double> &fac, std::vector<float> &fac32);
 pd_status pd_launch_line2d(pd_plan p, int mode, const void *in, const double *xv, void *out);
 void pd_line2d_set_attributes(size_t max_lds);
@@ -487,8 +488,9 @@ pd_status pd_cp_launch_batch(const CpJob *jobs, const int2 *map1, int nb1, const
                              size_t lds2, const int *active, int jv, hipStream_t s);
 // the capacitance solve in the sine eigenbasis (sinecap.hip)
 size_t pd_sc_max_doubles(int n, int s);
-bool pd_sc_build(pd_plan p, const std::vector<double> &fac, const std::vector<double> &ct,
-                 std::vector<double> &tab);
+bool pd_sc_choose(pd_plan p);
+size_t pd_sc_size(pd_plan p);
+pd_status pd_sc_finish(pd_plan p, std::vector<double> &s2);
 ScJob pd_sc_job(pd_plan p, const double *bin, double *x);
 size_t pd_sc_lds(const ScJob &J, int MX);
 pd_status pd_sc_enqueue(pd_plan p, const double *bin, double *x, double rtol);
@@ -497,9 +499,9 @@ pd_status pd_sc_batch(const ScJob *jobs, int count, const int2 *map, int nblocks
                       int MX, double rtol, double *status, hipStream_t s);
 void pd_sc_set_attributes(size_t max_lds);
 size_t pd_sc2_max_doubles(int n);
-bool pd_sc2_build(pd_plan p, std::vector<double> &tab);
+bool pd_sc2_choose(pd_plan p);
 size_t pd_sc2_size(pd_plan p);
-pd_status pd_sc2_finish(pd_plan p);
+pd_status pd_sc2_finish(pd_plan p, std::vector<double> &tab);
 // GMRES on diag(1 + Phi, 1) from (c + c2, rho), rho^2 = the sum of rpart (gmres.hip)
 pd_status pd_gmres_diag(pd_plan p, int nc, double *c, const double *c2, const double *Phi,
                         const double *rpart, int nparts, double *y, double rtol);

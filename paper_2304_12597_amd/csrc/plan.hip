@@ -802,12 +802,12 @@ static pd_status create_plan(pd_plan *out, int n, int ell, double tau, const pd_
       }
     }
   }
-  std::vector<double> cptab, sctab, lubad;
-  if (pd_sc_build(p, fac, bg_ct, sctab)) {
+  std::vector<double> cptab, scs2, lubad;
+  if (p->dims == 1 && pd_sc_choose(p)) {
     p->sc_on = 1;
     p->cp_on = 0;
   }
-  if (pd_sc2_build(p, sctab)) p->sc_on = 1;
+  if (p->dims == 2 && pd_sc2_choose(p)) p->sc_on = 1;
   if (p->cp_on) pd_cp_tables(p, cptab);
   const size_t nbar = p->nbar;
   p->spec_bytes = L.spec_bytes;
@@ -884,7 +884,7 @@ static pd_status create_plan(pd_plan *out, int n, int ell, double tau, const pd_
   if (p->cp_on) PD_TRY(dev_alloc(&p->cp_tab, p->cpl.total));
   if (L.lu) PD_TRY(dev_alloc(&p->lu_tab, L.lu));
   if (p->sc_on)
-    PD_TRY(dev_alloc(&p->sc_tab, p->dims == 2 ? pd_sc2_size(p) : sctab.size()));
+    PD_TRY(dev_alloc(&p->sc_tab, p->dims == 2 ? pd_sc2_size(p) : pd_sc_size(p)));
   if (p->krylov == PD_KRYLOV_FOM) {
     PD_TRY(dev_alloc(&p->fom, L.fom));
     PD_TRY(dev_alloc(reinterpret_cast<unsigned char **>(&p->fom_h), L.fom_h_bytes));
@@ -928,9 +928,8 @@ static pd_status create_plan(pd_plan *out, int n, int ell, double tau, const pd_
     PD_TRY(upload(p->fac32, fac32, p->stream));
   if (p->cp_on) PD_TRY(upload(p->cp_tab, cptab, p->stream));
   if (L.lu) PD_TRY(pd_lu_setup(p, lubad));
-  if (p->sc_on) PD_TRY(upload(p->sc_tab, sctab, p->stream));
-  if (p->sc_on && p->dims == 2) PD_TRY(pd_sc2_finish(p));
   if (p->bdf_s > 1) PD_TRY(upload(p->bdf_g, bg_gt, p->stream));
+  if (p->sc_on) PD_TRY(p->dims == 2 ? pd_sc2_finish(p, scs2) : pd_sc_finish(p, scs2));
   if (p->krylov == PD_KRYLOV_FOM) {
     std::vector<double> mf;
     pd_fom_mass_factors(p, mf);

@@ -18,10 +18,9 @@
 // of r coordinates and an s x s matrix per mode (I + C_j^ell (I - C_j^ell)^-1
 // up to similarity, C_j the mode's companion matrix).
 //
-// D is not taken from the closed form but summed over the frequencies from
-// the same rounded constants that the passes' solves use (the recurrence
-// form's r_k and 1/kappa_k act on mode j as 1 / (kappa_k ((1 - r_k)^2 +
-// 4 r_k sin^2(theta_j / 2)))), so that J stays consistent with pass B and C.
+// D is not taken from the closed form but summed over the frequencies from the
+// eigenvalues of the matrices P_k as the passes' tables round them, so that J
+// stays consistent with pass B and C (sc_phi_kernel).
 //
 // Three launches, whatever the iteration count: project (sums pass B's
 // partials into b and projects each 64-column block on the modes), norm
@@ -34,12 +33,12 @@
 // the combination took 87; n = 4095, alpha = 0.01: 7.0 + 6.6 + 15.6, before 150;
 // n <= 256 in one launch, n = 63 11.7 us.  Sums run in a fixed order and the batched
 // launches use the same bodies, so results are the same alone and in a batch.
+#include "pd_dd.h"
 #include "pd_internal.h"
 #include "pd_small.h"
 
 #include <algorithm>
 #include <cmath>
-#include <complex>
 
 namespace {
 
@@ -537,33 +536,83 @@ sc2_tile_kernel(int n, int ns, int q, const double *__restrict__ S,
   }
 }
 
-// Phi[j][m] = D(m, j) summed over the frequencies (once per plan): with the
-// recurrence form's constants of line (k, m), or the exact eigenvalues.
-// th[i]: the line operator's eigenvalues, s2[i] = sin^2(theta_i / 2).
-__global__ void __launch_bounds__(64)
-sc2_phi_kernel(int n, int F2, int q, size_t NF, int scan, const cpx<double> *__restrict__ fac,
-               const double *__restrict__ lam, const double *__restrict__ gJ,
-               const double *__restrict__ th, const double *__restrict__ s2,
-               double *__restrict__ Phi) {
-  const int m = blockIdx.y, j = blockIdx.x * 64 + threadIdx.x;
-  if (j >= q) return;
-  const double sj = 4.0 * s2[j], kap = th[m] + th[j];
-  double t = 0.0;
-  for (int k = 0; k < F2; ++k) {
-    const double gr = gJ[2 * k], gi = gJ[2 * k + 1];
-    cpx<double> den, num = {1.0, 0.0};
-    if (scan) {
-      const cpx<double> *f = fac + ((size_t)k * n + m) * NF;
-      const cpx<double> r = f[0], e = {1.0 - r.re, -r.im};
-      num = f[4];
-      den = cpx<double>{e.re * e.re - e.im * e.im + sj * r.re, 2.0 * e.re * e.im + sj * r.im};
-    } else {
-      den = cpx<double>{lam[2 * k] + kap, lam[2 * k + 1]};
+// ---- tables, once per plan ----
+
+// Orthonormal sine vectors j = 1..r in rows of ns entries, zero past n, and zero
+// rows past r.  Grid: (ns / 64, ceil(rows / 4)).
+__global__ void __launch_bounds__(256)
+sc_rows_kernel(int n, int r, int rows, int ns, double *__restrict__ S) {
+  const int i = blockIdx.x * 64 + (threadIdx.x & 63), j = blockIdx.y * 4 + (threadIdx.x >> 6);
+  if (j >= rows) return;
+  const int N = n + 1, q = (int)((long)(j + 1) * (i + 1) % (2 * N));
+  int a = q > N ? 2 * N - q : q;          // folded into [0, pi / 2]
+  if (2 * a > N) a = N - a;
+  const double v = sqrt(2.0 / N) * sinpi((double)a / (double)N);
+  S[(size_t)j * ns + i] = (j < r && i < n) ? (q > N ? -v : v) : 0.0;
+}
+
+// Off-diagonal and diagonal entries of M and tau K, and their eigenvalues on the
+// mode with sin^2(theta / 2) = s2: (d + 2 o) - 4 o s2.
+struct SymmetricPair {
+  double m[2], k[2];
+};
+__device__ __forceinline__ pd_dd sc_eigenvalue(const double (&o)[2], pd_dd s2) {
+  return dd_add(dd_two_sum(o[1], 2.0 * o[0]), dd_mul(pd_dd{-4.0 * o[0], 0.0}, s2));
+}
+// The same of the symmetric complex matrix (o, d)
+__device__ __forceinline__ pd_ddc sc_eigenvalue(cpx<double> o, cpx<double> d, pd_dd s2) {
+  return pd_ddc{sc_eigenvalue({o.re, d.re}, s2), sc_eigenvalue({o.im, d.im}, s2)};
+}
+
+// Phi (J - I on the modes) sums terms of size up to D over the frequencies, and
+// an error in it is one of x, which the solution multiplies by D again: in plain
+// double, from the recurrence form's rounded constants, the error of U at D = 30
+// was up to 7 times the J product's (n = 511, 64 steps, BDF3, nu = 0.003: 6.5e-14
+// against 9.3e-15, now 1.5e-14; over 340 problems of D <= 1000 the two forms' errors
+// now differ by 0.99 in the mean, 1.6 at most).  The sums are double-double, a block
+// each; s2: sin^2(theta_j / 2), [r] high parts, then [r] low parts.
+// P_k's entries are rounded as the passes' tables round them (pd_uniform_factors):
+// near theta = 0 that rounding changes its eigenvalues most.
+// BDF: weight gamma^(k) theta^(h), g [s][F2], theta from tw.  Grid: (r, s s).
+__global__ void __launch_bounds__(256)
+sc_phi_kernel(int F2, int r, int s, SymmetricPair u, const double *__restrict__ lam,
+              const cpx<double> *__restrict__ g, const cpx<double> *__restrict__ tw, int ell,
+              const double *__restrict__ s2s, double *__restrict__ Phi) {
+  const int j = blockIdx.x, b = blockIdx.y / s, h = blockIdx.y - b * s;
+  const pd_dd s2 = {s2s[j], s2s[r + j]};
+  const pd_ddc m = {sc_eigenvalue(u.m, s2), pd_dd{0.0, 0.0}};
+  pd_dd t = {0.0, 0.0};
+  for (int k = threadIdx.x; k < F2; k += 256) {
+    cpx<double> P[2];
+    for (int i = 0; i < 2; ++i) {
+      const double v = lam[2 * k] * u.m[i];   // rounded before the sum
+      P[i] = cpx<double>{v + u.k[i], lam[2 * k + 1] * u.m[i]};
     }
-    const cpx<double> z = cmul(num, crecip(den));
-    t += gr * z.re - gi * z.im;
+    const pd_ddc z = dd_cdiv(m, sc_eigenvalue(P[0], P[1], s2));   // P_k^{-1} M on the mode
+    pd_ddc w = dd_cplx(g[(size_t)b * F2 + k]);
+    if (s > 1) w = dd_cmul(w, dd_cplx(tw[(k * h) & (ell - 1)]));
+    t = dd_add(t, dd_cmul(w, z).re);
   }
-  Phi[(size_t)j * q + m] = t;
+  t = dd_block_sum(t);
+  if (threadIdx.x == 0) Phi[(size_t)blockIdx.y * r + j] = t.h;
+}
+
+// The same in 2D (M = I): Phi[j][m] = D(m, j), th[m] the eigenvalue of line m as
+// pd_line2d_factors rounds it.  Grid: (q, q).
+__global__ void __launch_bounds__(64)
+sc2_phi_kernel(int F2, int q, double off, double diag, const double *__restrict__ th,
+               const double *__restrict__ lam, const cpx<double> *__restrict__ g,
+               const double *__restrict__ s2s, double *__restrict__ Phi) {
+  const int m = blockIdx.x, j = blockIdx.y;
+  const pd_dd s2 = {s2s[j], s2s[q + j]};
+  pd_dd t = {0.0, 0.0};
+  for (int k = threadIdx.x; k < F2; k += 64) {
+    const cpx<double> d = {lam[2 * k] + th[m] + diag, lam[2 * k + 1]};
+    const pd_ddc z = dd_cdiv(dd_cplx({1.0, 0.0}), sc_eigenvalue({off, 0.0}, d, s2));
+    t = dd_add(t, dd_cmul(dd_cplx(g[k]), z).re);
+  }
+  t = dd_block_sum(t);
+  if (threadIdx.x == 0) Phi[(size_t)j * q + m] = t.h;
 }
 
 // ---- host: eigenvalues, the number of modes, tables ----
@@ -583,24 +632,15 @@ Mode mode_of(pd_plan p, int j) {
   return o;
 }
 
-// Rows j = 1..r of the orthonormal sine vectors, ns entries apart.  sin(pi q /
-// (n + 1)) comes from one table of arguments folded into [0, pi / 2].
-void sine_rows(int n, int r, int ns, double *S) {
-  const int N = n + 1;
-  const double sc = std::sqrt(2.0 / N);
-  std::vector<double> quarter((size_t)N / 2 + 1);
-  for (int a = 0; a <= N / 2; ++a) quarter[a] = sc * std::sin(M_PI * (double)a / (double)N);
-  pd_parallel_rows(r, 1 + 65536 / n, [&](int j) {
-    double *row = S + (size_t)j * ns;
-    int q = 0;   // (j + 1) i mod 2 N
-    for (int i = 0; i < n; ++i) {
-      q += j + 1;
-      if (q >= 2 * N) q -= 2 * N;
-      int a = q > N ? 2 * N - q : q;
-      if (2 * a > N) a = N - a;
-      row[i] = q > N ? -quarter[a] : quarter[a];
-    }
-  });
+// sin^2(theta_j / 2), j = 1..r: high parts, then low parts.
+void mode_s2(int n, int r, std::vector<double> &out) {
+  out.resize(2 * (size_t)r);
+  const long double pi = 3.14159265358979323846264338327950288L;
+  for (int j = 1; j <= r; ++j) {
+    const long double s = std::sin(pi * j / (2.0L * (n + 1))), v = s * s;
+    out[j - 1] = (double)v;
+    out[r + j - 1] = (double)(v - (long double)out[j - 1]);
+  }
 }
 
 // J - I on a mode with ratio z = tau kappa / m (BDF: tau beta kappa / m).
@@ -678,13 +718,13 @@ size_t pd_sc_max_doubles(int n, int s) {
   return sc_doubles(n, s, std::min(n, SC_DMAX / s));
 }
 
-// Tables of a plan whose capacitance system is solved in the sine basis;
-// false (nothing changed) when the plan is not of that kind: see below.
-// fac: the shifted solves' constants; ct: BDF's weights [s][s][F2] complex.
-bool pd_sc_build(pd_plan p, const std::vector<double> &fac, const std::vector<double> &ct,
-                 std::vector<double> &tab) {
+size_t pd_sc_size(pd_plan p) { return sc_doubles(p->n, p->bdf_s, p->sc_r); }
+
+// Whether the plan's capacitance system is solved in the sine basis, and with
+// how many modes (nothing changed if not: see below).
+bool pd_sc_choose(pd_plan p) {
   const double *u = p->uni;
-  const int n = p->n, s = p->bdf_s, F2 = p->F2;
+  const int n = p->n, s = p->bdf_s;
   // float64 GMRES plans on uniform 1D grids with symmetric M and K
   if (p->dims != 1 || p->prec != PD_FP64 || p->krylov != PD_KRYLOV_GMRES || p->sine ||
       p->autotune || !p->uniform || u[0] != u[2] || u[3] != u[5])
@@ -709,10 +749,10 @@ bool pd_sc_build(pd_plan p, const std::vector<double> &fac, const std::vector<do
     if (r * s > SC_DMAX) return false;
   }
   if (r < 1) r = 1;
-  // The passes apply a rounded factorisation of every P_k; J must apply the
-  // same one.  The recurrence form's is known in closed form (above).  The
-  // partition form's is not: there the modes' exact eigenvalues differ from
-  // it by cond(P_0) u, which must not show.  Backward Euler's b comes from a pass
+  // The passes apply a rounded factorisation of every P_k, and J has to apply
+  // the same.  The recurrence form's scans carry powers of the rounded matrix's
+  // own root, so its eigenvalues are right over many rows.  The partition form's
+  // elimination is off by cond(P_0) u, which must not show.  Backward Euler's b comes from a pass
   // of its own, whose rounding is that large anyway (errors at n <= 256, limit
   // 1e-12, as with the product).  BDF's b is taken from U_1, and a consistent J
   // corrects U_1's rounding with it: at a limit of 1e-12 errors were up to 135
@@ -723,47 +763,45 @@ bool pd_sc_build(pd_plan p, const std::vector<double> &fac, const std::vector<do
   p->sc_r = r;
   p->sc_ns = ns;
   p->sc_nblk = nblk;
-  tab.assign(sc_doubles(n, s, r), 0.0);
-  sine_rows(n, r, ns, tab.data());
-  double *Phi = &tab[(size_t)r * ns];
-  const size_t NF = 6 * (size_t)(p->tri.MR - 1);
-  using C = std::complex<double>;
-  for (int j = 1; j <= r; ++j) {
-    const Mode q = mode_of(p, j);
-    for (int k = 0; k < F2; ++k) {
-      C z;   // P_k^{-1} M on the mode
-      if (scan) {
-        const double *f = &fac[(size_t)k * NF * 2];
-        const C rk(f[0], f[1]), ik(f[8], f[9]), e = 1.0 - rk;
-        z = q.m * ik / (e * e + 4.0 * q.s2 * rk);
-      } else {
-        z = q.m / (C(p->lam[2 * k], p->lam[2 * k + 1]) * q.m + q.kap);
-      }
-      if (s == 1) {
-        Phi[j - 1] += p->gJ[2 * k] * z.real() - p->gJ[2 * k + 1] * z.imag();
-      } else {
-        for (int b = 0; b < s * s; ++b) {
-          const double *g = &ct[2 * ((size_t)b * F2 + k)];
-          Phi[(size_t)b * r + j - 1] += g[0] * z.real() - g[1] * z.imag();
-        }
-      }
-    }
-  }
   return true;
 }
 
+// S and Phi on the device, after the tables they are made from are in place;
+// s2: host end of a copy, valid until the plan's stream is synchronised.
+pd_status pd_sc_finish(pd_plan p, std::vector<double> &s2) {
+  const int n = p->n, r = p->sc_r, s = p->bdf_s;
+  mode_s2(n, r, s2);
+  double *d = static_cast<double *>(p->spec);   // 2 r <= 2 n entries, not yet in use
+  PD_HIP_CHECK(hipMemcpyAsync(d, s2.data(), s2.size() * sizeof(double), hipMemcpyHostToDevice,
+                              p->stream));
+  hipLaunchKernelGGL(sc_rows_kernel, dim3(p->sc_ns / 64, (r + 3) / 4), dim3(256), 0, p->stream, n,
+                     r, r, p->sc_ns, p->sc_tab);
+  SymmetricPair u;
+  for (int i = 0; i < 2; ++i) {
+    u.m[i] = p->uni[i];
+    u.k[i] = p->uni[3 + i];
+  }
+  hipLaunchKernelGGL(sc_phi_kernel, dim3(r, s * s), dim3(256), 0, p->stream, p->F2, r, s, u,
+                     p->lam64,
+                     reinterpret_cast<const cpx<double> *>(s == 1 ? p->gJ64 : p->bdf_g),
+                     reinterpret_cast<const cpx<double> *>(p->tw64), p->ell, d,
+                     p->sc_tab + (size_t)r * p->sc_ns);
+  PD_HIP_CHECK(hipGetLastError());
+  return PD_OK;
+}
+
 // 2D: the sine modes along y of the lines m < q, q^2 + 1 coordinates for the
-// one-block GMRES; Phi is formed on the device by pd_sc2_finish.
+// one-block GMRES.
 constexpr int SC2_QMAX = 127;    // q^2 + 1 <= 16384 entries
 static int sc2_rows(int q) { return (q + 15) / 16 * 16; }
 static int sc2_tiles(int n) { return ((n + 63) / 64) * ((n + 15) / 16); }
 static size_t sc2_doubles(int n, int q) {
   const size_t q2 = (size_t)q * q;
-  return (size_t)sc2_rows(q) * sc_stride(n) + 4 * (q2 + 2) + 2 * (size_t)q + sc2_tiles(n);
+  return (size_t)sc2_rows(q) * sc_stride(n) + 4 * (q2 + 2) + 3 * (size_t)q + sc2_tiles(n);
 }
 size_t pd_sc2_max_doubles(int n) { return sc2_doubles(n, std::min(n, SC2_QMAX)); }
 
-bool pd_sc2_build(pd_plan p, std::vector<double> &tab) {
+bool pd_sc2_choose(pd_plan p) {
   const double *u = p->uni;
   const int n = p->n;
   // float64 GMRES plans of backward Euler with symmetric T
@@ -788,26 +826,19 @@ bool pd_sc2_build(pd_plan p, std::vector<double> &tab) {
   if (!pd_line2d_scan(p) && !(worst * cond0 * 0x1p-53 <= 1e-12)) return false;
   p->sc_r = q;
   p->sc_ns = sc_stride(n);
-  tab.assign((size_t)sc2_rows(q) * p->sc_ns + 2 * (size_t)q, 0.0);
-  sine_rows(n, q, p->sc_ns, tab.data());
-  for (int j = 1; j <= q; ++j) {
-    const Mode md = mode_of(p, j);
-    tab[(size_t)sc2_rows(q) * p->sc_ns + j - 1] = md.kap;
-    tab[(size_t)sc2_rows(q) * p->sc_ns + q + j - 1] = md.s2;
-  }
   return true;
 }
 size_t pd_sc2_size(pd_plan p) { return sc2_doubles(p->n, p->sc_r); }
 
 namespace {
 struct Sc2 {
-  double *S, *th, *s2, *Phi, *c, *c2, *y, *rpart;
+  double *S, *s2, *th, *Phi, *c, *c2, *y, *rpart;
   explicit Sc2(pd_plan p) {
     const size_t q = p->sc_r, q2 = q * q + 2;
     S = p->sc_tab;
-    th = S + (size_t)sc2_rows(p->sc_r) * p->sc_ns;
-    s2 = th + q;
-    Phi = s2 + q;
+    s2 = S + (size_t)sc2_rows(p->sc_r) * p->sc_ns;
+    th = s2 + 2 * q;
+    Phi = th + q;
     c = Phi + q2;
     c2 = c + q2;
     y = c2 + q2;
@@ -816,12 +847,17 @@ struct Sc2 {
 };
 }  // namespace
 
-pd_status pd_sc2_finish(pd_plan p) {
+pd_status pd_sc2_finish(pd_plan p, std::vector<double> &tab) {
   const Sc2 t(p);
-  const int q = p->sc_r;
-  hipLaunchKernelGGL(sc2_phi_kernel, dim3((q + 63) / 64, q), dim3(64), 0, p->stream, p->n, p->F2,
-                     q, pd_line2d_entries(p), pd_line2d_scan(p) ? 1 : 0,
-                     reinterpret_cast<const cpx<double> *>(p->fac64), p->lam64, p->gJ64, t.th,
+  const int n = p->n, q = p->sc_r, rows = sc2_rows(q);
+  mode_s2(n, q, tab);
+  for (int m = 0; m < q; ++m) tab.push_back(pd_line2d_theta(p, m));
+  PD_HIP_CHECK(hipMemcpyAsync(t.s2, tab.data(), tab.size() * sizeof(double),
+                              hipMemcpyHostToDevice, p->stream));
+  hipLaunchKernelGGL(sc_rows_kernel, dim3(p->sc_ns / 64, rows / 4), dim3(256), 0, p->stream, n, q,
+                     rows, p->sc_ns, t.S);
+  hipLaunchKernelGGL(sc2_phi_kernel, dim3(q, q), dim3(64), 0, p->stream, p->F2, q, p->uni[3],
+                     p->uni[4], t.th, p->lam64, reinterpret_cast<const cpx<double> *>(p->gJ64),
                      t.s2, t.Phi);
   PD_HIP_CHECK(hipGetLastError());
   return PD_OK;
