@@ -325,7 +325,7 @@ struct Mixed64 {
 
 pd_status mixed64_sweeps(pd_plan p, const double *u0, const double *F, double *U, double tol,
                          pd_info *info) {
-  const Mixed64 w{p, p->inner, u0, F, U, pd_gmres_tol(PD_FP64, tol)};
+  const Mixed64 w{p, p->inner, u0, F, U, pd_gmres_tol(p->inner->sc_on ? PD_FP64 : p->prec, tol)};
   double rel = -1.0, est = -1.0;
   bool converged = false, stalled = false;
   int its = 0;

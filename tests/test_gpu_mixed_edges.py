@@ -37,3 +37,23 @@ def test_a_failed_solve_leaves_nothing_running(lib, dims, n, ell, bad):
     finally:
         for plan in plans:
             lib.paradiag_plan_destroy(plan)
+
+
+@pytest.mark.parametrize("dims,n,ell,nu", [(1, 258, 8, 1e-4), (1, 511, 64, 1e-4), (2, 128, 2, 1e-3)])
+def test_capacitance_iterations_of_a_sweep(lib, dims, n, ell, nu):
+    """More modes than the sine-basis solve holds: GMRES with J products, which a
+    sweep iterates to 1e-7 (its right-hand side is rounded to float32), not to
+    tol / 100 = 1e-10: it stops at the first residual below its tolerance."""
+    rng = np.random.default_rng(n)
+    p = wl.heat_2d(n, ell, 0.1, nu, rng) if dims == 2 else wl.heat_1d("fd1", n, ell, 1.0, nu, rng, True)
+    dev = torch.device("cuda:0")
+    u0, F = torch.tensor(p.u0, device=dev), torch.tensor(p.F, device=dev)
+    U = torch.empty_like(F)
+    plan = lib.paradiag_plan_create(n, ell, p.tau, p.M, p.K, dims=dims, precision=lib.PD_MIXED,
+                                    stream=torch.cuda.current_stream().cuda_stream)
+    try:
+        info = lib.paradiag_solve(plan, u0, F, U, 1e-8)
+    finally:
+        lib.paradiag_plan_destroy(plan)
+    assert info.sweeps >= 2 and info.rel_residual <= 1e-8
+    assert 1e-10 < info.gmres_rel_residual <= 1e-7
