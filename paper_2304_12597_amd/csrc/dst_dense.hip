@@ -188,6 +188,18 @@ size_t pd_dst_dense_doubles(int n) {
   return 2 * (size_t)(n + 1) + (size_t)s.tiles * (s.ki / 8) * 256;
 }
 
+// Whether the product is the faster form for this many rows.  Its time hardly
+// depends on them until every CU has its blocks of 32 (one a CU for n > 316, else
+// two), and is that of one block, which grows with n^2; the chirp-z form takes one
+// or two rows a block and grows from some 1000 rows on.  Chirp-z / product, us:
+// n = 100: 9.1 / 4.5 at 2 rows, 13.4 / 5.4 at 4096; n = 160: 8.7 / 8.8 and 20.2 /
+// 10.1; n = 200: 9.6 / 10.9 at 512, 13.3 / 11.3 at 2048; n = 300: 16.5 / 20.3 at 1024,
+// 25.1 / 20.8 at 2048; n = 400: 25.5 / 34.6 at 2048, 44.8 / 37.0 at 4096; n = 440:
+// 11.3 / 35.5 at 2, 45.1 / 41.1 at 4096.
+bool pd_dst_dense_pays(int n, long rows) {
+  return n <= 144 || rows >= (n <= 316 ? 6L : 10L) * n;
+}
+
 // q (2N doubles at the start of the table) is in place on the stream.
 pd_status pd_dst_dense_build(int n, double *tab, hipStream_t stream) {
   hipLaunchKernelGGL(dense_table_kernel, dim3(64), dim3(256), 0, stream, n, sqrt(2.0 / (n + 1)),

@@ -264,7 +264,7 @@ fft_inverse_kernel(int N, int nbar, int C, int stride, const cpx<R> *__restrict_
 // Z[k] = 2 S_b[k] - 2i S_a[k].
 // MODE 0: v = h (tau f + u0 at t = 0); 1: v = float64 residual R (norms to
 // red); 2: v = in.  ACC: out += S instead of out = S.
-// Modes 0 and 2 run here for n < 31 only (dst_odd.hip, dst_dense.hip).
+// Modes 0 and 2 run here for n < 31 only (dst_odd.hip).
 template <int MODE, int ACC>
 __global__ void __launch_bounds__(1024)
 dst_x_kernel(int n, int ell, int C, int stride, double tau, const double *__restrict__ u0,
@@ -673,7 +673,7 @@ static Stencil2 pd_stencil2(pd_plan p) {
 
 pd_status pd_launch_dst_x(pd_plan p, int mode, const double *u0, const double *F,
                           const double *U, const double *in, double *out, int accumulate) {
-  if (p->twd_dense && mode != 1)
+  if (p->twd_dense && mode != 1 && pd_dst_dense_pays(p->n, (long)p->ell * p->n))
     return pd_launch_dst_dense(p->n, p->ell * p->n, mode, p->tau, u0, p->nbar, F, in,
                                p->twd + p->twd_dense, out, accumulate, p->stream);
   if (pd_dst_odd_ok(p->n) && mode != 1)
@@ -713,7 +713,7 @@ pd_status pd_launch_dst_x(pd_plan p, int mode, const double *u0, const double *F
 // added to it): the mode-2 transform on a [trows][nbar] array.
 pd_status pd_launch_dst_x_rows(pd_plan p, const double *in, double *out, int trows,
                                int accumulate) {
-  if (p->twd_dense)
+  if (p->twd_dense && pd_dst_dense_pays(p->n, (long)trows * p->n))
     return pd_launch_dst_dense(p->n, trows * p->n, 2, p->tau, nullptr, 0, nullptr, in,
                                p->twd + p->twd_dense, out, accumulate, p->stream);
   if (pd_dst_odd_ok(p->n))
@@ -754,7 +754,7 @@ pd_status pd_launch_dst_x_rows(pd_plan p, const double *in, double *out, int tro
 pd_status pd_launch_dst_rows1d(pd_plan p, int mode, const double *u0, const double *F,
                                const double *in, double *out) {
   if (!p->dst_L) return PD_EINVAL;
-  if (p->twd_dense)
+  if (p->twd_dense && pd_dst_dense_pays(p->n, p->ell))
     return pd_launch_dst_dense(p->n, p->ell, mode == 0 ? 0 : 2, p->tau, u0, p->n, F, in,
                                p->twd + p->twd_dense, out, 0, p->stream);
   const int N = p->dst_L, C = p->dst_C;

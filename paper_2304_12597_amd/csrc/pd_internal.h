@@ -429,6 +429,7 @@ pd_status pd_launch_dst_x(pd_plan p, int mode, const double *u0, const double *F
                           const double *U, const double *in, double *out, int accumulate);
 int pd_choose_dst_C(int n);
 size_t pd_dst_dense_doubles(int n);
+bool pd_dst_dense_pays(int n, long rows);
 pd_status pd_dst_dense_build(int n, double *tab, hipStream_t stream);
 pd_status pd_launch_dst_dense(int n, int rows, int mode, double tau, const double *u0, long nu0,
                               const double *F, const double *in, const double *tab, double *out,
