@@ -60,7 +60,9 @@ def largest_entry(p, s):
     ("fem1", 63, 32, 1e-2, 3), ("fd1", 60, 128, 1e-4, 2), ("fem1", 31, 64, 1e-3, 2), ("fd1", 16, 512, 1e-3, 2),
     ("fem1", 40, 128, 1e-4, 3), ("fd1", 31, 512, 1e-4, 4), ("fd1", 96, 32, 1e-5, 2), ("fem1", 64, 256, 1e-5, 3),
     ("fem1", 63, 64, 1e-3, 1), ("fd1", 192, 32, 1e-4, 1), ("fd1", 257, 64, 3e-3, 3), ("fd1", 300, 64, 1e-2, 1),
-    ("fd2", 15, 16, 1e-3, 1), ("fd2", 63, 32, 1e-2, 1), ("fd2", 100, 32, 1e-2, 1)])
+    ("fd2", 15, 16, 1e-3, 1), ("fd2", 63, 32, 1e-2, 1), ("fd2", 100, 32, 1e-2, 1),
+    # the limits of the 2D sine-basis solve: 96 modes a direction, from 200 points a side on 127
+    ("fd2", 96, 32, 1e-3, 1), ("fd2", 97, 32, 1e-3, 1), ("fd2", 199, 64, 2.8e-3, 1), ("fd2", 200, 64, 2.8e-3, 1)])
 def test_weakly_diffusive(lib, kind, n, ell, nu, s):
     rng = np.random.default_rng(n + s)
     p = wl.heat_2d(n, ell, 0.1, nu, rng) if kind == "fd2" else wl.heat_1d(kind, n, ell, 1.0, nu, rng, True)
