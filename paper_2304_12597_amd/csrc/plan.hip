@@ -172,6 +172,15 @@ bool pd_mixed64_ok(const pd_plan p, const pd_plan q64) {
          (p->dims == 1 ? p->n <= 8192 && pd_use_scan(q64) : pd_line2d_scan(q64));
 }
 
+pd_status compute_layout(pd_plan p, int cus, size_t max_lds, Layout &L);
+// The layout of a plan that the caller can do without: no message is left.
+bool try_layout(pd_plan p, int cus, size_t max_lds, Layout &L) {
+  const std::string kept = g_last_error;
+  const bool ok = compute_layout(p, cus, max_lds, L) == PD_OK;
+  g_last_error = kept;
+  return ok;
+}
+
 // Fills p->fft_C, fft_stride, tri, tri_G, l2d, dst_C; returns PD_OK or
 // PD_ENOTSUP when a tile does not fit in LDS.
 pd_status compute_layout(pd_plan p, int cus, size_t max_lds, Layout &L) {
@@ -315,7 +324,7 @@ pd_status compute_layout(pd_plan p, int cus, size_t max_lds, Layout &L) {
     pd_plan_s q = *p;
     q.prec = PD_FP64;
     Layout L64;
-    if (compute_layout(&q, cus, max_lds, L64) == PD_OK && pd_mixed64_ok(p, &q)) {
+    if (try_layout(&q, cus, max_lds, L64) && pd_mixed64_ok(p, &q)) {
       L.partials = std::max(L.partials, L64.partials);
       L.rstage = std::max(L.rstage, L64.rstage);
       L.red = std::max(L.red, L64.red);
@@ -671,7 +680,7 @@ static pd_status create_plan(pd_plan *out, int n, int ell, double tau, const pd_
       p->lu_G = pd_lu_blocks(p, cus);
       L.partials = std::max(L.partials, (size_t)p->lu_G * n);
       L.rstage = std::max(L.rstage, (size_t)((p->lu_G + 15) / 16) * n);
-      if (compute_layout(&u, cus, max_lds, Lu) != PD_OK || L.total_bytes() > Lu.total_bytes()) {
+      if (!try_layout(&u, cus, max_lds, Lu) || L.total_bytes() > Lu.total_bytes()) {
         L = partition;
         L.lu = 0;
       }

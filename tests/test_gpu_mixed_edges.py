@@ -57,3 +57,13 @@ def test_capacitance_iterations_of_a_sweep(lib, dims, n, ell, nu):
         lib.paradiag_plan_destroy(plan)
     assert info.sweeps >= 2 and info.rel_residual <= 1e-8
     assert 1e-10 < info.gmres_rel_residual <= 1e-7
+
+
+@pytest.mark.parametrize("n,ell", [(8192, 16), (8193, 16), (16383, 8)])
+def test_creation_leaves_no_message(lib, n, ell):
+    """Past n = 8192 a complex128 row does not fit and the complex64 solves are
+    kept: that is no failure of the creation."""
+    p = wl.heat_1d("fd1", n, ell, 1.0, 0.5, np.random.default_rng(0), False)
+    lib.paradiag_plan_destroy(lib.paradiag_plan_create(n, ell, p.tau, p.M, p.K, precision=lib.PD_MIXED,
+                                                       stream=torch.cuda.current_stream().cuda_stream))
+    assert lib.paradiag_last_error() == ""
