@@ -34,7 +34,7 @@ bool batchable(const pd_plan *plans, int count) {
     const pd_plan p = plans[i];
     if (!p || p->dims != 1 || !p->uniform || p->prec != p0->prec || p->prec == PD_MIXED ||
         p->tri.block != pd_tri_block_threads(p->prec) ||
-        p->maxit != p0->maxit || p->sc_on != p0->sc_on || p->early_exit || p->sine || p->krylov || p->bdf_s > 1 ||
+        p->maxit != p0->maxit || p->early_exit || p->sine || p->krylov || p->bdf_s > 1 ||
         !pd_gmres_fused_ok(p))
       return false;
     for (int j = 0; j < i; ++j)
@@ -72,8 +72,9 @@ struct BatchRun {
   const int2 *t0J = nullptr, *rmJ = nullptr;
   const CpJob *cj = nullptr;
   const int2 *c1m = nullptr, *c2m = nullptr, *c3m = nullptr;
-  // capacitance solves in the sine basis (every problem of the batch, or none)
-  int sc = 0, nsc = 0;
+  // the first nls problems' capacitance GMRES runs in lockstep, the others'
+  // capacitance systems are solved in the sine basis
+  int nls = 0, nsc = 0;
   const ScJob *sj = nullptr;
   const int2 *scm = nullptr;
   size_t sc_lds = 0;
@@ -94,6 +95,7 @@ std::mutex g_runs_mu;
 std::list<std::unique_ptr<BatchRun>> g_runs;   // most recent first
 constexpr size_t kMaxRuns = 4;
 
+// plans: those without the sine-basis capacitance solve first.
 pd_status build_run(BatchRun &r, const pd_plan *plans, int count, const double *const *u0,
                     const double *const *F, double *const *U) {
   const pd_plan p0 = plans[0];
@@ -104,15 +106,15 @@ pd_status build_run(BatchRun &r, const pd_plan *plans, int count, const double *
   r.prec = prec;
   r.MX = MX;
   r.s = p0->stream;
-  r.sc = p0->sc_on;
+  while (r.nls < count && !plans[r.nls]->sc_on) ++r.nls;
   {
     std::vector<FftJob> fj(count);
     std::vector<TriJob> tj(count);
-    std::vector<VecJob> vj(count);
+    std::vector<VecJob> vj(r.nls);
     std::vector<int2> fftmap, tri0map, tri1map, vmap, redmap, tri0mapJ, redmapJ;
     std::vector<CpJob> cj(count);
     std::vector<int2> c1map, c2map, c3map, k0map, scmap;
-    std::vector<ScJob> sj(r.sc ? count : 0);
+    std::vector<ScJob> sj(count - r.nls);
     int cthreads2 = 64;
     size_t clds1 = 0, clds2 = 0;
     int fft_threads = 64;
@@ -164,6 +166,13 @@ pd_status build_run(BatchRun &r, const pd_plan *plans, int count, const double *
       for (int b = 0; b < t.nblk; ++b) t1b[bi].push_back(make_int2(i, b));
       ldsb[bi] = std::max(ldsb[bi], pd_tri_lds(p));   // batchable: the same packing as p->tri
 
+      if (i >= r.nls) {
+        ScJob &j = sj[i - r.nls];
+        j = pd_sc_job(p, nullptr, p->xvec);
+        for (int b = 0; b < j.nblk; ++b) scmap.push_back(make_int2(i - r.nls, b));
+        r.sc_lds = std::max(r.sc_lds, pd_sc_lds(j, MX));
+        continue;
+      }
       VecJob &v = vj[i];
       v.n = p->nbar; v.B = pd_vec_blocks(p->nbar); v.G = t.nblk;
       v.V = p->V; v.w = p->wvec; v.x = p->xvec; v.red1 = p->red;
@@ -171,11 +180,7 @@ pd_status build_run(BatchRun &r, const pd_plan *plans, int count, const double *
       v.bout = p->bvec; v.b = p->bvec; v.done = p->gm + pd_gmres_done_index(MX);
       for (int b = 0; b < v.B; ++b) vmap.push_back(make_int2(i, b));
       for (int b = 0; b < (p->nbar + 255) / 256; ++b) redmap.push_back(make_int2(i, b));
-      if (r.sc) {
-        sj[i] = pd_sc_job(p, nullptr, p->xvec);
-        for (int b = 0; b < sj[i].nblk; ++b) scmap.push_back(make_int2(i, b));
-        r.sc_lds = std::max(r.sc_lds, pd_sc_lds(sj[i], MX));
-      } else if (p->cp_on) {
+      if (p->cp_on) {
         // J products of this problem by the chunked capacitance product (jobs
         // indexed by problem, like the activity flags)
         const CpJob J = pd_cp_job(p, p->V, p->wvec, p->gm + pd_gmres_done_index(MX));
@@ -364,16 +369,17 @@ pd_status j_products(const BatchRun &r, int j, const int *act, hipStream_t s) {
 pd_status enqueue_solve(const BatchRun &r, int K, double rtol, hipStream_t s) {
   PD_B(pd_launch_fft_forward_batch(r.prec, r.fj, r.fm, r.nf, r.fft_threads, r.fft_lds, s));
   PD_B(tri_batch(r, 0, r.tj, r.t0, &TB::o0, &TB::n0, nullptr, 0, s));
-  if (r.sc) {
-    PD_B(pd_sc_batch(r.sj, r.count, r.scm, r.nsc, r.sc_lds, r.MX, rtol, r.st, s));
-  } else {
+  if (r.nls < r.count)
+    PD_B(pd_sc_batch(r.sj, r.count - r.nls, r.scm, r.nsc, r.sc_lds, r.MX, rtol,
+                     r.st + 4 * (size_t)r.nls, s));
+  if (r.nls > 0) {
     PD_B(pd_launch_reduce_batch(r.vj, r.rm, r.nr, -1, nullptr, s));
-    PD_B(pd_gmres_batch_start(r.vj, r.count, r.MX, r.st, s));
+    PD_B(pd_gmres_batch_start(r.vj, r.nls, r.MX, r.st, s));
     for (int j = 0; j < K; ++j) {
       PD_B(j_products(r, j, nullptr, s));
-      PD_B(pd_gmres_batch_arnoldi(r.vj, r.count, j, r.MX, rtol, r.st, nullptr, s));
+      PD_B(pd_gmres_batch_arnoldi(r.vj, r.nls, j, r.MX, rtol, r.st, nullptr, s));
     }
-    PD_B(pd_gmres_batch_finish(r.vj, r.vm, r.nv, r.count, r.MX, nullptr, s));
+    PD_B(pd_gmres_batch_finish(r.vj, r.vm, r.nv, r.nls, r.MX, nullptr, s));
   }
   PD_B(tri_batch(r, 1, r.tj, r.t1, &TB::o1, &TB::n1, nullptr, 0, s));
   PD_B(pd_launch_fft_inverse_batch(r.prec, r.fj, r.fm, r.nf, r.fft_threads, r.fft_lds, s));
@@ -387,26 +393,26 @@ bool converged(const double *st, double rtol) {
   return beta == 0.0 || res <= rtol * beta || hn == 0.0;
 }
 
-// Problems still iterating after K steps (all at iteration K) continue
-// with host-checked steps; then pass A is redone for every problem (pass C
+// Problems of the lockstep GMRES still iterating after K steps (all at iteration
+// K) continue with host-checked steps; then pass A is redone for every problem (pass C
 // overwrote the spectra) and the tail is run again.
 pd_status finish_unconverged(const BatchRun &r, int K, double rtol) {
   const hipStream_t s = r.s;
-  std::vector<int> act(r.count);
+  std::vector<int> act(r.nls);
   int nact = 0;
-  for (int i = 0; i < r.count; ++i) {
+  for (int i = 0; i < r.nls; ++i) {
     act[i] = !converged(r.pin + 4 * i, rtol) && (int)r.pin[4 * i + 2] < r.MX;
     nact += act[i];
   }
   if (nact == 0) return PD_OK;
   for (int j = K; j < r.MX && nact > 0; ++j) {
-    PD_HIP_CHECK(hipMemcpyAsync(r.act, act.data(), r.count * sizeof(int), hipMemcpyHostToDevice, s));
+    PD_HIP_CHECK(hipMemcpyAsync(r.act, act.data(), r.nls * sizeof(int), hipMemcpyHostToDevice, s));
     PD_B(j_products(r, j, r.act, s));
-    PD_B(pd_gmres_batch_arnoldi(r.vj, r.count, j, r.MX, rtol, r.st, r.act, s));
+    PD_B(pd_gmres_batch_arnoldi(r.vj, r.nls, j, r.MX, rtol, r.st, r.act, s));
     PD_HIP_CHECK(hipMemcpyAsync(r.pin, r.st, 4 * (size_t)r.count * sizeof(double),
                                 hipMemcpyDeviceToHost, s));
     PD_HIP_CHECK(hipStreamSynchronize(s));
-    for (int i = 0; i < r.count; ++i) {
+    for (int i = 0; i < r.nls; ++i) {
       if (!act[i]) continue;
       const double *st = r.pin + 4 * i;
       if (!std::isfinite(st[0]) || converged(st, rtol)) {
@@ -416,7 +422,7 @@ pd_status finish_unconverged(const BatchRun &r, int K, double rtol) {
     }
   }
   PD_B(pd_launch_fft_forward_batch(r.prec, r.fj, r.fm, r.nf, r.fft_threads, r.fft_lds, s));
-  PD_B(pd_gmres_batch_finish(r.vj, r.vm, r.nv, r.count, r.MX, nullptr, s));
+  PD_B(pd_gmres_batch_finish(r.vj, r.vm, r.nv, r.nls, r.MX, nullptr, s));
   PD_B(tri_batch(r, 1, r.tj, r.t1, &TB::o1, &TB::n1, nullptr, 0, s));
   PD_B(pd_launch_fft_inverse_batch(r.prec, r.fj, r.fm, r.nf, r.fft_threads, r.fft_lds, s));
   PD_HIP_CHECK(hipStreamSynchronize(s));
@@ -440,16 +446,38 @@ pd_status pd_solve_batch_impl(const pd_plan *plans, int count, const double *con
   const pd_plan p0 = plans[0];
   const int MX = p0->maxit;
   const double rtol = pd_gmres_tol(p0->prec, tol);
-  bool learned = true;
+  int nls = 0;   // problems of the lockstep GMRES: in front
+  for (int i = 0; i < count; ++i) nls += !plans[i]->sc_on;
+  for (int i = 0; i < nls; ++i)
+    if (plans[i]->sc_on) {
+      std::vector<int> at(count);
+      for (int j = 0, a = 0, b = nls; j < count; ++j) at[plans[j]->sc_on ? b++ : a++] = j;
+      std::vector<pd_plan> op(count);
+      std::vector<const double *> ou(count), of(count);
+      std::vector<double *> oU(count);
+      std::vector<pd_info> oi(infos ? count : 0);
+      for (int j = 0; j < count; ++j) {
+        op[j] = plans[at[j]];
+        ou[j] = u0[at[j]];
+        of[j] = F[at[j]];
+        oU[j] = U[at[j]];
+        if (infos) oi[j] = infos[at[j]];
+      }
+      const pd_status st = pd_solve_batch_impl(op.data(), count, ou.data(), of.data(), oU.data(),
+                                               tol, infos ? oi.data() : nullptr);
+      if (infos)
+        for (int j = 0; j < count; ++j) infos[at[j]] = oi[j];
+      return st;
+    }
+  bool learned = nls > 0;
   int K = 1;
-  for (int i = 0; i < count; ++i) {
+  for (int i = 0; i < nls; ++i) {
     learned = learned && plans[i]->gm_seen;
     K = std::max(K, plans[i]->gm_pred);
   }
-  // in the sine basis the iterations need no launches of their own: seven
-  // launches in all, enqueued directly
-  K = p0->sc_on ? 0 : std::min(K, MX);
-  learned = learned && !p0->sc_on;
+  // in the sine basis the iterations need no launches of their own: without
+  // a lockstep GMRES the launches are few and enqueued directly
+  K = nls > 0 ? std::min(K, MX) : 0;
   std::vector<const void *> key;
   key.reserve(4 * (size_t)count);
   for (int i = 0; i < count; ++i) key.push_back(plans[i]);
@@ -514,7 +542,7 @@ pd_status pd_solve_batch_impl(const pd_plan *plans, int count, const double *con
       return PD_ENONFINITE;
     }
   }
-  if (!run->sc) PD_B(finish_unconverged(*run, K, rtol));
+  if (run->nls > 0) PD_B(finish_unconverged(*run, K, rtol));
 
   pd_status worst = PD_OK;
   for (int i = 0; i < count; ++i) {
