@@ -743,7 +743,6 @@ void pd_cp_tables(pd_plan p, std::vector<double> &tab) {
   const int F2 = p->F2, N0 = c.N0, NL = c.NL, Q = c.Q;
   tab.assign(c.total, 0.0);
   const double ml = p->uni[0], md = p->uni[1], tkl = p->uni[3], tkd = p->uni[4];
-  std::vector<HC> fa((size_t)N0), fb((size_t)NL), ha((size_t)N0 + 2), hb((size_t)NL + 2);
   auto put = [&tab](size_t at, HC z) {
     tab[at] = z.re;
     tab[at + 1] = z.im;
@@ -783,7 +782,8 @@ void pd_cp_tables(pd_plan p, std::vector<double> &tab) {
   c.pair = p->ell % 2 == 0 && F2 >= 5 && last % 4 == 0 && p->lam[1] == 0.0 &&
            p->gJ[1] == 0.0 && p->lam[2 * last + 1] == 0.0 && p->gJ[2 * last + 1] == 0.0;
   c.G1run = c.pair ? last / 4 : c.G1;
-  for (int k = 0; k < F2; ++k) {
+  auto frequency = [&](int k, std::vector<HC> &fa, std::vector<HC> &fb, std::vector<HC> &ha,
+                       std::vector<HC> &hb) {
     const HC lam{p->lam[2 * k], p->lam[2 * k + 1]};
     const HC g{p->gJ[2 * k], p->gJ[2 * k + 1]};
     const HC a{lam.re * ml + tkl, lam.im * ml};
@@ -833,7 +833,24 @@ void pd_cp_tables(pd_plan p, std::vector<double> &tab) {
     const HC di_L = hsub(b, hmul(a2, fb[0]));
     const HC vals[8] = {a, lo_i, di_i, lo_i, di_pen, up_pen, lo_L, di_L};
     for (int w = 0; w < 8; ++w) put(c.red + 2 * ((size_t)k * 8 + w), vals[w]);
+  };
+  // rows of different frequencies are apart: split over the host's threads where
+  // there is work for them (n = 8191, ell = 512: 2.1 ms), each with its own scratch
+  struct Scratch {
+    std::vector<HC> fa, fb, ha, hb;
+  };
+  const int parts = F2 >= 8 && (size_t)F2 * (N0 + NL) > 65536 ? 8 : 1;
+  std::vector<Scratch> scratch(parts);
+  for (auto &x : scratch) {
+    x.fa.resize(N0);
+    x.fb.resize(NL);
+    x.ha.resize((size_t)N0 + 2);
+    x.hb.resize((size_t)NL + 2);
   }
+  pd_parallel_rows(parts, 1, [&](int t) {
+    Scratch &x = scratch[t];
+    for (int k = t; k < F2; k += parts) frequency(k, x.fa, x.fb, x.ha, x.hb);
+  });
   // the chunk-local term L r_c: zero exactly when every rho_i is zero in
   // float64 (long horizons: (1 + tau kappa_1 / m_1)^ell overflows the terms)
   std::vector<double> Lh0, Lh1;

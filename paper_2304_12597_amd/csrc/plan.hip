@@ -67,7 +67,7 @@ void chirp_tables(int n, int L, double *chirp, double *bhat) {
     br[q] = chirp[2 * a];
     bi[q] = -chirp[2 * a + 1];
   }
-  for (int k = 0; k < L; ++k) {
+  pd_parallel_rows(L, 1 + 32768 / n, [&](int k) {
     long double sr = 0.0L, si = 0.0L;
     for (int d = -(n - 1); d <= n - 1; ++d) {
       const int q = d >= 0 ? d : d + L;
@@ -77,7 +77,7 @@ void chirp_tables(int n, int L, double *chirp, double *bhat) {
     }
     bhat[2 * k] = (double)(sr / L);
     bhat[2 * k + 1] = (double)(si / L);
-  }
+  });
 }
 
 bool is_pow2(int v) { return v > 0 && (v & (v - 1)) == 0; }
@@ -573,7 +573,10 @@ static pd_status create_plan(pd_plan *out, int n, int ell, double tau, const pd_
     coef[4 * n + i] = tk * K->diag[i];
     coef[5 * n + i] = (i < n - 1) ? tk * K->upper[i] : 0.0;
   }
-  std::vector<float> coef32(coef.begin(), coef.end());
+  // (an inner plan takes the tables that depend on the problem alone from its
+  // host: tables are formed for it only where they are its own)
+  std::vector<float> coef32;
+  if (!host) coef32.assign(coef.begin(), coef.end());
   // Error bound factor.  With M symmetric positive definite and K symmetric
   // positive semi-definite, the scaled step (I + tau M^-1/2 K M^-1/2)^-1 has
   // norm at most 1, so the error E of any U solves a block-bidiagonal system
@@ -642,19 +645,23 @@ static pd_status create_plan(pd_plan *out, int n, int ell, double tau, const pd_
       p->lam[2 * k + 1] = (k == 0 || 2 * k == ell) ? 0.0 : -si;
     }
   }
-  std::vector<float> lam32(p->lam.begin(), p->lam.end());
-  std::vector<double> tw(2 * (size_t)ell);
-  for (int m = 0; m < ell; ++m) {
-    double c, s;
-    cis(m, ell, c, s);
-    tw[2 * m] = c;
-    tw[2 * m + 1] = -s;
-  }
-  std::vector<float> tw32(tw.begin(), tw.end());
-  std::vector<double> dal(2 * (size_t)ell);
-  for (int t = 0; t < ell; ++t) {
-    dal[t] = (opt.alpha == 1.0) ? 1.0 : std::pow(opt.alpha, (double)t / ell);
-    dal[ell + t] = (opt.alpha == 1.0) ? 1.0 : std::pow(opt.alpha, -(double)t / ell);
+  std::vector<float> lam32, tw32;
+  std::vector<double> tw, dal;
+  if (!host) {
+    lam32.assign(p->lam.begin(), p->lam.end());
+    tw.resize(2 * (size_t)ell);
+    for (int m = 0; m < ell; ++m) {
+      double c, s;
+      cis(m, ell, c, s);
+      tw[2 * m] = c;
+      tw[2 * m + 1] = -s;
+    }
+    tw32.assign(tw.begin(), tw.end());
+    dal.resize(2 * (size_t)ell);
+    for (int t = 0; t < ell; ++t) {
+      dal[t] = (opt.alpha == 1.0) ? 1.0 : std::pow(opt.alpha, (double)t / ell);
+      dal[ell + t] = (opt.alpha == 1.0) ? 1.0 : std::pow(opt.alpha, -(double)t / ell);
+    }
   }
 
   // launch configurations and sizes
@@ -695,8 +702,11 @@ static pd_status create_plan(pd_plan *out, int n, int ell, double tau, const pd_
   std::vector<double> fac;
   std::vector<float> fac32;
   std::vector<double> twd;
-  if (p->dims == 2) {
+  if (p->dims == 2)
     pd_line2d_factors(p, fac, fac32);
+  else if (p->uniform)
+    pd_uniform_factors(p, p->tri.MR, fac);
+  if (p->dims == 2 && !host) {
     const int N = p->dst_L ? p->dst_L : 2 * (n + 1);
     twd.assign(p->twd_cos + (size_t)n, 0.0);
     for (int m = 0; m < N; ++m) {
@@ -711,8 +721,6 @@ static pd_status create_plan(pd_plan *out, int n, int ell, double tau, const pd_
       cis(j + 1, 2 * (n + 1), c, s);
       twd[p->twd_cos + j] = c;
     }
-  } else if (p->uniform) {
-    pd_uniform_factors(p, p->tri.MR, fac);
   }
   if (p->dims == 1 && p->prec != PD_FP64) fac32.assign(fac.begin(), fac.end());
   std::vector<double> sq, swN, stwH, sm, sk;   // sine-basis plans
@@ -726,7 +734,7 @@ static pd_status create_plan(pd_plan *out, int n, int ell, double tau, const pd_
     }
     chirp_tables(n, p->dst_L, &twd[p->twd_chirp], &twd[p->twd_bhat]);
   }
-  if (p->twd_dense) {
+  if (p->twd_dense && !host) {
     const int N2 = 2 * (n + 1);
     twd.resize(p->twd_dense + N2);
     for (int m = 0; m < N2; ++m) {
@@ -965,12 +973,17 @@ static pd_status create_plan(pd_plan *out, int n, int ell, double tau, const pd_
     PD_TRY(upload(p->sine_k, sk, p->stream));
   }
 #undef PD_TRY
-  if (hipStreamSynchronize(p->stream) != hipSuccess) {
+  // (with an inner plan its creation synchronises, for the copies of both)
+  if (!L.inner && hipStreamSynchronize(p->stream) != hipSuccess) {
     pd_set_error("stream synchronisation failed during plan creation");
     free_plan(p);
     return PD_EHIP;
   }
   p->lu_on = L.lu && std::find(lubad.begin(), lubad.end(), 1.0) == lubad.end();
+  if (L.lu && !p->lu_on) {
+    (void)hipFree(p->lu_tab);
+    p->lu_tab = nullptr;
+  }
   if (p->autotune) {
     const pd_status ts = autotune(p, cus, max_lds);
     if (ts != PD_OK) {
