@@ -420,7 +420,8 @@ pd_status pd_launch_tridiag(pd_plan p, int mode, const void *in,
 // the same for general matrices by two recurrences (tridiag_lu.hip)
 size_t pd_lu_doubles(const pd_plan p);
 int pd_lu_blocks(const pd_plan p, int cus);
-pd_status pd_lu_setup(pd_plan p, std::vector<double> &bad);
+pd_status pd_lu_setup(pd_plan p);
+pd_status pd_lu_flags(pd_plan p, std::vector<double> &bad);
 pd_status pd_launch_lu(pd_plan p, int mode, const void *in, const double *xv, void *out);
 void pd_lu_set_attributes(size_t max_lds);
 // 2D: orthonormal DST-I along x of every row. mode 0: h from (u0, F);

@@ -859,14 +859,20 @@ static pd_status create_plan(pd_plan *out, int n, int ell, double tau, const pd_
       return st;       \
     }                  \
   } while (0)
+  if (!host) {
+    PD_TRY(dev_alloc(&p->coef64, coef.size()));
+    PD_TRY(dev_alloc(&p->lam64, p->lam.size()));
+    if (L.lu) PD_TRY(dev_alloc(&p->lu_tab, L.lu));
+    PD_TRY(upload(p->coef64, coef, p->stream));
+    PD_TRY(upload(p->lam64, p->lam, p->stream));
+    if (L.lu) PD_TRY(pd_lu_setup(p));
+  }
   if (p->prec == PD_FP64)
     PD_TRY(dev_alloc(&p->fac64, std::max(fac.size(), L.fac)));
   else
     PD_TRY(dev_alloc(&p->fac32, std::max(fac32.size(), L.fac)));
   if (!host) {
-    PD_TRY(dev_alloc(&p->coef64, coef.size()));
     PD_TRY(dev_alloc(&p->coef32, coef32.size()));
-    PD_TRY(dev_alloc(&p->lam64, p->lam.size()));
     PD_TRY(dev_alloc(&p->lam32, lam32.size()));
     PD_TRY(dev_alloc(&p->gB64, p->gB.size()));
     PD_TRY(dev_alloc(&p->gJ64, p->gJ.size()));
@@ -899,7 +905,6 @@ static pd_status create_plan(pd_plan *out, int n, int ell, double tau, const pd_
     PD_TRY(dev_alloc(&p->red, L.red));
   }
   if (p->cp_on) PD_TRY(dev_alloc(&p->cp_tab, p->cpl.total));
-  if (L.lu) PD_TRY(dev_alloc(&p->lu_tab, L.lu));
   if (p->sc_on)
     PD_TRY(dev_alloc(&p->sc_tab, p->dims == 2 ? pd_sc2_size(p) : pd_sc_size(p)));
   if (p->krylov == PD_KRYLOV_FOM) {
@@ -927,9 +932,7 @@ static pd_status create_plan(pd_plan *out, int n, int ell, double tau, const pd_
     return PD_ENOMEM;
   }
   if (!host) {
-    PD_TRY(upload(p->coef64, coef, p->stream));
     PD_TRY(upload(p->coef32, coef32, p->stream));
-    PD_TRY(upload(p->lam64, p->lam, p->stream));
     PD_TRY(upload(p->lam32, lam32, p->stream));
     PD_TRY(upload(p->gB64, p->gB, p->stream));
     PD_TRY(upload(p->gJ64, p->gJ, p->stream));
@@ -944,7 +947,7 @@ static pd_status create_plan(pd_plan *out, int n, int ell, double tau, const pd_
   else
     PD_TRY(upload(p->fac32, fac32, p->stream));
   if (p->cp_on) PD_TRY(upload(p->cp_tab, cptab, p->stream));
-  if (L.lu) PD_TRY(pd_lu_setup(p, lubad));
+  if (L.lu) PD_TRY(pd_lu_flags(p, lubad));
   if (p->bdf_s > 1) PD_TRY(upload(p->bdf_g, bg_gt, p->stream));
   if (p->sc_on) PD_TRY(p->dims == 2 ? pd_sc2_finish(p, scs2) : pd_sc_finish(p, scs2));
   if (p->krylov == PD_KRYLOV_FOM) {

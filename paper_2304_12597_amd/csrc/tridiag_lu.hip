@@ -369,20 +369,30 @@ size_t pd_lu_doubles(const pd_plan p) {
 // Blocks of a launch that sums over the frequencies.
 int pd_lu_blocks(const pd_plan p, int cus) { return std::min(lu_items(p), cus); }
 
-// Fills p->lu_tab on the plan's stream; bad, the host's end of a copy, is
-// valid once it is synchronised.  The form may be used if no entry of bad (one
-// per frequency) is then set.
-pd_status pd_lu_setup(pd_plan p, std::vector<double> &bad) {
+static double *lu_flags(pd_plan p) {
+  const int P = lu_threads(p->n);
+  return p->lu_tab + 6 * (size_t)P * MR + 2 * (size_t)p->F2 * P;
+}
+
+// Fills p->lu_tab on the plan's stream from coef64 and lam64, the first tables
+// of a creation: the pivots are formed while the host makes the others.
+pd_status pd_lu_setup(pd_plan p) {
   const int n = p->n, P = lu_threads(n);
-  bad.assign(p->F2, 1.0);
-  double *piv = p->lu_tab + 6 * (size_t)P * MR, *flags = piv + 2 * (size_t)p->F2 * P;
+  double *piv = p->lu_tab + 6 * (size_t)P * MR;
   hipLaunchKernelGGL(lu_rows_kernel, dim3(P * MR / 64, 6), dim3(64), 0, p->stream, n, P, p->coef64,
                      p->lu_tab);
   hipLaunchKernelGGL(lu_pivots_kernel, dim3(p->F2), dim3(64), 0, p->stream, n, P, p->coef64,
-                     p->lam64, reinterpret_cast<Cx *>(piv), flags);
+                     p->lam64, reinterpret_cast<Cx *>(piv), lu_flags(p));
   PD_HIP_CHECK(hipGetLastError());
-  PD_HIP_CHECK(hipMemcpyAsync(bad.data(), flags, p->F2 * sizeof(double), hipMemcpyDeviceToHost,
-                              p->stream));
+  return PD_OK;
+}
+
+// bad, the host's end of a copy, is valid once the stream is synchronised.  The
+// form may be used if no entry of bad (one per frequency) is then set.
+pd_status pd_lu_flags(pd_plan p, std::vector<double> &bad) {
+  bad.assign(p->F2, 1.0);
+  PD_HIP_CHECK(hipMemcpyAsync(bad.data(), lu_flags(p), p->F2 * sizeof(double),
+                              hipMemcpyDeviceToHost, p->stream));
   return PD_OK;
 }
 
