@@ -332,7 +332,9 @@ typedef struct {
 pd_status pd_server_create(pd_server *out, int workers, size_t budget_bytes);
 
 /* Queue a request; returns at once with a ticket (>= 0).  PD_EBUDGET if the
- * request alone can never fit the budget.  The server copies *req (but not
+ * request alone can never fit the budget (a request whose arrays and
+ * paradiag_plan_bytes do not fit runs with a plan without the tables of the
+ * faster forms where that fits).  The server copies *req (but not
  * the arrays). */
 pd_status pd_server_submit(pd_server s, const pd_request *req, long *ticket);
 

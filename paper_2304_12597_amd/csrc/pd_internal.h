@@ -283,6 +283,10 @@ struct pd_plan_s {
   int gm_pred = 2;             // GMRES iterations enqueued ahead (the last solve's count)
   int gm_seen = 0;             // a solve has run (gm_pred is learned)
   int autotune = 0;            // buffers sized for every tuning candidate
+  int lean = 0;                // only the forms without tables of their own: capacitance
+                               // products, partition solves of general matrices, complex64
+                               // solves of mixed plans, FFT forms of the DST (n = 8191, 32
+                               // steps: 9 MB where a plan of the fast forms reserves 21)
   int early_exit = 0;          // Algorithm 3's test on U_1 before the correction
   int krylov = 0;              // capacitance solver: 0 GMRES, 1 Algorithm 2
   int fom_q = 1;               // Algorithm 2: residual check every fom_q steps
@@ -342,6 +346,11 @@ struct pd_plan_s {
   double *lu_tab = nullptr;    // general matrices: rows in thread order, pivots (tridiag_lu.hip)
   int lu_on = 0, lu_G = 0;     // lu_G: blocks (partial rows) of a launch that sums
 };
+
+// paradiag_plan_create and paradiag_plan_bytes, lean or not
+pd_status pd_plan_create(pd_plan *out, int n, int ell, double tau, const pd_tridiag *M,
+                         const pd_tridiag *K, const pd_options *opt, int lean);
+size_t pd_plan_bytes(int n, int ell, const pd_options *opt, int lean);
 
 // The stream that a plan's work goes to from now on.  A mixed plan and its
 // inner plan share buffers and launch in turn with nothing but the stream to

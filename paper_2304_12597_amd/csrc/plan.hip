@@ -188,7 +188,7 @@ pd_status compute_layout(pd_plan p, int cus, size_t max_lds, Layout &L) {
   const size_t cb = (p->prec == PD_FP64) ? 16 : 8;
   // the DST along x as a product: its tables after the FFT forms'
   auto dense = [&] {
-    const size_t d = pd_dst_dense_doubles(n);
+    const size_t d = p->lean ? 0 : pd_dst_dense_doubles(n);
     p->twd_dense = d ? (L.twd + 1) / 2 * 2 : 0;   // 16-byte aligned
     if (d) L.twd = p->twd_dense + d;
   };
@@ -289,9 +289,9 @@ pd_status compute_layout(pd_plan p, int cus, size_t max_lds, Layout &L) {
     p->cpl = pd_cp_layout(n, F2);
     L.cp = p->cpl.total;
   }
-  if (p->prec == PD_FP64 && p->dims == 1 && p->uniform && !p->sine)
+  if (p->prec == PD_FP64 && p->dims == 1 && p->uniform && !p->sine && !p->lean)
     L.cp = std::max(L.cp, pd_sc_max_doubles(n, p->bdf_s));
-  if (p->prec == PD_FP64 && p->dims == 2 && p->bdf_s == 1) L.cp = pd_sc2_max_doubles(n);
+  if (p->prec == PD_FP64 && p->dims == 2 && p->bdf_s == 1 && !p->lean) L.cp = pd_sc2_max_doubles(n);
   L.coef = 6 * (size_t)n;
   L.lam = 2 * (size_t)F2;
   L.tw = 2 * (size_t)ell;
@@ -299,7 +299,7 @@ pd_status compute_layout(pd_plan p, int cus, size_t max_lds, Layout &L) {
   L.spec_bytes = (size_t)F2 * p->nbar * cb;
   if (p->prec == PD_MIXED) L.spec2_bytes = L.spec_bytes;
   // 2D: the sine-basis capacitance solve has up to nbar + 1 coordinates
-  L.vec = p->ncap + (p->dims == 2 ? 2 : 0);
+  L.vec = p->ncap + (p->dims == 2 && !p->lean ? 2 : 0);
   L.V = (size_t)(p->maxit + 1) * L.vec;
   L.gm = pd_gmres_state_doubles(p->maxit);
   const int B = pd_vec_blocks(p->ncap);
@@ -319,7 +319,7 @@ pd_status compute_layout(pd_plan p, int cus, size_t max_lds, Layout &L) {
   }
   L.red = red_n;
   L.fac_bytes = p->prec == PD_FP64 ? 8 : 4;
-  if (p->prec == PD_MIXED && p->uniform) {
+  if (p->prec == PD_MIXED && p->uniform && !p->lean) {
     // the buffers that the inner float64 plan shares hold both plans' needs
     pd_plan_s q = *p;
     q.prec = PD_FP64;
@@ -499,9 +499,10 @@ extern "C" void paradiag_default_options(pd_options *opt) {
   opt->bdf_order = 1;
 }
 
-// host: the mixed plan whose inner plan this is (its buffers are shared), or null
+// host: the mixed plan whose inner plan this is (its buffers are shared), or null;
+// lean: see pd_plan_s
 static pd_status create_plan(pd_plan *out, int n, int ell, double tau, const pd_tridiag *M,
-                             const pd_tridiag *K, const pd_options &opt, pd_plan host) {
+                             const pd_tridiag *K, const pd_options &opt, pd_plan host, int lean) {
   pd_plan p = new (std::nothrow) pd_plan_s();
   if (!p) {
     pd_set_error("out of host memory");
@@ -527,6 +528,7 @@ static pd_status create_plan(pd_plan *out, int n, int ell, double tau, const pd_
   p->stream = reinterpret_cast<hipStream_t>(opt.stream);
   p->mass_identity = (M == nullptr);
   p->bdf_s = opt.bdf_order;
+  p->lean = lean;
   p->borrowed = host ? 1 : 0;
   p->in32 = host ? 1 : 0;
   bdf_coefficients(p->bdf_s, &p->bdf_beta, p->bdf_alpha);
@@ -678,7 +680,7 @@ static pd_status create_plan(pd_plan *out, int n, int ell, double tau, const pd_
     // known and counts a uniform plan's tables, so the recurrences' tables are
     // made only where they take no more than those (for many frequencies they
     // would; those plans keep the partition form).
-    L.lu = pd_lu_doubles(p);
+    L.lu = p->lean ? 0 : pd_lu_doubles(p);
     if (L.lu) {
       pd_plan_s u = *p;
       u.uniform = true;
@@ -820,11 +822,11 @@ static pd_status create_plan(pd_plan *out, int n, int ell, double tau, const pd_
     }
   }
   std::vector<double> cptab, scs2, lubad;
-  if (p->dims == 1 && pd_sc_choose(p)) {
+  if (p->dims == 1 && !p->lean && pd_sc_choose(p)) {
     p->sc_on = 1;
     p->cp_on = 0;
   }
-  if (p->dims == 2 && pd_sc2_choose(p)) p->sc_on = 1;
+  if (p->dims == 2 && !p->lean && pd_sc2_choose(p)) p->sc_on = 1;
   if (p->cp_on) pd_cp_tables(p, cptab);
   const size_t nbar = p->nbar;
   p->spec_bytes = L.spec_bytes;
@@ -1006,7 +1008,7 @@ static pd_status create_plan(pd_plan *out, int n, int ell, double tau, const pd_
       free_plan(p);
       return PD_EHIP;
     }
-    const pd_status is = create_plan(&p->inner, n, ell, tau, M, K, o64, p);
+    const pd_status is = create_plan(&p->inner, n, ell, tau, M, K, o64, p, 0);
     if (is != PD_OK) {
       p->spec2 = nullptr;
       free_plan(p);
@@ -1017,9 +1019,8 @@ static pd_status create_plan(pd_plan *out, int n, int ell, double tau, const pd_
   return PD_OK;
 }
 
-extern "C" pd_status paradiag_plan_create(pd_plan *out, int n, int ell, double tau,
-                                          const pd_tridiag *M, const pd_tridiag *K,
-                                          const pd_options *opt_in) {
+pd_status pd_plan_create(pd_plan *out, int n, int ell, double tau, const pd_tridiag *M,
+                         const pd_tridiag *K, const pd_options *opt_in, int lean) {
   PdRange whole("paradiag_plan_create");
   g_last_error.clear();
   if (!out) {
@@ -1036,7 +1037,13 @@ extern "C" pd_status paradiag_plan_create(pd_plan *out, int n, int ell, double t
     pd_set_error(msg);
     return st;
   }
-  return create_plan(out, n, ell, tau, M, K, opt, nullptr);
+  return create_plan(out, n, ell, tau, M, K, opt, nullptr, lean);
+}
+
+extern "C" pd_status paradiag_plan_create(pd_plan *out, int n, int ell, double tau,
+                                          const pd_tridiag *M, const pd_tridiag *K,
+                                          const pd_options *opt_in) {
+  return pd_plan_create(out, n, ell, tau, M, K, opt_in, 0);
 }
 
 extern "C" pd_status paradiag_plan_check(int n, int ell, double tau, const pd_tridiag *M,
@@ -1074,7 +1081,7 @@ extern "C" pd_status paradiag_plan_destroy(pd_plan p) {
 
 extern "C" size_t paradiag_spectrum_bytes(pd_plan p) { return p ? p->spec_bytes : 0; }
 
-extern "C" size_t paradiag_plan_bytes(int n, int ell, const pd_options *opt_in) {
+size_t pd_plan_bytes(int n, int ell, const pd_options *opt_in, int lean) {
   pd_options opt;
   paradiag_default_options(&opt);
   if (opt_in) opt = *opt_in;
@@ -1089,6 +1096,7 @@ extern "C" size_t paradiag_plan_bytes(int n, int ell, const pd_options *opt_in) 
   tmp.F2 = ell / 2 + 1;
   tmp.prec = opt.precision;
   tmp.maxit = opt.maxit;
+  tmp.lean = lean;
   tmp.uniform = true;
   tmp.autotune = (opt.autotune != 0 && opt.dims == 1) ? 1 : 0;
   tmp.sine = opt.shifted_solver == PD_SHIFTED_SINE ? 1 : 0;
@@ -1103,4 +1111,8 @@ extern "C" size_t paradiag_plan_bytes(int n, int ell, const pd_options *opt_in) 
   Layout L;
   if (compute_layout(&tmp, cus, (size_t)lds, L) != PD_OK) return 0;
   return L.total_bytes();
+}
+
+extern "C" size_t paradiag_plan_bytes(int n, int ell, const pd_options *opt_in) {
+  return pd_plan_bytes(n, ell, opt_in, 0);
 }

@@ -28,6 +28,7 @@ struct Key {
   int n, ell, dims, prec, maxit, max_sweeps;
   // every other option a plan is built with (all but the stream)
   int check_residual, autotune, early_exit, shifted_solver, krylov, fom_q, bdf_order;
+  int lean;
   double tau, alpha;
   std::vector<double> m, k;   // M (empty = identity) and K, row-major triples
   bool operator<(const Key &o) const {
@@ -37,11 +38,11 @@ struct Key {
     if (prec != o.prec) return prec < o.prec;
     if (maxit != o.maxit) return maxit < o.maxit;
     if (max_sweeps != o.max_sweeps) return max_sweeps < o.max_sweeps;
-    const int a[7] = {check_residual, autotune, early_exit, shifted_solver, krylov, fom_q,
-                      bdf_order};
-    const int b[7] = {o.check_residual, o.autotune, o.early_exit, o.shifted_solver, o.krylov,
-                      o.fom_q, o.bdf_order};
-    for (int q = 0; q < 7; ++q)
+    const int a[8] = {check_residual, autotune, early_exit, shifted_solver, krylov, fom_q,
+                      bdf_order, lean};
+    const int b[8] = {o.check_residual, o.autotune, o.early_exit, o.shifted_solver, o.krylov,
+                      o.fom_q, o.bdf_order, o.lean};
+    for (int q = 0; q < 8; ++q)
       if (a[q] != b[q]) return a[q] < b[q];
     if (tau != o.tau) return tau < o.tau;
     if (alpha != o.alpha) return alpha < o.alpha;
@@ -123,8 +124,8 @@ struct pd_server_s {
       } else {
         pd_options opt = job->req.opt;
         opt.stream = stream;
-        st = paradiag_plan_create(&plan, job->req.n, job->req.ell, job->req.tau,
-                                  job->req.M ? &job->M : nullptr, &job->K, &opt);
+        st = pd_plan_create(&plan, job->req.n, job->req.ell, job->req.tau,
+                            job->req.M ? &job->M : nullptr, &job->K, &opt, job->key.lean);
       }
       if (st == PD_OK) {
         pd_bind_stream(plan, stream);   // a cached plan may come from another worker
@@ -224,6 +225,12 @@ extern "C" pd_status pd_server_submit(pd_server s, const pd_request *req, long *
   const size_t starts = req->opt.bdf_order > 1 ? (size_t)req->opt.bdf_order : 1;
   job->io_bytes = (2 * (size_t)req->ell * nbar + starts * nbar) * sizeof(double);
   job->plan_bytes = paradiag_plan_bytes(req->n, req->ell, &req->opt);
+  job->key.lean = 0;
+  if (job->plan_bytes && !s->policy.fits_alone(job->io_bytes, job->plan_bytes)) {
+    // the budget may still hold a plan without the fast forms' tables
+    job->key.lean = 1;
+    job->plan_bytes = pd_plan_bytes(req->n, req->ell, &req->opt, 1);
+  }
   if (job->plan_bytes == 0) {
     pd_set_error("pd_server_submit: unsupported problem");
     return PD_ENOTSUP;
