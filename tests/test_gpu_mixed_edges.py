@@ -1,9 +1,13 @@
-"""Mixed-precision solves with float64 shifted solves (1D, n > 256; 2D): what a
-failed solve leaves behind."""
+"""Mixed-precision solves with float64 shifted solves (1D, 256 < n <= 8192; 2D): the
+staging of complex64 rows at its edges, iterations of a sweep, and what a failed
+solve or a creation leaves behind."""
 import numpy as np
 import pytest
 
+from oracle import modal
 from paper_2304_12597_amd import workloads as wl
+
+from bounds import fp64_error_bound
 
 pytestmark = pytest.mark.gpu
 torch = pytest.importorskip("torch")
@@ -67,3 +71,31 @@ def test_creation_leaves_no_message(lib, n, ell):
     lib.paradiag_plan_destroy(lib.paradiag_plan_create(n, ell, p.tau, p.M, p.K, precision=lib.PD_MIXED,
                                                        stream=torch.cuda.current_stream().cuda_stream))
     assert lib.paradiag_last_error() == ""
+
+
+# complex64 right-hand sides two rows to a staged entry: whole and ragged last
+# chunks, 8 and 16 rows a thread, odd and even n, the two real frequencies'
+# 4-byte loads, the residual scaled by alpha^(t / ell) as float
+@pytest.mark.parametrize("n,ell,alpha", [(257, 2, 1.0), (257, 64, 0.1), (258, 32, 1.0), (264, 16, 1.0), (511, 8, 1e-3),
+                                         (512, 32, 1.0), (513, 16, 0.1), (1024, 64, 1.0), (2047, 4, 1.0),
+                                         (2048, 64, 0.1), (2049, 32, 1.0), (4095, 16, 1e-3), (4096, 32, 1.0),
+                                         (4097, 16, 1.0), (4098, 32, 0.1), (4104, 8, 1.0), (8190, 16, 0.1),
+                                         (8191, 32, 1.0), (8192, 16, 1.0)])
+@pytest.mark.parametrize("kind", ["fd1", "fem1"])
+def test_row_pairs(lib, kind, n, ell, alpha):
+    p = wl.heat_1d(kind, n, ell, 1.0, 0.3, np.random.default_rng(n + ell), True)
+    dev = torch.device("cuda:0")
+    F = torch.tensor(p.F, device=dev)
+    U = torch.full_like(F, float("nan"))
+    plan = lib.paradiag_plan_create(n, ell, p.tau, p.M, p.K, precision=lib.PD_MIXED, alpha=alpha, check_residual=1,
+                                    stream=torch.cuda.current_stream().cuda_stream)
+    try:
+        info = lib.paradiag_solve(plan, torch.tensor(p.u0, device=dev), F, U, 1e-9)
+        torch.cuda.synchronize()
+    finally:
+        lib.paradiag_plan_destroy(plan)
+    ref = modal.modal_solution(p)
+    err = np.linalg.norm(U.cpu().numpy() - ref) / np.linalg.norm(ref)
+    # the bound that the solve reports holds, beside the oracle's own rounding
+    assert info.sweeps == 2 and 0 <= info.rel_residual <= 1e-9
+    assert err <= max(1.01 * info.est_rel_error, fp64_error_bound(p))
