@@ -23,30 +23,14 @@ namespace {
 
 typedef double v4d __attribute__((ext_vector_type(4)));
 typedef double pair8 __attribute__((ext_vector_type(2), aligned(8)));   // rows start on 8 bytes
-constexpr int RB = 32;   // rows per block
-
-struct DenseShape {
-  int kv, ki, ko, stride, tiles, waves;
-};
-__host__ __device__ inline DenseShape dense_shape(int n) {
-  DenseShape s;
-  s.kv = (n + 1) / 2;                  // inputs and outputs of the odd part
-  s.ki = (s.kv + 7) / 8 * 8;           // inputs: two steps of 4 at a time
-  s.ko = (s.kv + 15) / 16 * 16;        // outputs: tiles of 16
-  s.stride = s.ki + 2;                 // 2 x odd: 16 rows' pairs of inputs on distinct banks
-  s.tiles = s.ko / 16;
-  const int rounds = (s.tiles + 9) / 10;
-  s.waves = (s.tiles + rounds - 1) / rounds;
-  if (s.waves < 8) s.waves = 8;        // 4 rows a wave in the load
-  return s;
-}
+constexpr int RB = PD_DENSE_ROWS;
 
 // Fragments: [tile][chunk of 8 inputs][part: v, u][lane][2 steps]; lane l holds
 // output 16 tile + l % 16 + 1 and input 8 chunk + 2 (l / 16) + step + 1.
 // q[m] = sin(pi m / N), m = 0..2N-1.
 __global__ void __launch_bounds__(256)
 dense_table_kernel(int n, double scale, const double *__restrict__ q, double *__restrict__ tab) {
-  const DenseShape s = dense_shape(n);
+  const DenseShape s = pd_dense_shape(n);
   const int chunks = s.ki / 8, N = n + 1;
   const long total = (long)s.tiles * chunks * 256;
   for (long e = blockIdx.x * 256L + threadIdx.x; e < total; e += 256L * gridDim.x) {
@@ -70,7 +54,7 @@ dst_dense_kernel(int n, int rows, double tau, const double *__restrict__ u0, lon
                  const double *__restrict__ F, const double *in, const double *__restrict__ tab,
                  double *out) {
   extern __shared__ __align__(16) double fold[];   // [part][RB][stride]
-  const DenseShape s = dense_shape(n);
+  const DenseShape s = pd_dense_shape(n);
   const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
   const int N = n + 1, nblk = (rows + RB - 1) / RB;
   const double *src = MODE == 0 ? F : in;
@@ -164,7 +148,7 @@ template <int MODE, int ACC, int JI>
 void dense_launch(const DenseShape &s, int n, int rows, double tau, const double *u0, long nu0,
                   const double *F, const double *in, const double *frag, double *out,
                   hipStream_t stream) {
-  const size_t lds = 2 * (size_t)RB * s.stride * sizeof(double);
+  const size_t lds = pd_dense_lds(s);
   const int nblk = (rows + RB - 1) / RB, fit = lds <= 80 * 1024 ? 512 : 256;
   const dim3 grid(nblk < fit ? nblk : fit), block(64 * s.waves);
   if (JI == 1 && s.tiles <= 4)
@@ -183,8 +167,8 @@ void dense_launch(const DenseShape &s, int n, int rows, double tau, const double
 // 9.3 / 11.2 at 400, 12.7 / 11.3 at 500 (4096 rows).  Where n + 1 is a power of
 // two the FFT of half the length wins: n = 255, 130560 rows: 161 us, product 218.
 size_t pd_dst_dense_doubles(int n) {
-  if (n < 16 || n > 440 || ((n + 1) & n) == 0) return 0;
-  const DenseShape s = dense_shape(n);
+  if (n < 16 || n > PD_DENSE_MAX || ((n + 1) & n) == 0) return 0;
+  const DenseShape s = pd_dense_shape(n);
   return 2 * (size_t)(n + 1) + (size_t)s.tiles * (s.ki / 8) * 256;
 }
 
@@ -211,7 +195,7 @@ pd_status pd_dst_dense_build(int n, double *tab, hipStream_t stream) {
 pd_status pd_launch_dst_dense(int n, int rows, int mode, double tau, const double *u0, long nu0,
                               const double *F, const double *in, const double *tab, double *out,
                               int accumulate, hipStream_t stream) {
-  const DenseShape s = dense_shape(n);
+  const DenseShape s = pd_dense_shape(n);
   const double *frag = tab + 2 * (size_t)(n + 1);
 #define PD_DD(J)                                                                                \
   do {                                                                                          \
@@ -222,7 +206,7 @@ pd_status pd_launch_dst_dense(int n, int rows, int mode, double tau, const doubl
     else                                                                                        \
       dense_launch<2, 0, J>(s, n, rows, tau, u0, nu0, F, in, frag, out, stream);                \
   } while (0)
-  switch ((s.ki + 63) / 64) {
+  switch (pd_dense_loads(s)) {
     case 1: PD_DD(1); break;
     case 2: PD_DD(2); break;
     case 3: PD_DD(3); break;

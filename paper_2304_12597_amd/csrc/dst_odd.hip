@@ -131,32 +131,19 @@ dst_odd_kernel(int n, int rows, int C, int stride, double tau, const double *__r
   }
 }
 
-int odd_pairs(int n) {
-  const int M = (n + 1) / 4;
-  return 512 / M;   // 5 waves, three blocks to a CU
-}
-size_t odd_lds(int n) {
-  const int M = (n + 1) / 4;
-  return ((size_t)5 * odd_pairs(n) * pd_fft_col_stride(M) + pd_tw_entries(M)) * 16;
-}
-
 }  // namespace
-
-// n + 1 a power of two, at least 32 (a thread per butterfly and the M / 2
-// ones); 2D plans end at n = 1024.
-bool pd_dst_odd_ok(int n) { return ((n + 1) & n) == 0 && n >= 31 && n <= 1023; }
 
 // tw[m] = exp(-pi i m / (n + 1))
 pd_status pd_launch_dst_odd(int n, int rows, int mode, double tau, const double *u0, long nu0,
                             const double *F, const double *in, const double *tw, double *out,
                             int accumulate, hipStream_t stream) {
-  const int M = (n + 1) / 4, C = odd_pairs(n), stride = pd_fft_col_stride(M);
-  const int T = (5 * C * M / 8 + 63) / 64 * 64;
-  if (!pd_dst_odd_ok(n) || T > 320 || T < C * M / 2 + C) return PD_ENOTSUP;
+  const int M = (n + 1) / 4, C = pd_odd_pairs(n), stride = pd_fft_col_stride(M);
+  const int T = pd_odd_threads(n);
+  if (!pd_odd_ok(n) || T > 320 || T < C * M / 2 + C) return PD_ENOTSUP;
   const Cx *w = reinterpret_cast<const Cx *>(tw);
 #define PD_DO(MO, A)                                                                             \
   hipLaunchKernelGGL((dst_odd_kernel<MO, A>), dim3((rows + 2 * C - 1) / (2 * C)), dim3(T),       \
-                     odd_lds(n), stream, n, rows, C, stride, tau, u0, nu0, F, in, w, out)
+                     pd_odd_lds(n), stream, n, rows, C, stride, tau, u0, nu0, F, in, w, out)
   if (mode == 0) PD_DO(0, 0);
   else if (accumulate) PD_DO(2, 1);
   else PD_DO(2, 0);

@@ -676,7 +676,7 @@ pd_status pd_launch_dst_x(pd_plan p, int mode, const double *u0, const double *F
   if (p->twd_dense && mode != 1 && pd_dst_dense_pays(p->n, (long)p->ell * p->n))
     return pd_launch_dst_dense(p->n, p->ell * p->n, mode, p->tau, u0, p->nbar, F, in,
                                p->twd + p->twd_dense, out, accumulate, p->stream);
-  if (pd_dst_odd_ok(p->n) && mode != 1)
+  if (pd_odd_ok(p->n) && mode != 1)
     return pd_launch_dst_odd(p->n, p->ell * p->n, mode, p->tau, u0, p->nbar, F, in, p->twd, out,
                              accumulate, p->stream);
   DstLaunch L = dst_config(p, p->ell);
@@ -716,7 +716,7 @@ pd_status pd_launch_dst_x_rows(pd_plan p, const double *in, double *out, int tro
   if (p->twd_dense && pd_dst_dense_pays(p->n, (long)trows * p->n))
     return pd_launch_dst_dense(p->n, trows * p->n, 2, p->tau, nullptr, 0, nullptr, in,
                                p->twd + p->twd_dense, out, accumulate, p->stream);
-  if (pd_dst_odd_ok(p->n))
+  if (pd_odd_ok(p->n))
     return pd_launch_dst_odd(p->n, trows * p->n, 2, p->tau, nullptr, 0, nullptr, in, p->twd, out,
                              accumulate, p->stream);
   DstLaunch L = dst_config(p, trows);

@@ -173,19 +173,6 @@ line2d_kernel(int n, int F2, int P, int S, int mgroups, int kchunk,
   }
 }
 
-// LDS of the kernel below: entry i of a line at i + i/8 (a thread's 8 rows 9
-// apart), lines apart so that the 16 lanes of a staging access, 16 / S rows of S
-// lines, fall on different banks.
-__host__ __device__ inline int line_entry(int i) { return i + (i >> 3); }
-__host__ __device__ inline int line_stride(int n, int S) {
-  const int e = line_entry(n - 1);
-  return S < 16 ? (e + 16) / 16 * 16 + 16 / S : (e + 1) | 1;
-}
-template <int MR>
-size_t line_lds(int n, int S) {
-  return (size_t)S * (line_stride(n, S) + pd_scan_entries<MR>()) * 16;
-}
-
 // Modes 0 and 1 in the recurrence form (float64, a line within a wave).  A
 // block keeps its S columns and walks over a chunk of the frequencies; the
 // blocks that walk over the same frequencies side by side are on one XCD, where
@@ -208,7 +195,7 @@ line2d_scan_kernel(int n, int F2, int P, int S, int mgroups, int kchunk,
   constexpr int NF = pd_scan_entries<MR>();
   constexpr int FU = MR == 8 ? 2 : NF;   // constants per thread: NF / P, P >= 16 with 8 rows
   const int tid = threadIdx.x, g = tid / P, lt = tid - g * P;
-  const int stride = line_stride(n, S);
+  const int stride = pd_line_stride(n, S);
   const size_t nbar = (size_t)n * n;
   Cx *tile = reinterpret_cast<Cx *>(smem_raw);
   Cx *tabs = tile + (size_t)S * stride;
@@ -238,9 +225,9 @@ line2d_scan_kernel(int n, int F2, int P, int S, int mgroups, int kchunk,
   int y0 = tid >> lgS;
   auto at = [&](int u) {   // entry of row y0 + u P
     if constexpr (MR == 8)
-      return cl * stride + line_entry(y0) + u * (P + (P >> 3));   // P a multiple of 8
+      return cl * stride + pd_line_entry(y0) + u * (P + (P >> 3));   // P a multiple of 8
     else
-      return cl * stride + line_entry(y0 + u * P);
+      return cl * stride + pd_line_entry(y0 + u * P);
   };
   In v[MR];
   Cx fv[FU];
@@ -280,7 +267,7 @@ line2d_scan_kernel(int n, int F2, int P, int S, int mgroups, int kchunk,
     for (int q = 0; q < MR; ++q) {
       Cx t = zero;
       if (q < len) {
-        t = line[line_entry(s0 + q)];
+        t = line[pd_line_entry(s0 + q)];
         if constexpr (MODE == 1) t.re += xr[q];
       }
       d[q] = t;
@@ -293,7 +280,7 @@ line2d_scan_kernel(int n, int F2, int P, int S, int mgroups, int kchunk,
       // every thread reads and writes its own rows of the tile only
 #pragma unroll
       for (int q = 0; q < MR; ++q)
-        if (q < len) line[line_entry(s0 + q)] = d[q];
+        if (q < len) line[pd_line_entry(s0 + q)] = d[q];
       __syncthreads();
       Cx *dst = out + (size_t)k * nbar;
 #pragma unroll
@@ -316,7 +303,7 @@ line2d_scan_kernel(int n, int F2, int P, int S, int mgroups, int kchunk,
     double *sd = reinterpret_cast<double *>(smem_raw);
 #pragma unroll
     for (int q = 0; q < MR; ++q)
-      if (q < len) sd[2 * ((size_t)g * stride + line_entry(s0 + q))] = acc[q];
+      if (q < len) sd[2 * ((size_t)g * stride + pd_line_entry(s0 + q))] = acc[q];
     __syncthreads();
     double *dst = partials + (size_t)kc * nbar;
 #pragma unroll
@@ -331,7 +318,7 @@ template <int MR, int MODE, bool IN32>
 void launch2d_scan(pd_plan p, const void *in, const double *xv, void *out) {
   const Line2DConfig &L = p->l2d;
   hipLaunchKernelGGL((line2d_scan_kernel<MR, MODE, IN32>), dim3(L.nkc * L.mgroups), dim3(L.block),
-                     line_lds<MR>(p->n, L.S), p->stream, p->n, p->F2, L.P, L.S, L.mgroups,
+                     pd_line_lds(p->n, LineShape{MR, L.P, L.S}), p->stream, p->n, p->F2, L.P, L.S, L.mgroups,
                      L.kchunk, reinterpret_cast<const cpx<double> *>(p->fac64), p->gB64, in, xv,
                      p->w, static_cast<cpx<double> *>(out), p->partials);
 }
@@ -387,15 +374,10 @@ pd_status launch2d(pd_plan p, int mode, const void *in, const double *xv, void *
 Line2DConfig pd_choose_line2d(int n, int F2, int prec, int cus) {
   Line2DConfig L;
   const size_t cb = (prec == PD_FP64) ? 16 : 8;
-  L.MR = (n <= 64) ? 4 : 8;
-  L.P = 1;
-  while (L.P * L.MR < n) L.P *= 2;
-  L.S = 1;
-  while (L.P * L.S * 2 <= 512) L.S *= 2;
-  if (L.S > n) {
-    L.S = 1;
-    while (L.S * 2 <= n) L.S *= 2;
-  }
+  const LineShape shape = pd_line_shape(n);
+  L.MR = shape.MR;
+  L.P = shape.P;
+  L.S = shape.S;
   L.block = L.P * L.S;
   L.mgroups = (n + L.S - 1) / L.S;
   // enough blocks for the frequency sums: split k into chunks

@@ -10,6 +10,7 @@
 #include <vector>
 
 #include "../../include/paradiag.h"
+#include "pd_shapes.h"
 #include <rocprofiler-sdk-roctx/roctx.h>
 
 // ---------------------------------------------------------------------------
@@ -73,22 +74,6 @@ constexpr double PD_GMRES_TOL_FACTOR = 1e-2;
 inline double pd_gmres_tol(int prec, double tol) {
   const double t = tol * PD_GMRES_TOL_FACTOR;
   return (prec != PD_FP64 && t < 1e-7) ? 1e-7 : t;
-}
-
-// LDS column layout of the time and DST transforms: entry i of a column sits
-// at pd_fpad(i) = i + i/8, which spreads the power-of-two strides of the
-// Stockham stages over all LDS banks; columns are pd_fft_col_stride(N)
-// entries apart (odd, so that columns start on different banks).
-__host__ __device__ __forceinline__ int pd_fpad(int i) { return i + (i >> 3); }
-__host__ __device__ __forceinline__ int pd_fft_col_stride(int N) {
-  const int s = pd_fpad(N - 1) + 1;
-  return s | 1;
-}
-// Twiddles of a length-N transform in LDS: lo[m] = w^m for m < min(N, 64) and
-// hi[h] = w^(64 h) for h < max(N / 64, 1); w^m = hi[m / 64] lo[m % 64].
-__host__ __device__ __forceinline__ int pd_tw_lo(int N) { return N < 64 ? N : 64; }
-__host__ __device__ __forceinline__ int pd_tw_entries(int N) {
-  return pd_tw_lo(N) + (N < 64 ? 1 : N / 64);
 }
 
 // ---------------------------------------------------------------------------
@@ -446,7 +431,6 @@ pd_status pd_launch_dst_dense(int n, int rows, int mode, double tau, const doubl
                               int accumulate, hipStream_t stream);
 void pd_dst_dense_set_attributes(size_t max_lds);
 // ... of rows of 2^m - 1 by the odd extension's own FFT (dst_odd.hip)
-bool pd_dst_odd_ok(int n);
 pd_status pd_launch_dst_odd(int n, int rows, int mode, double tau, const double *u0, long nu0,
                             const double *F, const double *in, const double *tw, double *out,
                             int accumulate, hipStream_t stream);

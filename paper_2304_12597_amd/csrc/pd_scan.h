@@ -51,7 +51,9 @@
 #include "pd_partition.h"
 
 template <int MR>
-constexpr int pd_scan_entries() { return 9 + MR; }
+constexpr int pd_scan_entries() {
+  return pd_line_constants(MR);
+}
 
 // Lane moves by DPP (data-parallel primitives: a VALU operand modifier, no
 // LDS round trip).  CTRL: row_shr:s = 0x110 + s, row_shl:s = 0x100 + s,

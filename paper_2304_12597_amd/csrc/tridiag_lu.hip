@@ -44,7 +44,7 @@
 namespace {
 
 using Cx = cpx<double>;
-constexpr int MR = 8;
+constexpr int MR = PD_LU_ROWS;
 
 // 1 / |a|^2: the hardware reciprocal and one step of third order.
 __device__ __forceinline__ double lu_rsq(Cx a) {
@@ -126,9 +126,6 @@ lu_pivots_kernel(int n, int P, const double *__restrict__ coef, const double *__
   if (lane == 0) bad[k] = small ? 1.0 : 0.0;
 }
 
-// entry of row i of a group's staging area: 8 rows of a thread 9 apart
-__device__ __forceinline__ int lu_entry(int i) { return i + (i >> 3); }
-
 // MODE as for tridiag_kernel: 0 accumulates Re(gw_k y_k) into partial rows, 1
 // writes y_k, 2 accumulates with the right-hand side M v.
 template <int MODE>
@@ -144,7 +141,7 @@ lu_solve_kernel(int n, int F2, int P, int spb, int nitems, const double *__restr
   if (skip && *skip != 0.0) return;
   const int tid = threadIdx.x, g = tid / P, lt = tid - g * P;
   const int lane = lt & 63, wv = lt >> 6, NW = P >> 6, w0 = (tid - lt) >> 6;
-  const int gs = lu_entry(P * MR + 1) + 1;          // entries per group, 1 halo row each side
+  const int gs = pd_lu_group(P);
   Cx *stage = reinterpret_cast<Cx *>(smem_raw) + (size_t)g * gs;
   const int s0 = lt * MR;
   const Cx zero = {0.0, 0.0}, one = {1.0, 0.0};
@@ -163,15 +160,15 @@ lu_solve_kernel(int n, int F2, int P, int spb, int nitems, const double *__restr
     for (int i = lt; i < P * MR + 2; i += P) {      // entry i: v_{i-1}
       const int r = i - 1, rc = r < 0 ? 0 : (r < n ? r : n - 1);
       const double t = v ? v[rc] : 0.0;
-      sv[lu_entry(i)] = (r >= 0 && r < n) ? t : 0.0;
+      sv[pd_lu_entry(i)] = (r >= 0 && r < n) ? t : 0.0;
     }
     __syncthreads();
 #pragma unroll
     for (int q = 0; q < MR; ++q) {
       const int i = s0 + q + 1;
-      double t = coef(1, q) * sv[lu_entry(i)];
-      t += coef(0, q) * sv[lu_entry(i - 1)];
-      t += coef(2, q) * sv[lu_entry(i + 1)];
+      double t = coef(1, q) * sv[pd_lu_entry(i)];
+      t += coef(0, q) * sv[pd_lu_entry(i - 1)];
+      t += coef(2, q) * sv[pd_lu_entry(i + 1)];
       base[q] = MODE == 2 ? t : -wscale * t;
     }
   }
@@ -193,10 +190,10 @@ lu_solve_kernel(int n, int F2, int P, int spb, int nitems, const double *__restr
       for (int u = 0; u < MR; ++u) {
         const int r = (int)lq + u * P;
         const Cx t = src[r < n ? r : n - 1];
-        stage[lu_entry(r + 1)] = r < n ? t : zero;
+        stage[pd_lu_entry(r + 1)] = r < n ? t : zero;
       }
-      if (lt == 0) stage[lu_entry(0)] = zero;
-      if (lt == 1) stage[lu_entry(P * MR + 1)] = zero;
+      if (lt == 0) stage[pd_lu_entry(0)] = zero;
+      if (lt == 1) stage[pd_lu_entry(P * MR + 1)] = zero;
     }
     // this system's rows and the pivot before them, while the loads land
     Cx e = lu_recip(piv[(size_t)k * P + lq]), cp = zero;   // 1 / d_{q-1}, c_{q-1}
@@ -210,10 +207,10 @@ lu_solve_kernel(int n, int F2, int P, int spb, int nitems, const double *__restr
 #pragma unroll
       for (int q = 0; q < MR; ++q) {
         const int i = s0 + q + 1;
-        Cx t = stage[lu_entry(i)];
+        Cx t = stage[pd_lu_entry(i)];
         if (!rhs_has_mass) {
           const double md = coef(1, q), ml = coef(0, q), mu = coef(2, q);
-          const Cx l = stage[lu_entry(i - 1)], r = stage[lu_entry(i + 1)];
+          const Cx l = stage[pd_lu_entry(i - 1)], r = stage[pd_lu_entry(i + 1)];
           t = Cx{md * t.re + ml * l.re + mu * r.re, md * t.im + ml * l.im + mu * r.im};
         }
         if constexpr (MODE == 1) t.re += base[q];
@@ -303,14 +300,14 @@ lu_solve_kernel(int n, int F2, int P, int spb, int nitems, const double *__restr
     if constexpr (MODE == 1) {
       // the staging area was last read before the two barriers above
 #pragma unroll
-      for (int q = 0; q < MR; ++q) stage[lu_entry(s0 + q + 1)] = d[q];
+      for (int q = 0; q < MR; ++q) stage[pd_lu_entry(s0 + q + 1)] = d[q];
       __syncthreads();
       if (active) {
         Cx *dst = out + (size_t)k * n;
 #pragma unroll
         for (int j = 0; j < MR; ++j) {
           const int r = (int)lq + j * P;
-          if (r < n) dst[r] = stage[lu_entry(r + 1)];
+          if (r < n) dst[r] = stage[pd_lu_entry(r + 1)];
         }
       }
     } else if (active) {
@@ -324,33 +321,22 @@ lu_solve_kernel(int n, int F2, int P, int spb, int nitems, const double *__restr
     __syncthreads();
     double *sd = reinterpret_cast<double *>(stage);
 #pragma unroll
-    for (int q = 0; q < MR; ++q) sd[lu_entry(s0 + q)] = acc[q];
+    for (int q = 0; q < MR; ++q) sd[pd_lu_entry(s0 + q)] = acc[q];
     __syncthreads();
     const Cx *all = reinterpret_cast<const Cx *>(smem_raw);
     for (int i = tid; i < n; i += blockDim.x) {
       double s = 0.0;
       for (int h = 0; h < spb; ++h)
-        s += reinterpret_cast<const double *>(all + (size_t)h * gs)[lu_entry(i)];
+        s += reinterpret_cast<const double *>(all + (size_t)h * gs)[pd_lu_entry(i)];
       partials[(size_t)blockIdx.x * n + i] = s;
     }
   }
 }
 
-// Threads of a group (a power of two, whole waves), of a block, and work items.
-constexpr int LU_T = 512;
-int lu_threads(int n) {
-  int P = 64;
-  while (P * MR < n) P *= 2;
-  return P;
-}
+constexpr int LU_T = PD_LU_BLOCK;
 int lu_items(const pd_plan p) {
-  const int spb = LU_T / lu_threads(p->n);
+  const int spb = LU_T / pd_lu_threads(p->n);
   return (p->F2 + spb - 1) / spb;
-}
-
-size_t lu_lds(int P, int spb) {
-  const int last = P * MR + 1;
-  return (size_t)spb * (last + (last >> 3) + 1) * 16;
 }
 
 }  // namespace
@@ -362,7 +348,7 @@ size_t lu_lds(int P, int spb) {
 size_t pd_lu_doubles(const pd_plan p) {
   if (p->dims != 1 || p->prec != PD_FP64 || p->uniform || p->autotune || p->n <= 64 || p->n > 4096)
     return 0;
-  const int P = lu_threads(p->n);
+  const int P = pd_lu_threads(p->n);
   return 6 * (size_t)P * MR + 2 * (size_t)p->F2 * P + p->F2;
 }
 
@@ -370,14 +356,14 @@ size_t pd_lu_doubles(const pd_plan p) {
 int pd_lu_blocks(const pd_plan p, int cus) { return std::min(lu_items(p), cus); }
 
 static double *lu_flags(pd_plan p) {
-  const int P = lu_threads(p->n);
+  const int P = pd_lu_threads(p->n);
   return p->lu_tab + 6 * (size_t)P * MR + 2 * (size_t)p->F2 * P;
 }
 
 // Fills p->lu_tab on the plan's stream from coef64 and lam64, the first tables
 // of a creation: the pivots are formed while the host makes the others.
 pd_status pd_lu_setup(pd_plan p) {
-  const int n = p->n, P = lu_threads(n);
+  const int n = p->n, P = pd_lu_threads(n);
   double *piv = p->lu_tab + 6 * (size_t)P * MR;
   hipLaunchKernelGGL(lu_rows_kernel, dim3(P * MR / 64, 6), dim3(64), 0, p->stream, n, P, p->coef64,
                      p->lu_tab);
@@ -399,11 +385,11 @@ pd_status pd_lu_flags(pd_plan p, std::vector<double> &bad) {
 pd_status pd_launch_lu(pd_plan p, int mode, const void *in, const double *xv, void *out) {
   const int has_mass = (mode & 0x100) ? 1 : 0;
   mode &= 0xff;
-  const int P = lu_threads(p->n), spb = LU_T / P, nitems = lu_items(p);
+  const int P = pd_lu_threads(p->n), spb = LU_T / P, nitems = lu_items(p);
   const int G = mode == 1 ? nitems : p->lu_G;
   const Cx *piv = reinterpret_cast<const Cx *>(p->lu_tab + 6 * (size_t)P * MR);
 #define PD_LU(M, GW, IN, VIN, XV, O, PART)                                                     \
-  hipLaunchKernelGGL((lu_solve_kernel<M>), dim3(G), dim3(LU_T), lu_lds(P, spb), p->stream,     \
+  hipLaunchKernelGGL((lu_solve_kernel<M>), dim3(G), dim3(LU_T), pd_lu_lds(P, spb), p->stream,     \
                      p->n, p->F2, P, spb, nitems, p->lu_tab, p->lam64, piv, GW, IN, VIN, XV,     \
                      p->w, has_mass, O, PART, p->gm_skip)
   if (mode == 1)
