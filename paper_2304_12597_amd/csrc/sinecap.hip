@@ -798,15 +798,17 @@ pd_status pd_sc_finish(pd_plan p, std::vector<double> &s2) {
 // than at 130.  Solves of 26 to 31 iterations, general / one-block, ms: n = q = 80
 // 2.53 / 2.15, 90 2.67 / 2.47, 100 2.77 / 2.96, 120 3.01 / 4.14; n = 120, q = 97 2.98 /
 // 2.78; n = 140, q = 103 3.69 / 3.23, q = 122 3.68 / 4.28; n = 160, q = 112 2.96 / 2.71.
+// Where J - I is small the iterations are few (5 at 0.01, 14 at 5) and the one-block
+// form wins at any q: n = q = 100, 4 steps, alpha = 0.01: 0.37 / 0.24.
 constexpr int SC2_QMAX = 127;    // q^2 + 1 <= 16384 entries
-static int sc2_limit(int n) { return n < 200 ? 96 : SC2_QMAX; }
+static int sc2_limit(int n, double size) { return n < 200 && size > 8.0 ? 96 : SC2_QMAX; }
 static int sc2_rows(int q) { return (q + 15) / 16 * 16; }
 static int sc2_tiles(int n) { return ((n + 63) / 64) * ((n + 15) / 16); }
 static size_t sc2_doubles(int n, int q) {
   const size_t q2 = (size_t)q * q;
   return (size_t)sc2_rows(q) * sc_stride(n) + 4 * (q2 + 2) + 3 * (size_t)q + sc2_tiles(n);
 }
-size_t pd_sc2_max_doubles(int n) { return sc2_doubles(n, std::min(n, sc2_limit(n))); }
+size_t pd_sc2_max_doubles(int n) { return sc2_doubles(n, std::min(n, SC2_QMAX)); }
 
 bool pd_sc2_choose(pd_plan p) {
   const double *u = p->uni;
@@ -825,7 +827,7 @@ bool pd_sc2_choose(pd_plan p) {
     if (D <= SC_CUT) break;
     worst = std::max(worst, D);
     q = j;
-    if (q > sc2_limit(n)) return false;   // more modes: the general product
+    if (q > sc2_limit(n, worst)) return false;   // more modes: the general product
   }
   if (q < 1) q = 1;
   // partition-form lines (more than a wave each): as in 1D
