@@ -74,10 +74,10 @@ typedef enum {
                              /* method), capacitance system by GMRES (any M, K)   */
   PD_SHIFTED_SINE = 1        /* 1D, float64, symmetric Toeplitz M and K (uniform */
                              /* grid, zero Dirichlet ends), n + 1 a power of two */
-                             /* >= 16 or n <= 4095 (DST as a product or in       */
-                             /* chirp-z form): every shifted matrix and J_ell     */
-                             /* diagonal in the DST-I basis;                     */
-                             /* capacitance solved exactly                       */
+                             /* >= 16 or n <= 4095 (DST-I by an FFT, a matrix    */
+                             /* product or the chirp-z form, by n and ell):      */
+                             /* every shifted matrix and J_ell diagonal in the   */
+                             /* DST-I basis; capacitance solved exactly          */
 } pd_shifted_solver;
 
 typedef enum {
@@ -85,8 +85,9 @@ typedef enum {
   PD_MIXED = 1,       /* complex64 forward transform and spectra, float64    */
                       /* capacitance system, residual and refinement; shifted */
                       /* solves and inverse transform in float64 where the    */
-                      /* recurrence form runs (uniform grids, n > 256 in 1D,  */
-                      /* n <= 512 a side in 2D), else complex64               */
+                      /* recurrence form runs (uniform grids, 256 < n <= 8192 */
+                      /* in 1D, n <= 512 a side in 2D; not with early_exit or */
+                      /* autotune), else in complex64                         */
   PD_FP32 = 2         /* one complex64 sweep, no refinement                  */
 } pd_precision;
 
@@ -173,8 +174,9 @@ pd_status paradiag_plan_check(int n, int ell, double tau, const pd_tridiag *M,
  * device workspace and uploads the constants.
  * Sizes: ell a power of two, 2 <= ell <= 4096.  1D: 2 <= n <= 8192 for
  * PD_FP64, n <= 16384 otherwise.  2D: 2 <= n <= 1024 (the DST-I along x is
- * one FFT of length 2(n+1) per pair of rows when n + 1 is a power of two,
- * else the chirp-z form with FFTs of length L >= 2n - 1).
+ * an FFT when n + 1 is a power of two; else a float64 matrix product for
+ * 16 <= n <= 440, where there are rows enough for it, and otherwise the
+ * chirp-z form with FFTs of length L >= 2n - 1).
  * M == NULL means M = I.  Errors: PD_EINVAL, PD_ENOTSUP, PD_ENOMEM, PD_EHIP. */
 pd_status paradiag_plan_create(pd_plan *out, int n, int ell, double tau,
                                const pd_tridiag *M, const pd_tridiag *K,
@@ -183,9 +185,10 @@ pd_status paradiag_plan_create(pd_plan *out, int n, int ell, double tau,
 /* Algorithm 1 end to end: U = solution of the all-at-once system for
  * initial value u0 [nbar] and nodal source F [ell][nbar] (device float64),
  * written to U [ell][nbar] (device float64, must not alias u0 or F).
- * tol: the capacitance GMRES stops at residual <= tol/100 * ||b|| (with
- * float32 shifted solves at no less than 1e-7 * ||b||, the resolution of
- * float32 capacitance products); PD_MIXED refines until
+ * tol: the capacitance GMRES stops at residual <= tol/100 * ||b||, but for
+ * PD_FP32 plans, and for PD_MIXED plans whose capacitance products run over
+ * all frequencies, at no less than 1e-7 * ||b|| (a product's resolution in
+ * float32; the refinement sweeps make up for it).  PD_MIXED refines until
  * the float64 relative all-at-once residual is <= tol, or until a sweep
  * fails to lower it: then that sweep's correction is taken back and the best
  * iterate is returned with PD_ENOTCONV (info->rel_residual is its residual).
@@ -202,10 +205,11 @@ pd_status paradiag_solve(pd_plan plan, const double *u0, const double *F,
  * backward Euler with the GMRES capacitance solver, the same precision and
  * maxit, no repeats -- form groups, and every stage of a group is one launch
  * for all of its problems (the capacitance GMRES one block per problem, or in
- * lockstep, each problem stopping on its own convergence flag; a group's
- * results equal the problems' results solved alone, bit for bit).  Every other problem (2D, PD_MIXED, non-uniform
- * grids, BDF, the sine basis, Algorithm 2) and any group of one is solved
- * with paradiag_solve, one after another.  Arrays as in paradiag_solve, one
+ * lockstep, each problem stopping on its own convergence flag, as its plan
+ * solves it alone; a group's results equal the problems' results solved
+ * alone, bit for bit).  Every other problem (2D, PD_MIXED, non-uniform grids,
+ * BDF, the sine basis, Algorithm 2) and any group of one is solved with
+ * paradiag_solve, one after another.  Arrays as in paradiag_solve, one
  * per problem.  infos may be NULL.  Synchronises each group's first plan's
  * stream. */
 pd_status paradiag_solve_batch(const pd_plan *plans, int count,
@@ -266,8 +270,8 @@ pd_status paradiag_capacitance_apply(pd_plan plan, const double *v,
                                      double *Jv);
 
 /* GMRES on J_ell x = b (BDF plans: J^(s), b and x [s][nbar]) from x = 0
- * until residual <= rtol * ||b|| or the plan's maxit.  iters and relres (may be NULL) receive the iteration count
- * and final residual / ||b||.  Returns PD_ENOTCONV if rtol was not met.
+ * until residual <= rtol * ||b|| or the plan's maxit.  iters and relres (may
+ * be NULL) receive the iteration count and final residual / ||b||.  Returns PD_ENOTCONV if rtol was not met.
  * Synchronises the plan's stream. */
 pd_status paradiag_capacitance_solve(pd_plan plan, const double *b,
                                      double *x, double rtol, int *iters,

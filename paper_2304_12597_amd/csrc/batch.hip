@@ -6,10 +6,11 @@
 // the rest of the batch.
 //
 // Problems whose capacitance system is solved in the sine basis (sinecap.hip)
-// run in eight launches: the two transforms, the two parfors, and projection,
-// norm, GMRES (one block per problem, to its own convergence) and columns of x.
+// take six launches and two for each size class of shifted solves that occurs:
+// the transforms, projection, norm, GMRES (one block per problem, to its own
+// convergence), columns of x, and the two parfors, once a size class.
 //
-// Of the others the capacitance GMRES runs in lockstep, each problem stopping
+// Of the others, which share the transforms and parfors, the capacitance GMRES runs in lockstep, each problem stopping
 // on its own device-side convergence flag.  Their whole solve is one launch
 // sequence with no host round trip; once every plan of a batch has been solved
 // before (K = the largest iteration count they needed), the sequence is

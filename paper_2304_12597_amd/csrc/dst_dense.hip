@@ -15,6 +15,7 @@
 // What bounds it: the products (n = 256, 65536 rows: 55 us at the peak rate) and
 // the rows' bytes (56 us) about equally.  Measured there: chirp-z 310 us (MODE
 // 0) and 282 us (MODE 2), this 115 and 106 us (matrix cores busy 62% of it).
+// With few rows or many points the chirp-z form wins (pd_dst_dense_pays).
 #include "pd_internal.h"
 
 #include <cmath>

@@ -565,7 +565,7 @@ __device__ __forceinline__ void tridiag_uniform_body(
 //
 // LDS: [spb*P*MR cpx stage][spb*P Row3 exchange][2*spb*NFP cpx factors]; the
 // recurrence form needs 3 P/64 entries of exchange and 32 of constants a
-// system (pd_pipe_lds), so that two blocks fit on a CU at 8 rows per thread
+// system (pd_pipe_scan_lds), so that two blocks fit on a CU at 8 rows per thread
 template <int MR>
 constexpr int pipe_nfp() { return (6 * (MR - 1) + 63) / 64 * 64; }
 

@@ -1,5 +1,5 @@
 // Shifted solves of general (non-constant) tridiagonal M and K in float64:
-// the parfor of Algorithm 1 on graded meshes, n <= 4096.
+// the parfor of Algorithm 1 on graded meshes, 64 < n <= 4096.
 //
 // P_k = L U without pivoting, l_i = a_i / d_{i-1}, d_i = b_i - l_i c_{i-1}, so a
 // solve is two first-order recurrences,
@@ -13,8 +13,8 @@
 // rows take it times their products; backwards the same.  The pivots are a
 // serial recurrence, but only the one before each chunk is needed from
 // outside: a plan keeps P of them per frequency (formed once on the device, a
-// wave per frequency: 180 us at n = 3001), and the thread's own 8 are 8
-// reciprocals.  That is 2 F2 P doubles instead of
+// wave per frequency: 180 us at n = 3001, beside the host's work on the other
+// tables), and the thread's own 8 are 8 reciprocals.  That is 2 F2 P doubles instead of
 // a table of every row's factors.
 //
 // What bounds it is latency -- 129 systems of 3001 rows leave half the CUs
@@ -22,8 +22,9 @@
 // two scans of 6 steps, three barriers, against two such sweeps, 9 reduction
 // steps of a reciprocal and two barriers each in the partition form
 // (tridiag_kernel).  n = 3001, ell = 256: pass B 68 -> 18 us, pass C 68 -> 22 us,
-// J product 55 -> 15 us, the solve 375 -> 155 us.  Coefficients are kept a second time in the threads'
-// order (row q of every thread side by side), so that their loads coalesce.
+// J product 55 -> 15 us, the solve 375 -> 155 us.  Coefficients are kept a second
+// time in the threads' order (row q of every thread side by side), so that their
+// loads coalesce.
 //
 // There is no pivoting.  A plan uses this form only if every pivot is at least 1/16
 // of its diagonal entry (checked when the pivots are formed); otherwise, and for
