@@ -50,10 +50,17 @@ __device__ __forceinline__ pd_ddc dd_cmul(pd_ddc a, pd_ddc b) {
 __device__ __forceinline__ pd_ddc dd_scale(pd_ddc a, pd_dd s) {
   return pd_ddc{dd_mul(a.re, s), dd_mul(a.im, s)};
 }
-// num / den; 0 where |den|^2 is beyond the range
+__device__ __forceinline__ pd_ddc dd_ldexp(pd_ddc a, int e) {
+  return pd_ddc{pd_dd{ldexp(a.re.h, e), ldexp(a.re.l, e)}, pd_dd{ldexp(a.im.h, e), ldexp(a.im.l, e)}};
+}
+// num / den, both scaled by a power of two first: matrices may be of any scale,
+// and |den|^2 of entries of 1e-150 or 1e150 leaves the range.
 __device__ __forceinline__ pd_ddc dd_cdiv(pd_ddc num, pd_ddc den) {
+  int e;
+  (void)frexp(fmax(fabs(den.re.h), fabs(den.im.h)), &e);
+  num = dd_ldexp(num, -e);
+  den = dd_ldexp(den, -e);
   const pd_dd d = dd_add(dd_mul(den.re, den.re), dd_mul(den.im, den.im));
-  if (!(d.h < 1e300)) return pd_ddc{pd_dd{0.0, 0.0}, pd_dd{0.0, 0.0}};
   return dd_scale(dd_cmul(num, pd_ddc{den.re, dd_neg(den.im)}), dd_recip(d));
 }
 
