@@ -10,13 +10,13 @@
 // the transforms, projection, norm, GMRES (one block per problem, to its own
 // convergence), columns of x, and the two parfors, once a size class.
 //
-// Of the others, which share the transforms and parfors, the capacitance GMRES runs in lockstep, each problem stopping
-// on its own device-side convergence flag.  Their whole solve is one launch
-// sequence with no host round trip; once every plan of a batch has been solved
-// before (K = the largest iteration count they needed), the sequence is
-// captured as a HIP graph, cached per (plans, arrays, tol, K) and replayed.
-// If some problem has not converged after K iterations, an uncaptured loop
-// continues it and the tail is redone.
+// Of the others, which share the transforms and parfors, the capacitance GMRES
+// runs in lockstep, each problem stopping on its own device-side convergence
+// flag.  Their whole solve is one launch sequence with no host round trip; once
+// every plan of a batch has been solved before (K = the largest iteration count
+// they needed), the sequence is captured as a HIP graph, cached per (plans,
+// arrays, tol, K) and replayed.  If some problem has not converged after K
+// iterations, an uncaptured loop continues it and the tail is redone.
 #include "pd_internal.h"
 
 #include <algorithm>

@@ -752,11 +752,12 @@ bool pd_sc_choose(pd_plan p) {
   // The passes apply a rounded factorisation of every P_k, and J has to apply
   // the same.  The recurrence form's scans carry powers of the rounded matrix's
   // own root, so its eigenvalues are right over many rows.  The partition form's
-  // elimination is off by cond(P_0) u, which must not show.  Backward Euler's b comes from a pass
-  // of its own, whose rounding is that large anyway (errors at n <= 256, limit
-  // 1e-12, as with the product).  BDF's b is taken from U_1, and a consistent J
-  // corrects U_1's rounding with it: at a limit of 1e-12 errors were up to 135
-  // times the product's (n = 63, 32 steps, order 3, nu = 0.01: 4.8e-13, 3.5e-15).
+  // elimination is off by cond(P_0) u, which must not show.  Backward Euler's b
+  // comes from a pass of its own, whose rounding is that large anyway (errors at
+  // n <= 256, limit 1e-12, as with the product).  BDF's b is taken from U_1, and a
+  // consistent J corrects U_1's rounding with it: at a limit of 1e-12 errors were
+  // up to 135 times the product's (n = 63, 32 steps, order 3, nu = 0.01: 4.8e-13,
+  // 3.5e-15).
   const double cond0 = std::max(e1, en) / std::min(e1, en);
   if (!scan && !(worst * cond0 * 0x1p-53 <= (s == 1 ? 1e-12 : 1e-14))) return false;
   const int ns = sc_stride(n), nblk = ns / 64;
