@@ -79,8 +79,8 @@ lu_rows_kernel(int n, int P, const double *__restrict__ coef, double *__restrict
 // One wave per frequency: the pivots before every chunk, piv[k P + lt] =
 // d_{lt MR - 1} (1 for lt = 0), by the serial recurrence, which every lane
 // runs (64 rows' b_i and a_i c_{i-1} at a time from LDS); bad[k] is 1 where a
-// pivot is too small against its diagonal entry or an entry's square near the
-// ends of the range, else 0.
+// pivot is too small against its diagonal entry or that entry beyond 1e-93 and
+// 1e93, else 0.
 __global__ void __launch_bounds__(64)
 lu_pivots_kernel(int n, int P, const double *__restrict__ coef, const double *__restrict__ lam,
                  Cx *__restrict__ piv, double *__restrict__ bad) {
@@ -120,7 +120,9 @@ lu_pivots_kernel(int n, int P, const double *__restrict__ coef, const double *__
     __syncthreads();
     const Cx dl = piv64[lane];
     const double dd = dl.re * dl.re + dl.im * dl.im, bb = b.re * b.re + b.im * b.im;
-    small = small || !(dd * 256.0 >= bb) || !(bb > 1e-280 && bb < 1e280);
+    // the numerator above is of the entries' third power: entries beyond 1e-93 and
+    // 1e93 leave the form to the partition method
+    small = small || !(dd * 256.0 >= bb) || !(bb > 1e-186 && bb < 1e186) || !(dd < 1e300);
     if (lane % MR == MR - 1 && lane < 63) piv[(size_t)k * P + (i + 1) / MR] = dl;
   }
   small = __any(small);

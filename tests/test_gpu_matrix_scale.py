@@ -40,3 +40,23 @@ def test_uniform(lib, n, ell, nu, kw):
     for e in (-800, -520, -490, 300, 490, 520, 800):
         U = solve(lib, n, ell, M, K, 2.0**e, **kw)
         assert np.linalg.norm(U - ref) <= 8 * 2.0**-53 * np.linalg.norm(ref), e
+
+
+def graded(n, nu):
+    t = np.linspace(0.0, 1.0, n + 2)
+    h = np.diff(t - 0.5 * np.sin(2 * np.pi * t) / (2 * np.pi))
+    M = (h[:-1] / 6, (h[:-1] + h[1:]) / 3, h[1:] / 6)
+    return M, (-nu / h[:-1], nu / h[:-1] + nu / h[1:], -nu / h[1:])
+
+
+# Scales of the recurrences (2^-290, 2^290) and beyond them, where the partition
+# form runs: there the two forms' rounding, at most 40 u times the condition number
+# of P_0, about n^2, stands between the results.
+@pytest.mark.parametrize("n,ell,nu", [(200, 64, 1.0), (200, 64, 1e-3), (1000, 32, 1.0), (3001, 16, 1e-2)])
+def test_general(lib, n, ell, nu):
+    M, K = graded(n, nu)
+    ref = solve(lib, n, ell, M, K, 1.0)
+    for e in (-480, -400, -350, -320, -290, 290, 320, 400, 480):
+        U = solve(lib, n, ell, M, K, 2.0**e)
+        bound = 8 if abs(e) < 300 else 40 * n * n
+        assert np.linalg.norm(U - ref) <= bound * 2.0**-53 * np.linalg.norm(ref), e
