@@ -601,6 +601,13 @@ gm_diag_kernel(int nc, double *__restrict__ c, const double *__restrict__ c2,
     }
     arnoldi_step_body<RPT>(n, V, w, gm, MX, j, rtol, host, true);
     __syncthreads();
+    if (j + 1 == n) {   // the vectors span the space: done, as in sc_gmres
+      if (tid == 0) {
+        host[1] = 0.0;
+        host[4] = 1.0;
+      }
+      break;
+    }
   }
   const int m = (int)gm[L.st(2)];
   if (wv == 0) {

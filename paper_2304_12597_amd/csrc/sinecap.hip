@@ -275,8 +275,10 @@ __device__ __forceinline__ void sc_gmres(const ScJob &J, int MX, double rtol, do
       if (lane == 0) {
         const double res = fabs(g);
         res_s = res;
-        hn_s = hn;
-        done_s = (res <= rtol * beta || hn == 0.0 || !isfinite(res)) ? 1 : 0;
+        // dim vectors span the space: the solution is in it, and what is left of
+        // hn is rounding that no further vector lowers
+        hn_s = nv < dim ? hn : 0.0;
+        done_s = (res <= rtol * beta || hn_s == 0.0 || !isfinite(res)) ? 1 : 0;
       }
     }
     if (tid < dim) V[(size_t)(j + 1) * dim + tid] = hn > 0.0 ? wr * (1.0 / hn) : 0.0;
