@@ -864,10 +864,15 @@ static pd_status create_plan(pd_plan *out, int n, int ell, double tau, const pd_
   if (!host) {
     PD_TRY(dev_alloc(&p->coef64, coef.size()));
     PD_TRY(dev_alloc(&p->lam64, p->lam.size()));
-    if (L.lu) PD_TRY(dev_alloc(&p->lu_tab, L.lu));
-    PD_TRY(upload(p->coef64, coef, p->stream));
-    PD_TRY(upload(p->lam64, p->lam, p->stream));
-    if (L.lu) PD_TRY(pd_lu_setup(p));
+  }
+  auto matrices = [&]() -> pd_status {
+    const pd_status st = upload(p->coef64, coef, p->stream);
+    return st != PD_OK ? st : upload(p->lam64, p->lam, p->stream);
+  };
+  if (L.lu) {
+    PD_TRY(dev_alloc(&p->lu_tab, L.lu));
+    PD_TRY(matrices());
+    PD_TRY(pd_lu_setup(p));
   }
   if (p->prec == PD_FP64)
     PD_TRY(dev_alloc(&p->fac64, std::max(fac.size(), L.fac)));
@@ -934,6 +939,7 @@ static pd_status create_plan(pd_plan *out, int n, int ell, double tau, const pd_
     return PD_ENOMEM;
   }
   if (!host) {
+    if (!L.lu) PD_TRY(matrices());
     PD_TRY(upload(p->coef32, coef32, p->stream));
     PD_TRY(upload(p->lam32, lam32, p->stream));
     PD_TRY(upload(p->gB64, p->gB, p->stream));
