@@ -289,9 +289,11 @@ pd_status compute_layout(pd_plan p, int cus, size_t max_lds, Layout &L) {
     p->cpl = pd_cp_layout(n, F2);
     L.cp = p->cpl.total;
   }
-  if (p->prec == PD_FP64 && p->dims == 1 && p->uniform && !p->sine && !p->lean)
+  // where pd_sc_choose and pd_sc2_choose may say yes
+  const bool gmres64 = p->prec == PD_FP64 && p->krylov == PD_KRYLOV_GMRES && !p->lean;
+  if (gmres64 && p->dims == 1 && p->uniform && !p->sine && !p->autotune)
     L.cp = std::max(L.cp, pd_sc_max_doubles(n, p->bdf_s));
-  if (p->prec == PD_FP64 && p->dims == 2 && p->bdf_s == 1 && !p->lean) L.cp = pd_sc2_max_doubles(n);
+  if (gmres64 && p->dims == 2 && p->bdf_s == 1) L.cp = pd_sc2_max_doubles(n);
   L.coef = 6 * (size_t)n;
   L.lam = 2 * (size_t)F2;
   L.tw = 2 * (size_t)ell;
