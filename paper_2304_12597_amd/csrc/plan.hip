@@ -186,9 +186,11 @@ bool try_layout(pd_plan p, int cus, size_t max_lds, Layout &L) {
 pd_status compute_layout(pd_plan p, int cus, size_t max_lds, Layout &L) {
   const int n = p->n, ell = p->ell, F2 = p->F2;
   const size_t cb = (p->prec == PD_FP64) ? 16 : 8;
-  // the DST along x as a product: its tables after the FFT forms'
+  // the DST along x as a product: its tables after the FFT forms', if the plan's
+  // largest transform takes it
   auto dense = [&] {
-    const size_t d = p->lean ? 0 : pd_dst_dense_doubles(n);
+    const long rows = p->dims == 2 ? (long)ell * n : ell;
+    const size_t d = p->lean || !pd_dst_dense_pays(n, rows) ? 0 : pd_dst_dense_doubles(n);
     p->twd_dense = d ? (L.twd + 1) / 2 * 2 : 0;   // 16-byte aligned
     if (d) L.twd = p->twd_dense + d;
   };

@@ -1,5 +1,5 @@
-"""paradiag_plan_bytes counts the sine-basis capacitance tables only for plans that
-may use them."""
+"""paradiag_plan_bytes counts the sine-basis capacitance tables, and those of the DST
+as a product, only for plans that may use them."""
 import numpy as np
 import pytest
 
@@ -27,3 +27,10 @@ def test_no_tables(lib, kw):
     est = lib.paradiag_plan_bytes(n, ell, **kw)
     print("estimate %d, used %d" % (est, used))
     assert est < used + tables // 2
+
+
+# 441 points never take the product; fewer points that do not for these numbers of
+# rows need no more memory than those
+@pytest.mark.parametrize("n,ell", [(300, 128), (400, 64), (400, 512), (440, 2), (440, 2048)])
+def test_no_product_tables(lib, n, ell):
+    assert lib.paradiag_plan_bytes(n, ell, shifted_solver=1) <= lib.paradiag_plan_bytes(441, ell, shifted_solver=1)
